@@ -90,8 +90,15 @@ struct MicroParams {
     int32_t  la, lb;                 // ta / vec and tb / vec: vectors per row of the tile, blocks per column
     int32_t  pitch;                  // 16-byte chunks per row of the LDS tile: la rounded up to a multiple of 8
     uint32_t swizzle;                // 7: chunk c of row r sits at c ^ ((r / vec) & 7); 0: rows laid out plainly (measurement aid)
-    int32_t  loads;                  // vectors a lane loads per tile: ceil(la * tb / threads)
-    int32_t  blocks;                 // vec x vec blocks a lane owns: ceil(la * lb / threads)
+    union {
+        int32_t loads;               // vectors a lane loads per tile: ceil(la * tb / threads)
+        int32_t lines;               // line kernel: LineShape::lines (a skewed tile writes one line less per column)
+    };
+    union {
+        int32_t blocks;              // vec x vec blocks a lane owns: ceil(la * lb / threads)
+        int32_t skewed;              // line kernel: 1: the columns of B start at different places inside a line, so every
+                                     // column of a tile is cut where its own lines end; 0: tiles are cut at the same row everywhere
+    };
     FastDiv  la_div, lb_div;
     int64_t  size_a0, size_p0;       // extents of the column index and of the row index (the product where two are merged)
     // A column x sits at element x of A's run and at (x % in) * stride_in + (x / in) * stride_out in B, where `in`
@@ -100,6 +107,54 @@ struct MicroParams {
     int64_t  col_b_in, col_b_out;    // element strides in B of the column index's inner and outer part
     int64_t  row_a_in, row_a_out;    // element strides in A of the row index's inner and outer part
 };
+
+// The line kernel's tile: `cols` columns (the contiguous direction of A) by the rows of `lines` 128-byte lines of B.
+// Everything follows from those two and the element sizes; the kernels take it at compile time, the planner and the
+// replay at run time.
+struct LineShape {
+    int32_t  cols, lines;
+    int32_t  va, vb;                 // elements in 16 bytes of A and of B
+    int32_t  line;                   // elements of B in a line
+    int32_t  rows;                   // rows of A held in LDS: lines * line
+    int32_t  lanes;                  // lanes that load one row (16 bytes each)
+    int32_t  pass;                   // rows the workgroup loads at once
+    int32_t  passes;                 // 16-byte loads per lane
+    int32_t  side;                   // columns the workgroup stores at once, eight lanes each ...
+    int32_t  groups;                 // ... and how many lines of each: 32 / side
+    int32_t  pitch;                  // elements from one row to the next in LDS
+    int32_t  lds_bytes;
+};
+constexpr int kLineThreads = 256;
+constexpr int kLineBytes = 128;
+constexpr int64_t kLineMaxExtent = (int64_t(1) << 31) - 4096;    // rows and columns: tile limits are worked out in 32 bits
+// LDS pitch: a lane of the store phase reads the elements of one column, eight lanes with rows 16 bytes of B apart
+// times eight neighbouring columns per instruction.  cols + 2 (4- and 8-byte elements) or cols + 1 (16-byte) spreads
+// those 64 addresses evenly over the banks and keeps the row starts aligned for the 8- and 16-byte LDS writes.
+constexpr LineShape line_shape(int cols, int lines, int eb_a, int eb_b)
+{
+    LineShape s = {};
+    s.cols = cols;
+    s.lines = lines;
+    s.va = 16 / eb_a;
+    s.vb = 16 / eb_b;
+    s.line = kLineBytes / eb_b;
+    s.rows = lines * s.line;
+    s.lanes = cols / s.va;
+    s.pass = kLineThreads / s.lanes;
+    s.passes = s.rows / s.pass;
+    s.side = cols < kLineThreads / 8 ? cols : kLineThreads / 8;
+    s.groups = kLineThreads / 8 / s.side;
+    s.pitch = cols + (eb_a == 16 ? 1 : 2);
+    s.lds_bytes = s.rows * s.pitch * eb_a;
+    return s;
+}
+// which tiles exist as kernels: rows of 128 to 512 bytes, whole passes, at most 44 KB of LDS (three workgroups per compute unit)
+constexpr bool line_shape_ok(int cols, int lines, int eb_a, int eb_b)
+{
+    const LineShape s = line_shape(cols, lines, eb_a, eb_b);
+    return (cols == 16 || cols == 32 || cols == 64) && (lines == 2 || lines == 4 || lines == 8) &&
+           cols * eb_a >= 128 && cols * eb_a <= 512 && s.rows % s.pass == 0 && lines % s.groups == 0 && s.lds_bytes <= 44 * 1024;
+}
 
 // Everything a kernel launch needs; passed by value as the kernel argument.
 struct KernelParams {
@@ -176,9 +231,13 @@ struct RowsParams {
     double   beta[2];
 };
 
+// The line kernel's internal class.  Plans report it as TTC_KERNEL_LDS (its tile is staged through LDS) with a
+// non-zero `unroll`.
+constexpr int kKernelLines = 4;
+
 // One candidate launch configuration ("candidate" in the paper's Section 3).
 struct Candidate {
-    int      kernel_class;           // TTC_KERNEL_*
+    int      kernel_class;           // TTC_KERNEL_*, or kKernelLines
     int      threads;
     int      wg_per_cu;              // workgroups launched per compute unit (each walks several tiles)
     int      lds_bytes;              // dynamic LDS per workgroup: shared tile records, spare slots, position tables, one or two tile buffers

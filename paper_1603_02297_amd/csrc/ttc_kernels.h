@@ -527,6 +527,180 @@ inline hipError_t launch_micro(const Candidate& c, const void* A, void* B, hipSt
     return hipErrorInvalidValue;
 }
 
+// ---------------------------------------------------------------------------------
+// The line kernel: a tile of COLS columns by the rows of LINES 128-byte lines of B.
+// What it is for: columns of B that do not start on lines (odd extents, leading dimensions).  A tile cut at one row
+// for all its columns then begins and ends inside a line in almost every column, and a line written in two parts by
+// two workgroups costs two masked writes: 7200 x 7200 fp32 took 72 us with both tensors' leading dimension 7232
+// (whole lines) and 99 us (82 searched) with B's 7241, although the bytes are the same.  Here every column is cut
+// where its own lines end, so each line is written once and whole; the price is that a tile reads up to a line's
+// worth of rows of its neighbour again (all but a few per cent of them from the caches).  77 us, whatever B's leading
+// dimension; 79 against 92-105 us with both at 7241.
+// It also takes what the micro-tile kernel does not: 16-byte elements and two precisions (B's lines aligned or not).
+//
+// Loads: 16 bytes a lane along A, all of a tile's rows in flight at once, parked row by row in LDS.
+// Stores: eight lanes per line and eight neighbouring columns per instruction; a lane keeps its column for the whole
+// tile, so a line costs it LDS reads at constant offsets and one 16-byte store.  With an update, B's lines are loaded
+// before the barrier, beside the loads of A.  One tile per workgroup.
+// ---------------------------------------------------------------------------------
+template <typename TA, typename TB, int MODE, int COLS, int LINES>
+__global__ __launch_bounds__(kLineThreads) void line_kernel(const MicroArgs args_by_value, const TA* __restrict__ A, TB* __restrict__ B)
+{
+    const MicroArgs& p = *reinterpret_cast<const MicroArgs*>((const void*)__builtin_amdgcn_kernarg_segment_ptr());
+    constexpr LineShape S = line_shape(COLS, LINES, (int)sizeof(TA), (int)sizeof(TB));
+    static_assert(line_shape_ok(COLS, LINES, (int)sizeof(TA), (int)sizeof(TB)), "no such tile");
+    constexpr int VA = S.va, VB = S.vb, L = S.line, U = S.passes;
+    constexpr int G = COLS / S.side, N = LINES / S.groups;     // columns a lane stores, and lines of each
+    __shared__ __align__(16) unsigned char smem[S.lds_bytes];
+    TA* const lds = reinterpret_cast<TA*>(smem);
+    const MicroParams& m = p.micro;
+    const Epilogue<TA, TB, MODE> epi(p.alpha, p.beta);
+    const uint32_t tid = threadIdx.x;
+    const int32_t rows = (int32_t)m.size_p0;
+    const TileSeq seq = tile_sequence(p, blockIdx.x);
+    for (uint32_t q = seq.first; q < seq.end; q += seq.step) {
+        const LineTile t = line_tile(p, S, tile_of(seq, q));
+        auto run = [&](auto stream_a, auto stream_b) {
+            constexpr bool NTA = decltype(stream_a)::value, NTB = decltype(stream_b)::value;
+            union Vec { Pack<TA, VA> p; uint32_t w[4]; };
+            Vec in[U];
+            const unsigned char* At = reinterpret_cast<const unsigned char*>(A + t.a);
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const LineLoad x = line_load(m, S, t, tid, u);
+                if (x.needed) in[u].p = load_pack<TA, VA, NTA>(At, (micro_row_a(m, x.row) + (int64_t)x.start) * (int64_t)sizeof(TA));
+            }
+            // the lane's columns: where row 0 of each lies in B, and at which place of a line
+            unsigned char* to[G];
+            int32_t y0[G];
+            bool mine[G];
+            Pack<TB, VB> old[G][N];
+#pragma unroll
+            for (int g = 0; g < G; ++g) {
+                const int32_t c = line_column(S, tid, g);
+                mine[g] = c < t.cols;
+                TB* col = B + (t.b + micro_col_b(m, t.col0 + (uint32_t)(mine[g] ? c : 0)));
+                const int32_t phase = (int32_t)((reinterpret_cast<uintptr_t>(col) & (kLineBytes - 1)) / sizeof(TB));
+                y0[g] = line_row(m, S, t, phase, tid);
+                to[g] = reinterpret_cast<unsigned char*>(col);
+                if (MODE == TTC_EPI_AXPBY) {
+#pragma unroll
+                    for (int i = 0; i < N; ++i) {               // a vector that is not whole is loaded from the column's edge
+                        const int32_t y = y0[g] + i * S.groups * L, top = rows - VB;
+                        old[g][i] = load_pack<TB, VB, NTB>(to[g], (int64_t)(y < 0 ? 0 : (y > top ? top : y)) * (int64_t)sizeof(TB));
+                    }
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const LineLoad x = line_load(m, S, t, tid, u);
+                if (!x.needed || x.col >= t.cols) continue;
+                TA* dst = lds + x.lds_row * S.pitch + x.start;
+                if (x.start == x.col) {
+                    typedef uint32_t Half __attribute__((ext_vector_type(2)));
+                    typedef uint32_t Quad __attribute__((ext_vector_type(4)));
+                    if (sizeof(TA) == 4) {                     // rows start on 8-byte boundaries
+                        Half* h = reinterpret_cast<Half*>(dst);
+                        h[0] = Half{in[u].w[0], in[u].w[1]};
+                        h[1] = Half{in[u].w[2], in[u].w[3]};
+                    } else {
+                        *reinterpret_cast<Quad*>(dst) = Quad{in[u].w[0], in[u].w[1], in[u].w[2], in[u].w[3]};
+                    }
+                } else {                                       // moved back: what lies before the tile belongs to another one
+#pragma unroll
+                    for (int j = 0; j < VA; ++j)
+                        if (x.start + j >= 0) dst[j] = in[u].p.v[j];
+                }
+            }
+            __syncthreads();
+#pragma unroll
+            for (int g = 0; g < G; ++g) {
+                if (!mine[g]) continue;
+                const TA* src = lds + (y0[g] - t.row0) * S.pitch + line_column(S, tid, g);
+#pragma unroll
+                for (int i = 0; i < N; ++i) {
+                    if (line_last(m, S, tid, i)) continue;
+                    const int32_t y = y0[g] + i * S.groups * L;
+                    TA a[VB];
+#pragma unroll
+                    for (int j = 0; j < VB; ++j) a[j] = src[(i * S.groups * L + j) * S.pitch];
+                    const int64_t at = (int64_t)y * (int64_t)sizeof(TB);
+                    if (y >= 0 && y + VB <= rows) {
+                        Pack<TB, VB> out;
+#pragma unroll
+                        for (int j = 0; j < VB; ++j) {
+                            TB b_old = TB();
+                            if (MODE == TTC_EPI_AXPBY) b_old = old[g][i].v[j];
+                            out.v[j] = epi(a[j], b_old);
+                        }
+                        store_pack<TB, VB, NTB>(to[g], at, out);
+                    } else {
+                        // The first and the last vector of a column: element by element.  What B held was loaded from
+                        // the column's edge: row y + j is element j + (y - edge) of that vector.  (Loads here, one
+                        // waiting for the other, made 85^4 fp32 (3,0,2,1) with an update 40 % slower.)
+                        const int32_t shift = y < 0 ? y : y - (rows - VB);
+#pragma unroll
+                        for (int j = 0; j < VB; ++j) {
+                            TB b_old = TB();
+                            if (MODE == TTC_EPI_AXPBY) {
+#pragma unroll
+                                for (int e = 0; e < VB; ++e) if (e == j + shift) b_old = old[g][i].v[e];
+                            }
+                            if (y + j >= 0 && y + j < rows) reinterpret_cast<TB*>(to[g] + at)[j] = epi(a[j], b_old);
+                        }
+                    }
+                }
+            }
+        };
+        if (p.nt_a) { if (p.nt_b) run(std::true_type(), std::true_type()); else run(std::true_type(), std::false_type()); }
+        else        { if (p.nt_b) run(std::false_type(), std::true_type()); else run(std::false_type(), std::false_type()); }
+        __syncthreads();                                       // the tile buffer is refilled by the next tile
+    }
+}
+
+template <typename TA, typename TB, int MODE, int COLS, int LINES>
+inline hipError_t launch_line_shape(const Candidate& c, const void* A, void* B, hipStream_t stream)
+{
+    if constexpr (line_shape_ok(COLS, LINES, (int)sizeof(TA), (int)sizeof(TB))) {
+        constexpr LineShape S = line_shape(COLS, LINES, (int)sizeof(TA), (int)sizeof(TB));
+        const KernelParams& kp = c.kp;
+        const MicroParams& m = kp.micro;
+        if (m.ta != COLS || m.lines != LINES || (m.skewed | 1) != 1 || m.tb != (LINES - m.skewed) * S.line || c.threads != kLineThreads ||
+            c.lds_bytes != S.lds_bytes || kp.num_tiles < 1 || kp.grid != kp.num_tiles || m.size_a0 < S.va || m.size_p0 < S.vb ||
+            m.size_a0 >= kLineMaxExtent || m.size_p0 >= kLineMaxExtent || m.col_in_div.div < 1 || m.row_in_div.div < 1)
+            return hipErrorInvalidValue;
+        const void* fn = reinterpret_cast<const void*>(&line_kernel<TA, TB, MODE, COLS, LINES>);
+        const TA* a = static_cast<const TA*>(A);
+        TB* b = static_cast<TB*>(B);
+        MicroArgs ready = micro_args(c);
+        void* args[] = {&ready, &a, &b};
+        return hipLaunchKernel(fn, dim3(kp.num_tiles), dim3(kLineThreads), args, 0, stream);
+    }
+    return hipErrorInvalidValue;
+}
+
+template <typename TA, typename TB, int MODE, int COLS>
+inline hipError_t launch_line_cols(const Candidate& c, const void* A, void* B, hipStream_t s)
+{
+    switch (c.kp.micro.lines) {
+    case 2: return launch_line_shape<TA, TB, MODE, COLS, 2>(c, A, B, s);
+    case 4: return launch_line_shape<TA, TB, MODE, COLS, 4>(c, A, B, s);
+    case 8: return launch_line_shape<TA, TB, MODE, COLS, 8>(c, A, B, s);
+    default: return hipErrorInvalidValue;
+    }
+}
+
+template <typename TA, typename TB, int MODE>
+inline hipError_t launch_lines(const Candidate& c, const void* A, void* B, hipStream_t s)
+{
+    switch (c.kp.micro.ta) {
+    case 16: return launch_line_cols<TA, TB, MODE, 16>(c, A, B, s);
+    case 32: return launch_line_cols<TA, TB, MODE, 32>(c, A, B, s);
+    case 64: return launch_line_cols<TA, TB, MODE, 64>(c, A, B, s);
+    default: return hipErrorInvalidValue;
+    }
+}
+
 // Compute units of the current device (256 on MI355X), asked once per process and device.
 inline int device_cus()
 {
@@ -602,6 +776,7 @@ inline hipError_t launch_vec(const Candidate& c, const void* A, void* B, hipStre
 {
     constexpr int VD = VMAXA < VMAXB ? VMAXA : VMAXB;      // direct and row kernel: one width for both sides
     if (c.kernel_class == TTC_KERNEL_MICRO) return launch_micro<TA, TB, MODE>(c, A, B, s);
+    if (c.kernel_class == kKernelLines) return launch_lines<TA, TB, MODE>(c, A, B, s);
     if (c.kernel_class == TTC_KERNEL_ROWS) {
         const int v = c.rows.vec;
         if (v == 1) return launch_rows_one<TA, TB, MODE, 1>(c, A, B, s);

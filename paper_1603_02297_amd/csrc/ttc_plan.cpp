@@ -805,7 +805,100 @@ static bool make_micro_candidate(const Problem& P, int ta, int tb, int threads, 
     return true;
 }
 
-// The micro-tile kernel's argument block from a candidate as it stands (tile mapping, streaming hints and grid are
+// The line kernel's candidate: `cols` columns by `lines` lines of B per column.  Columns and rows are what the
+// micro-tile kernel takes (A's index 0 and B's first index, each possibly merged with the next), for every type pair.
+static bool make_line_candidate(const Problem& P, int cols_tile, int lines, const int* tile_order, bool merge_a, bool merge_b, Candidate* out)
+{
+    if (P.ndim < 2 || P.perm[0] == 0 || !line_shape_ok(cols_tile, lines, P.eb_a, P.eb_b)) return false;
+    const LineShape S = line_shape(cols_tile, lines, P.eb_a, P.eb_b);
+    const int p0 = P.perm[0], p1 = P.perm[1], a1 = 1;
+    if (P.stride_a[0] != 1 || P.stride_b[p0] != 1) return false;
+    if (merge_a && (P.ndim < 3 || a1 == p0 || P.stride_a[a1] != P.size[0])) return false;
+    if (merge_b && (P.ndim < 3 || p1 == 0 || P.stride_b[p1] != P.size[p0])) return false;
+    if (merge_a && merge_b && a1 == p1) return false;
+    const int64_t cols = merge_a ? P.size[0] * P.size[a1] : P.size[0], rows = merge_b ? P.size[p0] * P.size[p1] : P.size[p0];
+    if (cols >= kLineMaxExtent || rows >= kLineMaxExtent || cols < S.va || rows < S.vb) return false;
+    // do all columns of B start at the same place inside a line?
+    bool skewed = false;
+    for (int k = 0; k < P.ndim; ++k)
+        if (k != p0 && !(merge_b && k == p1) && P.stride_b[k] * P.eb_b % kLineBytes != 0) skewed = true;
+    const int tb = (lines - (skewed ? 1 : 0)) * S.line;
+    Candidate C;
+    std::memset(&C, 0, sizeof(C));
+    C.kernel_class = kKernelLines;
+    C.threads = kLineThreads;
+    C.wg_per_cu = 0;                   // one tile per workgroup
+    C.lds_bytes = S.lds_bytes;
+    KernelParams& kp = C.kp;
+    kp.n = P.ndim;
+    int64_t extent[kMaxDim];           // as the tile decode sees the indices: see make_micro_candidate
+    for (int k = 0; k < kMaxDim; ++k) {
+        extent[k] = (k < P.ndim) ? P.size[k] : 1;
+        C.tile[k] = 1;
+        kp.stride_a[k] = (k < P.ndim) ? P.stride_a[k] : 0;
+        kp.stride_b[k] = (k < P.ndim) ? P.stride_b[k] : 0;
+        kp.tile_below[k] = kp.tile_cnt[k] = make_fastdiv(1);
+    }
+    extent[0] = cols; C.tile[0] = cols_tile; kp.stride_a[0] = 1; kp.stride_b[0] = 0;
+    extent[p0] = rows + (skewed ? S.line - 1 : 0); C.tile[p0] = tb; kp.stride_a[p0] = 0; kp.stride_b[p0] = 1;
+    if (merge_a) { extent[a1] = 1; kp.stride_a[a1] = kp.stride_b[a1] = 0; }
+    if (merge_b) { extent[p1] = 1; kp.stride_a[p1] = kp.stride_b[p1] = 0; }
+    for (int k = 0; k < kMaxDim; ++k) kp.tile[k] = C.tile[k];
+    uint32_t ordered = 0;
+    for (int i = 0; i < P.ndim; ++i) if (tile_order[i] >= 0 && tile_order[i] < P.ndim) ordered |= 1u << tile_order[i];
+    if (ordered != (1u << P.ndim) - 1u) return false;
+    int64_t ntiles = 1;
+    for (int i = 0; i < P.ndim; ++i) {
+        const int k = tile_order[i];
+        const int64_t cnt = ceil_div(extent[k], C.tile[k]);
+        if (cnt > INT32_MAX / 2 || ntiles > INT32_MAX / 2) return false;
+        kp.tile_below[k] = make_fastdiv((uint32_t)ntiles);
+        kp.tile_cnt[k] = make_fastdiv((uint32_t)cnt);
+        ntiles *= cnt;
+        if (ntiles > INT32_MAX / 2) return false;
+        C.tile_order[i] = k;
+    }
+    kp.num_tiles = (uint32_t)ntiles;
+    kp.tiles_per_xcd = kp.num_tiles / 8;
+    kp.tiles_rem_xcd = kp.num_tiles % 8;
+    if (!set_tile_mapping(&kp, kDefaultTileMapping)) return false;
+    set_grid(&kp, kp.num_tiles);
+    kp.alpha[0] = P.alpha[0]; kp.alpha[1] = P.alpha[1];
+    kp.beta[0] = P.beta[0];   kp.beta[1] = P.beta[1];
+    kp.a.vec = S.va; kp.b.vec = S.vb;
+    kp.lds_buffers = 1;
+    kp.lds_tile_elems = S.rows * S.pitch;
+    for (int j = 0; j < kBoxDims; ++j) {
+        kp.slot[j].tile = 1; kp.slot[j].size = 1;
+        kp.slot[j].tile_below = kp.slot[j].tile_cnt = make_fastdiv(1);
+    }
+    MicroParams& m = kp.micro;
+    m.ta = cols_tile; m.tb = tb; m.p0 = p0; m.vec = S.va;
+    m.merged_a = merge_a ? 1 : 0; m.merged_b = merge_b ? 1 : 0;
+    m.lines = lines; m.skewed = skewed ? 1 : 0;
+    m.la_div = m.lb_div = make_fastdiv(1);
+    m.size_a0 = cols; m.size_p0 = rows;
+    m.col_in_div = make_fastdiv((uint32_t)P.size[0]);
+    m.row_in_div = make_fastdiv((uint32_t)P.size[p0]);
+    m.col_b_in = P.stride_b[0];  m.col_b_out = merge_a ? P.stride_b[a1] : 0;
+    m.row_a_in = P.stride_a[p0]; m.row_a_out = merge_b ? P.stride_a[p1] : 0;
+    // the tile per index of A, as the plan reports it
+    C.tile[0] = (int)std::min<int64_t>(cols_tile, P.size[0]);
+    if (merge_a) C.tile[a1] = (int)std::min<int64_t>(ceil_div(cols_tile, P.size[0]), P.size[a1]);
+    C.tile[p0] = (int)std::min<int64_t>(tb, P.size[p0]);
+    if (merge_b) C.tile[p1] = (int)std::min<int64_t>(ceil_div(tb, P.size[p0]), P.size[p1]);
+    C.digits_a = C.digits_b = 2;
+    C.dtile_a[0] = cols_tile; C.dtile_a[1] = S.rows; C.dlane_a[0] = cols_tile; C.dlane_a[1] = std::max(1, kWave / S.lanes);
+    C.dtile_b[0] = tb; C.dtile_b[1] = cols_tile; C.dlane_b[0] = S.line; C.dlane_b[1] = std::min(S.side, kWave / 8);
+    C.dlane_a[2] = m.merged_a; C.dlane_b[2] = m.merged_b;       // part of what names the configuration
+    C.lds_conflict_a = C.lds_conflict_b = 2;
+    C.lds_stride[0] = 1;
+    C.lds_stride[p0] = S.pitch;
+    *out = C;
+    return true;
+}
+
+// The argument block of the micro-tile and the line kernel from a candidate as it stands (tile mapping, streaming hints and grid are
 // the plan's current ones).
 MicroArgs micro_args(const Candidate& c)
 {
@@ -923,7 +1016,7 @@ bool set_tile_mapping(KernelParams* kp, int mode)
 
 uint32_t launch_grid(const Candidate& c, int cus)
 {
-    if (c.kernel_class == TTC_KERNEL_MICRO || c.kernel_class == TTC_KERNEL_ROWS) return c.kp.num_tiles;    // one-shot workgroups
+    if (c.kernel_class == TTC_KERNEL_MICRO || c.kernel_class == TTC_KERNEL_ROWS || c.kernel_class == kKernelLines) return c.kp.num_tiles;    // one-shot workgroups
     const uint64_t want = (uint64_t)std::max(cus, 1) * (uint64_t)std::max(c.wg_per_cu, 1);
     return (uint32_t)std::min<uint64_t>(want, c.kp.num_tiles);
 }
@@ -1066,9 +1159,68 @@ static double micro_cost(const Problem& P, const Candidate& C)
     return std::exp(e);
 }
 
+// The line kernel's ranking model, log-linear like the others, fitted to the timings of every line candidate of 300
+// problems (the 57-case benchmark in fp32, fp64, complex128 and fp32 -> fp64, and random problems of every type, 64 KB
+// to 240 MB) against the candidate that the other models rank first.  Two sets of weights: from 16 MB of traffic on a
+// tile costs what it loads and stores, below what counts is how long one tile takes.  Choosing by it takes 7 % (large)
+// and 15 % (small) off the time of the other families' first candidate, geometric mean over all problems, those that
+// stay with the other families included (held-out problems: 7 % and 15 %).
+static double line_cost(const Problem& P, const Candidate& C)
+{
+    const MicroParams& m = C.kp.micro;
+    const LineShape S = line_shape(m.ta, m.lines, P.eb_a, P.eb_b);
+    const double rows = (double)m.size_p0, cols = (double)m.size_a0;
+    const int64_t segs = (int64_t)C.kp.tile_cnt[m.p0].div;
+    const bool update = P.epilogue == TTC_EPI_AXPBY;
+    bool split_a = m.ta * P.eb_a % kLineBytes != 0;                       // runs of A that start or end inside lines
+    for (int k = 1; k < P.ndim; ++k)
+        if (!(m.merged_a && k == 1) && P.stride_a[k] * P.eb_a % kLineBytes != 0) split_a = true;
+    const double run_a = std::min<double>(m.ta, cols) * P.eb_a;
+    const double split = split_a ? (double)kLineBytes / run_a : 0.0;
+    const double pad_cols = std::log((double)ceil_div(m.size_a0, m.ta) * m.ta / cols);
+    const bool one_precision = P.eb_a == P.eb_b && P.eb_a < 16;           // the others' first is then a micro-tile candidate, ranked by its own model
+    const double line_rows = rows / S.line;                               // lines per column
+    const double traffic = (double)P.elements * (P.eb_a + (update ? 2 : 1) * P.eb_b);
+    double e;
+    if (traffic >= 16e6) {
+        const int64_t last_row0 = (segs - 1) * (int64_t)m.tb - (m.skewed ? S.line : 0);
+        int64_t loaded = segs * (int64_t)S.rows;                          // rows loaded per column: whole passes
+        loaded -= S.rows - std::min<int64_t>(S.rows, ceil_div(m.size_p0 - last_row0, S.pass) * S.pass);
+        if (m.skewed) loaded -= S.line / S.pass * S.pass;                 // the first tile needs no rows before it
+        e = -0.245 - (m.skewed ? 0.082 : 0.0) - (update ? 0.083 : 0.0);
+        if (one_precision) e += m.skewed ? -0.073 : (split_a || update ? -0.010 : 0.075);     // whole lines on both sides: the micro-tile kernel is as good
+        if (update && m.merged_a && P.size[0] * P.eb_a >= 512) e += 0.08 + (P.perm[1] == 0 ? 0.12 : 0.0);    // a tile that crosses the end of a row
+                                                                          // reads and writes B in two places, and leaves a contiguous block
+        e += 0.343 * std::log((double)loaded / rows) + 0.340 * pad_cols + 0.293 * std::log((double)segs * m.tb / rows) + 0.087 * split;
+        if (m.skewed) e += 0.178 * 2.0 / (line_rows + 1.0);               // lines that no tile writes whole: a column's first and last
+        if (m.size_p0 < S.line) e += 0.258;
+        if (m.lines == 2) e += 0.10;
+        if (update && m.ta == 64 && m.lines >= 4) e += 0.20;              // eight old vectors a lane: half the wavefronts fit
+        const double tiles_wanted = std::min(2048.0, std::max(1.0, (double)P.elements * P.eb_a / 8192.0));
+        if (C.kp.num_tiles < tiles_wanted) e += 0.30 * (tiles_wanted - C.kp.num_tiles) / 2048.0;
+    } else {
+        e = -0.40 + (m.skewed ? 0.057 : 0.0) + (one_precision ? 0.08 : 0.0) - (update ? 0.126 : 0.0);
+        e += 0.05 * pad_cols + 0.167 * split + 0.18 * C.lds_bytes / 65536.0;
+        e -= 0.058 * std::log2(std::min<double>(m.lines - m.skewed, std::ceil(line_rows)));
+        // vectors a lane stores: the fewer the quicker the tile
+        e += std::min(0.14, std::max(0.05, 0.12 - 0.025 * std::log2(traffic / 2e6))) * std::log2((double)(m.ta / S.side) * (m.lines / S.groups));
+        // two lines' rows: the quickest tile, the best one below 2 MB; one line of a skewed tile's two is its neighbour's
+        if (m.lines == 2) e += 0.016 + 0.061 * std::min(3.0, std::max(-2.0, std::log2(traffic / 2e6)));
+        if (m.size_p0 < S.line) e += 0.374;
+        const double cus_wanted = std::min(256.0, std::max(1.0, (double)P.elements * P.eb_a / 4096.0));
+        if (C.kp.num_tiles < cus_wanted) e += 0.38 * (cus_wanted - C.kp.num_tiles) / 256.0;
+    }
+    bool b_order = true;
+    for (int i = 0; i < P.ndim; ++i) if (C.tile_order[i] != P.perm[i]) b_order = false;
+    if (!b_order) e += 0.08;
+    if (rows * P.eb_b < 64.0) e += 0.25 * std::log2(64.0 / (rows * P.eb_b));          // outside the fitted range: most of a tile's rows are not there
+    return std::exp(e);
+}
+
 static double heuristic_cost(const Problem& P, const Candidate& C)
 {
     if (C.kernel_class == TTC_KERNEL_ROWS) return rows_cost(P, C);
+    if (C.kernel_class == kKernelLines) return line_cost(P, C);
     if (C.kernel_class == TTC_KERNEL_MICRO) return micro_cost(P, C);
     // Weights fitted to timings of every candidate of 105 problems on MI355X (the benchmark workloads, 3-D and
     // 5-D problems with odd extents, a 57-case benchmark drawn by the paper's rules, power-of-two shapes): log-linear least
@@ -1176,6 +1328,20 @@ void default_streaming(const Problem& P, Candidate* c)
 {
     if (c->kernel_class == TTC_KERNEL_ROWS) {      // B is written front to back and A's rows are read once: stream both
         c->kp.nt_a = c->kp.nt_b = 1;
+        return;
+    }
+    if (c->kernel_class == kKernelLines) {
+        // B's lines are written once and whole: streamed (A's rows then stay in the caches: tiles share them where
+        // they are skewed or A's runs split lines; both sides streamed is 14 % slower on the average of such problems,
+        // neither side 13 %).  A is streamed too where nothing of it is shared, B is not read and A exceeds half the
+        // last-level cache (1.6 % faster; at smaller sizes 14 % slower if A was written not long ago; with an update 0-12 %).  Below 8 MB of traffic everything stays in the
+        // caches and the hints make no difference: none, B's reader comes next.
+        const MicroParams& m = c->kp.micro;
+        bool whole_a = !m.skewed && P.epilogue != TTC_EPI_AXPBY && P.elements * P.eb_a >= (int64_t(128) << 20);
+        for (int k = 1; k < P.ndim; ++k)
+            if (!(m.merged_a && k == 1) && P.stride_a[k] * P.eb_a % kLineBytes != 0) whole_a = false;
+        c->kp.nt_a = whole_a ? 1 : 0;
+        c->kp.nt_b = P.elements * (P.eb_a + (P.epilogue == TTC_EPI_AXPBY ? 2 : 1) * P.eb_b) >= 8000000 ? 1 : 0;
         return;
     }
     const AccessShape sh = access_shape(P, *c);
@@ -1376,6 +1542,22 @@ static void enumerate(const Problem& P, std::vector<Candidate>& out_list, bool q
             }
     }
 
+    // -- the line kernel
+    if (!stride1_fixed && n >= 2) {
+        const int p0 = P.perm[0], p1 = P.perm[1];
+        for (int merge_a = 0; merge_a < 2; ++merge_a)
+            for (int merge_b = 0; merge_b < 2; ++merge_b) {
+                if (merge_a && (n < 3 || p0 == 1)) continue;
+                if (merge_b && (n < 3 || p1 == 0)) continue;
+                for (int cols : {16, 32, 64})
+                    for (int lines : {4, 8, 2})
+                        for (int o = 0; o < (quick ? 1 : 2); ++o) {
+                            Candidate c;
+                            if (make_line_candidate(P, cols, lines, orders[o], merge_a != 0, merge_b != 0, &c)) add_candidate(P, out, c);
+                        }
+            }
+    }
+
     // -- staged candidates: a box spanning the leading indices of A and of B
     if (n >= 2) {
         const int p0 = P.perm[0];
@@ -1447,12 +1629,12 @@ int build_plan(int dtype, int ndim, const int64_t* sizes, const int* perm, const
     if (verbose()) {
         const Candidate& c = plan->cands[0];
         std::fprintf(stderr, "ttc: plan dtype %d, %d fused indices, %s kernel, tile", P.dtype, P.ndim,
-                     c.kernel_class == TTC_KERNEL_DIRECT ? "direct" : (c.kernel_class == TTC_KERNEL_ROWS ? "row" : (c.kernel_class == TTC_KERNEL_MICRO ? "micro-tile" : "staged")));
+                     c.kernel_class == TTC_KERNEL_DIRECT ? "direct" : (c.kernel_class == TTC_KERNEL_ROWS ? "row" : (c.kernel_class == TTC_KERNEL_MICRO ? "micro-tile" : (c.kernel_class == kKernelLines ? "line" : "staged"))));
         for (int k = 0; k < P.ndim; ++k) std::fprintf(stderr, " %d", c.tile[k]);
-        size_t per_class[4] = {0, 0, 0, 0};
-        for (const Candidate& q : quick) if (q.kernel_class >= 0 && q.kernel_class < 4) ++per_class[q.kernel_class];
-        std::fprintf(stderr, ", vectors %d/%d, %d threads, %d B LDS, cost %.4f (best of %zu candidates of the short list: %zu direct, %zu staged, %zu row, %zu micro-tile)\n",
-                     c.kp.a.vec, c.kp.b.vec, c.threads, c.lds_bytes, c.score, quick.size(), per_class[0], per_class[1], per_class[2], per_class[3]);
+        size_t per_class[5] = {0, 0, 0, 0, 0};
+        for (const Candidate& q : quick) if (q.kernel_class >= 0 && q.kernel_class < 5) ++per_class[q.kernel_class];
+        std::fprintf(stderr, ", vectors %d/%d, %d threads, %d B LDS, cost %.4f (best of %zu candidates of the short list: %zu direct, %zu staged, %zu row, %zu micro-tile, %zu line)\n",
+                     c.kp.a.vec, c.kp.b.vec, c.threads, c.lds_bytes, c.score, quick.size(), per_class[0], per_class[1], per_class[2], per_class[3], per_class[4]);
     }
     return TTC_OK;
 }
@@ -1579,7 +1761,7 @@ int ttc_plan_get_info(ttc_plan_t plan, ttc_plan_info_t* out)
         out->digit_tile_b[i] = C.dtile_b[i];  out->digit_lane_b[i] = C.dlane_b[i];
     }
     out->stride1_fixed = (P.perm[0] == 0) ? 1 : 0;
-    out->kernel_class = C.kernel_class;
+    out->kernel_class = C.kernel_class == ttc::kKernelLines ? TTC_KERNEL_LDS : C.kernel_class;
     out->epilogue = P.epilogue;
     out->vec_a = C.kp.a.vec;
     out->vec_b = C.kp.b.vec;
@@ -1610,8 +1792,9 @@ int ttc_plan_get_info(ttc_plan_t plan, ttc_plan_info_t* out)
     out->candidate_count = (int)plan->cands.size();
     out->tuned_ms = C.tuned_ms;
     out->heuristic_cost = C.score;
-    out->merged = C.kernel_class == TTC_KERNEL_MICRO ? (C.kp.micro.merged_a | (C.kp.micro.merged_b << 1)) : 0;
-    out->unroll = C.kernel_class == TTC_KERNEL_ROWS ? C.rows.unroll : (C.kernel_class == TTC_KERNEL_MICRO ? C.kp.micro.blocks : 0);
+    out->merged = (C.kernel_class == TTC_KERNEL_MICRO || C.kernel_class == ttc::kKernelLines) ? (C.kp.micro.merged_a | (C.kp.micro.merged_b << 1)) : 0;
+    out->unroll = C.kernel_class == TTC_KERNEL_ROWS ? C.rows.unroll : 
+                  (C.kernel_class == TTC_KERNEL_MICRO ? C.kp.micro.blocks : (C.kernel_class == ttc::kKernelLines ? C.kp.micro.lines : 0));
     return TTC_OK;
     });
 }
@@ -1824,6 +2007,90 @@ static int emulate_micro(const ttc::Problem& P, const ttc::Candidate& C, int64_t
     return written == P.elements ? TTC_OK : TTC_ERR_INTERNAL;
 }
 
+// Replay of the line kernel, every workgroup and every lane, for a B that starts `phase0` elements behind the start of a line.
+static int emulate_lines(const ttc::Problem& P, const ttc::Candidate& C, int phase0, int64_t* b_from_a)
+{
+    using namespace ttc;
+    const MicroArgs p = micro_args(C);
+    const MicroParams& m = p.micro;
+    const int p0 = P.perm[0], p1 = P.ndim >= 2 ? P.perm[1] : -1, a1 = 1;
+    if (p0 == 0 || P.ndim < 2 || !line_shape_ok(m.ta, m.lines, P.eb_a, P.eb_b)) return TTC_ERR_INTERNAL;
+    const LineShape S = line_shape(m.ta, m.lines, P.eb_a, P.eb_b);
+    const int64_t cols = m.merged_a ? P.size[0] * P.size[a1] : P.size[0], rows = m.merged_b ? P.size[p0] * P.size[p1] : P.size[p0];
+    if (p.col_pos < 0 || p.row_pos < 0 || p.col_pos == p.row_pos || p.grid != p.num_tiles || C.threads != kLineThreads || C.lds_bytes != S.lds_bytes ||
+        S.passes * S.pass != S.rows || S.lanes * S.pass != kLineThreads || S.lanes * S.va != m.ta || 8 * S.vb != S.line ||
+        S.side * S.groups * 8 != kLineThreads || m.ta % S.side != 0 || m.lines % S.groups != 0 || m.tb != (m.lines - m.skewed) * S.line || m.p0 != p0 ||
+        P.stride_a[0] != 1 || P.stride_b[p0] != 1 || (m.merged_a | 1) != 1 || (m.merged_b | 1) != 1 || (m.skewed | 1) != 1 ||
+        (m.merged_a && (P.ndim < 3 || a1 == p0 || P.stride_a[a1] != P.size[0] || (m.merged_b && a1 == p1))) ||
+        (m.merged_b && (P.ndim < 3 || p1 == 0 || P.stride_b[p1] != P.size[p0])) ||
+        m.size_a0 != cols || m.size_p0 != rows || cols < S.va || rows < S.vb || cols >= kLineMaxExtent || rows >= kLineMaxExtent ||
+        m.col_in_div.div != (uint32_t)P.size[0] || m.row_in_div.div != (uint32_t)P.size[p0] ||
+        m.col_b_in != P.stride_b[0] || m.col_b_out != (m.merged_a ? P.stride_b[a1] : 0) ||
+        m.row_a_in != P.stride_a[p0] || m.row_a_out != (m.merged_b ? P.stride_a[p1] : 0))
+        return TTC_ERR_INTERNAL;
+    for (int64_t i = 0; i < P.span_b; ++i) b_from_a[i] = -1;
+    auto inside = [&](int64_t off, const int64_t* stride, bool b_side) {
+        if (off < 0) return false;
+        for (int i = P.ndim - 1; i >= 0; --i) {
+            const int k = b_side ? P.perm[i] : i;
+            const int64_t c = off / stride[k];
+            if (c >= P.size[k]) return false;
+            off -= c * stride[k];
+        }
+        return off == 0;
+    };
+    std::vector<int64_t> lds((size_t)(S.rows * S.pitch));
+    std::vector<char> seen(p.num_tiles, 0);
+    int64_t written = 0;
+    for (uint32_t wg = 0; wg < p.grid; ++wg) {
+        const TileSeq seq = tile_sequence(p, wg);
+        for (uint32_t q = seq.first; q < seq.end; q += seq.step) {
+            const uint32_t tile = tile_of(seq, q);
+            if (tile >= p.num_tiles || seen[tile]) return TTC_ERR_INTERNAL;
+            seen[tile] = 1;
+            const LineTile t = line_tile(p, S, tile);
+            if (t.cols < 1 || t.cols > m.ta) return TTC_ERR_INTERNAL;
+            std::fill(lds.begin(), lds.end(), (int64_t)-1);
+            for (int k = 0; k < S.passes; ++k)
+                for (uint32_t tid = 0; tid < (uint32_t)kLineThreads; ++tid) {
+                    const LineLoad x = line_load(m, S, t, tid, k);
+                    if (!x.needed) continue;
+                    const int64_t y = (int64_t)t.row0 + x.lds_row;
+                    for (int j = 0; j < S.va; ++j) {             // every lane loads, whether it keeps what it got or not
+                        const int64_t src = t.a + micro_row_a(m, x.row) + x.start + j;
+                        if (!inside(src, P.stride_a, false)) return TTC_ERR_INTERNAL;
+                        if (x.col >= t.cols || x.start + j < 0) continue;
+                        const int64_t slot = (int64_t)x.lds_row * S.pitch + x.start + j;
+                        if (x.start + j >= m.ta || slot < 0 || slot >= (int64_t)lds.size()) return TTC_ERR_INTERNAL;
+                        if (x.start == x.col && (slot - j) * P.eb_a % (P.eb_a == 4 ? 8 : 16) != 0) return TTC_ERR_INTERNAL;     // the wide LDS write
+                        const int64_t value = y >= 0 && y < rows ? src : -2;            // rows outside the tensor: parked, never stored
+                        if (lds[(size_t)slot] != -1 && lds[(size_t)slot] != value) return TTC_ERR_INTERNAL;
+                        lds[(size_t)slot] = value;
+                    }
+                }
+            for (uint32_t tid = 0; tid < (uint32_t)kLineThreads; ++tid)
+                for (int g = 0; g < m.ta / S.side; ++g) {
+                    const int32_t c = line_column(S, tid, g);
+                    if (c >= t.cols) continue;
+                    const int64_t col = t.b + micro_col_b(m, t.col0 + (uint32_t)c);
+                    const int32_t phase = (int32_t)((col + phase0) % S.line);
+                    for (int i = 0; i < m.lines / S.groups; ++i)
+                        for (int j = 0; j < S.vb; ++j) {
+                            if (line_last(m, S, tid, i)) continue;
+                            const int64_t y = (int64_t)line_row(m, S, t, phase, tid) + i * S.groups * S.line + j, slot = (y - t.row0) * S.pitch + c;
+                            if (slot < 0 || slot >= (int64_t)lds.size()) return TTC_ERR_INTERNAL;
+                            if (y < 0 || y >= rows) continue;
+                            const int64_t dst = col + y;
+                            if (lds[(size_t)slot] < 0 || !inside(dst, P.stride_b, true) || b_from_a[dst] != -1) return TTC_ERR_INTERNAL;
+                            b_from_a[dst] = lds[(size_t)slot];
+                            ++written;
+                        }
+                }
+        }
+    }
+    return written == P.elements ? TTC_OK : TTC_ERR_INTERNAL;
+}
+
 static int emulate_map(ttc_plan_t plan, int64_t* b_from_a)
 {
     using namespace ttc;
@@ -1831,6 +2098,16 @@ static int emulate_map(ttc_plan_t plan, int64_t* b_from_a)
     const Candidate& C = plan->cands[plan->selected];
     if (C.kernel_class == TTC_KERNEL_ROWS) return emulate_rows(P, C, b_from_a);
     if (C.kernel_class == TTC_KERNEL_MICRO) return emulate_micro(P, C, b_from_a);
+    if (C.kernel_class == kKernelLines) {
+        // where a tile is cut depends on the address B will have: every place inside a line that matters (the first,
+        // the last, one between), the aligned one last
+        const int line = kLineBytes / P.eb_b;
+        for (int phase : {line - 1, line / 2 + 1, 0}) {
+            const int st = emulate_lines(P, C, phase, b_from_a);
+            if (st != TTC_OK) return st;
+        }
+        return TTC_OK;
+    }
     KernelParams p = C.kp;
     set_grid(&p, launch_grid(C, 256));
     const int32_t eba = P.eb_a, ebb = P.eb_b;

@@ -185,13 +185,15 @@ TTC_HD SideLim side_lim(const Side& s, const TileLim& t)
 // own_a, own_b: the first column and row that are this tile's own (not 0 where the tile was moved back over its neighbour).
 struct MicroTile { int64_t a, b; uint32_t col0, row0, lim_a, lim_b, own_a, own_b; };
 
-TTC_HD MicroTile micro_tile(const MicroArgs& p, uint32_t tile)
+// Tile id -> what the tile contributes to the offsets in A and B, and its coordinates along the column and row index.
+struct TilePlace { int64_t a, b; uint32_t col, row; };
+
+TTC_HD TilePlace tile_place(const MicroArgs& p, uint32_t tile)
 {
-    const MicroParams& m = p.micro;
     // mixed radix in tile order; straight-line over all kMaxDim places (unused ones hold one tile and no step).
     // The steps leave out what depends on the column in B and on the row in A.
-    struct { int64_t a, b; } t = {0, 0};
-    uint32_t rest = tile, da = 0, db = 0;
+    TilePlace t = {0, 0, 0, 0};
+    uint32_t rest = tile;
 #pragma unroll
     for (int i = 0; i < kMaxDim; ++i) {
         const uint32_t next = fdiv(rest, p.cnt[i]);
@@ -199,9 +201,17 @@ TTC_HD MicroTile micro_tile(const MicroArgs& p, uint32_t tile)
         rest = next;
         t.a += (int64_t)d * p.step_a[i];
         t.b += (int64_t)d * p.step_b[i];
-        if (i == p.col_pos) da = d;
-        if (i == p.row_pos) db = d;
+        if (i == p.col_pos) t.col = d;
+        if (i == p.row_pos) t.row = d;
     }
+    return t;
+}
+
+TTC_HD MicroTile micro_tile(const MicroArgs& p, uint32_t tile)
+{
+    const MicroParams& m = p.micro;
+    const TilePlace t = tile_place(p, tile);
+    const uint32_t da = t.col, db = t.row;
     const int64_t oa = (int64_t)da * m.ta, ob = (int64_t)db * m.tb;
     int64_t lim_a = m.size_a0 - oa < (int64_t)m.ta ? m.size_a0 - oa : (int64_t)m.ta;
     int64_t lim_b = m.size_p0 - ob < (int64_t)m.tb ? m.size_p0 - ob : (int64_t)m.tb;
@@ -273,6 +283,62 @@ TTC_HD MicroBlock micro_block(const MicroParams& m, uint32_t threads, uint32_t t
     r.col = r.lane_c << m.vec_log;
     r.valid = r.lane_c < (uint32_t)m.la;
     return r;
+}
+
+// ---- line kernel -----------------------------------------------------------------------------
+// A tile holds m.ta columns.  Along the rows it is cut where lines of B end: with `phase` = the place inside its line
+// of row 0 of a column (in elements, 0 unless m.skewed), tile number g writes rows g * tb - phase ... (g + 1) * tb -
+// phase of that column, as far as they exist.  Skewed, it needs rows from line - 1 before g * tb on and writes one
+// line less than LDS holds rows for (tb = (lines - 1) * line); else tb = lines * line.  row0 is the row of LDS row 0.
+struct LineTile { int64_t a, b; uint32_t col0; int32_t row0, cols, first; };
+
+TTC_HD LineTile line_tile(const MicroArgs& p, const LineShape& s, uint32_t tile)
+{
+    const MicroParams& m = p.micro;
+    const TilePlace t = tile_place(p, tile);
+    LineTile r;
+    r.col0 = t.col * (uint32_t)m.ta;
+    r.row0 = (int32_t)(t.row * (uint32_t)m.tb) - (m.skewed ? s.line : 0);
+    r.a = t.a;                                                       // the first column included
+    r.b = t.b - (int64_t)t.row * m.tb;                               // row 0 of the tensor
+    const int64_t left = m.size_a0 - (int64_t)r.col0;
+    r.cols = (int32_t)(left < (int64_t)m.ta ? left : (int64_t)m.ta);
+    r.first = r.row0 < 0 ? s.line : 0;                               // LDS rows before this one are not needed
+    return r;
+}
+
+// Load `k` of lane `tid`: LDS row, the column the vector nominally starts at, the one it really starts at (moved back to
+// end with the tensor; negative if the tile holds fewer columns than a vector: it then starts in the tile before),
+// and the row of the tensor (clamped into it: rows outside are loaded from its edge and never stored).
+struct LineLoad { int32_t lds_row, col, start; uint32_t row; bool needed; };
+
+TTC_HD LineLoad line_load(const MicroParams& m, const LineShape& s, const LineTile& t, uint32_t tid, int k)
+{
+    LineLoad r;
+    r.lds_row = (int32_t)tid / s.lanes + k * s.pass;
+    r.col = (int32_t)tid % s.lanes * s.va;
+    r.start = r.col < t.cols - s.va ? r.col : t.cols - s.va;
+    const int32_t y = t.row0 + r.lds_row, last = (int32_t)m.size_p0 - 1;
+    r.row = (uint32_t)(y < 0 ? 0 : (y > last ? last : y));
+    // uniform over the workgroup: whole passes may lie before the first or behind the last row that is needed
+    r.needed = (k + 1) * s.pass > t.first && t.row0 + k * s.pass <= last;
+    return r;
+}
+
+// Stores: lane `tid` keeps column line_column(tid, g) of the tile, g = 0 ... cols / side - 1, and writes 16 bytes of every
+// groups-th of its lines: rows y ... y + vb - 1 with y = line_row() + i * groups * line, i = 0 ... lines / groups - 1,
+// taken from LDS rows y - row0 on.  The last line of a skewed tile is not the tile's (line_last()).
+TTC_HD int32_t line_column(const LineShape& s, uint32_t tid, int g) { return (int32_t)(tid >> 3) % s.side + g * s.side; }
+TTC_HD int32_t line_group(const LineShape& s, uint32_t tid) { return (int32_t)(tid >> 3) / s.side; }
+
+TTC_HD int32_t line_row(const MicroParams& m, const LineShape& s, const LineTile& t, int32_t phase, uint32_t tid)
+{
+    return t.row0 + (m.skewed ? s.line - phase : 0) + line_group(s, tid) * s.line + (int32_t)(tid & 7u) * s.vb;
+}
+
+TTC_HD bool line_last(const MicroParams& m, const LineShape& s, uint32_t tid, int i)
+{
+    return m.skewed && line_group(s, tid) + i * s.groups == s.lines - 1;
 }
 
 // ---- lane entry ------------------------------------------------------------------------------

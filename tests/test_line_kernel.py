@@ -1,0 +1,96 @@
+"""The line kernel (tiles cut where lines of B end): every candidate against the oracle, replayed on the host and run on
+the GPU, at the sizes where its tiles can go wrong: fewer columns than a vector in the last tile, rows that end
+inside the first line, one row or one column more than a tile, columns of B at every place inside a line."""
+import numpy as np
+import pytest
+
+import oracle
+import paper_1603_02297_amd as ttc
+from paper_1603_02297_amd import workloads as wl
+
+# sizes, perm, lda, ldb
+SHAPES = [
+    ((33, 129), (1, 0), None, None),                 # one column and one row more than a tile
+    ((65, 31), (1, 0), None, None),                  # rows shorter than a line of fp32
+    ((64, 256), (1, 0), None, None),                 # B's columns on whole lines: tiles not skewed
+    ((34, 70), (1, 0), (37, 70), (71, 34)),          # leading dimensions on both sides
+    ((4, 4), (1, 0), None, None),                    # the smallest tensor: one vector each way
+    ((7, 11, 9), (2, 1, 0), None, None),
+    ((5, 13, 40), (2, 0, 1), None, None),            # fuses to (65, 40)
+    ((12, 5, 7, 9), (3, 2, 1, 0), None, None),       # two indices taken as one on both sides
+    ((6, 7, 5, 9), (3, 1, 0, 2), (6, 8, 5, 9), None),
+    ((9, 4, 3, 5, 8), (4, 1, 3, 0, 2), None, (9, 4, 5, 9, 3)),
+]
+DTYPES = [wl.F32, wl.F64, wl.C64, wl.C128, wl.F32_F64, wl.F64_F32, wl.C64_C128, wl.C128_C64]
+
+
+def line_candidates(plan):
+    """Indices of the plan's line-kernel candidates: staged through LDS, and `unroll` (lines per tile) is set."""
+    for k in range(ttc.ttc_plan_candidate_count(plan)):
+        ttc.ttc_plan_select_candidate(plan, k)
+        info = ttc.ttc_plan_get_info(plan)
+        if info["kernel_class"] == ttc.TTC_KERNEL_LDS and info["unroll"] > 0:
+            yield k, info
+
+
+def scalars(dtype):
+    cplx = wl.COMPONENTS[dtype] == 2
+    return [(1.0, 0.0), (0.5 + 0.5j if cplx else 1.5, 0.0), (0.5 - 0.25j if cplx else 0.75, 1.0 + 0.5j if cplx else -1.25)]
+
+
+@pytest.mark.parametrize("dtype", DTYPES, ids=[wl.DTYPE_NAME[d] for d in DTYPES])
+def test_walks_of_every_line_candidate(dtype):
+    seen = 0
+    for sizes, perm, lda, ldb in SHAPES:
+        for beta in (0.0, 1.0):
+            p = ttc.ttc_plan_create_ex(dtype, len(sizes), sizes, perm, lda, ldb, 1.0, beta)
+            want = [-1] * ttc.ttc_plan_get_info(p)["span_b"]
+            for off_a, off_b in oracle.element_pairs(sizes, perm, lda, ldb):
+                want[off_b] = off_a
+            for k, info in line_candidates(p):
+                assert list(ttc.ttc_debug_emulate_map(p)) == want, (sizes, perm, k, info)
+                seen += 1
+            ttc.ttc_plan_destroy(p)
+    assert seen >= 40
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", DTYPES, ids=[wl.DTYPE_NAME[d] for d in DTYPES])
+def test_line_kernel_against_the_oracle(dtype):
+    """Every candidate, every epilogue, both streaming settings; B at three places inside a line; what lies around the
+    sub-tensor stays as it was.  Fixed evaluation order on both sides: bit-equal but for the ulp the library allows."""
+    import torch
+    dev = torch.device("cuda:0")
+    stream = torch.cuda.current_stream().cuda_stream
+    prod = lambda v: int(np.prod(v))  # noqa: E731
+    ran = 0
+    for shape, (sizes, perm, lda, ldb) in enumerate(SHAPES):
+        na, nb = prod(lda or sizes), prod(ldb or sizes)
+        A = wl.uniform_tensor(dtype, na, 7000 + shape, "a")
+        B0 = wl.uniform_tensor(dtype, nb, 7100 + shape, "b")
+        comp, room = wl.COMPONENTS[dtype], 128
+        dA = torch.from_numpy(A).to(dev)
+        for alpha, beta in scalars(dtype):
+            want = oracle.transpose(dtype, sizes, perm, alpha, beta, A, B0.copy(), 4, lda=lda, ldb=ldb)
+            plan = ttc.ttc_plan_create_ex(dtype, len(sizes), sizes, perm, lda, ldb, alpha, beta)
+            try:
+                for k, info in line_candidates(plan):
+                    for nt, phase in ((0, 0), (1, 1), (0, 7)):
+                        ttc.ttc_plan_set_streaming(plan, nt, nt)
+                        buf = torch.full((nb * comp + 2 * room,), 77.0, dtype=torch.from_numpy(B0).dtype, device=dev)
+                        at = room + phase * comp
+                        buf[at:at + nb * comp] = torch.from_numpy(B0).to(dev)
+                        ttc.ttc_execute(plan, dA.data_ptr(), buf.data_ptr() + at * buf.element_size(), stream)
+                        torch.cuda.synchronize()
+                        got = buf.cpu().numpy()
+                        assert (got[:at] == 77).all() and (got[at + nb * comp:] == 77).all(), (sizes, perm, k, info)
+                        got = got[at:at + nb * comp]
+                        if complex(alpha) == 1 and complex(beta) == 0:
+                            assert np.array_equal(got, want), (sizes, perm, k, info)
+                        else:
+                            ulp = np.spacing(np.abs(want).max())
+                            assert np.abs(got - want).max() <= ulp, (sizes, perm, alpha, beta, k, info)
+                        ran += 1
+            finally:
+                ttc.ttc_plan_destroy(plan)
+    assert ran >= 100
