@@ -218,15 +218,19 @@ struct RowsParams {
     int32_t  unroll;                 // accesses a lane keeps in flight
     int32_t  overlap;                // 1: rows are not a multiple of vec: the last vector of a row is moved back to end with it
     uint32_t row;                    // extent of index 0
-    uint32_t slots;                  // vectors per row: ceil(row / vec)
+    uint32_t slots;                  // vectors per row: ceil(row / vec); flat: elements per row
     uint32_t chunk;                  // vectors a workgroup moves: threads * unroll
     int32_t  nt_a, nt_b;             // non-temporal accesses per side
-    int32_t  pad;
+    int32_t  flat;                   // 1: B is dense: vectors are counted through B from its first element, across the ends of rows
+    int32_t  xcd_remap;              // how the workgroups' chunks are dealt to the XCDs (as KernelParams::xcd_remap)
+    uint32_t blocks;                 // chunks, one per workgroup
+    uint32_t rows;                   // rows of the tensor
     FastDiv  slot_div;               // x / slots
     FastDiv  size_div[kMaxDim];      // extent of B's index d, d = 1 .. n-1 (entry 0 unused)
     int64_t  stride_a[kMaxDim];      // element stride in A of B's index d
     int64_t  stride_b[kMaxDim];      // element stride in B of B's index d
-    int64_t  vectors;                // rows * slots
+    int64_t  vectors;                // rows * slots; flat: ceil(elements / vec)
+    int64_t  elements;
     double   alpha[2];
     double   beta[2];
 };

@@ -340,21 +340,29 @@ __global__ __launch_bounds__(kMaxThreads) void box_kernel(const KernelParams par
 // ---------------------------------------------------------------------------------
 // The row kernel, for the case where the stride-1 index keeps its place and rows are contiguous in both tensors
 // (paper Section 3.1, case 1: the first column is copied, inside loops over the other indices).  B is walked in the order of its
-// multi-index: workgroup w moves the `chunk` vectors that start at vector w * chunk, so consecutive
-// workgroups write consecutive memory (a dense B is written front to back like a copy), and every lane gathers
-// its vectors from the rows of A.  No tiles, no LDS, no tables: a lane finds its row by one division and the
-// row's place in both tensors by one division per index.  Where rows are not a multiple of the vector, the last
-// vector of a row is moved back to end with the row and repeats up to V-1 elements of its neighbour with the same
-// values (only where B is not read: with beta != 0 the planner picks a vector that divides the row).
+// multi-index: a workgroup moves a chunk of consecutive vectors, so consecutive chunks are consecutive memory (a dense B
+// is written front to back like a copy), and every lane gathers its vectors from the rows of A.  No tiles, no LDS, no
+// tables: a lane finds its row by one division and the row's place in both tensors by one division per index.
+// Dense B (FLAT): vectors are counted from B's first element, 16-byte aligned as B itself is, whatever the rows' length;
+// one that spans the end of a row takes its two parts from two rows of A (a second load for the few lanes that need
+// it), and every element of B is written once, so it serves an update too.  917 x 374 x 153 fp32 (0,2,1): 70 us; with
+// vectors counted row by row, 4-byte aligned, 76 us.
+// Else: a row holds `slots` vectors; where it is not a multiple of the vector, its last one is moved back to end with the
+// row and repeats up to V-1 elements of its neighbour with the same values (only where B is not read: with beta != 0
+// the planner picks a vector that divides the row).
+// Chunks are dealt to the XCDs 32 at a time: neighbours share lines of A, and of B where a chunk ends inside a line; dealt
+// one by one to eight L2s the same 917 x 374 x 153 took 76 us and 72 us in groups (before FLAT), 384^3 75.4 and 73.5 us.
 // ---------------------------------------------------------------------------------
 constexpr int kRowsThreads = 256;
 
-template <typename TA, typename TB, int MODE, int V, int U>
+template <typename TA, typename TB, int MODE, int V, int U, bool FLAT>
 __global__ __launch_bounds__(kRowsThreads) void rows_kernel(const RowsParams p, const TA* __restrict__ A, TB* __restrict__ B)
 {
     constexpr int32_t kScaleA = (int32_t)sizeof(TA), kScaleB = (int32_t)sizeof(TB);
+    const uint32_t block = rows_block(p, blockIdx.x);
+    if (block >= p.blocks) return;
     const Epilogue<TA, TB, MODE> epi(p.alpha, p.beta);
-    const int64_t base = (int64_t)blockIdx.x * (int64_t)p.chunk;
+    const int64_t base = (int64_t)block * (int64_t)p.chunk * (FLAT ? V : 1);
     const int64_t row0_wide = base / (int64_t)p.slots;                  // wave-uniform: once per workgroup
     const uint32_t row0 = (uint32_t)row0_wide;
     const uint32_t slot0 = (uint32_t)(base - row0_wide * (int64_t)p.slots);
@@ -365,20 +373,56 @@ __global__ __launch_bounds__(kRowsThreads) void rows_kernel(const RowsParams p, 
         Pack<TA, V> ra[U];
         Pack<TB, V> rb[U];
         int64_t to[U];
-        bool valid[U];
+        int32_t count[U];                                               // elements to store: V, 0 past the end, fewer at the end of a flat B
         // a lane past the end of the tensor loads the first vector instead and stores nothing, so that no load
-        // sits in divergent control flow
+        // sits in divergent control flow (the second part of a split vector is the exception)
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const RowAccess x = rows_access(p, base, row0, slot0, (uint32_t)u * kRowsThreads + threadIdx.x);
-            valid[u] = x.valid;
-            to[u] = x.at.b * kScaleB;
-            ra[u] = load_pack<TA, V, NTA>(Ab, x.at.a * kScaleA);
-            if (MODE == TTC_EPI_AXPBY) rb[u] = load_pack<TB, V, NTB>(Bb, to[u]);
+            const uint32_t k = (uint32_t)u * kRowsThreads + threadIdx.x;
+            if (FLAT) {
+                const FlatAccess x = flat_access(p, base, row0, slot0, k);
+                count[u] = x.valid ? (int32_t)(x.left < V ? x.left : V) : 0;
+                to[u] = (count[u] == V ? x.b : p.elements - V) * kScaleB;               // where B is loaded from
+                ra[u] = load_pack<TA, V, NTA>(Ab, x.a * kScaleA);
+                if (MODE == TTC_EPI_AXPBY) rb[u] = load_pack<TB, V, NTB>(Bb, to[u]);
+                if (V > 1 && x.split) {
+                    const Pack<TA, V> next = load_pack<TA, V, false>(Ab, x.a_next * kScaleA);
+                    Pack<TA, V> both;
+#pragma unroll
+                    for (int j = 0; j < V; ++j) {
+                        TA v = next.v[0];
+#pragma unroll
+                        for (int e = 0; e < V; ++e) {
+                            if (e == j + V - (int)x.head) v = ra[u].v[e];                // j < head: the last elements of row r
+                            if (e == j - (int)x.head) v = next.v[e];
+                        }
+                        both.v[j] = v;
+                    }
+                    ra[u] = both;
+                }
+                if (V > 1 && MODE == TTC_EPI_AXPBY && count[u] > 0 && count[u] < V) {    // the last vector of B: what was loaded ends with B
+                    Pack<TB, V> last;
+#pragma unroll
+                    for (int j = 0; j < V; ++j) {
+                        TB v = rb[u].v[0];
+#pragma unroll
+                        for (int e = 0; e < V; ++e) if (e == j + V - count[u]) v = rb[u].v[e];
+                        last.v[j] = v;
+                    }
+                    rb[u] = last;
+                }
+                if (count[u] > 0) to[u] = x.b * kScaleB;
+            } else {
+                const RowAccess x = rows_access(p, base, row0, slot0, k);
+                count[u] = x.valid ? V : 0;
+                to[u] = x.at.b * kScaleB;
+                ra[u] = load_pack<TA, V, NTA>(Ab, x.at.a * kScaleA);
+                if (MODE == TTC_EPI_AXPBY) rb[u] = load_pack<TB, V, NTB>(Bb, to[u]);
+            }
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            if (!valid[u]) continue;
+            if (count[u] == 0) continue;
             Pack<TB, V> out;
 #pragma unroll
             for (int j = 0; j < V; ++j) {
@@ -386,7 +430,12 @@ __global__ __launch_bounds__(kRowsThreads) void rows_kernel(const RowsParams p, 
                 if (MODE == TTC_EPI_AXPBY) old = rb[u].v[j];
                 out.v[j] = epi(ra[u].v[j], old);
             }
-            store_pack<TB, V, NTB>(Bb, to[u], out);
+            if (!FLAT || V == 1 || count[u] == V) {
+                store_pack<TB, V, NTB>(Bb, to[u], out);
+            } else {
+#pragma unroll
+                for (int j = 0; j < V; ++j) if (j < count[u]) reinterpret_cast<TB*>(Bb + to[u])[j] = out.v[j];
+            }
         }
     };
     if (p.nt_a) { if (p.nt_b) run(std::true_type(), std::true_type()); else run(std::true_type(), std::false_type()); }
@@ -742,30 +791,45 @@ inline hipError_t launch_one(const KernelParams& kp, const void* A, void* B, uin
     return hipLaunchKernel(fn, dim3(grid), dim3(threads), args, (size_t)lds_bytes, stream);
 }
 
-template <typename TA, typename TB, int MODE, int V, int U>
+template <typename TA, typename TB, int MODE, int V, int U, bool FLAT>
 inline hipError_t launch_rows_unrolled(const Candidate& c, const void* A, void* B, hipStream_t stream)
 {
     RowsParams rp = c.rows;
     rp.nt_a = c.kp.nt_a;
     rp.nt_b = c.kp.nt_b;
-    if (rp.vec != V || rp.unroll != U || c.threads != kRowsThreads || rp.chunk != (uint32_t)(kRowsThreads * U) ||
-        rp.row < (uint32_t)V || rp.slots != (rp.row + V - 1) / V || rp.vectors < 1 || (MODE == TTC_EPI_AXPBY && rp.overlap)) return hipErrorInvalidValue;
-    const int64_t grid = (rp.vectors + rp.chunk - 1) / rp.chunk;
+    rp.xcd_remap = c.kp.xcd_remap;
+    if (rp.vec != V || rp.unroll != U || c.threads != kRowsThreads || rp.chunk != (uint32_t)(kRowsThreads * U) || rp.row < (uint32_t)V ||
+        rp.slots != (FLAT ? rp.row : (rp.row + V - 1) / V) || rp.slot_div.div != rp.slots || rp.flat != (FLAT ? 1 : 0) || rp.vectors < 1 || rp.rows < 1 ||
+        (MODE == TTC_EPI_AXPBY && rp.overlap) || (int64_t)rp.blocks != (rp.vectors + rp.chunk - 1) / rp.chunk ||
+        (FLAT && (rp.vectors != (rp.elements + V - 1) / V || rp.elements != (int64_t)rp.rows * rp.row))) return hipErrorInvalidValue;
+    const int64_t grid = rows_grid(rp);
     if (grid < 1 || grid > INT32_MAX) return hipErrorInvalidValue;
     const TA* a = static_cast<const TA*>(A);
     TB* b = static_cast<TB*>(B);
     void* args[] = {&rp, &a, &b};
-    return hipLaunchKernel(reinterpret_cast<const void*>(&rows_kernel<TA, TB, MODE, V, U>), dim3((uint32_t)grid), dim3(kRowsThreads), args, 0, stream);
+    return hipLaunchKernel(reinterpret_cast<const void*>(&rows_kernel<TA, TB, MODE, V, U, FLAT>), dim3((uint32_t)grid), dim3(kRowsThreads), args, 0, stream);
 }
 
 template <typename TA, typename TB, int MODE, int V>
 inline hipError_t launch_rows_one(const Candidate& c, const void* A, void* B, hipStream_t stream)
 {
     switch (c.rows.unroll) {
-    case 1: return launch_rows_unrolled<TA, TB, MODE, V, 1>(c, A, B, stream);
-    case 2: return launch_rows_unrolled<TA, TB, MODE, V, 2>(c, A, B, stream);
-    case 4: return launch_rows_unrolled<TA, TB, MODE, V, 4>(c, A, B, stream);
-    case 8: return launch_rows_unrolled<TA, TB, MODE, V, 8>(c, A, B, stream);
+    case 1: return launch_rows_unrolled<TA, TB, MODE, V, 1, false>(c, A, B, stream);
+    case 2: return launch_rows_unrolled<TA, TB, MODE, V, 2, false>(c, A, B, stream);
+    case 4: return launch_rows_unrolled<TA, TB, MODE, V, 4, false>(c, A, B, stream);
+    case 8: return launch_rows_unrolled<TA, TB, MODE, V, 8, false>(c, A, B, stream);
+    default: return hipErrorInvalidValue;
+    }
+}
+
+template <typename TA, typename TB, int MODE, int V>
+inline hipError_t launch_rows_flat(const Candidate& c, const void* A, void* B, hipStream_t stream)
+{
+    switch (c.rows.unroll) {
+    case 1: return launch_rows_unrolled<TA, TB, MODE, V, 1, true>(c, A, B, stream);
+    case 2: return launch_rows_unrolled<TA, TB, MODE, V, 2, true>(c, A, B, stream);
+    case 4: return launch_rows_unrolled<TA, TB, MODE, V, 4, true>(c, A, B, stream);
+    case 8: return launch_rows_unrolled<TA, TB, MODE, V, 8, true>(c, A, B, stream);
     default: return hipErrorInvalidValue;
     }
 }
@@ -779,6 +843,7 @@ inline hipError_t launch_vec(const Candidate& c, const void* A, void* B, hipStre
     if (c.kernel_class == kKernelLines) return launch_lines<TA, TB, MODE>(c, A, B, s);
     if (c.kernel_class == TTC_KERNEL_ROWS) {
         const int v = c.rows.vec;
+        if (c.rows.flat) return v == VD ? launch_rows_flat<TA, TB, MODE, VD>(c, A, B, s) : hipErrorInvalidValue;
         if (v == 1) return launch_rows_one<TA, TB, MODE, 1>(c, A, B, s);
         if (v == 2 && VD >= 2) return launch_rows_one<TA, TB, MODE, (VD >= 2 ? 2 : 1)>(c, A, B, s);
         if (v == 4 && VD >= 4) return launch_rows_one<TA, TB, MODE, (VD >= 4 ? 4 : 1)>(c, A, B, s);

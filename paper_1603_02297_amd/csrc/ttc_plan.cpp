@@ -930,16 +930,18 @@ MicroArgs micro_args(const Candidate& c)
     return a;
 }
 
-// The row kernel's candidate: B walked front to back, `vec` elements per lane and access.  Needs rows that are
-// contiguous in both tensors and hold at least one vector, fewer than 2^31 rows, rows shorter than 2^30.
-static bool make_rows_candidate(const Problem& P, int vec, int unroll, Candidate* out)
+// The row kernel's candidate: B walked front to back, `vec` elements per lane and access; `flat`: vectors counted through
+// a dense B.  Needs rows that are contiguous in both tensors and hold at least one vector, fewer than 2^31 rows, rows
+// shorter than 2^30.
+static bool make_rows_candidate(const Problem& P, int vec, int unroll, bool flat, Candidate* out)
 {
     if (P.perm[0] != 0 || P.stride_a[0] != 1 || P.stride_b[0] != 1) return false;
     const int64_t row = P.size[0], rows = P.elements / P.size[0];
     if (row < vec || row >= (int64_t(1) << 30) || rows >= (int64_t(1) << 31)) return false;
+    if (flat && P.span_b != P.elements) return false;
     // rows that are not a multiple of the vector: their last vector overlaps its neighbour, which is only
     // harmless where B is not read
-    if (row % vec != 0 && P.epilogue == TTC_EPI_AXPBY) return false;
+    if (!flat && row % vec != 0 && P.epilogue == TTC_EPI_AXPBY) return false;
     Candidate C;
     std::memset(&C, 0, sizeof(C));
     C.kernel_class = TTC_KERNEL_ROWS;
@@ -951,11 +953,14 @@ static bool make_rows_candidate(const Problem& P, int vec, int unroll, Candidate
     r.vec = vec;
     r.unroll = unroll;
     r.row = (uint32_t)row;
-    r.slots = (uint32_t)ceil_div(row, vec);
+    r.rows = (uint32_t)rows;
+    r.elements = P.elements;
+    r.flat = flat ? 1 : 0;
+    r.slots = (uint32_t)(flat ? row : ceil_div(row, vec));
     r.chunk = (uint32_t)(C.threads * r.unroll);
-    r.overlap = (row % vec != 0) ? 1 : 0;
+    r.overlap = (!flat && row % vec != 0) ? 1 : 0;
     r.slot_div = make_fastdiv(r.slots);
-    r.vectors = rows * (int64_t)r.slots;
+    r.vectors = flat ? ceil_div(P.elements, vec) : rows * (int64_t)r.slots;
     for (int d = 0; d < kMaxDim; ++d) {
         r.size_div[d] = make_fastdiv(1);
         r.stride_a[d] = 0;
@@ -979,6 +984,8 @@ static bool make_rows_candidate(const Problem& P, int vec, int unroll, Candidate
     kp.a.partial = kp.b.partial = r.overlap;
     kp.num_tiles = (uint32_t)grid;
     kp.grid = (uint32_t)grid;
+    r.blocks = (uint32_t)grid;
+    if (!set_tile_mapping(&kp, kDefaultTileMapping)) return false;
     for (int k = 0; k < kMaxDim; ++k) {
         C.tile[k] = (k == 0) ? (int)row : 1;
         C.tile_order[k] = (k < P.ndim) ? P.perm[k] : k;
@@ -1097,6 +1104,27 @@ static double rows_cost(const Problem& P, const Candidate& C)
 {
     const double row_bytes = (double)P.size[0] * P.eb_a;
     auto oct_below = [](double x, double ref) { return x < ref ? std::log2(ref / x) : 0.0; };
+    if (C.rows.flat) {
+        // Dense B: fitted to 220 problems with rows of 20 bytes to 64 KB, 2 to 200 MB, fp32, fp64, complex128 and fp32 ->
+        // fp64, against the other families' first candidate.  Whole lines: ahead from 128-byte rows on (200 MB: 66-68 us
+        // against 72-75); rows that start inside lines: from 264-byte rows on (71-79 against 88-91; 68-byte rows 102 against
+        // 93); below 8 MB always (2.6-4 us against 5.4-8: no tables, no barrier); updates of ragged rows need no narrow
+        // vectors (340-byte rows 104 against 153-166).
+        const double traffic = (double)P.elements * (P.eb_a + (P.epilogue == TTC_EPI_AXPBY ? 2 : 1) * P.eb_b);
+        const bool whole = P.size[0] * P.eb_a % kLineBytes == 0;
+        double e = -0.373;
+        if (traffic < 8e6) e -= 0.425;
+        else if (traffic < 1e8) e -= 0.128;
+        if (!whole) e += 0.124;
+        if (traffic >= 1e8) e += 0.049 * oct_below(row_bytes, 128.0) + (whole ? 0.0 : 0.094 * oct_below(row_bytes, 512.0));
+        else if (!whole) e += 0.103 * oct_below(row_bytes, 128.0);
+        if (P.epilogue == TTC_EPI_AXPBY && P.size[0] % C.rows.vec != 0) e -= 0.131;
+        // bytes a lane keeps in flight: 16 (with an update 32); every doubling costs 1-5 %, eight bytes (the narrow side of
+        // fp32 -> fp64) 10 %
+        const double flight = (double)C.rows.vec * C.rows.unroll * P.eb_a;
+        e += flight < 16.0 ? (P.epilogue == TTC_EPI_AXPBY ? 0.0 : 0.10) : 0.03 * std::log2(flight / 16.0);
+        return std::exp(e);
+    }
     double e = -0.30;
     e += 0.60 * oct_below(row_bytes, 512.0);                            // 576-byte rows: 94 % of a copy; 340-byte rows: 62 %
     if (std::fmod(row_bytes, 128.0) != 0.0) e += 0.04;                  // rows that share lines with their neighbours
@@ -1326,8 +1354,14 @@ static bool same_config(const Candidate& x, const Candidate& y)
 // search tries the other settings on its finalists.)
 void default_streaming(const Problem& P, Candidate* c)
 {
-    if (c->kernel_class == TTC_KERNEL_ROWS) {      // B is written front to back and A's rows are read once: stream both
-        c->kp.nt_a = c->kp.nt_b = 1;
+    if (c->kernel_class == TTC_KERNEL_ROWS) {
+        // B is written front to back: streamed.  A is read once, but rows that start inside lines share them, and a
+        // tensor of a quarter of the last-level cache may still be there: streamed only if it is larger and its rows
+        // are whole lines or long (25 MB problems run 13 % faster without, 200 MB ones with 128-byte to 64 KB rows
+        // 3 % faster with the hint, 340- and 532-byte rows 5-8 % slower).
+        const int64_t row_bytes = P.size[0] * P.eb_a;
+        c->kp.nt_a = P.elements * P.eb_a >= (int64_t(64) << 20) && (row_bytes % kLineBytes == 0 || row_bytes >= 1024) ? 1 : 0;
+        c->kp.nt_b = 1;
         return;
     }
     if (c->kernel_class == kKernelLines) {
@@ -1451,10 +1485,12 @@ static void enumerate(const Problem& P, std::vector<Candidate>& out_list, bool q
     if (stride1_fixed) {
         const int vwide = std::max(1, 16 / eb);
         for (int v = vwide; v >= 1; v /= 2) {
-            for (int unroll : {2, 4, 1, 8}) {
+            for (int unroll : {1, 2, 4, 8}) {
                 Candidate c;
-                if (make_rows_candidate(P, v, unroll, &c)) add_candidate(P, out, c);
-                if (quick) break;
+                // a dense B is taken flat; only in the narrow forms, which the widest vector makes pointless, row by row
+                if (v == vwide ? make_rows_candidate(P, v, unroll, true, &c) || make_rows_candidate(P, v, unroll, false, &c)
+                               : make_rows_candidate(P, v, unroll, false, &c)) add_candidate(P, out, c);
+                if (quick && unroll == 2) break;
             }
         }
     }
@@ -1860,13 +1896,16 @@ int ttc_debug_emulate_map(ttc_plan_t plan, int64_t* b_from_a)
 static int emulate_rows(const ttc::Problem& P, const ttc::Candidate& C, int64_t* b_from_a)
 {
     using namespace ttc;
-    const RowsParams& p = C.rows;
+    RowsParams p = C.rows;
+    p.xcd_remap = C.kp.xcd_remap;               // as the launch does
     for (int64_t i = 0; i < P.span_b; ++i) b_from_a[i] = -1;
     const int64_t rows = P.elements / P.size[0];
     if ((p.vec != 1 && p.vec != 2 && p.vec != 4) || (p.unroll != 1 && p.unroll != 2 && p.unroll != 4 && p.unroll != 8) || C.threads != 256 ||
-        p.chunk != (uint32_t)(C.threads * p.unroll) || p.row < (uint32_t)p.vec || p.row != (uint32_t)P.size[0] ||
-        p.slots != (p.row + (uint32_t)p.vec - 1) / (uint32_t)p.vec || p.vectors != rows * (int64_t)p.slots ||
-        p.overlap != (P.size[0] % p.vec != 0 ? 1 : 0) || (p.overlap && P.epilogue == TTC_EPI_AXPBY) ||
+        p.chunk != (uint32_t)(C.threads * p.unroll) || p.row < (uint32_t)p.vec || p.row != (uint32_t)P.size[0] || p.rows != (uint32_t)rows ||
+        p.elements != P.elements || (p.flat && P.span_b != P.elements) || p.slot_div.div != p.slots ||
+        p.slots != (p.flat ? p.row : (p.row + (uint32_t)p.vec - 1) / (uint32_t)p.vec) ||
+        p.vectors != (p.flat ? (P.elements + p.vec - 1) / p.vec : rows * (int64_t)p.slots) || (int64_t)p.blocks != (p.vectors + p.chunk - 1) / p.chunk ||
+        p.overlap != (!p.flat && P.size[0] % p.vec != 0 ? 1 : 0) || (p.overlap && P.epilogue == TTC_EPI_AXPBY) ||
         P.size[0] >= (int64_t(1) << 30) || rows >= (int64_t(1) << 31))
         return TTC_ERR_INTERNAL;
     auto inside = [&](int64_t off, const int64_t* stride, bool b_side) {
@@ -1881,11 +1920,28 @@ static int emulate_rows(const ttc::Problem& P, const ttc::Candidate& C, int64_t*
     };
     int64_t written = 0;
     bool bad = false;
-    const int64_t grid = (p.vectors + p.chunk - 1) / p.chunk;
+    const int64_t grid = rows_grid(p);
+    std::vector<char> seen((size_t)p.blocks, 0);
     for (int64_t wg = 0; wg < grid && !bad; ++wg) {
-        const int64_t base = wg * (int64_t)p.chunk;
+        const uint32_t block = rows_block(p, (uint32_t)wg);
+        if (block >= p.blocks) continue;
+        if (seen[block]) return TTC_ERR_INTERNAL;
+        seen[block] = 1;
+        const int64_t base = block * (int64_t)p.chunk * (p.flat ? p.vec : 1);
         const int64_t row0_wide = base / (int64_t)p.slots;
         const uint32_t row0 = (uint32_t)row0_wide, slot0 = (uint32_t)(base - row0_wide * (int64_t)p.slots);
+        for (uint32_t i = 0; p.flat && i < p.chunk && !bad; ++i) {
+            const FlatAccess x = flat_access(p, base, row0, slot0, i);
+            for (int j = 0; j < p.vec; ++j) {                // what is loaded: whole vectors inside the tensors
+                if (!inside(x.a + j, P.stride_a, false) || (x.split && !inside(x.a_next + j, P.stride_a, false))) bad = true;
+                if (!x.valid || j >= x.left) continue;
+                const int64_t ea = j < (int)x.head ? x.a + j + (x.split ? p.vec - (int)x.head : 0) : x.a_next + j - (int)x.head, eo = x.b + j;
+                if (bad || !inside(ea, P.stride_a, false) || !inside(eo, P.stride_b, true) || b_from_a[eo] != -1) { bad = true; break; }
+                b_from_a[eo] = ea;
+                ++written;
+            }
+        }
+        if (p.flat) continue;
         for (int u = 0; u < p.unroll && !bad; ++u)
             for (uint32_t tid = 0; tid < (uint32_t)C.threads && !bad; ++tid) {
                 const RowAccess x = rows_access(p, base, row0, slot0, (uint32_t)u * (uint32_t)C.threads + tid);

@@ -70,6 +70,51 @@ TTC_HD RowAccess rows_access(const RowsParams& p, int64_t base, uint32_t row0, u
     return r;
 }
 
+// Flat: vector `k` of the workgroup's chunk, which starts at element `base` of a dense B = row `row0`, column `col0`.  Its first
+// `head` elements end row r (all of them unless the row ends inside the vector), the others begin the next row: `a` is where
+// a whole vector of row r lies that holds the head (as its last elements if the row ends), `a_next` where row r + 1 begins.
+// left: elements of B from the vector's first on (fewer than vec only at the end of B).  Rows hold at least one vector.
+struct FlatAccess { int64_t a, a_next, b, left; uint32_t head; bool valid, split; };
+
+TTC_HD FlatAccess flat_access(const RowsParams& p, int64_t base, uint32_t row0, uint32_t col0, uint32_t k)
+{
+    const uint32_t vec = (uint32_t)p.vec, x = col0 + k * vec;
+    const uint32_t rl = fdiv(x, p.slot_div);
+    const uint32_t c = x - rl * p.row;
+    FlatAccess f;
+    f.b = base + (int64_t)k * vec;
+    f.left = p.elements - f.b;
+    f.valid = f.left > 0;
+    const uint32_t r = f.valid ? row0 + rl : 0u, col = f.valid ? c : 0u;      // past the end: the first vector, never stored
+    f.head = p.row - col < vec ? p.row - col : vec;
+    f.split = f.head < vec;
+    f.a = rows_place(p, r, f.split ? p.row - vec : col).a;
+    f.a_next = f.split ? rows_place(p, r + 1u < p.rows ? r + 1u : r, 0u).a : 0;
+    return f;
+}
+
+// Which chunk workgroup `wg` of a row-kernel launch moves (p.blocks: none): consecutive chunks, which share a line of
+// B and lines of A, go to one XCD a few at a time, as with tiles.
+TTC_HD uint32_t rows_block(const RowsParams& p, uint32_t wg)
+{
+    if (p.xcd_remap == 0) return wg;
+    const uint32_t x = wg & 7u, q = wg >> 3;
+    if (p.xcd_remap == 1) {
+        const uint32_t per = (p.blocks + 7u) / 8u, block = x * per + q;
+        return q < per && block < p.blocks ? block : p.blocks;
+    }
+    const uint32_t log = (uint32_t)p.xcd_remap, block = ((x + 8u * (q >> log)) << log) + (q & ((1u << log) - 1u));
+    return block < p.blocks ? block : p.blocks;
+}
+
+// Workgroups to launch so that every chunk has one: whole rounds of chunks over the XCDs.
+TTC_HD int64_t rows_grid(const RowsParams& p)
+{
+    if (p.xcd_remap == 0) return p.blocks;
+    const int64_t round = p.xcd_remap == 1 ? 8 : int64_t(8) << p.xcd_remap;
+    return (p.blocks + round - 1) / round * round;
+}
+
 // ---- which tiles a workgroup walks ---------------------------------------------------------
 // Consecutive workgroup ids land on consecutive XCDs (8 of them, each with its own L2).  Every
 // XCD owns one contiguous range of tile ids; its workgroups take the tiles of that range round

@@ -1,0 +1,86 @@
+"""The row kernel over a dense B, whose vectors run across the ends of rows, and over a padded one: every candidate and
+every way of dealing its chunks to the XCDs against the oracle, replayed on the host and run on the GPU.  Sizes: rows
+of one vector, one element more, odd ones; a tensor that is no multiple of the vector; chunks that do not fill a round."""
+import numpy as np
+import pytest
+
+import oracle
+import paper_1603_02297_amd as ttc
+from paper_1603_02297_amd import workloads as wl
+
+# sizes, perm, lda, ldb
+SHAPES = [
+    ((4, 3, 5), (0, 2, 1), None, None),
+    ((5, 3, 7), (0, 2, 1), None, None),
+    ((7, 31, 29), (0, 2, 1), None, None),
+    ((45, 9, 37), (0, 2, 1), (47, 9, 37), None),          # A padded, B dense
+    ((45, 9, 37), (0, 2, 1), None, (48, 37, 9)),          # B padded: counted row by row
+    ((13, 5, 6, 4), (0, 3, 1, 2), None, None),
+    ((1001,), (0,), (1003,), None),                       # one row
+]
+DTYPES = [wl.F32, wl.F64, wl.C128, wl.F32_F64, wl.F64_F32]
+
+
+def rows_candidates(plan):
+    for k in range(ttc.ttc_plan_candidate_count(plan)):
+        ttc.ttc_plan_select_candidate(plan, k)
+        info = ttc.ttc_plan_get_info(plan)
+        if info["kernel_class"] == ttc.TTC_KERNEL_ROWS:
+            for mapping in (0, 1, 2, 5):
+                ttc.ttc_plan_set_tile_mapping(plan, mapping)
+                yield k, mapping, info
+
+
+@pytest.mark.parametrize("dtype", DTYPES, ids=[wl.DTYPE_NAME[d] for d in DTYPES])
+def test_walks_of_every_row_candidate(dtype):
+    seen = 0
+    for sizes, perm, lda, ldb in SHAPES:
+        for beta in (0.0, 1.0):
+            p = ttc.ttc_plan_create_ex(dtype, len(sizes), sizes, perm, lda, ldb, 1.0, beta)
+            want = [-1] * ttc.ttc_plan_get_info(p)["span_b"]
+            for off_a, off_b in oracle.element_pairs(sizes, perm, lda, ldb):
+                want[off_b] = off_a
+            for k, mapping, info in rows_candidates(p):
+                assert list(ttc.ttc_debug_emulate_map(p)) == want, (sizes, perm, k, mapping, info)
+                seen += 1
+            ttc.ttc_plan_destroy(p)
+    assert seen >= 100
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", DTYPES, ids=[wl.DTYPE_NAME[d] for d in DTYPES])
+def test_row_kernel_against_the_oracle(dtype):
+    """Every epilogue; what lies behind B stays as it was.  Fixed evaluation order on both sides: bit-equal but for the
+    ulp the library allows."""
+    import torch
+    dev = torch.device("cuda:0")
+    stream = torch.cuda.current_stream().cuda_stream
+    prod = lambda v: int(np.prod(v))  # noqa: E731
+    ran = 0
+    cplx = wl.COMPONENTS[dtype] == 2
+    for shape, (sizes, perm, lda, ldb) in enumerate(SHAPES):
+        na, nb = prod(lda or sizes), prod(ldb or sizes)
+        A = wl.uniform_tensor(dtype, na, 7200 + shape, "a")
+        B0 = wl.uniform_tensor(dtype, nb, 7300 + shape, "b")
+        comp, room = wl.COMPONENTS[dtype], 16
+        dA = torch.from_numpy(A).to(dev)
+        for alpha, beta in ((1.0, 0.0), (0.5 + 0.5j if cplx else 1.5, 0.0), (0.75, 1.0 + 0.5j if cplx else -1.25)):
+            want = oracle.transpose(dtype, sizes, perm, alpha, beta, A, B0.copy(), 4, lda=lda, ldb=ldb)
+            plan = ttc.ttc_plan_create_ex(dtype, len(sizes), sizes, perm, lda, ldb, alpha, beta)
+            try:
+                for k, mapping, info in rows_candidates(plan):
+                    buf = torch.full((nb * comp + 2 * room,), 77.0, dtype=torch.from_numpy(B0).dtype, device=dev)
+                    buf[room:room + nb * comp] = torch.from_numpy(B0).to(dev)
+                    ttc.ttc_execute(plan, dA.data_ptr(), buf.data_ptr() + room * buf.element_size(), stream)
+                    torch.cuda.synchronize()
+                    got = buf.cpu().numpy()
+                    assert (got[:room] == 77).all() and (got[room + nb * comp:] == 77).all(), (sizes, perm, k, info)
+                    got = got[room:room + nb * comp]
+                    if complex(alpha) == 1 and complex(beta) == 0:
+                        assert np.array_equal(got, want), (sizes, perm, k, mapping, info)
+                    else:
+                        assert np.abs(got - want).max() <= np.spacing(np.abs(want).max()), (sizes, perm, alpha, beta, k, mapping, info)
+                    ran += 1
+            finally:
+                ttc.ttc_plan_destroy(plan)
+    assert ran >= 100
