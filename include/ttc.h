@@ -51,7 +51,8 @@ enum {
 /* Kernel families (paper Section 3.1: the stride-1 index keeps its place, or not). */
 enum { TTC_KERNEL_DIRECT = 0 /* tiles, no staging: stride-1 index fixed */, TTC_KERNEL_LDS = 1 /* tile staged through LDS: a box over up to four
                                indices, or (unroll != 0) the line kernel: columns of A's direction by whole 128-byte lines of B */,
-       TTC_KERNEL_ROWS = 2 /* stride-1 index fixed: B walked front to back, rows gathered from A */,
+       TTC_KERNEL_ROWS = 2 /* B walked front to back: rows gathered from A (stride-1 index fixed), or single elements (the gather
+                               kernel: small problems, any permutation) */,
        TTC_KERNEL_MICRO = 3 /* tile over the two stride-1 indices only (each possibly merged with the index next to it in
                                its tensor): 128-bit LDS accesses, XOR-swizzled rows, register transposes of 4x4 (2x2)
                                blocks; one precision of 4- or 8-byte elements */ };
@@ -80,7 +81,8 @@ typedef struct {
     int     digit_tile_b[4], digit_lane_b[4]; /* the same for the store walk */
     int     tile_order[TTC_MAX_DIM];       /* fused indices from fastest to slowest in the workgroup-id -> tile map */
     int     lds_stride[TTC_MAX_DIM];       /* element stride of each fused index inside the LDS tile (0 = unused) */
-    int     vec_a, vec_b;                  /* elements per lane per global access on the A side / B side */
+    int     vec_a, vec_b;                  /* elements per lane per global access on the A side / B side (gather kernel: elements
+                                              a lane moves; it fetches them from A one by one) */
     int     partial_a, partial_b;          /* 1: runs are not a multiple of the vector: the last vector of a run is moved
                                               back to end with the run and overlaps its neighbour */
     int     threads;                       /* workgroup size */

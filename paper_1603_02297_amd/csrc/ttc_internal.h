@@ -210,7 +210,7 @@ struct MicroArgs {
     MicroParams micro;
 };
 
-// Parameters of the row kernel (stride-1 index fixed: rows are contiguous in both tensors).  B is walked in
+// Parameters of the row kernel (stride-1 index fixed: rows are contiguous in both tensors), and of the gather kernel.  B is walked in
 // the order of its multi-index, so the writes of consecutive workgroups are consecutive in memory.
 struct RowsParams {
     int32_t  n;                      // fused number of indices; index 0 is the row
@@ -224,9 +224,11 @@ struct RowsParams {
     int32_t  flat;                   // 1: B is dense: vectors are counted through B from its first element, across the ends of rows
     int32_t  xcd_remap;              // how the workgroups' chunks are dealt to the XCDs (as KernelParams::xcd_remap)
     uint32_t blocks;                 // chunks, one per workgroup
+    uint32_t per_xcd;                // gather kernel: 0, or chunks are numbered so that every eighth is the next one in B (eight ranges of
+                                     // this many chunks side by side)
     uint32_t rows;                   // rows of the tensor
     FastDiv  slot_div;               // x / slots
-    FastDiv  size_div[kMaxDim];      // extent of B's index d, d = 1 .. n-1 (entry 0 unused)
+    FastDiv  size_div[kMaxDim];      // extent of B's index d, d = 1 .. n-1 (entry 0: gather kernel only)
     int64_t  stride_a[kMaxDim];      // element stride in A of B's index d
     int64_t  stride_b[kMaxDim];      // element stride in B of B's index d
     int64_t  vectors;                // rows * slots; flat: ceil(elements / vec)
@@ -238,10 +240,12 @@ struct RowsParams {
 // The line kernel's internal class.  Plans report it as TTC_KERNEL_LDS (its tile is staged through LDS) with a
 // non-zero `unroll`.
 constexpr int kKernelLines = 4;
+// The gather kernel's; reported as TTC_KERNEL_ROWS (B is walked front to back).
+constexpr int kKernelGather = 5;
 
 // One candidate launch configuration ("candidate" in the paper's Section 3).
 struct Candidate {
-    int      kernel_class;           // TTC_KERNEL_*, or kKernelLines
+    int      kernel_class;           // TTC_KERNEL_*, kKernelLines or kKernelGather
     int      threads;
     int      wg_per_cu;              // workgroups launched per compute unit (each walks several tiles)
     int      lds_bytes;              // dynamic LDS per workgroup: shared tile records, spare slots, position tables, one or two tile buffers
@@ -252,6 +256,7 @@ struct Candidate {
     int      dtile_b[kBoxDims], dlane_b[kBoxDims];
     int      lds_conflict_a, lds_conflict_b;
     double   score;                  // heuristic cost, smaller is better
+    double   model_us;               // gather kernel: modelled time
     float    tuned_ms;
     KernelParams kp;                 // box kernels (staged and direct); the streaming flags and the tile mapping of every class
     RowsParams rows;                 // row kernel

@@ -791,6 +791,78 @@ inline hipError_t launch_one(const KernelParams& kp, const void* A, void* B, uin
     return hipLaunchKernel(fn, dim3(grid), dim3(threads), args, (size_t)lds_bytes, stream);
 }
 
+// ---------------------------------------------------------------------------------
+// The gather kernel: B is walked front to back, a lane writes 16 bytes of it and fetches their elements from A one by one.
+// No tiles, no LDS, no barrier: one memory latency between launch and store, which is what a small problem costs.
+// ---------------------------------------------------------------------------------
+template <typename TA, typename TB, int MODE, int V>
+__global__ __launch_bounds__(kRowsThreads) void gather_kernel(const RowsParams p, const TA* __restrict__ A, TB* __restrict__ B)
+{
+    static_assert(V * sizeof(TB) == 16, "one 16-byte vector of B");
+    const uint32_t block = rows_block(p, blockIdx.x);
+    if (block >= p.blocks) return;
+    const uint32_t e = gather_first(p, block, threadIdx.x);
+    if ((int64_t)e >= p.elements) return;
+    const Epilogue<TA, TB, MODE> epi(p.alpha, p.beta);
+    const int32_t count = p.elements - (int64_t)e < V ? (int32_t)(p.elements - (int64_t)e) : V;
+    auto run = [&](auto stream_a, auto stream_b) {
+        constexpr bool NTA = decltype(stream_a)::value, NTB = decltype(stream_b)::value;
+        const GatherPlace g = gather_place(p, e);
+        GatherPlace x[V];
+#pragma unroll
+        for (int j = 0; j < V; ++j) x[j] = j == 0 ? g : gather_next(p, g, e, (uint32_t)j);
+        const bool whole = count == V && (p.flat || g.first + (uint32_t)V <= p.row);      // one contiguous vector of B
+        Pack<TA, 1> a[V];
+#pragma unroll
+        for (int j = 0; j < V; ++j) a[j] = load_pack<TA, 1, NTA>(reinterpret_cast<const unsigned char*>(A), x[j].a * (int64_t)sizeof(TA));
+        Pack<TB, V> out;
+        unsigned char* Bb = reinterpret_cast<unsigned char*>(B);
+        Pack<TB, V> old;
+        if (MODE == TTC_EPI_AXPBY) {
+            if (whole) {
+                old = load_pack<TB, V, NTB>(Bb, g.b * (int64_t)sizeof(TB));
+            } else {
+#pragma unroll
+                for (int j = 0; j < V; ++j) old.v[j] = B[x[j].b];
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < V; ++j) {
+            TB b_old = TB();
+            if (MODE == TTC_EPI_AXPBY) b_old = old.v[j];
+            out.v[j] = epi(a[j].v[0], b_old);
+        }
+        if (whole) {
+            store_pack<TB, V, NTB>(Bb, g.b * (int64_t)sizeof(TB), out);
+        } else {
+#pragma unroll
+            for (int j = 0; j < V; ++j) if (j < count) B[x[j].b] = out.v[j];
+        }
+    };
+    if (p.nt_a) { if (p.nt_b) run(std::true_type(), std::true_type()); else run(std::true_type(), std::false_type()); }
+    else        { if (p.nt_b) run(std::false_type(), std::true_type()); else run(std::false_type(), std::false_type()); }
+}
+
+template <typename TA, typename TB, int MODE>
+inline hipError_t launch_gather(const Candidate& c, const void* A, void* B, hipStream_t stream)
+{
+    constexpr int V = 16 / (int)sizeof(TB);
+    RowsParams rp = c.rows;
+    rp.nt_a = c.kp.nt_a;
+    rp.nt_b = c.kp.nt_b;
+    rp.xcd_remap = c.kp.xcd_remap;
+    if (rp.vec != V || c.threads != kRowsThreads || rp.chunk != kRowsThreads || rp.elements < 1 || rp.elements >= (int64_t(1) << 30) ||
+        rp.row < 1 || rp.size_div[0].div != rp.row) return hipErrorInvalidValue;
+    const int64_t chunks = ((rp.elements + V - 1) / V + kRowsThreads - 1) / kRowsThreads;
+    if ((int64_t)rp.per_xcd != (rp.per_xcd ? (chunks + 7) / 8 : 0) || (int64_t)rp.blocks != (rp.per_xcd ? 8 * (int64_t)rp.per_xcd : chunks)) return hipErrorInvalidValue;
+    const int64_t grid = rows_grid(rp);
+    if (grid < 1 || grid > INT32_MAX) return hipErrorInvalidValue;
+    const TA* a = static_cast<const TA*>(A);
+    TB* b = static_cast<TB*>(B);
+    void* args[] = {&rp, &a, &b};
+    return hipLaunchKernel(reinterpret_cast<const void*>(&gather_kernel<TA, TB, MODE, V>), dim3((uint32_t)grid), dim3(kRowsThreads), args, 0, stream);
+}
+
 template <typename TA, typename TB, int MODE, int V, int U, bool FLAT>
 inline hipError_t launch_rows_unrolled(const Candidate& c, const void* A, void* B, hipStream_t stream)
 {
@@ -841,6 +913,7 @@ inline hipError_t launch_vec(const Candidate& c, const void* A, void* B, hipStre
     constexpr int VD = VMAXA < VMAXB ? VMAXA : VMAXB;      // direct and row kernel: one width for both sides
     if (c.kernel_class == TTC_KERNEL_MICRO) return launch_micro<TA, TB, MODE>(c, A, B, s);
     if (c.kernel_class == kKernelLines) return launch_lines<TA, TB, MODE>(c, A, B, s);
+    if (c.kernel_class == kKernelGather) return launch_gather<TA, TB, MODE>(c, A, B, s);
     if (c.kernel_class == TTC_KERNEL_ROWS) {
         const int v = c.rows.vec;
         if (c.rows.flat) return v == VD ? launch_rows_flat<TA, TB, MODE, VD>(c, A, B, s) : hipErrorInvalidValue;

@@ -1001,6 +1001,112 @@ static bool make_rows_candidate(const Problem& P, int vec, int unroll, bool flat
     return true;
 }
 
+static double traffic_bytes(const Problem& P)
+{
+    return (double)P.elements * (P.eb_a + (P.epilogue == TTC_EPI_AXPBY ? 2 : 1) * P.eb_b);
+}
+
+// What the loads of the gather kernel ask of the memory system, counted over two pairs of neighbouring workgroups: lines
+// that the 64 lanes of one load instruction touch (per wavefront, all of its loads), lines that a workgroup touches, and
+// which part of its lines a workgroup shares with the next one.
+struct GatherLines { double requests, lines, shared; };
+
+static GatherLines gather_lines(const Problem& P, const RowsParams& r)
+{
+    GatherLines g = {0, 0, 0};
+    const uint32_t vec = (uint32_t)r.vec, last = (uint32_t)(P.elements - 1);
+    double both = 0, single = 0;
+    std::vector<int64_t> one, two;
+    for (int s = 0; s < 2; ++s) {
+        const uint32_t wg = (uint32_t)((int64_t)r.blocks * (1 + 2 * s) / 4);
+        two.clear();
+        for (uint32_t w = wg; w < wg + 2; ++w) {
+            one.clear();
+            for (uint32_t wave = 0; wave < 4; ++wave)
+                for (uint32_t j = 0; j < vec; ++j) {
+                    const size_t from = one.size();
+                    for (uint32_t lane = 0; lane < (uint32_t)kWave; ++lane) {
+                        const uint64_t e = ((uint64_t)w * 256 + wave * kWave + lane) * vec + j;
+                        one.push_back(gather_place(r, (uint32_t)std::min<uint64_t>(e, last)).a * P.eb_a / kLineBytes);
+                    }
+                    std::sort(one.begin() + from, one.end());
+                    one.erase(std::unique(one.begin() + from, one.end()), one.end());
+                    g.requests += (double)(one.size() - from) / 16.0;          // per wavefront: 4 workgroups of 4
+                }
+            std::sort(one.begin(), one.end());
+            one.erase(std::unique(one.begin(), one.end()), one.end());
+            g.lines += (double)one.size() / 4.0;
+            single += (double)one.size();
+            two.insert(two.end(), one.begin(), one.end());
+        }
+        std::sort(two.begin(), two.end());
+        both += (double)(std::unique(two.begin(), two.end()) - two.begin());
+    }
+    g.shared = 2.0 * (1.0 - both / single);
+    return g;
+}
+
+// The gather kernel's candidate: every lane writes 16 bytes of B and fetches their elements one by one from A.  Any
+// problem of at most 64 MB of traffic (beyond that its repeated line requests never win).
+static bool make_gather_candidate(const Problem& P, Candidate* out)
+{
+    if (traffic_bytes(P) > 64e6) return false;
+    Candidate C;
+    std::memset(&C, 0, sizeof(C));
+    C.kernel_class = kKernelGather;
+    C.threads = 256;
+    C.wg_per_cu = 0;
+    RowsParams& r = C.rows;
+    r.n = P.ndim;
+    r.vec = 16 / P.eb_b;
+    r.unroll = 1;
+    r.row = (uint32_t)P.size[P.perm[0]];
+    r.elements = P.elements;
+    r.flat = P.span_b == P.elements ? 1 : 0;
+    r.chunk = 256;
+    r.vectors = ceil_div(P.elements, r.vec);
+    r.blocks = (uint32_t)ceil_div(r.vectors, r.chunk);
+    for (int d = 0; d < kMaxDim; ++d) {
+        r.size_div[d] = make_fastdiv(1);
+        if (d >= P.ndim) continue;
+        const int k = P.perm[d];                           // B's index d is A's index k
+        r.size_div[d] = make_fastdiv((uint32_t)P.size[k]);
+        r.stride_a[d] = P.stride_a[k];
+        r.stride_b[d] = P.stride_b[k];
+    }
+    r.alpha[0] = P.alpha[0]; r.alpha[1] = P.alpha[1];
+    r.beta[0] = P.beta[0];   r.beta[1] = P.beta[1];
+    KernelParams& kp = C.kp;
+    kp.n = P.ndim;
+    kp.a.vec = kp.b.vec = r.vec;           // what a lane moves
+    kp.lds_buffers = 1;
+    for (int k = 0; k < kMaxDim; ++k) {
+        C.tile[k] = kp.tile[k] = (k == P.perm[0]) ? (int)std::min<int64_t>(P.size[k], 256 * r.vec) : 1;
+        C.tile_order[k] = (k < P.ndim) ? P.perm[k] : k;
+        kp.tile_below[k] = kp.tile_cnt[k] = make_fastdiv(1);
+        kp.stride_a[k] = (k < P.ndim) ? P.stride_a[k] : 0;
+        kp.stride_b[k] = (k < P.ndim) ? P.stride_b[k] : 0;
+    }
+    // Workgroups that share lines of A with their neighbours belong on one XCD: one contiguous range each (2-D 581 x 779
+    // complex128 5.4 us against 10.0 dealt one by one); where they share none the ranges only spread the reads further
+    // (18 x 352 x 6 x 22 complex64, reversed, 16.0 against 9.6).
+    const GatherLines g = gather_lines(P, r);
+    const uint32_t chunks = r.blocks;
+    if (chunks >= 64 && g.shared > 0.25) {
+        r.per_xcd = (chunks + 7) / 8;
+        r.blocks = 8 * r.per_xcd;
+    }
+    kp.num_tiles = kp.grid = r.blocks;
+    if (!set_tile_mapping(&kp, kDefaultTileMapping)) return false;
+    // Fitted to 170 problems of 0.1 to 60 MB: 20 % rms.
+    C.model_us = 2.5 + 0.105e-6 * traffic_bytes(P) + 2.25e-6 * g.requests * 4.0 * chunks + 4.3e-6 * g.lines * chunks;
+    C.digits_a = C.digits_b = 1;
+    C.dtile_a[0] = 1; C.dlane_a[0] = 1;
+    C.dtile_b[0] = C.dlane_b[0] = kWave * r.vec;
+    *out = C;
+    return true;
+}
+
 bool set_tile_mapping(KernelParams* kp, int mode)
 {
     if (mode == kDefaultTileMapping) {
@@ -1023,7 +1129,8 @@ bool set_tile_mapping(KernelParams* kp, int mode)
 
 uint32_t launch_grid(const Candidate& c, int cus)
 {
-    if (c.kernel_class == TTC_KERNEL_MICRO || c.kernel_class == TTC_KERNEL_ROWS || c.kernel_class == kKernelLines) return c.kp.num_tiles;    // one-shot workgroups
+    if (c.kernel_class == TTC_KERNEL_MICRO || c.kernel_class == TTC_KERNEL_ROWS || c.kernel_class == kKernelLines ||
+        c.kernel_class == kKernelGather) return c.kp.num_tiles;    // one-shot workgroups
     const uint64_t want = (uint64_t)std::max(cus, 1) * (uint64_t)std::max(c.wg_per_cu, 1);
     return (uint32_t)std::min<uint64_t>(want, c.kp.num_tiles);
 }
@@ -1096,54 +1203,37 @@ static AccessShape access_shape(const Problem& P, const Candidate& C)
     return r;
 }
 
-// The row kernel against the tiled kernels: measured on 384^3, 376^3, 374^3 (0,2,1) and 4-D to 6-D problems with
-// the stride-1 index fixed (fp32, fp64, complex64).  Long rows gathered whole are what it is good at (87-94 % of a
-// copy where the tiled kernels reach 75-90 %); short rows leave it with sub-line pieces of A that a tile spanning
-// A's next index reads as one run (53-62 % against 71-81 %).
+// The row kernel against the tiled kernels, fitted to the times of both on 330 problems: rows of 16 bytes to 64 KB, 2 to
+// 200 MB, fp32, fp64, complex128 and fp32 -> fp64, dense and padded.
+// Dense B: whole lines are ahead from 128-byte rows on (200 MB: 66-68 us against 72-75), rows that start inside lines
+// from 264-byte rows on (71-79 us against 88-91; 68-byte rows 102 against 93), updates of ragged rows by more (340-byte
+// rows 104 against 153-166: no narrow vectors).  Padded B: tiles split lines as well there, and rows are ahead from
+// 36 bytes on (64-byte rows 87-115 us against 130-156, 800-byte ones 72 against 100; 32-byte ones 164 against 139).
+// Below 8 MB rows always are (2.6-4 us against 5.4-8: no tables, no barrier).
 static double rows_cost(const Problem& P, const Candidate& C)
 {
     const double row_bytes = (double)P.size[0] * P.eb_a;
     auto oct_below = [](double x, double ref) { return x < ref ? std::log2(ref / x) : 0.0; };
-    if (C.rows.flat) {
-        // Dense B: fitted to 220 problems with rows of 20 bytes to 64 KB, 2 to 200 MB, fp32, fp64, complex128 and fp32 ->
-        // fp64, against the other families' first candidate.  Whole lines: ahead from 128-byte rows on (200 MB: 66-68 us
-        // against 72-75); rows that start inside lines: from 264-byte rows on (71-79 against 88-91; 68-byte rows 102 against
-        // 93); below 8 MB always (2.6-4 us against 5.4-8: no tables, no barrier); updates of ragged rows need no narrow
-        // vectors (340-byte rows 104 against 153-166).
-        const double traffic = (double)P.elements * (P.eb_a + (P.epilogue == TTC_EPI_AXPBY ? 2 : 1) * P.eb_b);
-        const bool whole = P.size[0] * P.eb_a % kLineBytes == 0;
-        double e = -0.373;
-        if (traffic < 8e6) e -= 0.425;
-        else if (traffic < 1e8) e -= 0.128;
+    const bool update = P.epilogue == TTC_EPI_AXPBY, whole = P.size[0] * P.eb_a % kLineBytes == 0;
+    const double traffic = (double)P.elements * (P.eb_a + (update ? 2 : 1) * P.eb_b);
+    double e = traffic < 8e6 ? -0.425 : (traffic < 1e8 ? -0.128 : 0.0);
+    if (P.span_b == P.elements) {
+        e -= 0.373;
+        if (!C.rows.flat) e += 0.05;                                        // pieces of B that start at any element
         if (!whole) e += 0.124;
         if (traffic >= 1e8) e += 0.049 * oct_below(row_bytes, 128.0) + (whole ? 0.0 : 0.094 * oct_below(row_bytes, 512.0));
         else if (!whole) e += 0.103 * oct_below(row_bytes, 128.0);
-        if (P.epilogue == TTC_EPI_AXPBY && P.size[0] % C.rows.vec != 0) e -= 0.131;
-        // bytes a lane keeps in flight: 16 (with an update 32); every doubling costs 1-5 %, eight bytes (the narrow side of
-        // fp32 -> fp64) 10 %
-        const double flight = (double)C.rows.vec * C.rows.unroll * P.eb_a;
-        e += flight < 16.0 ? (P.epilogue == TTC_EPI_AXPBY ? 0.0 : 0.10) : 0.03 * std::log2(flight / 16.0);
-        return std::exp(e);
+        if (update && P.size[0] % (16 / std::max(P.eb_a, P.eb_b)) != 0 && C.rows.flat) e -= 0.131;
+    } else {
+        e -= 0.30;
+        e += traffic >= 1e8 ? 0.10 * oct_below(row_bytes, 128.0) : 0.05 * oct_below(row_bytes, 64.0);
+        if (row_bytes <= 32.0 && traffic >= 8e6) e += 2.0;
     }
-    double e = -0.30;
-    e += 0.60 * oct_below(row_bytes, 512.0);                            // 576-byte rows: 94 % of a copy; 340-byte rows: 62 %
-    if (std::fmod(row_bytes, 128.0) != 0.0) e += 0.04;                  // rows that share lines with their neighbours
-    if (C.rows.overlap) e += 0.02;                                      // the last vector of every row repeats part of its neighbour
-    // Access width and bytes a lane keeps in flight (loads of B count when beta != 0), measured on 384^3, 374^3,
-    // 917x374x153, 208x115x63x35 and 72^4 fp64: 16-byte accesses with 16 to 32 bytes in flight reach 94-97 % of a
-    // copy (4 to 8 KB per workgroup); every doubling beyond costs about 4 %, 8 bytes in flight reach 70 %,
-    // 8-byte accesses trail 16-byte ones by 5 %, 4-byte accesses stop at 62 %.
-    const int access = C.rows.vec * std::max(P.eb_a, P.eb_b);
-    if (access < 8) e += 0.40;
-    else if (access < 16) e += 0.05;
-    const double in_flight = (double)access * C.rows.unroll * (P.epilogue == TTC_EPI_AXPBY ? 2.0 : 1.0);
-    if (in_flight > 32.0) e += 0.045 * std::log2(in_flight / 32.0);
-    if (in_flight < 16.0) e += 0.30 * std::log2(16.0 / in_flight);
-    // small problems: a chunk is 4 to 32 KB, and too few of them leave compute units idle (the same guard rails as for tiles)
-    const double tiles_wanted = std::min(2048.0, std::max(1.0, (double)P.elements * P.eb_a / 8192.0));
-    if (C.kp.num_tiles < tiles_wanted) e += 1.28 * (tiles_wanted - C.kp.num_tiles) / 2048.0;
-    const double cus_wanted = std::min(256.0, std::max(1.0, (double)P.elements * P.eb_a / 4096.0));
-    if (C.kp.num_tiles < cus_wanted) e += 1.5 * (cus_wanted - C.kp.num_tiles) / 256.0;
+    // access width, and the bytes of A a lane keeps in flight: 16; every doubling costs 1-5 %, eight bytes (the narrow
+    // side of fp32 -> fp64) 10 % unless B is loaded too
+    e += 0.05 * oct_below(C.rows.vec * std::max(P.eb_a, P.eb_b), 16.0);
+    const double flight = (double)C.rows.vec * C.rows.unroll * P.eb_a;
+    e += flight < 16.0 ? (update ? 0.0 : 0.10) * std::log2(16.0 / flight) : 0.03 * std::log2(flight / 16.0);
     return std::exp(e);
 }
 
@@ -1227,7 +1317,7 @@ static double line_cost(const Problem& P, const Candidate& C)
         const double tiles_wanted = std::min(2048.0, std::max(1.0, (double)P.elements * P.eb_a / 8192.0));
         if (C.kp.num_tiles < tiles_wanted) e += 0.30 * (tiles_wanted - C.kp.num_tiles) / 2048.0;
     } else {
-        e = -0.40 + (m.skewed ? 0.057 : 0.0) + (one_precision ? 0.08 : 0.0) - (update ? 0.126 : 0.0);
+        e = -0.40 + (m.skewed ? 0.057 : 0.0) + (one_precision ? (update && m.skewed ? 0.16 : 0.08) : 0.0) - (update ? 0.126 : 0.0);
         e += 0.05 * pad_cols + 0.167 * split + 0.18 * C.lds_bytes / 65536.0;
         e -= 0.058 * std::log2(std::min<double>(m.lines - m.skewed, std::ceil(line_rows)));
         // vectors a lane stores: the fewer the quicker the tile
@@ -1245,8 +1335,19 @@ static double line_cost(const Problem& P, const Candidate& C)
     return std::exp(e);
 }
 
+// The gather kernel against the others.  For problems that the caches hold the families' first candidates take, to
+// within 10-13 %, 3.4 us + 0.18 us per MB of traffic (line), 3.9 + 0.19 (micro-tile), 2.4 + 0.15 (row) and 5.6 + 0.20 (box); the
+// gather kernel's modelled time against the line kernel's, whose candidates cost about 0.86 there.  (Large problems are
+// further from the fit: a margin.)
+static double gather_cost(const Problem& P, const Candidate& C)
+{
+    const double mb = traffic_bytes(P) * 1e-6;
+    return 0.86 * (1.0 + 0.004 * mb) * C.model_us / (3.4 + 0.18 * mb);
+}
+
 static double heuristic_cost(const Problem& P, const Candidate& C)
 {
+    if (C.kernel_class == kKernelGather) return gather_cost(P, C);
     if (C.kernel_class == TTC_KERNEL_ROWS) return rows_cost(P, C);
     if (C.kernel_class == kKernelLines) return line_cost(P, C);
     if (C.kernel_class == TTC_KERNEL_MICRO) return micro_cost(P, C);
@@ -1331,6 +1432,10 @@ static double heuristic_cost(const Problem& P, const Candidate& C)
     // small problems (outside the fitted range): a tile per compute unit comes before large tiles
     const double cus_wanted = std::min(256.0, std::max(1.0, (double)P.elements * eb_a / 4096.0));
     if (kp.num_tiles < cus_wanted) e += 1.5 * (cus_wanted - kp.num_tiles) / 256.0;
+    // ... and what tables, set-up and barriers cost in a problem that the caches hold (the times beside gather_cost): 33 %
+    // at 1 MB, 13 % at 16 MB
+    const double mb = traffic_bytes(P) * 1e-6;
+    e += std::max(0.0, std::log((5.56 + 0.199 * mb) / (3.4 + 0.18 * mb)) - 0.207);
     return std::exp(e);
 }
 
@@ -1354,13 +1459,16 @@ static bool same_config(const Candidate& x, const Candidate& y)
 // search tries the other settings on its finalists.)
 void default_streaming(const Problem& P, Candidate* c)
 {
+    if (c->kernel_class == kKernelGather) { c->kp.nt_a = c->kp.nt_b = 0; return; }      // lines of A are fetched several times, B is small
     if (c->kernel_class == TTC_KERNEL_ROWS) {
         // B is written front to back: streamed.  A is read once, but rows that start inside lines share them, and a
         // tensor of a quarter of the last-level cache may still be there: streamed only if it is larger and its rows
         // are whole lines or long (25 MB problems run 13 % faster without, 200 MB ones with 128-byte to 64 KB rows
         // 3 % faster with the hint, 340- and 532-byte rows 5-8 % slower).
         const int64_t row_bytes = P.size[0] * P.eb_a;
-        c->kp.nt_a = P.elements * P.eb_a >= (int64_t(64) << 20) && (row_bytes % kLineBytes == 0 || row_bytes >= 1024) ? 1 : 0;
+        bool whole = row_bytes % kLineBytes == 0;
+        for (int k = 1; k < P.ndim; ++k) if (P.stride_a[k] * P.eb_a % kLineBytes != 0) whole = false;
+        c->kp.nt_a = P.elements * P.eb_a >= (int64_t(64) << 20) && (whole || row_bytes >= 1024) ? 1 : 0;
         c->kp.nt_b = 1;
         return;
     }
@@ -1638,6 +1746,12 @@ static void enumerate(const Problem& P, std::vector<Candidate>& out_list, bool q
         }
     }
 
+    // -- the gather kernel
+    {
+        Candidate c;
+        if (make_gather_candidate(P, &c)) add_candidate(P, out, c);
+    }
+
     // -- last resort so that every problem has a candidate: scalar direct walk in A order
     if (out_list.empty() || n == 1) {
         int t[kMaxDim];
@@ -1665,10 +1779,10 @@ int build_plan(int dtype, int ndim, const int64_t* sizes, const int* perm, const
     if (verbose()) {
         const Candidate& c = plan->cands[0];
         std::fprintf(stderr, "ttc: plan dtype %d, %d fused indices, %s kernel, tile", P.dtype, P.ndim,
-                     c.kernel_class == TTC_KERNEL_DIRECT ? "direct" : (c.kernel_class == TTC_KERNEL_ROWS ? "row" : (c.kernel_class == TTC_KERNEL_MICRO ? "micro-tile" : (c.kernel_class == kKernelLines ? "line" : "staged"))));
+                     c.kernel_class == TTC_KERNEL_DIRECT ? "direct" : (c.kernel_class == TTC_KERNEL_ROWS ? "row" : (c.kernel_class == TTC_KERNEL_MICRO ? "micro-tile" : (c.kernel_class == kKernelLines ? "line" : (c.kernel_class == kKernelGather ? "gather" : "staged")))));
         for (int k = 0; k < P.ndim; ++k) std::fprintf(stderr, " %d", c.tile[k]);
-        size_t per_class[5] = {0, 0, 0, 0, 0};
-        for (const Candidate& q : quick) if (q.kernel_class >= 0 && q.kernel_class < 5) ++per_class[q.kernel_class];
+        size_t per_class[6] = {0, 0, 0, 0, 0, 0};
+        for (const Candidate& q : quick) if (q.kernel_class >= 0 && q.kernel_class < 6) ++per_class[q.kernel_class];
         std::fprintf(stderr, ", vectors %d/%d, %d threads, %d B LDS, cost %.4f (best of %zu candidates of the short list: %zu direct, %zu staged, %zu row, %zu micro-tile, %zu line)\n",
                      c.kp.a.vec, c.kp.b.vec, c.threads, c.lds_bytes, c.score, quick.size(), per_class[0], per_class[1], per_class[2], per_class[3], per_class[4]);
     }
@@ -1797,7 +1911,7 @@ int ttc_plan_get_info(ttc_plan_t plan, ttc_plan_info_t* out)
         out->digit_tile_b[i] = C.dtile_b[i];  out->digit_lane_b[i] = C.dlane_b[i];
     }
     out->stride1_fixed = (P.perm[0] == 0) ? 1 : 0;
-    out->kernel_class = C.kernel_class == ttc::kKernelLines ? TTC_KERNEL_LDS : C.kernel_class;
+    out->kernel_class = C.kernel_class == ttc::kKernelLines ? TTC_KERNEL_LDS : (C.kernel_class == ttc::kKernelGather ? TTC_KERNEL_ROWS : C.kernel_class);
     out->epilogue = P.epilogue;
     out->vec_a = C.kp.a.vec;
     out->vec_b = C.kp.b.vec;
@@ -1829,7 +1943,7 @@ int ttc_plan_get_info(ttc_plan_t plan, ttc_plan_info_t* out)
     out->tuned_ms = C.tuned_ms;
     out->heuristic_cost = C.score;
     out->merged = (C.kernel_class == TTC_KERNEL_MICRO || C.kernel_class == ttc::kKernelLines) ? (C.kp.micro.merged_a | (C.kp.micro.merged_b << 1)) : 0;
-    out->unroll = C.kernel_class == TTC_KERNEL_ROWS ? C.rows.unroll : 
+    out->unroll = (C.kernel_class == TTC_KERNEL_ROWS || C.kernel_class == ttc::kKernelGather) ? C.rows.unroll : 
                   (C.kernel_class == TTC_KERNEL_MICRO ? C.kp.micro.blocks : (C.kernel_class == ttc::kKernelLines ? C.kp.micro.lines : 0));
     return TTC_OK;
     });
@@ -1957,6 +2071,54 @@ static int emulate_rows(const ttc::Problem& P, const ttc::Candidate& C, int64_t*
             }
     }
     return (bad || written != P.elements) ? TTC_ERR_INTERNAL : TTC_OK;
+}
+
+// Replay of the gather kernel.
+static int emulate_gather(const ttc::Problem& P, const ttc::Candidate& C, int64_t* b_from_a)
+{
+    using namespace ttc;
+    RowsParams p = C.rows;
+    p.xcd_remap = C.kp.xcd_remap;
+    if (p.vec * P.eb_b != 16 || p.elements != P.elements || p.elements >= (int64_t(1) << 30) || p.chunk != 256 || C.threads != 256 ||
+        p.row != (uint32_t)P.size[P.perm[0]] || p.size_div[0].div != p.row || (p.flat != 0) != (P.span_b == P.elements) ||
+        (int64_t)p.per_xcd != (p.per_xcd ? (((p.elements + p.vec - 1) / p.vec + p.chunk - 1) / p.chunk + 7) / 8 : 0) ||
+        (int64_t)p.blocks != (p.per_xcd ? 8 * (int64_t)p.per_xcd : ((p.elements + p.vec - 1) / p.vec + p.chunk - 1) / p.chunk))
+        return TTC_ERR_INTERNAL;
+    for (int64_t i = 0; i < P.span_b; ++i) b_from_a[i] = -1;
+    auto inside = [&](int64_t off, const int64_t* stride, bool b_side) {
+        if (off < 0) return false;
+        for (int i = P.ndim - 1; i >= 0; --i) {
+            const int k = b_side ? P.perm[i] : i;
+            const int64_t c = off / stride[k];
+            if (c >= P.size[k]) return false;
+            off -= c * stride[k];
+        }
+        return off == 0;
+    };
+    std::vector<char> seen((size_t)p.blocks, 0);
+    int64_t written = 0;
+    for (int64_t wg = 0; wg < rows_grid(p); ++wg) {
+        const uint32_t block = rows_block(p, (uint32_t)wg);
+        if (block >= p.blocks) continue;
+        if (seen[block]) return TTC_ERR_INTERNAL;
+        seen[block] = 1;
+        for (uint32_t tid = 0; tid < p.chunk; ++tid) {
+            const uint32_t e = gather_first(p, block, tid);
+            if ((int64_t)e >= p.elements) continue;
+            const GatherPlace g = gather_place(p, e);
+            for (uint32_t j = 0; j < (uint32_t)p.vec; ++j) {
+                const bool there = (int64_t)(e + j) < p.elements;
+                const GatherPlace x = gather_next(p, g, e, j);
+                if (!inside(x.a, P.stride_a, false) || !inside(x.b, P.stride_b, true)) return TTC_ERR_INTERNAL;      // loaded even if not stored
+                if (!there) continue;
+                if (p.flat && x.b != (int64_t)(e + j)) return TTC_ERR_INTERNAL;
+                if (b_from_a[x.b] != -1) return TTC_ERR_INTERNAL;
+                b_from_a[x.b] = x.a;
+                ++written;
+            }
+        }
+    }
+    return written == P.elements ? TTC_OK : TTC_ERR_INTERNAL;
 }
 
 // Replay of the micro-tile kernel: every workgroup, every lane, the index code the kernel runs; every LDS slot
@@ -2153,6 +2315,7 @@ static int emulate_map(ttc_plan_t plan, int64_t* b_from_a)
     const Problem& P = plan->prob;
     const Candidate& C = plan->cands[plan->selected];
     if (C.kernel_class == TTC_KERNEL_ROWS) return emulate_rows(P, C, b_from_a);
+    if (C.kernel_class == kKernelGather) return emulate_gather(P, C, b_from_a);
     if (C.kernel_class == TTC_KERNEL_MICRO) return emulate_micro(P, C, b_from_a);
     if (C.kernel_class == kKernelLines) {
         // where a tile is cut depends on the address B will have: every place inside a line that matters (the first,

@@ -93,6 +93,43 @@ TTC_HD FlatAccess flat_access(const RowsParams& p, int64_t base, uint32_t row0, 
     return f;
 }
 
+// ---- gather kernel: where element `e` of B, in the order of B's multi-index, lies in both tensors ----
+struct GatherPlace { int64_t a, b; uint32_t first; };        // first: its coordinate along B's index 0
+
+TTC_HD GatherPlace gather_place(const RowsParams& p, uint32_t e)
+{
+    GatherPlace r = {0, 0, 0};
+    uint32_t rest = e;
+#pragma unroll
+    for (int d = 0; d < kMaxDim; ++d) {             // unused indices: extent 1, stride 0
+        const uint32_t q = fdiv(rest, p.size_div[d]);
+        const uint32_t j = rest - q * p.size_div[d].div;
+        if (d == 0) r.first = j;
+        r.a += (int64_t)j * p.stride_a[d];
+        r.b += (int64_t)j * p.stride_b[d];
+        rest = q;
+    }
+    return r;
+}
+
+// First element of lane `tid` of chunk `block` (past the end of B: nothing to do).
+TTC_HD uint32_t gather_first(const RowsParams& p, uint32_t block, uint32_t tid)
+{
+    if (p.per_xcd) block = (block & 7u) * p.per_xcd + (block >> 3);
+    return (block * p.chunk + tid) * (uint32_t)p.vec;
+}
+
+// Element e + j of B, given element e's place: a step along B's index 0 unless that ends before (past the end of B: the last element).
+TTC_HD GatherPlace gather_next(const RowsParams& p, const GatherPlace& g, uint32_t e, uint32_t j)
+{
+    if (g.first + j < p.row) {
+        GatherPlace r = {g.a + (int64_t)j * p.stride_a[0], g.b + (int64_t)j * p.stride_b[0], g.first + j};
+        return r;
+    }
+    const uint32_t last = (uint32_t)(p.elements - 1);
+    return gather_place(p, e + j < last ? e + j : last);
+}
+
 // Which chunk workgroup `wg` of a row-kernel launch moves (p.blocks: none): consecutive chunks, which share a line of
 // B and lines of A, go to one XCD a few at a time, as with tiles.
 TTC_HD uint32_t rows_block(const RowsParams& p, uint32_t wg)

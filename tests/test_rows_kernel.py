@@ -1,4 +1,5 @@
-"""The row kernel over a dense B, whose vectors run across the ends of rows, and over a padded one: every candidate and
+"""The row kernel over a dense B, whose vectors run across the ends of rows, and over a padded one, and the gather kernel
+(reported as the same class), which takes any permutation: every candidate and
 every way of dealing its chunks to the XCDs against the oracle, replayed on the host and run on the GPU.  Sizes: rows
 of one vector, one element more, odd ones; a tensor that is no multiple of the vector; chunks that do not fill a round."""
 import numpy as np
@@ -17,6 +18,12 @@ SHAPES = [
     ((45, 9, 37), (0, 2, 1), None, (48, 37, 9)),          # B padded: counted row by row
     ((13, 5, 6, 4), (0, 3, 1, 2), None, None),
     ((1001,), (0,), (1003,), None),                       # one row
+    # the stride-1 index moves: the gather kernel alone
+    ((3, 50), (1, 0), None, None),                        # B's runs longer than a vector, shorter, of two elements
+    ((50, 3), (1, 0), None, None),
+    ((2, 7, 2, 9), (2, 0, 3, 1), None, None),
+    ((5, 4, 3, 6), (3, 1, 0, 2), (6, 4, 5, 6), (7, 4, 5, 3)),
+    ((1, 8, 6, 10), (1, 2, 0, 3), (2, 9, 8, 10), (9, 7, 3, 14)),     # no stride-1 index at all
 ]
 DTYPES = [wl.F32, wl.F64, wl.C128, wl.F32_F64, wl.F64_F32]
 
