@@ -1081,7 +1081,8 @@ static bool make_gather_candidate(const Problem& P, Candidate* out)
     kp.a.vec = kp.b.vec = r.vec;           // what a lane moves
     kp.lds_buffers = 1;
     for (int k = 0; k < kMaxDim; ++k) {
-        C.tile[k] = kp.tile[k] = (k == P.perm[0]) ? (int)std::min<int64_t>(P.size[k], 256 * r.vec) : 1;
+        // nothing is tiled: the fields say whole vectors along either unit-stride index, as for every kernel
+        C.tile[k] = kp.tile[k] = (k == P.perm[0]) ? (int)std::min<int64_t>(P.size[k], 256 * r.vec) : (k == 0 ? r.vec : 1);
         C.tile_order[k] = (k < P.ndim) ? P.perm[k] : k;
         kp.tile_below[k] = kp.tile_cnt[k] = make_fastdiv(1);
         kp.stride_a[k] = (k < P.ndim) ? P.stride_a[k] : 0;
