@@ -1015,33 +1015,32 @@ static GatherLines gather_lines(const Problem& P, const RowsParams& r)
 {
     GatherLines g = {0, 0, 0};
     const uint32_t vec = (uint32_t)r.vec, last = (uint32_t)(P.elements - 1);
+    constexpr uint32_t kSlots = 4096;                      // at most 2 x 1024 lines a pair
+    struct Slot { int64_t line; uint32_t loads; } slot[kSlots];       // bit 16 w + 4 wave + j: load j of that wavefront touches it
     double both = 0, single = 0;
-    std::vector<int64_t> one, two;
     for (int s = 0; s < 2; ++s) {
         const uint32_t wg = (uint32_t)((int64_t)r.blocks * (1 + 2 * s) / 4);
-        two.clear();
-        for (uint32_t w = wg; w < wg + 2; ++w) {
-            one.clear();
-            for (uint32_t wave = 0; wave < 4; ++wave)
-                for (uint32_t j = 0; j < vec; ++j) {
-                    const size_t from = one.size();
-                    for (uint32_t lane = 0; lane < (uint32_t)kWave; ++lane) {
-                        const uint64_t e = ((uint64_t)w * 256 + wave * kWave + lane) * vec + j;
-                        one.push_back(gather_place(r, (uint32_t)std::min<uint64_t>(e, last)).a * P.eb_a / kLineBytes);
-                    }
-                    std::sort(one.begin() + from, one.end());
-                    one.erase(std::unique(one.begin() + from, one.end()), one.end());
-                    g.requests += (double)(one.size() - from) / 16.0;          // per wavefront: 4 workgroups of 4
-                }
-            std::sort(one.begin(), one.end());
-            one.erase(std::unique(one.begin(), one.end()), one.end());
-            g.lines += (double)one.size() / 4.0;
-            single += (double)one.size();
-            two.insert(two.end(), one.begin(), one.end());
+        for (Slot& x : slot) x.loads = 0;
+        for (uint32_t t = 0; t < 512; ++t) {
+            const uint32_t e = (wg * 256 + t) * vec;
+            const GatherPlace first = gather_place(r, std::min(e, last));
+            for (uint32_t j = 0; j < vec; ++j) {
+                const GatherPlace at = j == 0 ? first : (e + j <= last ? gather_next(r, first, e, j) : gather_place(r, last));
+                const int64_t line = at.a * P.eb_a / kLineBytes;
+                uint32_t h = (uint32_t)((uint64_t)line * 0x9e3779b97f4a7c15ull >> 52);
+                while (slot[h].loads != 0 && slot[h].line != line) h = (h + 1) % kSlots;
+                slot[h].line = line;
+                slot[h].loads |= 1u << (16 * (t / 256) + 4 * (t / kWave % 4) + j);
+            }
         }
-        std::sort(two.begin(), two.end());
-        both += (double)(std::unique(two.begin(), two.end()) - two.begin());
+        for (const Slot& x : slot) {
+            if (x.loads == 0) continue;
+            g.requests += (double)__builtin_popcount(x.loads) / 16.0;         // per wavefront: 4 workgroups of 4
+            single += (x.loads & 0xffffu ? 1 : 0) + (x.loads >> 16 ? 1 : 0);
+            both += 1;
+        }
     }
+    g.lines = single / 4.0;
     g.shared = 2.0 * (1.0 - both / single);
     return g;
 }
