@@ -811,7 +811,7 @@ __global__ __launch_bounds__(kRowsThreads) void gather_kernel(const RowsParams p
         GatherPlace x[V];
 #pragma unroll
         for (int j = 0; j < V; ++j) x[j] = j == 0 ? g : gather_next(p, g, e, (uint32_t)j);
-        const bool whole = count == V && (p.flat || g.first + (uint32_t)V <= p.row);      // one contiguous vector of B
+        const bool whole = gather_whole(p, g, count);
         Pack<TA, 1> a[V];
 #pragma unroll
         for (int j = 0; j < V; ++j) a[j] = load_pack<TA, 1, NTA>(reinterpret_cast<const unsigned char*>(A), x[j].a * (int64_t)sizeof(TA));
@@ -852,7 +852,7 @@ inline hipError_t launch_gather(const Candidate& c, const void* A, void* B, hipS
     rp.nt_b = c.kp.nt_b;
     rp.xcd_remap = c.kp.xcd_remap;
     if (rp.vec != V || c.threads != kRowsThreads || rp.chunk != kRowsThreads || rp.elements < 1 || rp.elements >= (int64_t(1) << 30) ||
-        rp.row < 1 || rp.size_div[0].div != rp.row) return hipErrorInvalidValue;
+        rp.row < 1 || rp.size_div[0].div != rp.row || (V > 1 && rp.stride_b[0] != 1)) return hipErrorInvalidValue;
     const int64_t chunks = ((rp.elements + V - 1) / V + kRowsThreads - 1) / kRowsThreads;
     if ((int64_t)rp.per_xcd != (rp.per_xcd ? (chunks + 7) / 8 : 0) || (int64_t)rp.blocks != (rp.per_xcd ? 8 * (int64_t)rp.per_xcd : chunks)) return hipErrorInvalidValue;
     const int64_t grid = rows_grid(rp);

@@ -1046,10 +1046,12 @@ static GatherLines gather_lines(const Problem& P, const RowsParams& r)
 }
 
 // The gather kernel's candidate: every lane writes 16 bytes of B and fetches their elements one by one from A.  Any
-// problem of at most 64 MB of traffic (beyond that its repeated line requests never win).
+// problem of at most 64 MB of traffic (beyond that its repeated line requests never win) whose B has a unit stride along
+// its first index: what a lane writes is one vector (of one element where that has 16 bytes: any stride will do).
 static bool make_gather_candidate(const Problem& P, Candidate* out)
 {
     if (traffic_bytes(P) > 64e6) return false;
+    if (P.eb_b < 16 && P.stride_b[P.perm[0]] != 1) return false;      // an index of extent 1 in front of it, padded by ldb
     Candidate C;
     std::memset(&C, 0, sizeof(C));
     C.kernel_class = kKernelGather;
@@ -2106,12 +2108,14 @@ static int emulate_gather(const ttc::Problem& P, const ttc::Candidate& C, int64_
             const uint32_t e = gather_first(p, block, tid);
             if ((int64_t)e >= p.elements) continue;
             const GatherPlace g = gather_place(p, e);
+            const bool whole = gather_whole(p, g, (int32_t)std::min<int64_t>(p.elements - (int64_t)e, p.vec));
             for (uint32_t j = 0; j < (uint32_t)p.vec; ++j) {
                 const bool there = (int64_t)(e + j) < p.elements;
                 const GatherPlace x = gather_next(p, g, e, j);
                 if (!inside(x.a, P.stride_a, false) || !inside(x.b, P.stride_b, true)) return TTC_ERR_INTERNAL;      // loaded even if not stored
                 if (!there) continue;
                 if (p.flat && x.b != (int64_t)(e + j)) return TTC_ERR_INTERNAL;
+                if (whole && x.b != g.b + (int64_t)j) return TTC_ERR_INTERNAL;       // the vector that the kernel stores
                 if (b_from_a[x.b] != -1) return TTC_ERR_INTERNAL;
                 b_from_a[x.b] = x.a;
                 ++written;

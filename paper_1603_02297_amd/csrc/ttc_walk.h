@@ -119,6 +119,13 @@ TTC_HD uint32_t gather_first(const RowsParams& p, uint32_t block, uint32_t tid)
     return (block * p.chunk + tid) * (uint32_t)p.vec;
 }
 
+// Whether a lane's `count` elements of B, the first at `g`, are one contiguous vector of it (the kernel then stores them as
+// one): a whole vector, inside one run of B unless B is dense.
+TTC_HD bool gather_whole(const RowsParams& p, const GatherPlace& g, int32_t count)
+{
+    return count == p.vec && (p.flat || g.first + (uint32_t)p.vec <= p.row);
+}
+
 // Element e + j of B, given element e's place: a step along B's index 0 unless that ends before (past the end of B: the last element).
 TTC_HD GatherPlace gather_next(const RowsParams& p, const GatherPlace& g, uint32_t e, uint32_t j)
 {

@@ -23,9 +23,22 @@ SHAPES = [
     ((50, 3), (1, 0), None, None),
     ((2, 7, 2, 9), (2, 0, 3, 1), None, None),
     ((5, 4, 3, 6), (3, 1, 0, 2), (6, 4, 5, 6), (7, 4, 5, 3)),
-    ((1, 8, 6, 10), (1, 2, 0, 3), (2, 9, 8, 10), (9, 7, 3, 14)),     # no stride-1 index at all
+    ((1, 8, 6, 10), (1, 2, 0, 3), (2, 9, 8, 10), (9, 7, 3, 14)),     # A has no stride-1 index
+    # nor has B: an index of extent 1 is its first, inside a larger one, so its elements lie apart
+    ((1, 64, 6, 10), (0, 2, 1, 3), None, (2, 6, 64, 10)),
+    ((64, 1, 60), (1, 2, 0), None, (3, 60, 64)),
+    ((1, 1000), (0, 1), None, (2, 1000)),
 ]
 DTYPES = [wl.F32, wl.F64, wl.C128, wl.F32_F64, wl.F64_F32]
+
+
+# B's elements lie apart: an index of extent 1 is its first, inside a larger one
+NO_UNIT_STRIDE_IN_B = [
+    ((1, 64, 60, 10), (0, 2, 1, 3), None, (2, 60, 64, 10)),
+    ((64, 1, 60), (1, 2, 0), None, (3, 60, 64)),
+    ((1, 1000), (0, 1), None, (2, 1000)),
+    ((300, 1, 200), (1, 2, 0), None, (2, 200, 300)),
+]
 
 
 def rows_candidates(plan):
@@ -52,6 +65,23 @@ def test_walks_of_every_row_candidate(dtype):
                 seen += 1
             ttc.ttc_plan_destroy(p)
     assert seen >= 100
+
+
+@pytest.mark.parametrize("dtype", DTYPES, ids=[wl.DTYPE_NAME[d] for d in DTYPES])
+def test_plans_as_created_where_b_has_no_unit_stride(dtype):
+    """Elements of B that lie apart are never written as one vector; only 16-byte elements may take the gather kernel."""
+    for sizes, perm, lda, ldb in NO_UNIT_STRIDE_IN_B:
+        for beta in (0.0, 1.0):
+            p = ttc.ttc_plan_create_ex(dtype, len(sizes), sizes, perm, lda, ldb, 1.0, beta)
+            want = [-1] * ttc.ttc_plan_get_info(p)["span_b"]
+            for off_a, off_b in oracle.element_pairs(sizes, perm, lda, ldb):
+                want[off_b] = off_a
+            assert list(ttc.ttc_debug_emulate_map(p)) == want, (sizes, perm, ttc.ttc_plan_get_info(p))
+            for k in range(ttc.ttc_plan_candidate_count(p)):
+                ttc.ttc_plan_select_candidate(p, k)
+                info = ttc.ttc_plan_get_info(p)
+                assert info["kernel_class"] != ttc.TTC_KERNEL_ROWS or wl.ELEM_BYTES_B[dtype] == 16, (sizes, perm, k)
+            ttc.ttc_plan_destroy(p)
 
 
 @pytest.mark.gpu
@@ -91,3 +121,25 @@ def test_row_kernel_against_the_oracle(dtype):
             finally:
                 ttc.ttc_plan_destroy(plan)
     assert ran >= 100
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", DTYPES, ids=[wl.DTYPE_NAME[d] for d in DTYPES])
+def test_plans_as_created_where_b_has_no_unit_stride_on_the_gpu(dtype):
+    """The plan as created writes the elements of the sub-tensor and nothing between them."""
+    import torch
+    dev = torch.device("cuda:0")
+    stream = torch.cuda.current_stream().cuda_stream
+    for shape, (sizes, perm, lda, ldb) in enumerate(NO_UNIT_STRIDE_IN_B):
+        A = wl.uniform_tensor(dtype, int(np.prod(sizes)), 7400 + shape, "a")
+        B0 = wl.uniform_tensor(dtype, int(np.prod(ldb)), 7500 + shape, "b")
+        dA = torch.from_numpy(A).to(dev)
+        for alpha, beta in ((1.0, 0.0), (0.75, -1.25)):
+            want = oracle.transpose(dtype, sizes, perm, alpha, beta, A, B0.copy(), 4, lda=lda, ldb=ldb)
+            plan = ttc.ttc_plan_create_ex(dtype, len(sizes), sizes, perm, lda, ldb, alpha, beta)
+            dB = torch.from_numpy(B0).to(dev)
+            ttc.ttc_execute(plan, dA.data_ptr(), dB.data_ptr(), stream)
+            got = dB.cpu().numpy()
+            ttc.ttc_plan_destroy(plan)
+            allowed = 0.0 if beta == 0 else np.spacing(np.abs(want).max())      # the one ulp the library allows an update
+            assert np.abs(got - want).max() <= allowed, (sizes, perm, ldb, beta)
