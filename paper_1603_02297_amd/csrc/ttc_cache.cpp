@@ -94,7 +94,7 @@ int cache_lookup(ttc_plan_s* plan, const char* path)
             if (tail) tailv.push_back(v); else sig.push_back(v);
         }
     }
-    if (tailv.size() != 4 || (tailv[0] | 1) != 1 || (tailv[1] | 1) != 1 || tailv[2] < 0 || tailv[2] > 10) return TTC_ERR_NOT_FOUND;
+    if (tailv.size() != 4 || (tailv[0] | 1) != 1 || (tailv[1] | 1) != 1 || tailv[2] < 0 || tailv[2] > kMaxTileMapping) return TTC_ERR_NOT_FOUND;
     us = tailv[3];
     const int st = complete_plan(plan);           // an entry may name any candidate of the full list
     if (st != TTC_OK) return st;

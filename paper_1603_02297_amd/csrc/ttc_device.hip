@@ -216,10 +216,15 @@ static int tune_pairs(ttc_plan_t plan, int npairs, const void* const* A_list, vo
     ttc::EventPair ev;
     if (!ev.ok) return TTC_ERR_HIP;
     int turn = 0;
-    // one launch configuration, timed: `warm` untimed launches, then the mean of `reps`
+    // one launch configuration, timed: `warm` untimed launches (at least one), then the mean of `reps`.  One that cannot be
+    // launched costs the search that candidate and no more.
+    constexpr int kNotLaunched = -1;
     auto time_one = [&](const ttc::Candidate& c, int warm, int reps, float* ms_out) -> int {
         for (int r = 0; r < warm; ++r, ++turn)
-            if (ttc::launch(plan->prob, c, A_list[turn % npairs], B_list[turn % npairs], s) != hipSuccess) return TTC_ERR_HIP;
+            if (ttc::launch(plan->prob, c, A_list[turn % npairs], B_list[turn % npairs], s) != hipSuccess) {
+                (void)hipGetLastError();         // not the next caller's
+                return kNotLaunched;
+            }
         if (hipEventRecord(ev.start, s) != hipSuccess) return TTC_ERR_HIP;
         for (int r = 0; r < reps; ++r, ++turn)
             if (ttc::launch(plan->prob, c, A_list[turn % npairs], B_list[turn % npairs], s) != hipSuccess) return TTC_ERR_HIP;
@@ -233,14 +238,15 @@ static int tune_pairs(ttc_plan_t plan, int npairs, const void* const* A_list, vo
     // pass 1: every candidate briefly; pass 2: the fastest few again, longer, to beat the noise.  Launches of a
     // few microseconds are repeated more often: both passes time at least 0.2 ms and 1 ms of work.
     float first_ms = 0.f;
-    const int st0 = time_one(plan->cands[0], 2, 3, &first_ms);
-    if (st0 != TTC_OK) return st0;
+    int lead = 0, st0 = time_one(plan->cands[0], 2, 3, &first_ms);
+    while (st0 == kNotLaunched && ++lead < total) st0 = time_one(plan->cands[lead], 2, 3, &first_ms);
+    if (st0 != TTC_OK) return TTC_ERR_HIP;
     const float unit = first_ms > 1e-4f ? first_ms : 1e-4f;
     {   // a GPU that has been idle runs its first milliseconds at low clocks (short launches measured 3-4x
         // slower there): keep it busy for about 3 ms before anything is compared
         float ignored = 0.f;
-        const int st_warm = time_one(plan->cands[0], std::min(2000, std::max(1, (int)std::ceil(3.0f / unit))), 1, &ignored);
-        if (st_warm != TTC_OK) return st_warm;
+        const int st_warm = time_one(plan->cands[lead], std::min(2000, std::max(1, (int)std::ceil(3.0f / unit))), 1, &ignored);
+        if (st_warm != TTC_OK) return TTC_ERR_HIP;
     }
     const int reps1 = std::min(40, std::max(3, (int)std::ceil(0.2f / unit)));
     const int reps2 = std::min(200, std::max(12, (int)std::ceil(1.0f / unit)));
@@ -276,6 +282,7 @@ static int tune_pairs(ttc_plan_t plan, int npairs, const void* const* A_list, vo
         ttc::Candidate& c = plan->cands[i];
         float ms = 0.f;
         const int st1 = time_one(c, 1, reps1, &ms);
+        if (st1 == kNotLaunched) continue;
         if (st1 != TTC_OK) return st1;
         // the streaming hints can be worth more than the choice of the tile (72^4 fp64 with beta != 0: 77 % of a copy
         // by the rule, 100 % with both sides streamed; 85^4: 66 % against 48 %): a candidate is ranked by the better
@@ -286,8 +293,8 @@ static int tune_pairs(ttc_plan_t plan, int npairs, const void* const* A_list, vo
             float ms_nt = 0.f;
             const int st1b = time_one(c, 1, reps1, &ms_nt);
             c.kp.nt_a = rule_a; c.kp.nt_b = rule_b;
-            if (st1b != TTC_OK) return st1b;
-            if (ms_nt < ms) ms = ms_nt;
+            if (st1b != TTC_OK && st1b != kNotLaunched) return st1b;
+            if (st1b == TTC_OK && ms_nt < ms) ms = ms_nt;
         }
         c.tuned_ms = ms;
         timed.emplace_back(ms, i);
@@ -312,7 +319,8 @@ static int tune_pairs(ttc_plan_t plan, int npairs, const void* const* A_list, vo
             c.kp.nt_b = variants[v][1];
             float ms = 0.f;
             const int st2 = time_one(c, 2, reps2, &ms);
-            if (st2 != TTC_OK) { c.kp.nt_a = rule_a; c.kp.nt_b = rule_b; return st2; }
+            if (st2 == kNotLaunched && v > 0) continue;
+            if (st2 != TTC_OK) { c.kp.nt_a = rule_a; c.kp.nt_b = rule_b; return TTC_ERR_HIP; }
             if (v == 0 || ms < cand_ms) { cand_ms = ms; keep_a = variants[v][0]; keep_b = variants[v][1]; }
         }
         c.kp.nt_a = keep_a;
@@ -326,6 +334,7 @@ static int tune_pairs(ttc_plan_t plan, int npairs, const void* const* A_list, vo
             if (mode == mapping0 || !ttc::set_tile_mapping(&c.kp, mode)) continue;
             float ms = 0.f;
             const int st3 = time_one(c, 2, reps2, &ms);
+            if (st3 == kNotLaunched) continue;
             if (st3 != TTC_OK) { (void)ttc::set_tile_mapping(&c.kp, mapping0); return st3; }
             if (ms < cand_ms) { cand_ms = ms; keep_map = mode; }
         }
@@ -333,7 +342,8 @@ static int tune_pairs(ttc_plan_t plan, int npairs, const void* const* A_list, vo
         c.tuned_ms = cand_ms;
         if (best < 0 || cand_ms < best_ms) { best = i; best_ms = cand_ms; }
     }
-    if (best >= 0) plan->selected = best;
+    if (best < 0) return TTC_ERR_HIP;            // nothing could be launched
+    plan->selected = best;
     if (ttc::verbose())
         std::fprintf(stderr, "ttc: search timed %d of %d candidates, selected %d (%.4f ms)\n", cap, total, plan->selected, best_ms);
     if (store && *store) (void)ttc::cache_store(plan, store);       // a store that cannot be written costs a later search, no more

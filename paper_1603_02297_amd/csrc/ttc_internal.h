@@ -156,6 +156,12 @@ constexpr bool line_shape_ok(int cols, int lines, int eb_a, int eb_b)
            cols * eb_a >= 128 && cols * eb_a <= 512 && s.rows % s.pass == 0 && lines % s.groups == 0 && s.lds_bytes <= 44 * 1024;
 }
 
+// HIP launches fewer than 2^32 work items; kernels that give every tile or chunk a workgroup of its own reach that.
+constexpr bool launchable(int64_t grid, int threads)
+{
+    return grid >= 1 && grid <= INT32_MAX && grid * threads < (int64_t(1) << 32);
+}
+
 // Everything a kernel launch needs; passed by value as the kernel argument.
 struct KernelParams {
     int32_t  n;                      // fused number of indices
@@ -307,6 +313,7 @@ void set_grid(KernelParams* kp, uint32_t grid);
 // tile ids -> XCDs: 0 round robin, 1 one contiguous range per XCD, 2..10: chunks of 2^mode tiles dealt in turn
 // mode -1: the default, chunks of 32 tiles; round robin below 2048 tiles
 constexpr int kDefaultTileMapping = -1;
+constexpr int kMaxTileMapping = 10;                  // chunks of 2^10
 bool set_tile_mapping(KernelParams* kp, int mode);
 void default_streaming(const Problem& P, Candidate* c);
 MicroArgs micro_args(const Candidate& c);

@@ -559,7 +559,7 @@ inline hipError_t launch_micro(const Candidate& c, const void* A, void* B, hipSt
             m.ta != m.la * V || m.tb != m.lb * V || m.pitch < m.la || (m.pitch & 7) || (m.swizzle != 7u && m.swizzle != 0u) || m.la_div.div != (uint32_t)m.la ||
             m.lb_div.div != (uint32_t)m.lb || (int64_t)m.loads * th < (int64_t)m.la * m.tb || (int64_t)m.blocks * th < (int64_t)m.la * m.lb ||
             (int64_t)(m.loads + 4) * th >= (int64_t(1) << 31) ||
-            c.lds_bytes != m.tb * m.pitch * 16 || c.lds_bytes > 64 * 1024 || grid < 1 || grid != kp.grid ||
+            c.lds_bytes != m.tb * m.pitch * 16 || c.lds_bytes > 64 * 1024 || !launchable(grid, c.threads) || grid != kp.grid ||
             m.size_a0 < V || m.size_p0 < V || m.size_a0 >= (int64_t(1) << 31) || m.size_p0 >= (int64_t(1) << 31) ||
             m.col_in_div.div < 1 || m.row_in_div.div < 1)
             return hipErrorInvalidValue;
@@ -715,7 +715,7 @@ inline hipError_t launch_line_shape(const Candidate& c, const void* A, void* B, 
         const KernelParams& kp = c.kp;
         const MicroParams& m = kp.micro;
         if (m.ta != COLS || m.lines != LINES || (m.skewed | 1) != 1 || m.tb != (LINES - m.skewed) * S.line || c.threads != kLineThreads ||
-            c.lds_bytes != S.lds_bytes || kp.num_tiles < 1 || kp.grid != kp.num_tiles || m.size_a0 < S.va || m.size_p0 < S.vb ||
+            c.lds_bytes != S.lds_bytes || !launchable(kp.num_tiles, kLineThreads) || kp.grid != kp.num_tiles || m.size_a0 < S.va || m.size_p0 < S.vb ||
             m.size_a0 >= kLineMaxExtent || m.size_p0 >= kLineMaxExtent || m.col_in_div.div < 1 || m.row_in_div.div < 1)
             return hipErrorInvalidValue;
         const void* fn = reinterpret_cast<const void*>(&line_kernel<TA, TB, MODE, COLS, LINES>);
@@ -856,7 +856,7 @@ inline hipError_t launch_gather(const Candidate& c, const void* A, void* B, hipS
     const int64_t chunks = ((rp.elements + V - 1) / V + kRowsThreads - 1) / kRowsThreads;
     if ((int64_t)rp.per_xcd != (rp.per_xcd ? (chunks + 7) / 8 : 0) || (int64_t)rp.blocks != (rp.per_xcd ? 8 * (int64_t)rp.per_xcd : chunks)) return hipErrorInvalidValue;
     const int64_t grid = rows_grid(rp);
-    if (grid < 1 || grid > INT32_MAX) return hipErrorInvalidValue;
+    if (!launchable(grid, kRowsThreads)) return hipErrorInvalidValue;
     const TA* a = static_cast<const TA*>(A);
     TB* b = static_cast<TB*>(B);
     void* args[] = {&rp, &a, &b};
@@ -875,7 +875,7 @@ inline hipError_t launch_rows_unrolled(const Candidate& c, const void* A, void* 
         (MODE == TTC_EPI_AXPBY && rp.overlap) || (int64_t)rp.blocks != (rp.vectors + rp.chunk - 1) / rp.chunk ||
         (FLAT && (rp.vectors != (rp.elements + V - 1) / V || rp.elements != (int64_t)rp.rows * rp.row))) return hipErrorInvalidValue;
     const int64_t grid = rows_grid(rp);
-    if (grid < 1 || grid > INT32_MAX) return hipErrorInvalidValue;
+    if (!launchable(grid, kRowsThreads)) return hipErrorInvalidValue;
     const TA* a = static_cast<const TA*>(A);
     TB* b = static_cast<TB*>(B);
     void* args[] = {&rp, &a, &b};

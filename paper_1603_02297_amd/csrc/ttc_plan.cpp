@@ -762,6 +762,7 @@ static bool make_micro_candidate(const Problem& P, int ta, int tb, int threads, 
         if (ntiles > INT32_MAX / 2) return false;
         C.tile_order[i] = k;
     }
+    if (!launchable(ntiles, C.threads)) return false;
     kp.num_tiles = (uint32_t)ntiles;
     kp.tiles_per_xcd = kp.num_tiles / 8;
     kp.tiles_rem_xcd = kp.num_tiles % 8;
@@ -858,6 +859,7 @@ static bool make_line_candidate(const Problem& P, int cols_tile, int lines, cons
         if (ntiles > INT32_MAX / 2) return false;
         C.tile_order[i] = k;
     }
+    if (!launchable(ntiles, C.threads)) return false;
     kp.num_tiles = (uint32_t)ntiles;
     kp.tiles_per_xcd = kp.num_tiles / 8;
     kp.tiles_rem_xcd = kp.num_tiles % 8;
@@ -980,7 +982,7 @@ static bool make_rows_candidate(const Problem& P, int vec, int unroll, bool flat
     kp.a.vec = vec; kp.b.vec = vec;
     kp.lds_buffers = 1;
     const int64_t grid = ceil_div(r.vectors, r.chunk);
-    if (grid > INT32_MAX / 2) return false;
+    if (!launchable(grid + (8 << kMaxTileMapping), C.threads)) return false;       // a launch rounds up to whole rounds over the XCDs
     kp.a.partial = kp.b.partial = r.overlap;
     kp.num_tiles = (uint32_t)grid;
     kp.grid = (uint32_t)grid;
@@ -1114,7 +1116,7 @@ bool set_tile_mapping(KernelParams* kp, int mode)
     if (mode == kDefaultTileMapping) {
         mode = kp->num_tiles >= 2048u ? 5 : 0;      // few tiles (a workgroup gets one or two): round robin spreads them best
     }
-    if (mode < 0 || mode > 10) return false;
+    if (mode < 0 || mode > kMaxTileMapping) return false;
     kp->xcd_remap = mode;
     for (int x = 0; x < 8; ++x) kp->xcd_tiles[x] = 0;
     if (mode >= 2) {
@@ -1969,7 +1971,7 @@ int ttc_plan_set_streaming(ttc_plan_t plan, int stream_a, int stream_b)
 int ttc_plan_set_tile_mapping(ttc_plan_t plan, int mode)
 {
     if (!plan) return TTC_ERR_NULL_POINTER;
-    if (mode < -1 || mode > 10) return TTC_ERR_INVALID_VALUE;
+    if (mode < -1 || mode > ttc::kMaxTileMapping) return TTC_ERR_INVALID_VALUE;
     ttc::Candidate& C = plan->cands[plan->selected];
     return ttc::set_tile_mapping(&C.kp, mode) ? TTC_OK : TTC_ERR_INVALID_VALUE;
 }

@@ -506,3 +506,23 @@ def test_default_tile_mapping_follows_the_tile_count():
     assert big["num_tiles"] >= 2048 and big["xcd_remap"] == 5
     small = info_of(ttc.TTC_F32, (256, 256), (1, 0))
     assert small["num_tiles"] < 256 and small["xcd_remap"] == 0
+
+
+@pytest.mark.parametrize("dtype,sizes,perm,ldb,beta", [
+    (ttc.TTC_C128, (2, 2, 9_000_000), (1, 0, 2), None, 0.0),
+    (ttc.TTC_C128, (4, 8, 20_000_000), (1, 0, 2), None, 1.0),
+    (ttc.TTC_F32, (4, 4, 31_250_000), (1, 0, 2), None, 0.0),
+    (ttc.TTC_F32, (4099, 6000, 6000), (0, 2, 1), (4101, 6000, 6000), 1.0),         # rows in single elements
+])
+def test_a_workgroup_for_every_tile_stays_within_a_launch(dtype, sizes, perm, ldb, beta):
+    """HIP launches fewer than 2^32 work items: no candidate whose tiles (or chunks) each take a workgroup asks for more."""
+    p = ttc.ttc_plan_create_ex(dtype, len(sizes), sizes, perm, None, ldb, 1.0, beta)
+    n = ttc.ttc_plan_candidate_count(p)
+    assert n >= 10
+    for k in range(n):
+        ttc.ttc_plan_select_candidate(p, k)
+        i = ttc.ttc_plan_get_info(p)
+        one_shot = i["kernel_class"] in (ttc.TTC_KERNEL_ROWS, ttc.TTC_KERNEL_MICRO) or (i["kernel_class"] == ttc.TTC_KERNEL_LDS and i["unroll"] > 0)
+        if one_shot:
+            assert i["num_tiles"] * i["threads"] < 2 ** 32, (k, i["kernel_class"], i["tile"])
+    ttc.ttc_plan_destroy(p)
