@@ -51,8 +51,8 @@ enum {
 /* Kernel families (paper Section 3.1: the stride-1 index keeps its place, or not). */
 enum { TTC_KERNEL_DIRECT = 0 /* tiles, no staging: stride-1 index fixed */, TTC_KERNEL_LDS = 1 /* tile staged through LDS: a box over up to four
                                indices, or (unroll != 0) the line kernel: columns of A's direction by whole 128-byte lines of B */,
-       TTC_KERNEL_ROWS = 2 /* B walked front to back: rows gathered from A (stride-1 index fixed), or single elements (the gather
-                               kernel: small problems, any permutation) */,
+       TTC_KERNEL_ROWS = 2 /* B walked front to back: rows gathered from A (stride-1 index fixed), or (unroll == 0) single elements
+                               (the gather kernel: small problems, any permutation) */,
        TTC_KERNEL_MICRO = 3 /* tile over the two stride-1 indices only (each possibly merged with the index next to it in
                                its tensor): 128-bit LDS accesses, XOR-swizzled rows, register transposes of 4x4 (2x2)
                                blocks; one precision of 4- or 8-byte elements */ };
@@ -109,7 +109,8 @@ typedef struct {
     float   tuned_ms;                      /* time of the selected candidate in the last ttc_plan_tune, else 0 */
     double  heuristic_cost;                /* the ranking key: modelled relative cost, smaller is better */
     int     unroll;                        /* row kernel: vectors a lane keeps in flight (1, 2, 4 or 8); micro-tile kernel: blocks a lane owns
-                                              (1 to 6); line kernel: lines of B whose rows a tile holds (2, 4 or 8); 0 for the box kernels */
+                                              (1 to 6); line kernel: lines of B whose rows a tile holds (2, 4 or 8); 0 for the box kernels
+                                              and the gather kernel */
     int     merged;                        /* micro-tile and line kernel: bit 0: the tile's column index is A's indices 0 and 1 taken as one,
                                               bit 1: its row index is B's first two indices taken as one; else 0 */
 } ttc_plan_info_t;

@@ -1782,13 +1782,17 @@ int build_plan(int dtype, int ndim, const int64_t* sizes, const int* perm, const
     plan->complete = false;
     if (verbose()) {
         const Candidate& c = plan->cands[0];
-        std::fprintf(stderr, "ttc: plan dtype %d, %d fused indices, %s kernel, tile", P.dtype, P.ndim,
-                     c.kernel_class == TTC_KERNEL_DIRECT ? "direct" : (c.kernel_class == TTC_KERNEL_ROWS ? "row" : (c.kernel_class == TTC_KERNEL_MICRO ? "micro-tile" : (c.kernel_class == kKernelLines ? "line" : (c.kernel_class == kKernelGather ? "gather" : "staged")))));
+        static const char* const names[] = {"direct", "staged", "row", "micro-tile", "line", "gather"};       // by kernel class
+        constexpr int kClasses = (int)(sizeof(names) / sizeof(names[0]));
+        static_assert(TTC_KERNEL_MICRO == 3 && kKernelLines == 4 && kKernelGather == kClasses - 1, "one name per class");
+        std::fprintf(stderr, "ttc: plan dtype %d, %d fused indices, %s kernel, tile", P.dtype, P.ndim, names[c.kernel_class]);
         for (int k = 0; k < P.ndim; ++k) std::fprintf(stderr, " %d", c.tile[k]);
-        size_t per_class[6] = {0, 0, 0, 0, 0, 0};
-        for (const Candidate& q : quick) if (q.kernel_class >= 0 && q.kernel_class < 6) ++per_class[q.kernel_class];
-        std::fprintf(stderr, ", vectors %d/%d, %d threads, %d B LDS, cost %.4f (best of %zu candidates of the short list: %zu direct, %zu staged, %zu row, %zu micro-tile, %zu line)\n",
-                     c.kp.a.vec, c.kp.b.vec, c.threads, c.lds_bytes, c.score, quick.size(), per_class[0], per_class[1], per_class[2], per_class[3], per_class[4]);
+        size_t per_class[kClasses] = {0};
+        for (const Candidate& q : quick) ++per_class[q.kernel_class];
+        std::fprintf(stderr, ", vectors %d/%d, %d threads, %d B LDS, cost %.4f (best of %zu candidates of the short list:",
+                     c.kp.a.vec, c.kp.b.vec, c.threads, c.lds_bytes, c.score, quick.size());
+        for (int k = 0; k < kClasses; ++k) std::fprintf(stderr, "%s %zu %s", k ? "," : "", per_class[k], names[k]);
+        std::fprintf(stderr, ")\n");
     }
     return TTC_OK;
 }
@@ -1947,7 +1951,7 @@ int ttc_plan_get_info(ttc_plan_t plan, ttc_plan_info_t* out)
     out->tuned_ms = C.tuned_ms;
     out->heuristic_cost = C.score;
     out->merged = (C.kernel_class == TTC_KERNEL_MICRO || C.kernel_class == ttc::kKernelLines) ? (C.kp.micro.merged_a | (C.kp.micro.merged_b << 1)) : 0;
-    out->unroll = (C.kernel_class == TTC_KERNEL_ROWS || C.kernel_class == ttc::kKernelGather) ? C.rows.unroll : 
+    out->unroll = C.kernel_class == TTC_KERNEL_ROWS ? C.rows.unroll :
                   (C.kernel_class == TTC_KERNEL_MICRO ? C.kp.micro.blocks : (C.kernel_class == ttc::kKernelLines ? C.kp.micro.lines : 0));
     return TTC_OK;
     });

@@ -186,7 +186,7 @@ def search_set(families, cap):
 
 def micro_family(info):
     """0: not the micro-tile kernel; 1: its tile is over single indices; 2: two indices taken as one on a side."""
-    if info["kernel_class"] != ttc.TTC_KERNEL_MICRO:
+    if ttc.kernel_family(info) != "micro":
         return 0
     return 2 if info["merged"] else 1
 
@@ -234,8 +234,8 @@ def study_search(out, dump=None):
 def unpadded_ms(dtype, sizes, perm, alpha, beta, best_info, a_ptrs, b_ptrs, stream, tmp):
     """Time of the configuration `best_info` names when its LDS tile is laid out without pads (without the swizzle), or None."""
     import os
-    if best_info["kernel_class"] not in (ttc.TTC_KERNEL_LDS, ttc.TTC_KERNEL_MICRO):
-        return None                              # no LDS tile (the micro-tile kernel's is swizzled, not padded: the swizzle goes)
+    if ttc.kernel_family(best_info) not in ("lds", "micro"):
+        return None                              # no LDS tile (the micro-tile kernel's is swizzled, not padded: the swizzle goes), or a fixed pitch (line)
     plan = ttc.ttc_plan_create(dtype, len(sizes), sizes, perm, alpha, beta)
     ttc.ttc_plan_select_candidate(plan, best_info["candidate_index"])
     ttc.ttc_plan_set_streaming(plan, best_info["nt_a"], best_info["nt_b"])
@@ -257,7 +257,7 @@ def unpadded_ms(dtype, sizes, perm, alpha, beta, best_info, a_ptrs, b_ptrs, stre
     return ms, info
 
 
-ONE_SHOT = (ttc.TTC_KERNEL_ROWS, ttc.TTC_KERNEL_MICRO)      # one tile (chunk) per workgroup: no workgroups-per-CU knob
+BOX = ("direct", "lds")      # the box kernels; the others give every tile (chunk) a workgroup: no workgroups-per-CU knob, one tile buffer or none
 
 
 def ablations(rows):
@@ -272,12 +272,12 @@ def ablations(rows):
         return (min(sel) / best) if sel else float("nan")
 
     return {
-        "tile shape": best_where(lambda i: i["tile"] == first["tile"] and i["kernel_class"] == first["kernel_class"]),
+        "tile shape": best_where(lambda i: i["tile"] == first["tile"] and ttc.kernel_family(i) == ttc.kernel_family(first)),
         "vector width": best_where(lambda i: i["vec_a"] == 1 and i["vec_b"] == 1),
         "tile order": best_where(lambda i: i["tile_order"] == i["perm"]),
-        "LDS buffering": best_where(lambda i: i["kernel_class"] != ttc.TTC_KERNEL_LDS or i["lds_buffers"] == 2),
-        "launch shape": best_where(lambda i: i["threads"] == 256 and (i["wg_per_cu"] == 16 or i["kernel_class"] in ONE_SHOT)),
-        "kernel family": best_where(lambda i: i["kernel_class"] in (ttc.TTC_KERNEL_LDS, ttc.TTC_KERNEL_DIRECT)),
+        "LDS buffering": best_where(lambda i: ttc.kernel_family(i) != "lds" or i["lds_buffers"] == 2),
+        "launch shape": best_where(lambda i: i["threads"] == 256 and (i["wg_per_cu"] == 16 or ttc.kernel_family(i) not in BOX)),
+        "kernel family": best_where(lambda i: ttc.kernel_family(i) in BOX),
     }
 
 
@@ -345,7 +345,7 @@ def study_sweep(out, limit=None, dump=None):
             "tile order": "tiles numbered in B's index order", "LDS buffering": "two tile buffers",
             "launch shape": "256 threads, 16 workgroups per CU",
             "LDS pads": "the best configuration with an unpadded LDS tile",
-            "kernel family": "box kernels only (no row kernel, no micro-tile kernel)"}
+            "kernel family": "box kernels only (no micro-tile, line, row or gather kernel)"}
     for name in held:
         g = [r["abl"][name] - 1.0 for r in results if r["abl"][name] == r["abl"][name]]
         if g:
@@ -471,9 +471,9 @@ def study_fit(out, dumps, ridge=0.05, sharpness=3.0, folds=8, family="box"):
             for line in fh:
                 d = json.loads(line)
                 if family == "micro":
-                    d["rows"] = [r for r in d["rows"] if r["kernel_class"] == ttc.TTC_KERNEL_MICRO]
+                    d["rows"] = [r for r in d["rows"] if ttc.kernel_family(r) == "micro"]
                 else:
-                    d["rows"] = [r for r in d["rows"] if r["kernel_class"] not in ONE_SHOT]
+                    d["rows"] = [r for r in d["rows"] if ttc.kernel_family(r) in BOX]
                 if len(d["rows"]) >= 4:
                     data.append(d)
     features, free_sign = (fit_micro_features, FREE_SIGN_MICRO) if family == "micro" else (fit_features, FREE_SIGN)

@@ -34,6 +34,32 @@ def test_search_set_keeps_places_for_both_micro_tile_families():
     assert st.search_set(fam, 400) == list(range(300))
 
 
+def test_every_kernel_has_a_family_of_its_own():
+    """The line and the gather kernel report another kernel's class: the studies, the benchmark and the smoke run tell
+    them apart by it, and nothing but box kernels enters the box model's fit and its ablation."""
+    def families(dtype, sizes, perm):
+        p = ttc.ttc_plan_create(dtype, len(sizes), sizes, perm, 1.0, 0.0)
+        seen = {}
+        for k in range(ttc.ttc_plan_candidate_count(p)):
+            ttc.ttc_plan_select_candidate(p, k)
+            info = ttc.ttc_plan_get_info(p)
+            seen.setdefault(ttc.kernel_family(info), []).append(info)
+        ttc.ttc_plan_destroy(p)
+        return seen
+
+    moved, fixed = families(ttc.TTC_F32, (70, 33, 45), (2, 0, 1)), families(ttc.TTC_F32, (96, 20, 31), (0, 2, 1))
+    assert set(moved) == {"lds", "line", "gather", "micro"} and set(fixed) == {"direct", "lds", "rows", "gather"}
+    assert len(moved["gather"]) == len(fixed["gather"]) == 1             # one candidate, whatever the problem
+    assert {i["unroll"] for i in moved["line"]} <= {2, 4, 8} and {i["unroll"] for i in fixed["rows"]} <= {1, 2, 4, 8}
+    assert all(i["wg_per_cu"] == 0 for f in ("line", "gather", "micro") for i in moved[f])
+    assert all(i["wg_per_cu"] > 0 for f in st.BOX for i in moved.get(f, []) + fixed.get(f, []))
+    rows = [(i, 1.0 if f in st.BOX else 0.5) for f in moved for i in moved[f]]
+    rows.sort(key=lambda r: r[0]["candidate_index"])
+    abl = st.ablations(rows)
+    assert abl["kernel family"] == 2.0 and abl["LDS buffering"] == abl["launch shape"] == 1.0
+    assert st.ablations([r for r in rows if ttc.kernel_family(r[0]) in ("lds", "line")])["launch shape"] == 1.0
+
+
 def test_micro_tile_features_mirror_the_library_model():
     """micro_cost() of the library = exp(offset + sum of the fitted weights times these features)."""
     weights = {"A<128": 0.05, "B<128": 0.012, "A>1K": -0.01, "B>1K": -0.03, "pad": 0.11, "unA*A<512": 0.028,
