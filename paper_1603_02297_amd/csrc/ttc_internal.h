@@ -230,8 +230,8 @@ struct RowsParams {
     int32_t  flat;                   // 1: B is dense: vectors are counted through B from its first element, across the ends of rows
     int32_t  xcd_remap;              // how the workgroups' chunks are dealt to the XCDs (as KernelParams::xcd_remap)
     uint32_t blocks;                 // chunks, one per workgroup
-    uint32_t per_xcd;                // gather kernel: 0, or chunks are numbered so that every eighth is the next one in B (eight ranges of
-                                     // this many chunks side by side)
+    uint32_t per_xcd;                // gather kernel, round robin over the XCDs (xcd_remap 0): 0, or chunks are numbered so that every
+                                     // eighth is the next one in B (eight ranges of this many chunks side by side)
     uint32_t rows;                   // rows of the tensor
     FastDiv  slot_div;               // x / slots
     FastDiv  size_div[kMaxDim];      // extent of B's index d, d = 1 .. n-1 (entry 0: gather kernel only)

@@ -1091,9 +1091,11 @@ static bool make_gather_candidate(const Problem& P, Candidate* out)
         kp.stride_a[k] = (k < P.ndim) ? P.stride_a[k] : 0;
         kp.stride_b[k] = (k < P.ndim) ? P.stride_b[k] : 0;
     }
-    // Workgroups that share lines of A with their neighbours belong on one XCD: one contiguous range each (2-D 581 x 779
-    // complex128 5.4 us against 10.0 dealt one by one); where they share none the ranges only spread the reads further
-    // (18 x 352 x 6 x 22 complex64, reversed, 16.0 against 9.6).
+    // Workgroups that share lines of A with their neighbours belong on one XCD: one contiguous range each, dealt round robin
+    // at any size (transposes, against chunks numbered as they lie in B: 600 x 600 fp32 4.1 us and 5.3, 1500 x 1500 12.7
+    // and 17.6, 700 x 500 fp64 4.0 and 6.0; in chunks of 32 1500 x 1500 takes 13.2).  Where they share none the ranges may
+    // only spread the reads further (40 x 50 x 60 x 20 complex64, reversed, 45 against 31); that workgroups further apart
+    // share some is not seen (581 x 783 complex128 runs at 9.9, 5.3 in ranges; the line kernel is ranked first there).
     const GatherLines g = gather_lines(P, r);
     const uint32_t chunks = r.blocks;
     if (chunks >= 64 && g.shared > 0.25) {
@@ -1101,7 +1103,7 @@ static bool make_gather_candidate(const Problem& P, Candidate* out)
         r.blocks = 8 * r.per_xcd;
     }
     kp.num_tiles = kp.grid = r.blocks;
-    if (!set_tile_mapping(&kp, kDefaultTileMapping)) return false;
+    if (!set_tile_mapping(&kp, r.per_xcd ? 0 : kDefaultTileMapping)) return false;
     // Fitted to 170 problems of 0.1 to 60 MB: 20 % rms.
     C.model_us = 2.5 + 0.105e-6 * traffic_bytes(P) + 2.25e-6 * g.requests * 4.0 * chunks + 4.3e-6 * g.lines * chunks;
     C.digits_a = C.digits_b = 1;
@@ -1977,7 +1979,7 @@ int ttc_plan_set_tile_mapping(ttc_plan_t plan, int mode)
     if (!plan) return TTC_ERR_NULL_POINTER;
     if (mode < -1 || mode > ttc::kMaxTileMapping) return TTC_ERR_INVALID_VALUE;
     ttc::Candidate& C = plan->cands[plan->selected];
-    return ttc::set_tile_mapping(&C.kp, mode) ? TTC_OK : TTC_ERR_INVALID_VALUE;
+    return ttc::set_tile_mapping(&C.kp, mode < 0 && C.rows.per_xcd ? 0 : mode) ? TTC_OK : TTC_ERR_INVALID_VALUE;
 }
 
 int ttc_plan_candidate_count(ttc_plan_t plan)

@@ -115,7 +115,7 @@ TTC_HD GatherPlace gather_place(const RowsParams& p, uint32_t e)
 // First element of lane `tid` of chunk `block` (past the end of B: nothing to do).
 TTC_HD uint32_t gather_first(const RowsParams& p, uint32_t block, uint32_t tid)
 {
-    if (p.per_xcd) block = (block & 7u) * p.per_xcd + (block >> 3);
+    if (p.per_xcd && p.xcd_remap == 0) block = (block & 7u) * p.per_xcd + (block >> 3);
     return (block * p.chunk + tid) * (uint32_t)p.vec;
 }
 

@@ -84,6 +84,48 @@ def test_plans_as_created_where_b_has_no_unit_stride(dtype):
             ttc.ttc_plan_destroy(p)
 
 
+# sizes, perm, type, whether neighbouring workgroups of the gather kernel share lines of A: several hundred to 2200 chunks of 256
+# vectors, the numbers of chunks no multiples of eight
+GATHER_CHUNKS = [
+    ((301, 203), (1, 0), wl.C128, True),
+    ((301, 509), (1, 0), wl.F32, True),
+    ((1500, 1500), (1, 0), wl.F32, True),
+    ((301, 37, 21), (2, 1, 0), wl.F64, True),
+    ((581, 783), (1, 0), wl.C128, False),
+    ((700, 900), (1, 0), wl.C128, False),
+]
+
+
+def gather_candidate(plan):
+    for k in range(ttc.ttc_plan_candidate_count(plan)):
+        ttc.ttc_plan_select_candidate(plan, k)
+        if ttc.kernel_family(ttc.ttc_plan_get_info(plan)) == "gather":
+            return ttc.ttc_plan_get_info(plan)
+    raise AssertionError("no gather candidate")
+
+
+@pytest.mark.parametrize("sizes,perm,dtype,shared", GATHER_CHUNKS)
+def test_gather_chunks_are_dealt_one_way(sizes, perm, dtype, shared):
+    """Where neighbours share lines the chunks are numbered range by range and dealt round robin, whatever their number: a
+    second dealing on top would give every XCD pieces of all ranges.  Else by the number of chunks, as tiles are.
+    Every mapping covers B."""
+    p = ttc.ttc_plan_create(dtype, len(sizes), sizes, perm, 1.0, 0.0)
+    info = gather_candidate(p)
+    chunks = -(-int(np.prod(sizes)) * wl.ELEM_BYTES_B[dtype] // 4096)
+    assert chunks >= 64 and chunks % 8 != 0
+    assert info["num_tiles"] == (-(-chunks // 8) * 8 if shared else chunks)
+    default = 0 if shared or chunks < 2048 else 5
+    assert info["xcd_remap"] == default
+    n = len(sizes)
+    stride = np.cumprod([1] + list(sizes[:-1]))                       # B in its own order: where each element comes from
+    want = (np.indices([sizes[k] for k in perm][::-1]) * np.array([stride[k] for k in perm][::-1]).reshape((n,) + (1,) * n)).sum(0).ravel()
+    for mode in (-1, 0, 1, 5, -1):
+        ttc.ttc_plan_set_tile_mapping(p, mode)
+        assert ttc.ttc_plan_get_info(p)["xcd_remap"] == (default if mode < 0 else mode)
+        assert np.array_equal(np.array(ttc.ttc_debug_emulate_map(p)), want), mode
+    ttc.ttc_plan_destroy(p)
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("dtype", DTYPES, ids=[wl.DTYPE_NAME[d] for d in DTYPES])
 def test_row_kernel_against_the_oracle(dtype):
