@@ -94,3 +94,36 @@ def test_line_kernel_against_the_oracle(dtype):
             finally:
                 ttc.ttc_plan_destroy(plan)
     assert ran >= 100
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", [wl.C128, wl.C64_C128, wl.C128_C64], ids=["c128", "c64c128", "c128c64"])
+def test_elements_that_start_halfway(dtype):
+    """complex128 operands need 8-byte alignment only: elements, and lines of B, that start in the middle of 16 bytes."""
+    import torch
+    dev = torch.device("cuda:0")
+    stream = torch.cuda.current_stream().cuda_stream
+    shift_a, shift_b = (1 if wl.ELEM_BYTES[dtype] == 16 else 2), (1 if wl.ELEM_BYTES_B[dtype] == 16 else 2)        # in components
+    ran = 0
+    for shape, (sizes, perm, lda, ldb) in enumerate(SHAPES[:4] + SHAPES[-2:]):
+        A = wl.uniform_tensor(dtype, int(np.prod(lda or sizes)), 7900 + shape, "a")
+        B0 = wl.uniform_tensor(dtype, int(np.prod(ldb or sizes)), 7950 + shape, "b")
+        bufa = torch.zeros(A.size + 4, dtype=torch.from_numpy(A).dtype, device=dev)
+        bufa[shift_a:shift_a + A.size] = torch.from_numpy(A).to(dev)
+        for alpha, beta in scalars(dtype)[::2]:
+            want = oracle.transpose(dtype, sizes, perm, alpha, beta, A, B0.copy(), 4, lda=lda, ldb=ldb)
+            plan = ttc.ttc_plan_create_ex(dtype, len(sizes), sizes, perm, lda, ldb, alpha, beta)
+            try:
+                for k, info in line_candidates(plan):
+                    buf = torch.full((B0.size + 128,), 77.0, dtype=torch.from_numpy(B0).dtype, device=dev)
+                    at = 64 + shift_b
+                    buf[at:at + B0.size] = torch.from_numpy(B0).to(dev)
+                    ttc.ttc_execute(plan, bufa.data_ptr() + shift_a * bufa.element_size(), buf.data_ptr() + at * buf.element_size(), stream)
+                    got = buf.cpu().numpy()
+                    assert (got[:at] == 77).all() and (got[at + B0.size:] == 77).all(), (sizes, perm, k, info)
+                    allowed = 0.0 if complex(alpha) == 1 and complex(beta) == 0 else np.spacing(np.abs(want).max())
+                    assert np.abs(got[at:at + B0.size] - want).max() <= allowed, (sizes, perm, alpha, beta, k, info)
+                    ran += 1
+            finally:
+                ttc.ttc_plan_destroy(plan)
+    assert ran >= 40

@@ -185,3 +185,72 @@ def test_plans_as_created_where_b_has_no_unit_stride_on_the_gpu(dtype):
             ttc.ttc_plan_destroy(plan)
             allowed = 0.0 if beta == 0 else np.spacing(np.abs(want).max())      # the one ulp the library allows an update
             assert np.abs(got - want).max() <= allowed, (sizes, perm, ldb, beta)
+
+
+def execute_and_compare(plan, dtype, dA, B0, want, moved_only, setup, tag):
+    """One ttc_execute on a B that starts `first` elements behind an aligned address, `setup` = (streaming hint, first): what
+    lies around B stays as it was, B is the oracle's: bit-equal where elements are only moved, else within the one ulp the
+    library allows (same evaluation order)."""
+    import torch
+    comp, room = wl.COMPONENTS[dtype], 64
+    nt, first = setup
+    ttc.ttc_plan_set_streaming(plan, nt, nt)
+    buf = torch.full((B0.size + 2 * room,), 77.0, dtype=torch.from_numpy(B0).dtype, device=dA.device)
+    at = room + int(first * comp)
+    buf[at:at + B0.size] = torch.from_numpy(B0).to(dA.device)
+    ttc.ttc_execute(plan, dA.data_ptr(), buf.data_ptr() + at * buf.element_size(), torch.cuda.current_stream().cuda_stream)
+    got = buf.cpu().numpy()
+    assert (got[:at] == 77).all() and (got[at + B0.size:] == 77).all(), tag
+    got = got[at:at + B0.size]
+    if moved_only:
+        assert np.array_equal(got, want), tag
+    else:
+        assert np.abs(got - want).max() <= np.spacing(np.abs(want).max()), tag
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", DTYPES, ids=[wl.DTYPE_NAME[d] for d in DTYPES])
+def test_streaming_and_odd_addresses_against_the_oracle(dtype):
+    """Every row and gather candidate with both settings of the streaming hints, and on a B aligned to its element only."""
+    import torch
+    dev = torch.device("cuda:0")
+    cplx, ran = wl.COMPONENTS[dtype] == 2, 0
+    setups = ((0, 1), (1, 3), (1, 0)) + (((0, 0.5),) if dtype == wl.C128 else ())          # 8 bytes are enough for complex128
+    for shape, (sizes, perm, lda, ldb) in enumerate(SHAPES):
+        A = wl.uniform_tensor(dtype, int(np.prod(lda or sizes)), 7600 + shape, "a")
+        B0 = wl.uniform_tensor(dtype, int(np.prod(ldb or sizes)), 7700 + shape, "b")
+        dA = torch.from_numpy(A).to(dev)
+        for alpha, beta in ((1.0, 0.0), (0.75, 1.0 + 0.5j if cplx else -1.25)):
+            want = oracle.transpose(dtype, sizes, perm, alpha, beta, A, B0.copy(), 4, lda=lda, ldb=ldb)
+            plan = ttc.ttc_plan_create_ex(dtype, len(sizes), sizes, perm, lda, ldb, alpha, beta)
+            try:
+                for k in range(ttc.ttc_plan_candidate_count(plan)):
+                    ttc.ttc_plan_select_candidate(plan, k)
+                    if ttc.kernel_family(ttc.ttc_plan_get_info(plan)) not in ("rows", "gather"):
+                        continue
+                    for setup in setups:
+                        execute_and_compare(plan, dtype, dA, B0, want, beta == 0, setup, (sizes, perm, beta, k, setup))
+                        ran += 1
+            finally:
+                ttc.ttc_plan_destroy(plan)
+    assert ran >= 100
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("sizes,perm,dtype,shared", GATHER_CHUNKS)
+def test_many_gather_chunks_against_the_oracle(sizes, perm, dtype, shared):
+    """Hundreds of chunks, their numbers no multiples of eight: every dealing of them, with and without an update of B."""
+    import torch
+    dev = torch.device("cuda:0")
+    A = wl.uniform_tensor(dtype, int(np.prod(sizes)), 7800, "a")
+    B0 = wl.uniform_tensor(dtype, int(np.prod(sizes)), 7801, "b")
+    dA = torch.from_numpy(A).to(dev)
+    for alpha, beta in ((1.0, 0.0), (0.75, -1.25)):
+        want = oracle.transpose(dtype, sizes, perm, alpha, beta, A, B0.copy(), 4)
+        plan = ttc.ttc_plan_create(dtype, len(sizes), sizes, perm, alpha, beta)
+        gather_candidate(plan)
+        for mapping in (-1, 0, 1, 5):
+            ttc.ttc_plan_set_tile_mapping(plan, mapping)
+            for setup in ((0, 1), (1, 0)):
+                execute_and_compare(plan, dtype, dA, B0, want, beta == 0, setup, (sizes, perm, beta, mapping, setup))
+        ttc.ttc_plan_destroy(plan)
