@@ -188,7 +188,8 @@ int ttc_plan_set_streaming(ttc_plan_t plan, int stream_a, int stream_b);
  * 1: one contiguous range of tile ids per XCD; 2..10: chunks of 2^mode consecutive tile ids dealt to the
  * XCDs in turn; -1: the default (chunks of 32; round robin below 2048 tiles, and for the gather kernel where neighbouring
  * workgroups share lines of A: its tile ids are then numbered so that mode 0 gives every XCD one range of B).  Reported as
- * xcd_remap by ttc_plan_get_info.  The search times its finalists with modes 1 and 3 as well.  Host only.
+ * xcd_remap by ttc_plan_get_info.  The search times its finalists with modes 1 and 3 as well (not those of the row
+ * kernel).  Host only.
  */
 int ttc_plan_set_tile_mapping(ttc_plan_t plan, int mode);
 

@@ -326,11 +326,14 @@ static int tune_pairs(ttc_plan_t plan, int npairs, const void* const* A_list, vo
         c.kp.nt_a = keep_a;
         c.kp.nt_b = keep_b;
         // the same for the mapping of tiles to XCDs: the default (chunks of 32 if there are enough tiles), one
-        // range per XCD, chunks of 8
+        // range per XCD, chunks of 8.  Not for the row kernel, whose default no other mapping beats: over twelve
+        // problems of 16 to 400 MB round robin was 0.2 % ahead at best (85^4 fp32 (0,3,2,1) with an update) and 4 %
+        // behind at worst (208 x 115 x 63 x 35), chunks of 8 2-8 % behind on most, one range 1-13 %; trying them made the
+        // search keep a slower one on 384^3, where the timings of 12 launches differ by more than that.
         const int mapping0 = c.kp.xcd_remap;
         int keep_map = mapping0;
         for (int mode : {1, 3}) {
-            if (c.kernel_class == TTC_KERNEL_ROWS) break;           // no tiles to deal
+            if (c.kernel_class == TTC_KERNEL_ROWS) break;
             if (mode == mapping0 || !ttc::set_tile_mapping(&c.kp, mode)) continue;
             float ms = 0.f;
             const int st3 = time_one(c, 2, reps2, &ms);

@@ -135,8 +135,8 @@ def retime_best(plan, rows, a_ptrs, b_ptrs, stream, keep=8):
         info = best[0]
         ttc.ttc_plan_set_streaming(plan, info["nt_a"], info["nt_b"])
         for mode in (1, 3):                      # tiles dealt to the XCDs: one range each, chunks of 8 (default: chunks of 32)
-            if info["kernel_class"] == ttc.TTC_KERNEL_ROWS:
-                break                            # no tiles to deal
+            if ttc.kernel_family(info) == "rows":
+                break                            # as the library's search: its default is ahead
             ttc.ttc_plan_set_tile_mapping(plan, mode)
             ms = ttc.ttc_time_execute(plan, a_ptrs, b_ptrs, stream, 2, 12)
             if ms < best[1]:
