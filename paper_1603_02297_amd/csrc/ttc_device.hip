@@ -326,10 +326,10 @@ static int tune_pairs(ttc_plan_t plan, int npairs, const void* const* A_list, vo
         c.kp.nt_a = keep_a;
         c.kp.nt_b = keep_b;
         // the same for the mapping of tiles to XCDs: the default (chunks of 32 if there are enough tiles), one
-        // range per XCD, chunks of 8.  Not for the row kernel, whose default no other mapping beats: over twelve
-        // problems of 16 to 400 MB round robin was 0.2 % ahead at best (85^4 fp32 (0,3,2,1) with an update) and 4 %
-        // behind at worst (208 x 115 x 63 x 35), chunks of 8 2-8 % behind on most, one range 1-13 %; trying them made the
-        // search keep a slower one on 384^3, where the timings of 12 launches differ by more than that.
+        // range per XCD, chunks of 8.  Not for the row kernel, whose default is ahead: over eleven problems of 200 to 630 MB
+        // of traffic round robin took 0.2 % less at best (85^4 fp32 (0,3,2,1) with an update) and 4 % more at worst (208 x
+        // 115 x 63 x 35), chunks of 8 1-8 % more, one range 1-11 % more; at 16 MB (384 x 72 x 72) one range took 2 % less.
+        // Trying them made the search keep round robin on 384^3 (74.2 us, default 72.9).
         const int mapping0 = c.kp.xcd_remap;
         int keep_map = mapping0;
         for (int mode : {1, 3}) {

@@ -1313,6 +1313,15 @@ static double line_cost(const Problem& P, const Candidate& C)
         if (m.skewed) loaded -= S.line / S.pass * S.pass;                 // the first tile needs no rows before it
         e = -0.245 - (m.skewed ? 0.082 : 0.0) - (update ? 0.083 : 0.0);
         if (one_precision) e += m.skewed ? -0.073 : (split_a || update ? -0.010 : 0.075);     // whole lines on both sides: the micro-tile kernel is as good
+        // Updates with whole lines on both sides, where neither kernel splits one: line against micro-tile kernel on one pair
+        // of tensors, on pairs in rotation and on new ones, geometric means.  Tensors beyond the 256 MB of the last-level
+        // cache (15 problems): 1.13, 1.01 and 1.28 times the micro-tile kernel's time (288 x 608 x 221 complex64 (1,0,2):
+        // 144 us against 130, 146 against 158, 189 against 138).  Smaller ones of 4-byte elements (12): 0.98, 1.09 and
+        // 1.06; of 8-byte elements (15): 0.99, 0.97 and 1.02.
+        if (one_precision && update && !m.skewed && !split_a) {
+            if (P.elements * P.eb_a >= (int64_t(256) << 20)) e += 0.30;
+            else if (P.eb_a == 4) e += 0.17;
+        }
         if (update && m.merged_a && P.size[0] * P.eb_a >= 512) e += 0.08 + (P.perm[1] == 0 ? 0.12 : 0.0);    // a tile that crosses the end of a row
                                                                           // reads and writes B in two places, and leaves a contiguous block
         e += 0.343 * std::log((double)loaded / rows) + 0.340 * pad_cols + 0.293 * std::log((double)segs * m.tb / rows) + 0.087 * split;

@@ -526,3 +526,19 @@ def test_a_workgroup_for_every_tile_stays_within_a_launch(dtype, sizes, perm, ld
         if one_shot:
             assert i["num_tiles"] * i["threads"] < 2 ** 32, (k, i["kernel_class"], i["tile"])
     ttc.ttc_plan_destroy(p)
+
+
+@pytest.mark.parametrize("dtype,sizes,perm,family", [
+    (ttc.TTC_C64, (8, 64, 48, 40, 80), (2, 0, 4, 3, 1), "micro"),       # 629 MB
+    (ttc.TTC_F64, (32, 2368, 590), (1, 2, 0), "micro"),                 # 358 MB
+    (ttc.TTC_F32, (64, 5312, 336), (1, 0, 2), "micro"),                 # 457 MB
+    (ttc.TTC_F32, (864, 128, 381), (1, 0, 2), "micro"),                 # 169 MB, 4-byte elements
+    (ttc.TTC_F64, (72, 72, 72, 72), (3, 2, 1, 0), "line"),              # rows of A and columns of B end inside lines
+    (ttc.TTC_C64, (291, 603, 221), (1, 0, 2), "line"),
+])
+def test_large_updates_with_whole_lines_take_the_micro_tile_kernel(dtype, sizes, perm, family):
+    """Where no line is split the line kernel has nothing to save: an update of tensors beyond the last-level cache takes it
+    a quarter longer on new buffers."""
+    p = plan(dtype, sizes, perm, 0.5, 1.0)
+    assert ttc.kernel_family(ttc.ttc_plan_get_info(p)) == family
+    ttc.ttc_plan_destroy(p)
