@@ -1018,7 +1018,8 @@ static GatherLines gather_lines(const Problem& P, const RowsParams& r)
     GatherLines g = {0, 0, 0};
     const uint32_t vec = (uint32_t)r.vec, last = (uint32_t)(P.elements - 1);
     constexpr uint32_t kSlots = 4096;                      // at most 2 x 1024 lines a pair
-    struct Slot { int64_t line; uint32_t loads; } slot[kSlots];       // bit 16 w + 4 wave + j: load j of that wavefront touches it
+    struct Slot { int64_t line; uint32_t loads; };         // bit 16 w + 4 wave + j: load j of that wavefront touches it
+    std::vector<Slot> slot(kSlots);                        // 64 KB: more than a thread's stack may have
     double both = 0, single = 0;
     for (int s = 0; s < 2; ++s) {
         const uint32_t wg = (uint32_t)((int64_t)r.blocks * (1 + 2 * s) / 4);

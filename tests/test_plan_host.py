@@ -2,6 +2,9 @@
 candidate list, and -- through the library's host-side replay of its own index arithmetic --
 that every candidate's walk stays in bounds and realises the element map of Eq. 1."""
 import itertools
+import os
+import subprocess
+import sys
 
 import numpy as np
 import pytest
@@ -542,3 +545,26 @@ def test_large_updates_with_whole_lines_take_the_micro_tile_kernel(dtype, sizes,
     p = plan(dtype, sizes, perm, 0.5, 1.0)
     assert ttc.kernel_family(ttc.ttc_plan_get_info(p)) == family
     ttc.ttc_plan_destroy(p)
+
+
+def test_a_plan_is_created_on_a_small_stack():
+    """Threads of a host program may have little stack: planning keeps its tables elsewhere.  In a process of its own, which
+    an overflow would end."""
+    program = ("import sys, threading\n"
+               "import paper_1603_02297_amd as ttc\n"
+               "ttc.lib()\n"
+               "threading.stack_size(64 * 1024)\n"
+               "done = []\n"
+               "def create():\n"
+               "    for sizes, perm in (((300, 200), (1, 0)), ((24, 20, 16, 18, 22, 17), (5, 4, 3, 2, 1, 0)), ((917, 374, 153), (0, 2, 1))):\n"
+               "        p = ttc.ttc_plan_create(ttc.TTC_F32, len(sizes), sizes, perm, 1.0, 0.0)\n"
+               "        ttc.ttc_plan_candidate_count(p)\n"
+               "        ttc.ttc_plan_destroy(p)\n"
+               "        done.append(sizes)\n"
+               "t = threading.Thread(target=create)\n"
+               "t.start()\n"
+               "t.join()\n"
+               "assert len(done) == 3\n")
+    r = subprocess.run([sys.executable, "-c", program], cwd=os.path.dirname(os.path.dirname(os.path.abspath(__file__))),
+                       capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0, r.stderr
