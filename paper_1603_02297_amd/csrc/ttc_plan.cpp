@@ -1222,7 +1222,7 @@ static double rows_cost(const Problem& P, const Candidate& C)
     const double row_bytes = (double)P.size[0] * P.eb_a;
     auto oct_below = [](double x, double ref) { return x < ref ? std::log2(ref / x) : 0.0; };
     const bool update = P.epilogue == TTC_EPI_AXPBY, whole = P.size[0] * P.eb_a % kLineBytes == 0;
-    const double traffic = (double)P.elements * (P.eb_a + (update ? 2 : 1) * P.eb_b);
+    const double traffic = traffic_bytes(P);
     double e = traffic < 8e6 ? -0.425 : (traffic < 1e8 ? -0.128 : 0.0);
     if (P.span_b == P.elements) {
         e -= 0.373;
@@ -1305,7 +1305,7 @@ static double line_cost(const Problem& P, const Candidate& C)
     const double pad_cols = std::log((double)ceil_div(m.size_a0, m.ta) * m.ta / cols);
     const bool one_precision = P.eb_a == P.eb_b && P.eb_a < 16;           // the others' first is then a micro-tile candidate, ranked by its own model
     const double line_rows = rows / S.line;                               // lines per column
-    const double traffic = (double)P.elements * (P.eb_a + (update ? 2 : 1) * P.eb_b);
+    const double traffic = traffic_bytes(P);
     double e;
     if (traffic >= 16e6) {
         const int64_t last_row0 = (segs - 1) * (int64_t)m.tb - (m.skewed ? S.line : 0);
@@ -1499,7 +1499,7 @@ void default_streaming(const Problem& P, Candidate* c)
         for (int k = 1; k < P.ndim; ++k)
             if (!(m.merged_a && k == 1) && P.stride_a[k] * P.eb_a % kLineBytes != 0) whole_a = false;
         c->kp.nt_a = whole_a ? 1 : 0;
-        c->kp.nt_b = P.elements * (P.eb_a + (P.epilogue == TTC_EPI_AXPBY ? 2 : 1) * P.eb_b) >= 8000000 ? 1 : 0;
+        c->kp.nt_b = traffic_bytes(P) >= 8e6 ? 1 : 0;
         return;
     }
     const AccessShape sh = access_shape(P, *c);
