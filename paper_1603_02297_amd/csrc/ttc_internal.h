@@ -124,8 +124,10 @@ constexpr int kLineThreads = 256;
 constexpr int kLineBytes = 128;
 constexpr int64_t kLineMaxExtent = (int64_t(1) << 31) - 4096;    // rows and columns: tile limits are worked out in 32 bits
 // LDS pitch: a lane of the store phase reads the elements of one column, eight lanes with rows 16 bytes of B apart
-// times eight neighbouring columns per instruction.  cols + 2 (4- and 8-byte elements) or cols + 1 (16-byte) spreads
-// those 64 addresses evenly over the banks and keeps the row starts aligned for the 8- and 16-byte LDS writes.
+// times eight neighbouring columns per instruction.  cols + 2 (4- and 8-byte elements) or cols + 1 (16-byte) keeps the
+// row starts aligned for the 8- and 16-byte LDS writes and spreads the reads of one precision of 4 or 8 bytes evenly
+// over the banks; two precisions and 16-byte elements meet some bank twice, and so do the writes of rows of 128 bytes (a
+// plan's lds_conflict_a and lds_conflict_b).
 constexpr LineShape line_shape(int cols, int lines, int eb_a, int eb_b)
 {
     LineShape s = {};

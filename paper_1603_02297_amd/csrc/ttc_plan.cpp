@@ -442,6 +442,27 @@ static int bank_multiplicity(const LaneCoords& lc, const int* lstride /* per slo
     return worst32 + worst64;
 }
 
+// The same for the line kernel's tile, one instruction of a wavefront each: writes of 8 bytes (4-byte elements) or 16
+// along the rows, reads of one element, eight lanes with rows 16 bytes of B apart times eight neighbouring columns.
+static void line_conflicts(const LineShape& S, int eb_a, int* writes, int* reads)
+{
+    const int unit = eb_a == 16 ? 1 : 2;            // elements per write; rows are whole numbers of them
+    LaneCoords w, r;
+    w.lanes = r.lanes = kWave;
+    w.vec = r.vec = 1;
+    std::memset(w.c, 0, sizeof(w.c));
+    std::memset(r.c, 0, sizeof(r.c));
+    for (int lane = 0; lane < kWave; ++lane) {
+        w.c[lane][0] = lane / S.lanes;              // row
+        w.c[lane][1] = lane % S.lanes * S.va / unit;
+        r.c[lane][0] = (lane & 7) * S.vb;
+        r.c[lane][1] = (lane >> 3) % S.side;
+    }
+    const int write_stride[kBoxDims] = {S.pitch / unit, 1, 0, 0}, read_stride[kBoxDims] = {S.pitch, 1, 0, 0};
+    *writes = bank_multiplicity(w, write_stride, 0, unit * eb_a / 4);
+    *reads = bank_multiplicity(r, read_stride, 0, eb_a / 4);
+}
+
 struct LdsLayout { int stride[kMaxDim]; int elems; int conflict_a, conflict_b; };
 
 static LdsLayout choose_lds_layout(const Problem& P, const int* t, const int* slot_of_dim,
@@ -893,7 +914,6 @@ static bool make_line_candidate(const Problem& P, int cols_tile, int lines, cons
     C.dtile_a[0] = cols_tile; C.dtile_a[1] = S.rows; C.dlane_a[0] = cols_tile; C.dlane_a[1] = std::max(1, kWave / S.lanes);
     C.dtile_b[0] = tb; C.dtile_b[1] = cols_tile; C.dlane_b[0] = S.line; C.dlane_b[1] = std::min(S.side, kWave / 8);
     C.dlane_a[2] = m.merged_a; C.dlane_b[2] = m.merged_b;       // part of what names the configuration
-    C.lds_conflict_a = C.lds_conflict_b = 2;
     C.lds_stride[0] = 1;
     C.lds_stride[p0] = S.pitch;
     *out = C;
@@ -1946,6 +1966,8 @@ int ttc_plan_get_info(ttc_plan_t plan, ttc_plan_info_t* out)
     out->nt_b = C.kp.nt_b;
     out->lds_conflict_a = C.lds_conflict_a;
     out->lds_conflict_b = C.lds_conflict_b;
+    if (C.kernel_class == ttc::kKernelLines)
+        ttc::line_conflicts(ttc::line_shape(C.kp.micro.ta, C.kp.micro.lines, P.eb_a, P.eb_b), P.eb_a, &out->lds_conflict_a, &out->lds_conflict_b);
     {
         const ttc::AccessShape sh = ttc::access_shape(P, C);
         out->run_bytes_a = sh.run[0]; out->run_bytes_b = sh.run[1];

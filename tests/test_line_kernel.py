@@ -54,6 +54,33 @@ def test_walks_of_every_line_candidate(dtype):
     assert seen >= 40
 
 
+def multiplicity(addresses, words):
+    """Distinct addresses that the lanes of one LDS instruction (`words` 4-byte words each) send to one bank, over the
+    unavoidable number: for 32 and for 64 banks, added (2: no conflict)."""
+    total = 0
+    for banks in (32, 64):
+        load = np.bincount([(a + w) % banks for a in set(addresses) for w in range(words)], minlength=banks).max()
+        total += -(-int(load) // max(1, -(-len(set(addresses)) * words // banks)))
+    return total
+
+
+@pytest.mark.parametrize("dtype", DTYPES, ids=[wl.DTYPE_NAME[d] for d in DTYPES])
+def test_reported_bank_conflicts_are_those_of_the_tile(dtype):
+    ea, eb = wl.ELEM_BYTES[dtype], wl.ELEM_BYTES_B[dtype]
+    p = ttc.ttc_plan_create(dtype, 2, (301, 203), (1, 0), 1.0, 0.0)
+    seen = set()
+    for k, info in line_candidates(p):
+        cols, pitch = info["digit_tile_a"][0], info["lds_stride"][1]            # elements
+        per_row, wide = cols * ea // 16, 8 if ea == 4 else 16                   # lanes that write a row, bytes of a write
+        writes = [(t // per_row * pitch + t % per_row * (16 // ea)) * ea // 4 for t in range(64)]
+        reads = [((t % 8) * (16 // eb) * pitch + t // 8) * ea // 4 for t in range(64)]
+        want = (multiplicity(writes, wide // 4), multiplicity(reads, ea // 4))
+        assert (info["lds_conflict_a"], info["lds_conflict_b"]) == want, (cols, info["unroll"])
+        seen.add(cols)
+    assert len(seen) >= 2
+    ttc.ttc_plan_destroy(p)
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("dtype", DTYPES, ids=[wl.DTYPE_NAME[d] for d in DTYPES])
 def test_line_kernel_against_the_oracle(dtype):
