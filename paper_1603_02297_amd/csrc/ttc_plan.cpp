@@ -1336,9 +1336,9 @@ static double line_cost(const Problem& P, const Candidate& C)
         if (one_precision) e += m.skewed ? -0.073 : (split_a || update ? -0.010 : 0.075);     // whole lines on both sides: the micro-tile kernel is as good
         // Updates with whole lines on both sides, where neither kernel splits one: line against micro-tile kernel on one pair
         // of tensors, on pairs in rotation and on new ones, geometric means.  Tensors beyond the 256 MB of the last-level
-        // cache (15 problems): 1.13, 1.01 and 1.28 times the micro-tile kernel's time (288 x 608 x 221 complex64 (1,0,2):
+        // cache (14 problems): 1.15, 1.01 and 1.30 times the micro-tile kernel's time (288 x 608 x 221 complex64 (1,0,2):
         // 144 us against 130, 146 against 158, 189 against 138).  Smaller ones of 4-byte elements (12): 0.98, 1.09 and
-        // 1.06; of 8-byte elements (15): 0.99, 0.97 and 1.02.
+        // 1.06; of 8-byte elements (15): 0.99, 0.97 and 1.04.  Held-out problems (24) agree.
         if (one_precision && update && !m.skewed && !split_a) {
             if (P.elements * P.eb_a >= (int64_t(256) << 20)) e += 0.30;
             else if (P.eb_a == 4) e += 0.17;

@@ -160,8 +160,9 @@ def d2d_copy_gbps(nbytes, a_ptrs, b_ptrs, stream):
 def search_set(families, cap):
     """Ranks the library's search times when capped at `cap` candidates (the rule of ttc_plan_tune_pairs): the
     first `cap` of the ranking, a fifth of the places going to the best-ranked micro-tile candidates over single
-    indices and another fifth to those over merged indices where the ranking would have left them out.
-    families: per candidate in rank order, 0 = other kernels, 1 = micro-tile, 2 = micro-tile over merged indices."""
+    indices and another fifth to those over merged indices where the ranking would have left them out, instead of the
+    lowest-ranked candidates of the box, row and gather kernels.
+    families: per candidate in rank order, micro_family()."""
     total = len(families)
     cap = min(cap, total)
     chosen = list(range(cap))
@@ -185,7 +186,9 @@ def search_set(families, cap):
 
 
 def micro_family(info):
-    """0: not the micro-tile kernel; 1: its tile is over single indices; 2: two indices taken as one on a side."""
+    """1: the micro-tile kernel over single indices; 2: over two indices taken as one on a side; 3: the line kernel; 0: others."""
+    if ttc.kernel_family(info) == "line":
+        return 3
     if ttc.kernel_family(info) != "micro":
         return 0
     return 2 if info["merged"] else 1

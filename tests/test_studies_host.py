@@ -32,6 +32,9 @@ def test_search_set_keeps_places_for_both_micro_tile_families():
     chosen = st.search_set(fam, 100)
     assert len(set(chosen)) == 100 and {150, 210, 220, 230, 280} <= set(chosen)
     assert st.search_set(fam, 400) == list(range(300))
+    # where few others are left to give way, the line kernel's candidates keep their places
+    fam = [3, 0, 3, 1] + [1] * 30 + [2] * 100
+    assert st.search_set(fam, 20) == [0, 37] + list(range(2, 20))
 
 
 def test_every_kernel_has_a_family_of_its_own():
