@@ -198,7 +198,7 @@ int ttc_plan_set_tile_mapping(ttc_plan_t plan, int mode);
  * Table 1 --maxImplementations).  Times at most max_candidates candidates, in heuristic
  * rank order (up to two fifths of the places are kept for the best-ranked candidates of
  * the micro-tile kernel, over single and over merged indices, whose ranking is a model
- * of its own), on the caller's buffers and stream (HIP events, a few launches each, more
+ * of its own; candidates of the line kernel do not give way), on the caller's buffers and stream (HIP events, a few launches each, more
  * of them if a launch takes only microseconds, after about 3 ms of untimed launches that
  * bring an idle GPU up to its clocks), each with the non-temporal hints of the rule and
  * with both sides streamed, and selects the fastest; the best few are timed again, with

@@ -1249,6 +1249,8 @@ static double rows_cost(const Problem& P, const Candidate& C)
         if (!C.rows.flat) e += 0.05;                                        // pieces of B that start at any element
         if (!whole) e += 0.124;
         if (traffic >= 1e8) e += 0.049 * oct_below(row_bytes, 128.0) + (whole ? 0.0 : 0.094 * oct_below(row_bytes, 512.0));
+        if (traffic >= 1e8 && !whole && !update && row_bytes < 160.0) e += 0.02;     // 140 bytes: 35^5 98 us, tiles 88; 35 x 63 x 115 x 208 100
+                                                                            // and 97 (184 bytes 71 and 74, 208 bytes 106 and 113)
         else if (!whole) e += 0.103 * oct_below(row_bytes, 128.0);
         if (update && P.size[0] % (16 / std::max(P.eb_a, P.eb_b)) != 0 && C.rows.flat) e -= 0.131;
     } else {

@@ -547,6 +547,17 @@ def test_large_updates_with_whole_lines_take_the_micro_tile_kernel(dtype, sizes,
     ttc.ttc_plan_destroy(p)
 
 
+@pytest.mark.parametrize("sizes,perm,beta,family", [
+    ((35, 35, 35, 35, 35), (0, 3, 2, 1, 4), 0.0, "lds"),          # rows of 140 bytes, 420 MB of traffic
+    ((35, 35, 35, 35, 35), (0, 3, 2, 1, 4), 1.0, "rows"),         # an update: 111 us, tiles 157
+    ((85, 85, 85, 85), (0, 3, 2, 1), 0.0, "rows"),                # 340 bytes: 79 us, tiles 100
+])
+def test_large_copies_of_short_ragged_rows_take_tiles(sizes, perm, beta, family):
+    p = plan(ttc.TTC_F32, sizes, perm, 1.0, beta)
+    assert ttc.kernel_family(ttc.ttc_plan_get_info(p)) == family
+    ttc.ttc_plan_destroy(p)
+
+
 def test_a_plan_is_created_on_a_small_stack():
     """Threads of a host program may have little stack: planning keeps its tables elsewhere.  In a process of its own, which
     an overflow would end."""
