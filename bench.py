@@ -66,7 +66,10 @@ def parse():
                     help="run the best-ranked candidate of this kernel family instead of the stored or searched plan")
     ap.add_argument("--store-plans", type=str, default="",
                     help="append what the run selected for every case to this file (the format of --plan-cache)")
-    return ap.parse_args()
+    args = ap.parse_args()
+    if args.problem and args.problem.split(":")[0] not in ("f32", "f64", "c64", "c128"):
+        ap.error("--problem: f32, f64, c64 or c128, one type for both tensors")
+    return args
 
 
 def ulp_distance(x, y) -> int:

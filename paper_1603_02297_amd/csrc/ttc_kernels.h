@@ -351,7 +351,7 @@ __global__ __launch_bounds__(kMaxThreads) void box_kernel(const KernelParams par
 // row and repeats up to V-1 elements of its neighbour with the same values (only where B is not read: with beta != 0
 // the planner picks a vector that divides the row).
 // Chunks are dealt to the XCDs 32 at a time: neighbours share lines of A, and of B where a chunk ends inside a line; dealt
-// one by one to eight L2s the same 917 x 374 x 153 took 76 us and 72 us in groups (before FLAT), 384^3 75.4 and 73.5 us.
+// one by one to eight L2s the same 917 x 374 x 153 takes 69.9 us, in groups 69.1; 384^3 74.0 and 72.9 us.
 // ---------------------------------------------------------------------------------
 constexpr int kRowsThreads = 256;
 
@@ -583,8 +583,11 @@ inline hipError_t launch_micro(const Candidate& c, const void* A, void* B, hipSt
 // two workgroups costs two masked writes: 7200 x 7200 fp32 took 72 us with both tensors' leading dimension 7232
 // (whole lines) and 99 us (82 searched) with B's 7241, although the bytes are the same.  Here every column is cut
 // where its own lines end, so each line is written once and whole; the price is that a tile reads up to a line's
-// worth of rows of its neighbour again (all but a few per cent of them from the caches).  77 us, whatever B's leading
-// dimension; 79 against 92-105 us with both at 7241.
+// worth of rows of its neighbour again, and both tiles the line of A that their common edge splits.  77 us, whatever B's
+// leading dimension; 79 against 92-105 us with both at 7241.
+// How much of that comes from the caches depends on the order of the tiles.  The 6-D reversal 24 x 20 x 16 x 18 x 22 x 17
+// (merged on both sides, 24-element runs of A) asks for 1.32 lines per line of A and reads 1.03 times A from memory (81 us);
+// 85^4 reversed asks for 2.25 and reads A 2.03 times (97 us): the next tile along A comes 33 tiles later there, on another XCD.
 // It also takes what the micro-tile kernel does not: 16-byte elements and two precisions (B's lines aligned or not).
 //
 // Loads: 16 bytes a lane along A, all of a tile's rows in flight at once, parked row by row in LDS.
@@ -794,6 +797,7 @@ inline hipError_t launch_one(const KernelParams& kp, const void* A, void* B, uin
 // ---------------------------------------------------------------------------------
 // The gather kernel: B is walked front to back, a lane writes 16 bytes of it and fetches their elements from A one by one.
 // No tiles, no LDS, no barrier: one memory latency between launch and store, which is what a small problem costs.
+// 70 x 33 x 45 fp32 (2,0,1): 3.4 us a launch (box kernel 4.2), 2.4 line requests per line of A, all but 0.4 of them from L2.
 // ---------------------------------------------------------------------------------
 template <typename TA, typename TB, int MODE, int V>
 __global__ __launch_bounds__(kRowsThreads) void gather_kernel(const RowsParams p, const TA* __restrict__ A, TB* __restrict__ B)

@@ -101,7 +101,7 @@ def uniform_tensor(dtype: int, elements: int, seed: int, side: str = "a") -> np.
 def case_inputs(case: Case):
     """(A, B0) for a benchmark case: A from seed base+10*config, B0 from the next seed."""
     a = uniform_tensor(case.dtype, case.elements, SEED_BASE + 10 * case.config + 0)
-    b = uniform_tensor(case.dtype, case.elements, SEED_BASE + 10 * case.config + 1)
+    b = uniform_tensor(case.dtype, case.elements, SEED_BASE + 10 * case.config + 1, "b")
     return a, b
 
 

@@ -1,10 +1,15 @@
 """Host-side checks of the study helpers (no GPU): the benchmark's permutations and shapes, the rule by which the
 search fills its places (mirrored from the library), and the feature functions the ranking models are fitted with."""
+import os
+import subprocess
+import sys
+
 import numpy as np
 import pytest
 
 import paper_1603_02297_amd as ttc
 from paper_1603_02297_amd import studies as st
+from paper_1603_02297_amd import workloads as wl
 
 
 def test_benchmark_has_57_cases_without_mergeable_indices():
@@ -19,6 +24,17 @@ def test_benchmark_has_57_cases_without_mergeable_indices():
         for cfg in (0, 1, 2):
             sizes = st.shape_for(n, cfg)
             assert len(sizes) == n and 150e6 < 4 * np.prod(sizes) < 260e6
+
+
+def test_benchmark_takes_problems_of_one_type_only():
+    """bench.py sizes both tensors, its copies and its traffic by one element size: two precisions are refused before
+    anything is allocated (B of a widening problem would be half as large as what is written to it)."""
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    r = subprocess.run([sys.executable, "bench.py", "--problem", "f32f64:8x8:10:1:0"], cwd=root, capture_output=True, text=True, timeout=120)
+    assert r.returncode == 2 and "one type" in r.stderr, r.stderr
+    for dtype in (wl.F32_F64, wl.F64_F32, wl.C64_C128, wl.C128_C64, wl.C64, wl.F64):
+        a, b = wl.case_inputs(wl.Case(9, dtype, (4, 3), (1, 0), 1.0, 0.0))
+        assert a.nbytes == 12 * wl.ELEM_BYTES[dtype] and b.nbytes == 12 * wl.ELEM_BYTES_B[dtype]
 
 
 def test_search_set_keeps_places_for_both_micro_tile_families():
