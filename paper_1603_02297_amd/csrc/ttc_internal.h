@@ -126,8 +126,9 @@ constexpr int64_t kLineMaxExtent = (int64_t(1) << 31) - 4096;    // rows and col
 // LDS pitch: a lane of the store phase reads the elements of one column, eight lanes with rows 16 bytes of B apart
 // times eight neighbouring columns per instruction.  cols + 2 (4- and 8-byte elements) or cols + 1 (16-byte) keeps the
 // row starts aligned for the 8- and 16-byte LDS writes and spreads the reads of one precision of 4 or 8 bytes evenly
-// over the banks; two precisions and 16-byte elements meet some bank twice, and so do the writes of rows of 128 bytes (a
-// plan's lds_conflict_a and lds_conflict_b).
+// over the banks; by the bank model two precisions and 16-byte elements meet some bank twice, and so do the writes of rows of
+// 128 bytes (a plan's lds_conflict_a and lds_conflict_b).  Measured, LDS cycles per instruction and conflicts among them: 384^3
+// fp32 -> fp64 5.3 and 0.0, 1024^2 fp32 8.0 and 2.7, complex128 9.8 and 3.6; the micro-tile kernel's swizzled tile 8.0 and 2.0.
 constexpr LineShape line_shape(int cols, int lines, int eb_a, int eb_b)
 {
     LineShape s = {};
