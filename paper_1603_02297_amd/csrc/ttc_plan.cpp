@@ -1345,6 +1345,11 @@ static double line_cost(const Problem& P, const Candidate& C)
             if (P.elements * P.eb_a >= (int64_t(256) << 20)) e += 0.30;
             else if (P.eb_a == 4) e += 0.17;
         }
+        // Copies of 8-byte elements whose columns of B start inside lines, both tensors together a quarter to a half of the
+        // last-level cache: the line kernel takes 1.09, 1.02 and 1.09 times the micro-tile kernel's time (one pair, pairs in
+        // rotation, new ones; 28 problems of 32 to 64 MB per tensor: 795 x 6248 fp64 19.7 us against 17.2, 22.7 against 21.3
+        // and 22.2 against 20.3).  Below, 0.93, 0.94 and 0.95 (15 problems from 9 MB on); above, 1.01, 0.97 and 1.04 (17 up to 127 MB).
+        if (one_precision && !update && m.skewed && P.eb_a == 8 && traffic >= 64e6 && traffic < 128e6) e += 0.16;
         if (update && m.merged_a && P.size[0] * P.eb_a >= 512) e += 0.08 + (P.perm[1] == 0 ? 0.12 : 0.0);    // a tile that crosses the end of a row
                                                                           // reads and writes B in two places, and leaves a contiguous block
         e += 0.343 * std::log((double)loaded / rows) + 0.340 * pad_cols + 0.293 * std::log((double)segs * m.tb / rows) + 0.087 * split;

@@ -547,6 +547,20 @@ def test_large_updates_with_whole_lines_take_the_micro_tile_kernel(dtype, sizes,
     ttc.ttc_plan_destroy(p)
 
 
+@pytest.mark.parametrize("dtype,sizes,family", [
+    (ttc.TTC_F64, (816, 1341), "line"),          # 9 MB per tensor
+    (ttc.TTC_F64, (795, 6248), "micro"),         # 40 MB
+    (ttc.TTC_C64, (5007, 1102), "micro"),        # 44 MB
+    (ttc.TTC_F64, (16509, 535), "line"),         # 71 MB
+    (ttc.TTC_F32, (3163, 3577), "line"),         # 45 MB of 4-byte elements
+])
+def test_copies_of_8_byte_elements_whose_columns_start_inside_lines(dtype, sizes, family):
+    """A quarter to a half of the last-level cache in both tensors together: the micro-tile kernel is ahead."""
+    p = plan(dtype, sizes, (1, 0))
+    assert ttc.kernel_family(ttc.ttc_plan_get_info(p)) == family
+    ttc.ttc_plan_destroy(p)
+
+
 @pytest.mark.parametrize("sizes,perm,beta,family", [
     ((35, 35, 35, 35, 35), (0, 3, 2, 1, 4), 0.0, "lds"),          # rows of 140 bytes, 420 MB of traffic
     ((35, 35, 35, 35, 35), (0, 3, 2, 1, 4), 1.0, "rows"),         # an update: 111 us, tiles 157
