@@ -55,7 +55,8 @@ enum { TTC_KERNEL_DIRECT = 0 /* tiles, no staging: stride-1 index fixed */, TTC_
                                (the gather kernel: small problems, any permutation) */,
        TTC_KERNEL_MICRO = 3 /* tile over the two stride-1 indices only (each possibly merged with the index next to it in
                                its tensor): 128-bit LDS accesses, XOR-swizzled rows, register transposes of 4x4 (2x2)
-                               blocks; one precision of 4- or 8-byte elements */ };
+                               blocks; one precision of 4- or 8-byte elements.  Or (merged == 4) the block kernel: a tile over
+                               the leading indices of both tensors, which may overlap; every type pair */ };
 /* Epilogues chosen from alpha, beta. */
 enum { TTC_EPI_COPY = 0 /* alpha=1, beta=0 */, TTC_EPI_SCALE = 1 /* beta=0: B never read */, TTC_EPI_AXPBY = 2 };
 
@@ -109,10 +110,10 @@ typedef struct {
     float   tuned_ms;                      /* time of the selected candidate in the last ttc_plan_tune, else 0 */
     double  heuristic_cost;                /* the ranking key: modelled relative cost, smaller is better */
     int     unroll;                        /* row kernel: vectors a lane keeps in flight (1, 2, 4 or 8); micro-tile kernel: blocks a lane owns
-                                              (1 to 6); line kernel: lines of B whose rows a tile holds (2, 4 or 8); 0 for the box kernels
+                                              (1 to 6), its block form: vectors a lane loads (2, 4 or 8); line kernel: lines of B whose rows a tile holds (2, 4 or 8); 0 for the box kernels
                                               and the gather kernel */
     int     merged;                        /* micro-tile and line kernel: bit 0: the tile's column index is A's indices 0 and 1 taken as one,
-                                              bit 1: its row index is B's first two indices taken as one; else 0 */
+                                              bit 1: its row index is B's first two indices taken as one; 4: the block kernel; else 0 */
 } ttc_plan_info_t;
 
 /*

@@ -250,11 +250,50 @@ struct RowsParams {
     double   beta[2];
 };
 
+// The block kernel: a tile is a box whose leading indices are one contiguous run of A (run_a elements, `rows` of them) and one
+// contiguous run of B (run_b elements, `outs` of them); an index may be part of both runs.  At most two indices are cut into
+// tiles: the last one of A's run and the last one of B's (they may be one and the same); all others of the box lie whole in it.
+// LDS holds the tile in A's order, a row every `pitch` elements.
+struct BlockParams {
+    int32_t  run_a, run_b;           // elements of a whole tile's runs
+    int32_t  inner_a, inner_b;       // elements of a run per step of the index it ends with
+    int32_t  tile_a, tile_b;         // tile extents of the two indices the runs end with
+    int32_t  pos_a, pos_b;           // where these stand in the tile order
+    int32_t  cut_row, cut_out;       // which digit of a row's place (0, 1; -1: none) is the index B's run ends with, and which
+                                     // digit of an out's place the one A's run ends with
+    int32_t  rows, outs, pitch, even;// even: B's first index is a multiple of the vector
+    int32_t  unroll, pad;            // vectors a lane loads
+    int64_t  size_a, size_b;         // extents of the two indices in the tensor
+    FastDiv  va_div, vb_div;         // vectors of a run
+    FastDiv  row_div, out_div;       // extent of digit 0 of a row's place, of an out's place
+    FastDiv  x_div[2];               // place in B's run -> indices: extents of the first two
+    int32_t  x_lds[3], out_lds[2];   // LDS strides of B's run's indices and of an out's digits
+    int32_t  pad_end;
+    int64_t  row_step[2], out_step[2];   // element strides in A of a row's digits, in B of an out's
+};
+
+// The block kernel's whole argument.
+struct BlockArgs {
+    int32_t  xcd_remap;              // how the tiles are dealt to the XCDs (as KernelParams::xcd_remap)
+    uint32_t blocks;                 // tiles, one per workgroup
+    int32_t  nt_a, nt_b;
+    FastDiv  cnt[kMaxDim];
+    int64_t  step_a[kMaxDim], step_b[kMaxDim];
+    double   alpha[2], beta[2];
+    BlockParams block;
+};
+constexpr int kBlockThreads = 256;
+constexpr int kBlockMaxLds = 64 * 1024;
+// vectors a lane stores where it loads `unroll`
+constexpr int block_stores(int unroll, int eb_a, int eb_b) { return unroll * eb_b / eb_a < 1 ? 1 : unroll * eb_b / eb_a; }
+
 // The line kernel's internal class.  Plans report it as TTC_KERNEL_LDS (its tile is staged through LDS) with a
 // non-zero `unroll`.
 constexpr int kKernelLines = 4;
 // The gather kernel's; reported as TTC_KERNEL_ROWS (B is walked front to back).
 constexpr int kKernelGather = 5;
+// The block kernel's; reported as TTC_KERNEL_MICRO with bit 2 of `merged` set.
+constexpr int kKernelBlock = 6;
 
 // One candidate launch configuration ("candidate" in the paper's Section 3).
 struct Candidate {
@@ -273,6 +312,7 @@ struct Candidate {
     float    tuned_ms;
     KernelParams kp;                 // box kernels (staged and direct); the streaming flags and the tile mapping of every class
     RowsParams rows;                 // row kernel
+    BlockParams block;               // block kernel
 };
 
 // Element kinds of one tensor (the two tensors of a mixed-precision problem differ).
@@ -324,5 +364,6 @@ constexpr int kMaxTileMapping = 10;                  // chunks of 2^10
 bool set_tile_mapping(KernelParams* kp, int mode);
 void default_streaming(const Problem& P, Candidate* c);
 MicroArgs micro_args(const Candidate& c);
+BlockArgs block_args(const Candidate& c);
 
 }  // namespace ttc

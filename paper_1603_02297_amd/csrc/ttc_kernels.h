@@ -753,6 +753,140 @@ inline hipError_t launch_lines(const Candidate& c, const void* A, void* B, hipSt
     }
 }
 
+// ---------------------------------------------------------------------------------
+// The block kernel: a box of the tensor that is one or a few long contiguous runs of B and runs of whole lines of A, moved by
+// a one-shot workgroup.
+// What it is for: problems whose leading indices in A and in B overlap, or are short.  The box kernel moves the same boxes, but
+// a workgroup first builds position tables and then walks several tiles between barriers; here a lane finds its U vectors
+// by a few divisions, has all of them in flight at once (an update: B's as well), and one barrier separates loads from stores.
+// What bounds it is memory, then how fast the device starts workgroups: one of 256 threads every 1.7 ns, so a tile of 6-12 KB is
+// best (24 x 20 x 16 x 18 x 22 x 17 fp32 (1,0,2,3,5,4), tiles of 1.9, 3.8, 5.8, 11.5 and 31 KB: 181, 97, 75, 70 and 74 us).  Reads reach
+// 6.0-6.9 TB/s in any order of whole lines, writes 6.4 TB/s front to back but 4.7-5.8 where a launch writes 32 and more
+// places at once: as much of B's run as the tile can hold is better than more of A's.
+// Box kernel -> here: the same problem as an update 109 -> 95 us (6.5 TB/s), 3 x 307200 x 64 fp32 (1,0,2) 82.4 -> 74.0
+// (6.4 TB/s), 12 x 1000 x 12 x 300 fp32 (2,1,0,3) 62 -> 56, 8 x 9 x 7 x 96 x 104 complex128 (1,2,3,4,0) 35.5 -> 28.6.
+// One tile per workgroup, and no loop over tiles around it: with one the same two problems took 111 and 89 us.
+// ---------------------------------------------------------------------------------
+template <typename TA, typename TB, int MODE, int U>
+__global__ __launch_bounds__(kBlockThreads) void block_kernel(const BlockArgs args_by_value, const TA* __restrict__ A, TB* __restrict__ B)
+{
+    const BlockArgs& p = *reinterpret_cast<const BlockArgs*>((const void*)__builtin_amdgcn_kernarg_segment_ptr());
+    constexpr int VA = 16 / (int)sizeof(TA), VB = 16 / (int)sizeof(TB), UB = block_stores(U, (int)sizeof(TA), (int)sizeof(TB));
+    extern __shared__ __align__(16) unsigned char smem[];
+    TA* const lds = reinterpret_cast<TA*>(smem);
+    const BlockParams& m = p.block;
+    const Epilogue<TA, TB, MODE> epi(p.alpha, p.beta);
+    const uint32_t tid = threadIdx.x;
+    const uint32_t block = rows_block(p, blockIdx.x);
+    if (block >= p.blocks) return;
+    const BlockTile t = block_tile(p, block);
+    const unsigned char* At = reinterpret_cast<const unsigned char*>(A + t.a);
+    unsigned char* Bt = reinterpret_cast<unsigned char*>(B + t.b);
+    auto run = [&](auto stream_a, auto stream_b) {
+        constexpr bool NTA = decltype(stream_a)::value, NTB = decltype(stream_b)::value;
+        union Vec { Pack<TA, VA> p; uint32_t w[4]; };
+        typedef uint32_t Quad __attribute__((ext_vector_type(4)));
+        Vec in[U];
+        Pack<TB, VB> old[UB];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            in[u].p = load_pack<TA, VA, NTA>(At, block_load(m, t, tid + (uint32_t)(u * kBlockThreads), VA).a * (int64_t)sizeof(TA));
+        if (MODE == TTC_EPI_AXPBY) {
+#pragma unroll
+            for (int u = 0; u < UB; ++u)
+                old[u] = load_pack<TB, VB, NTB>(Bt, block_store(m, t, tid + (uint32_t)(u * kBlockThreads), VB).from * (int64_t)sizeof(TB));
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const BlockLoad x = block_load(m, t, tid + (uint32_t)(u * kBlockThreads), VA);
+            if (!x.ok) continue;
+            if (x.start == x.col) {
+                *reinterpret_cast<Quad*>(lds + x.lds) = Quad{in[u].w[0], in[u].w[1], in[u].w[2], in[u].w[3]};
+            } else {                                           // moved back: what lies before the tile belongs to another one
+#pragma unroll
+                for (int j = 0; j < VA; ++j)
+                    if (x.start + j >= 0) lds[x.lds + j] = in[u].p.v[j];
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < UB; ++u) {
+            const BlockStore x = block_store(m, t, tid + (uint32_t)(u * kBlockThreads), VB);
+            if (x.count == 0) continue;
+            TA a[VB];
+            if (m.even) {
+#pragma unroll
+                for (int j = 0; j < VB; ++j) a[j] = lds[x.lds + j * m.x_lds[0]];
+            } else {
+                int32_t at = x.lds, x0 = x.x0, x1 = x.x1;
+#pragma unroll
+                for (int j = 0; j < VB; ++j) {
+                    a[j] = lds[at];
+                    if (j + 1 < x.count) block_next(m, &at, &x0, &x1);
+                }
+            }
+            if (x.count == VB) {
+                Pack<TB, VB> out;
+#pragma unroll
+                for (int j = 0; j < VB; ++j) {
+                    TB b_old = TB();
+                    if (MODE == TTC_EPI_AXPBY) b_old = old[u].v[j];
+                    out.v[j] = epi(a[j], b_old);
+                }
+                store_pack<TB, VB, NTB>(Bt, x.b * (int64_t)sizeof(TB), out);
+            } else {
+                // the end of a run: element j of it is element j + (x.b - x.from) of the vector that B was read with
+                const int32_t shift = (int32_t)(x.b - x.from);
+#pragma unroll
+                for (int j = 0; j < VB; ++j) {
+                    TB b_old = TB();
+                    if (MODE == TTC_EPI_AXPBY) {
+#pragma unroll
+                        for (int e = 0; e < VB; ++e) if (e == j + shift) b_old = old[u].v[e];
+                    }
+                    if (j < x.count) reinterpret_cast<TB*>(Bt + x.b * (int64_t)sizeof(TB))[j] = epi(a[j], b_old);
+                }
+            }
+        }
+    };
+    if (p.nt_a) { if (p.nt_b) run(std::true_type(), std::true_type()); else run(std::true_type(), std::false_type()); }
+    else        { if (p.nt_b) run(std::false_type(), std::true_type()); else run(std::false_type(), std::false_type()); }
+}
+
+template <typename TA, typename TB, int MODE, int U>
+inline hipError_t launch_block_unrolled(const Candidate& c, const void* A, void* B, hipStream_t stream)
+{
+    constexpr int VA = 16 / (int)sizeof(TA), VB = 16 / (int)sizeof(TB), UB = block_stores(U, (int)sizeof(TA), (int)sizeof(TB));
+    const KernelParams& kp = c.kp;
+    const BlockParams& m = c.block;
+    if (c.threads != kBlockThreads || m.unroll != U || m.rows < 1 || m.outs < 1 || m.run_a < 1 || m.run_b < 1 || m.pitch < m.run_a ||
+        m.pitch % VA != 0 || c.lds_bytes > kBlockMaxLds || (int64_t)m.rows * m.pitch * (int64_t)sizeof(TA) > c.lds_bytes ||
+        (int64_t)m.va_div.div * VA < m.run_a || (int64_t)m.vb_div.div * VB < m.run_b ||
+        (int64_t)m.va_div.div * m.rows > U * kBlockThreads || (int64_t)m.vb_div.div * m.outs > UB * kBlockThreads ||
+        (int64_t)m.rows * m.run_a != (int64_t)m.outs * m.run_b || m.run_a != m.inner_a * m.tile_a || m.run_b != m.inner_b * m.tile_b ||
+        m.run_a < VA || m.run_b < VB || kp.grid != kp.num_tiles)
+        return hipErrorInvalidValue;
+    const TA* a = static_cast<const TA*>(A);
+    TB* b = static_cast<TB*>(B);
+    BlockArgs ready = block_args(c);
+    const int64_t grid = rows_grid(ready);
+    if (!launchable(grid, kBlockThreads)) return hipErrorInvalidValue;
+    void* args[] = {&ready, &a, &b};
+    return hipLaunchKernel(reinterpret_cast<const void*>(&block_kernel<TA, TB, MODE, U>), dim3((uint32_t)grid), dim3(kBlockThreads), args,
+                           (size_t)c.lds_bytes, stream);
+}
+
+template <typename TA, typename TB, int MODE>
+inline hipError_t launch_block(const Candidate& c, const void* A, void* B, hipStream_t s)
+{
+    switch (c.block.unroll) {
+    case 2: return launch_block_unrolled<TA, TB, MODE, 2>(c, A, B, s);
+    case 4: return launch_block_unrolled<TA, TB, MODE, 4>(c, A, B, s);
+    case 8: return launch_block_unrolled<TA, TB, MODE, 8>(c, A, B, s);
+    default: return hipErrorInvalidValue;
+    }
+}
+
 // Compute units of the current device (256 on MI355X), asked once per process and device.
 inline int device_cus()
 {
@@ -918,6 +1052,7 @@ inline hipError_t launch_vec(const Candidate& c, const void* A, void* B, hipStre
     if (c.kernel_class == TTC_KERNEL_MICRO) return launch_micro<TA, TB, MODE>(c, A, B, s);
     if (c.kernel_class == kKernelLines) return launch_lines<TA, TB, MODE>(c, A, B, s);
     if (c.kernel_class == kKernelGather) return launch_gather<TA, TB, MODE>(c, A, B, s);
+    if (c.kernel_class == kKernelBlock) return launch_block<TA, TB, MODE>(c, A, B, s);
     if (c.kernel_class == TTC_KERNEL_ROWS) {
         const int v = c.rows.vec;
         if (c.rows.flat) return v == VD ? launch_rows_flat<TA, TB, MODE, VD>(c, A, B, s) : hipErrorInvalidValue;

@@ -952,6 +952,182 @@ MicroArgs micro_args(const Candidate& c)
     return a;
 }
 
+// The block kernel's candidate: a box of extents t[] (whole indices, but for the last ones of A's and of B's run), tile ids in
+// the order `tile_order`.  Needs both unit strides to be 1.
+static bool make_block_candidate(const Problem& P, const int* t, const int* tile_order, Candidate* out)
+{
+    if (P.ndim < 2 || P.stride_a[0] != 1 || P.stride_b[P.perm[0]] != 1) return false;
+    const int va = 16 / P.eb_a, vb = 16 / P.eb_b;
+    // the runs: leading indices, contiguous in the tensor, all whole but the last
+    struct Run { int n, last; int dim[kMaxDim]; int64_t elems; uint32_t in; } run[2];
+    for (int side = 0; side < 2; ++side) {
+        Run& r = run[side];
+        r.n = 0; r.last = -1; r.elems = 1; r.in = 0;
+        const int64_t* stride = side ? P.stride_b : P.stride_a;
+        for (int i = 0; i < P.ndim; ++i) {
+            const int k = side ? P.perm[i] : i;
+            if (stride[k] != r.elems || (t[k] == 1 && r.n > 0)) break;
+            r.dim[r.n++] = k; r.last = k; r.in |= 1u << k;
+            r.elems *= t[k];
+            if (t[k] < P.size[k]) break;
+        }
+        if (r.n < 1) return false;
+    }
+    int row[2] = {-1, -1}, outd[2] = {-1, -1}, nrow = 0, nout = 0;
+    int64_t volume = 1;
+    for (int i = 0; i < P.ndim; ++i) {
+        const int k = P.perm[i];
+        if (t[k] < 1 || t[k] > P.size[k]) return false;
+        volume *= t[k];
+        if (volume * P.eb_a > kBlockMaxLds) return false;
+        if (t[k] == 1 || ((run[0].in >> k) & 1u)) continue;
+        if (nrow == 2 || (t[k] < P.size[k] && k != run[1].last)) return false;
+        row[nrow++] = k;
+    }
+    for (int k = 0; k < P.ndim; ++k) {
+        if (t[k] == 1 || ((run[1].in >> k) & 1u)) continue;
+        if (nout == 2 || (t[k] < P.size[k] && k != run[0].last)) return false;
+        outd[nout++] = k;
+    }
+    if (run[1].n > 3) return false;
+    Candidate C;
+    std::memset(&C, 0, sizeof(C));
+    BlockParams& m = C.block;
+    const int sa = run[0].last, sb = run[1].last;
+    m.run_a = (int32_t)run[0].elems; m.run_b = (int32_t)run[1].elems;
+    m.tile_a = t[sa]; m.tile_b = t[sb];
+    m.inner_a = m.run_a / m.tile_a; m.inner_b = m.run_b / m.tile_b;
+    m.size_a = P.size[sa]; m.size_b = P.size[sb];
+    if (m.run_a < va || m.run_b < vb) return false;              // a cut run may hold less: its vectors then begin in the tile before
+    // runs of one index each that are not the same are the micro-tile kernel's; so are those that an index of 1 KB and more begins
+    if (run[0].n == 1 && run[1].n == 1) return false;
+    if ((run[0].n > 1 && P.size[0] * P.eb_a > 1024) || (run[1].n > 1 && P.size[P.perm[0]] * P.eb_b > 1024)) return false;
+    m.rows = (int32_t)(volume / m.run_a); m.outs = (int32_t)(volume / m.run_b);
+    const int64_t per_row = ceil_div(m.run_a, va), per_out = ceil_div(m.run_b, vb);
+    int unroll = 0;
+    for (int u : {2, 4, 8})
+        if (!unroll && per_row * m.rows <= u * kBlockThreads && per_out * m.outs <= block_stores(u, P.eb_a, P.eb_b) * kBlockThreads) unroll = u;
+    if (!unroll) return false;
+    m.unroll = unroll;
+    m.va_div = make_fastdiv((uint32_t)per_row); m.vb_div = make_fastdiv((uint32_t)per_out);
+    m.cut_row = m.cut_out = -1;
+    for (int d = 0; d < 2; ++d) {
+        m.row_step[d] = row[d] >= 0 ? P.stride_a[row[d]] : 0;
+        m.out_step[d] = outd[d] >= 0 ? P.stride_b[outd[d]] : 0;
+        if (row[d] >= 0 && row[d] == sb) m.cut_row = d;
+        if (outd[d] >= 0 && outd[d] == sa) m.cut_out = d;
+    }
+    m.row_div = make_fastdiv((uint32_t)(row[0] >= 0 ? t[row[0]] : 1));
+    m.out_div = make_fastdiv((uint32_t)(outd[0] >= 0 ? t[outd[0]] : 1));
+    m.even = t[P.perm[0]] % vb == 0 ? 1 : 0;
+    m.x_div[0] = make_fastdiv((uint32_t)t[run[1].dim[0]]);
+    m.x_div[1] = make_fastdiv((uint32_t)(run[1].n > 1 ? t[run[1].dim[1]] : 1));
+    // The LDS tile: A's order, rows padded by up to three vectors, so that the first elements of 64 neighbouring vectors of B
+    // meet as few banks twice as may be.
+    int64_t best = INT64_MAX;
+    int lstride[kMaxDim] = {0};
+    for (int pad = 0; pad < 4; ++pad) {
+        const int pitch = (int)((per_row + pad) * va);
+        if ((int64_t)m.rows * pitch * P.eb_a > kBlockMaxLds || (pad > 0 && m.rows == 1)) break;
+        int ls[kMaxDim] = {0}, step = 1;
+        for (int i = 0; i < run[0].n; ++i) { ls[run[0].dim[i]] = step; step *= t[run[0].dim[i]]; }
+        if (row[0] >= 0) ls[row[0]] = pitch;
+        if (row[1] >= 0) ls[row[1]] = pitch * t[row[0]];
+        int bank[32] = {0};
+        const int words = P.eb_a / 4;
+        int worst = 0;
+        for (int lane = 0; lane < kWave; ++lane) {
+            const int64_t o = lane / per_out, x = lane % per_out * vb;
+            if (o >= m.outs) break;
+            const int64_t x0 = x % t[run[1].dim[0]], q = x / t[run[1].dim[0]], e1 = run[1].n > 1 ? t[run[1].dim[1]] : 1;
+            int64_t at = x0 * ls[run[1].dim[0]] + (run[1].n > 1 ? q % e1 * ls[run[1].dim[1]] : 0) + (run[1].n > 2 ? q / e1 * ls[run[1].dim[2]] : 0);
+            const int64_t e0 = outd[0] >= 0 ? t[outd[0]] : 1;
+            if (outd[0] >= 0) at += o % e0 * ls[outd[0]];
+            if (outd[1] >= 0) at += o / e0 * ls[outd[1]];
+            for (int w = 0; w < words; ++w) worst = std::max(worst, ++bank[(at * words + w) & 31]);
+        }
+        const int64_t cost = (int64_t)worst * 16 + pad;
+        if (cost >= best) continue;
+        best = cost;
+        m.pitch = pitch;
+        for (int k = 0; k < kMaxDim; ++k) lstride[k] = ls[k];
+        C.lds_conflict_b = 2 * std::max(1, worst / (2 * words));
+    }
+    if (m.pitch == 0) return false;
+    C.lds_conflict_a = 2;
+    for (int i = 0; i < 3; ++i) m.x_lds[i] = i < run[1].n ? lstride[run[1].dim[i]] : 0;
+    for (int d = 0; d < 2; ++d) m.out_lds[d] = outd[d] >= 0 ? lstride[outd[d]] : 0;
+    C.kernel_class = kKernelBlock;
+    C.threads = kBlockThreads;
+    C.wg_per_cu = 0;
+    C.lds_bytes = m.rows * m.pitch * P.eb_a;
+    KernelParams& kp = C.kp;
+    kp.n = P.ndim;
+    int64_t ntiles = 1;
+    for (int k = 0; k < kMaxDim; ++k) {
+        C.tile[k] = kp.tile[k] = k < P.ndim ? t[k] : 1;
+        C.lds_stride[k] = lstride[k];
+        kp.stride_a[k] = k < P.ndim ? P.stride_a[k] : 0;
+        kp.stride_b[k] = k < P.ndim ? P.stride_b[k] : 0;
+        kp.tile_below[k] = kp.tile_cnt[k] = make_fastdiv(1);
+    }
+    m.pos_a = m.pos_b = -1;
+    for (int i = 0; i < P.ndim; ++i) {
+        const int k = tile_order[i];
+        const int64_t cnt = ceil_div(P.size[k], t[k]);
+        if (cnt > INT32_MAX / 2 || ntiles > INT32_MAX / 2) return false;
+        kp.tile_below[k] = make_fastdiv((uint32_t)ntiles);
+        kp.tile_cnt[k] = make_fastdiv((uint32_t)cnt);
+        ntiles *= cnt;
+        if (ntiles > INT32_MAX / 2) return false;
+        C.tile_order[i] = k;
+        if (k == sa) m.pos_a = i;
+        if (k == sb) m.pos_b = i;
+    }
+    if (!launchable(ntiles + (8 << kMaxTileMapping), C.threads)) return false;       // a launch rounds up to whole rounds over the XCDs
+    kp.num_tiles = (uint32_t)ntiles;
+    kp.tiles_per_xcd = kp.num_tiles / 8;
+    kp.tiles_rem_xcd = kp.num_tiles % 8;
+    if (!set_tile_mapping(&kp, kDefaultTileMapping)) return false;
+    set_grid(&kp, kp.num_tiles);
+    kp.alpha[0] = P.alpha[0]; kp.alpha[1] = P.alpha[1];
+    kp.beta[0] = P.beta[0];   kp.beta[1] = P.beta[1];
+    kp.a.vec = va; kp.b.vec = vb;
+    kp.lds_buffers = 1;
+    kp.lds_tile_elems = m.rows * m.pitch;
+    for (int j = 0; j < kBoxDims; ++j) {
+        kp.slot[j].tile = 1; kp.slot[j].size = 1;
+        kp.slot[j].tile_below = kp.slot[j].tile_cnt = make_fastdiv(1);
+    }
+    C.digits_a = C.digits_b = 2;
+    C.dtile_a[0] = m.run_a; C.dtile_a[1] = m.rows; C.dlane_a[0] = std::min(m.run_a, kWave * va); C.dlane_a[1] = 1;
+    C.dtile_b[0] = m.run_b; C.dtile_b[1] = m.outs; C.dlane_b[0] = std::min(m.run_b, kWave * vb); C.dlane_b[1] = 1;
+    *out = C;
+    return true;
+}
+
+// The argument block of the block kernel from a candidate as it stands.
+BlockArgs block_args(const Candidate& c)
+{
+    const KernelParams& kp = c.kp;
+    BlockArgs a;
+    std::memset(&a, 0, sizeof(a));
+    a.xcd_remap = kp.xcd_remap;
+    a.blocks = kp.num_tiles;
+    a.nt_a = kp.nt_a; a.nt_b = kp.nt_b;
+    for (int i = 0; i < kMaxDim; ++i) a.cnt[i] = make_fastdiv(1);
+    for (int i = 0; i < kp.n && i < kMaxDim; ++i) {
+        const int k = c.tile_order[i];
+        a.cnt[i] = kp.tile_cnt[k];
+        a.step_a[i] = (int64_t)kp.tile[k] * kp.stride_a[k];
+        a.step_b[i] = (int64_t)kp.tile[k] * kp.stride_b[k];
+    }
+    a.alpha[0] = kp.alpha[0]; a.alpha[1] = kp.alpha[1];
+    a.beta[0] = kp.beta[0];   a.beta[1] = kp.beta[1];
+    a.block = c.block;
+    return a;
+}
+
 // The row kernel's candidate: B walked front to back, `vec` elements per lane and access; `flat`: vectors counted through
 // a dense B.  Needs rows that are contiguous in both tensors and hold at least one vector, fewer than 2^31 rows, rows
 // shorter than 2^30.
@@ -1157,7 +1333,7 @@ bool set_tile_mapping(KernelParams* kp, int mode)
 uint32_t launch_grid(const Candidate& c, int cus)
 {
     if (c.kernel_class == TTC_KERNEL_MICRO || c.kernel_class == TTC_KERNEL_ROWS || c.kernel_class == kKernelLines ||
-        c.kernel_class == kKernelGather) return c.kp.num_tiles;    // one-shot workgroups
+        c.kernel_class == kKernelGather || c.kernel_class == kKernelBlock) return c.kp.num_tiles;    // one-shot workgroups
     const uint64_t want = (uint64_t)std::max(cus, 1) * (uint64_t)std::max(c.wg_per_cu, 1);
     return (uint32_t)std::min<uint64_t>(want, c.kp.num_tiles);
 }
@@ -1388,8 +1564,43 @@ static double gather_cost(const Problem& P, const Candidate& C)
     return 0.86 * (1.0 + 0.004 * mb) * C.model_us / (3.4 + 0.18 * mb);
 }
 
+// The block kernel's ranking model, log-linear, fitted to the timings of every block candidate of 112 problems of 9 MB to 1.9 GB of
+// traffic (every type; the first index of A or of B short, or the two runs overlapping) against the candidate that the other
+// models rank first, above and below 100 MB.  By it the first block candidate is 3-4 % behind the best one, and the joint
+// choice takes 8 % (large) and 10 % (small) off the time of the others' first; the best of all would take 10 % and 13 %.  The
+// constants are 0.04 above the fit's, so that near ties stay where they were.
+static double block_cost(const Problem& P, const Candidate& C)
+{
+    const BlockParams& m = C.block;
+    const AccessShape sh = access_shape(P, C);
+    const bool update = P.epilogue == TTC_EPI_AXPBY;
+    const double traffic = traffic_bytes(P);
+    const bool large = traffic >= 100e6;
+    double e = large ? -0.344 + (update ? 0.056 : 0.0) + (P.eb_b > P.eb_a ? 0.161 : 0.0)
+                     : -0.351 - (update ? 0.042 : 0.0) + (P.eb_b > P.eb_a ? 0.124 : 0.0);
+    // The device starts a workgroup of 256 threads every 1.7 ns (tiles of 0.5 to 4 KB, every type): what a small tile costs.
+    const double starts = 1.7e-3 * C.kp.num_tiles / (traffic / 6.2e6);
+    e += std::log(1.0 + std::pow(starts, 6.0)) / 6.0;
+    const double tile_bytes = (double)m.rows * m.run_a * P.eb_a;
+    if (tile_bytes > 8192.0) e += (large ? 0.044 : 0.085) * std::log2(tile_bytes / 8192.0);
+    // lines that a run shares with another one, per line of the run
+    e += (large ? 0.072 : 0.18) * (1.0 - sh.align[0] / 128.0) * 128.0 / sh.run[0];
+    e += (large && update ? 0.106 : 0.34) * (1.0 - sh.align[1] / 128.0) * 128.0 / sh.run[1];
+    for (int k = 0; k < P.ndim && large; ++k) e += 0.19 * std::log((double)ceil_div(P.size[k], C.tile[k]) * C.tile[k] / (double)P.size[k]);
+    e += 0.025 * std::log2(std::max(1.0, C.lds_conflict_b / 2.0));
+    for (int i = 0; i < P.ndim; ++i) if (C.tile_order[i] != P.perm[i]) { e += large ? 0.054 : 0.006; break; }
+    if (C.kp.num_tiles < 512) e += 0.19 * std::log2(512.0 / C.kp.num_tiles);
+    // Updates of tensors beyond the last-level cache whose first index is B's second, whole lines on both sides: on new tensors the
+    // micro-tile kernel finds what the launch before left in that cache (8 x 64 x 48 x 40 x 80 complex64 (2,0,4,3,1): first pass
+    // 309 us, this kernel 332; pairs in rotation 358 and 332, one pair again and again 325 and 323).
+    if (update && P.perm[1] == 0 && sh.align[0] >= 128 && sh.align[1] >= 128 && P.elements * P.eb_b >= (int64_t(256) << 20)) e += 0.30;
+    if (traffic < 8e6) e += 0.1 + 0.15 * std::log2(8e6 / traffic);       // below the fitted range: a launch is what such a problem costs
+    return std::exp(e);
+}
+
 static double heuristic_cost(const Problem& P, const Candidate& C)
 {
+    if (C.kernel_class == kKernelBlock) return block_cost(P, C);
     if (C.kernel_class == kKernelGather) return gather_cost(P, C);
     if (C.kernel_class == TTC_KERNEL_ROWS) return rows_cost(P, C);
     if (C.kernel_class == kKernelLines) return line_cost(P, C);
@@ -1530,6 +1741,16 @@ void default_streaming(const Problem& P, Candidate* c)
         return;
     }
     const AccessShape sh = access_shape(P, *c);
+    if (c->kernel_class == kKernelBlock) {
+        // Whole lines of B, and long runs, which share their two ends only, are streamed: 5-10 % faster from 1 KB runs on in
+        // problems of 100 MB and more (256-byte runs 3-7 % slower, shorter ones up to 30 %), and from 256 bytes on in smaller ones.
+        // So are A's in the large problems if they are whole lines (2 %) or at least 4 KB long (1 %); smaller problems keep
+        // A in the caches (2 %).  By the medians of 112 problems.
+        const bool large = traffic_bytes(P) >= 100e6;
+        c->kp.nt_a = large && (sh.align[0] >= 128 || sh.run[0] >= 4096) ? 1 : 0;
+        c->kp.nt_b = sh.align[1] >= 128 || sh.run[1] >= (large ? 1024 : 256) ? 1 : 0;
+        return;
+    }
     c->kp.nt_a = (sh.align[0] >= 128) ? 1 : 0;
     c->kp.nt_b = (sh.align[1] >= 128) ? 1 : 0;
     if (c->kernel_class == TTC_KERNEL_MICRO && P.epilogue == TTC_EPI_AXPBY && sh.align[0] >= 32 && sh.align[1] >= 32) {
@@ -1745,6 +1966,30 @@ static void enumerate(const Problem& P, std::vector<Candidate>& out_list, bool q
             }
     }
 
+    // -- the block kernel
+    if (!stride1_fixed && n >= 2) {
+        std::vector<std::vector<int>> tried;
+        for (int64_t ra : {128, 256, 512, 1024, 2048, 4096, 8192, 16384, 32768})
+            for (int64_t rb : {128, 256, 512, 1024, 2048, 4096, 8192, 16384, 32768})
+                for (int style = 0; style < 2; ++style) {
+                    int ta[kMaxDim], tb[kMaxDim], t[kMaxDim];
+                    build_group(P, order_a, P.eb_a, ra / P.eb_a, max_vec(P.eb_a, P.size[0]), 3, ta, style);
+                    build_group(P, order_b, P.eb_b, rb / P.eb_b, max_vec(P.eb_b, P.size[P.perm[0]]), 3, tb, style);
+                    for (int k = 0; k < kMaxDim; ++k) t[k] = std::max(ta[k], tb[k]);
+                    // the other tensor's group may have cut an index that vectors run along anywhere
+                    const int p0 = P.perm[0];
+                    t[0] = (int)std::min<int64_t>(P.size[0], round_up(t[0], max_vec(P.eb_a, P.size[0])));
+                    t[p0] = (int)std::min<int64_t>(P.size[p0], round_up(t[p0], max_vec(P.eb_b, P.size[p0])));
+                    const std::vector<int> key(t, t + kMaxDim);
+                    if (std::find(tried.begin(), tried.end(), key) != tried.end()) continue;
+                    tried.push_back(key);
+                    for (int o = 0; o < (quick ? 1 : 2); ++o) {
+                        Candidate c;
+                        if (make_block_candidate(P, t, orders[o], &c)) add_candidate(P, out, c);
+                    }
+                }
+    }
+
     // -- staged candidates: a box spanning the leading indices of A and of B
     if (n >= 2) {
         const int p0 = P.perm[0];
@@ -1821,9 +2066,9 @@ int build_plan(int dtype, int ndim, const int64_t* sizes, const int* perm, const
     plan->complete = false;
     if (verbose()) {
         const Candidate& c = plan->cands[0];
-        static const char* const names[] = {"direct", "staged", "row", "micro-tile", "line", "gather"};       // by kernel class
+        static const char* const names[] = {"direct", "staged", "row", "micro-tile", "line", "gather", "block"};       // by kernel class
         constexpr int kClasses = (int)(sizeof(names) / sizeof(names[0]));
-        static_assert(TTC_KERNEL_MICRO == 3 && kKernelLines == 4 && kKernelGather == kClasses - 1, "one name per class");
+        static_assert(TTC_KERNEL_MICRO == 3 && kKernelLines == 4 && kKernelGather == 5 && kKernelBlock == kClasses - 1, "one name per class");
         std::fprintf(stderr, "ttc: plan dtype %d, %d fused indices, %s kernel, tile", P.dtype, P.ndim, names[c.kernel_class]);
         for (int k = 0; k < P.ndim; ++k) std::fprintf(stderr, " %d", c.tile[k]);
         size_t per_class[kClasses] = {0};
@@ -1958,7 +2203,8 @@ int ttc_plan_get_info(ttc_plan_t plan, ttc_plan_info_t* out)
         out->digit_tile_b[i] = C.dtile_b[i];  out->digit_lane_b[i] = C.dlane_b[i];
     }
     out->stride1_fixed = (P.perm[0] == 0) ? 1 : 0;
-    out->kernel_class = C.kernel_class == ttc::kKernelLines ? TTC_KERNEL_LDS : (C.kernel_class == ttc::kKernelGather ? TTC_KERNEL_ROWS : C.kernel_class);
+    out->kernel_class = C.kernel_class == ttc::kKernelLines ? TTC_KERNEL_LDS : C.kernel_class == ttc::kKernelGather ? TTC_KERNEL_ROWS :
+                        C.kernel_class == ttc::kKernelBlock ? TTC_KERNEL_MICRO : C.kernel_class;
     out->epilogue = P.epilogue;
     out->vec_a = C.kp.a.vec;
     out->vec_b = C.kp.b.vec;
@@ -1991,9 +2237,11 @@ int ttc_plan_get_info(ttc_plan_t plan, ttc_plan_info_t* out)
     out->candidate_count = (int)plan->cands.size();
     out->tuned_ms = C.tuned_ms;
     out->heuristic_cost = C.score;
-    out->merged = (C.kernel_class == TTC_KERNEL_MICRO || C.kernel_class == ttc::kKernelLines) ? (C.kp.micro.merged_a | (C.kp.micro.merged_b << 1)) : 0;
+    out->merged = (C.kernel_class == TTC_KERNEL_MICRO || C.kernel_class == ttc::kKernelLines) ? (C.kp.micro.merged_a | (C.kp.micro.merged_b << 1)) :
+                  C.kernel_class == ttc::kKernelBlock ? 4 : 0;
     out->unroll = C.kernel_class == TTC_KERNEL_ROWS ? C.rows.unroll :
-                  (C.kernel_class == TTC_KERNEL_MICRO ? C.kp.micro.blocks : (C.kernel_class == ttc::kKernelLines ? C.kp.micro.lines : 0));
+                  C.kernel_class == TTC_KERNEL_MICRO ? C.kp.micro.blocks : C.kernel_class == ttc::kKernelLines ? C.kp.micro.lines :
+                  C.kernel_class == ttc::kKernelBlock ? C.block.unroll : 0;
     return TTC_OK;
     });
 }
@@ -2360,6 +2608,70 @@ static int emulate_lines(const ttc::Problem& P, const ttc::Candidate& C, int pha
     return written == P.elements ? TTC_OK : TTC_ERR_INTERNAL;
 }
 
+// Replay of the block kernel: every workgroup, every lane, the index code the kernel runs.
+static int emulate_block(const ttc::Problem& P, const ttc::Candidate& C, int64_t* b_from_a)
+{
+    using namespace ttc;
+    const BlockArgs p = block_args(C);
+    const BlockParams& m = p.block;
+    const int va = 16 / P.eb_a, vb = 16 / P.eb_b, stores = block_stores(m.unroll, P.eb_a, P.eb_b);
+    if (P.stride_a[0] != 1 || P.stride_b[P.perm[0]] != 1 || p.blocks != C.kp.num_tiles || C.threads != kBlockThreads || C.lds_bytes > kBlockMaxLds ||
+        (int64_t)m.rows * m.pitch * P.eb_a != C.lds_bytes || m.pitch % va != 0 || m.run_a > m.pitch ||
+        (int64_t)m.va_div.div * m.rows > m.unroll * kBlockThreads || (int64_t)m.vb_div.div * m.outs > stores * kBlockThreads ||
+        (int64_t)m.rows * m.run_a != (int64_t)m.outs * m.run_b)
+        return TTC_ERR_INTERNAL;
+    for (int64_t i = 0; i < P.span_b; ++i) b_from_a[i] = -1;
+    auto inside = [&](int64_t off, const int64_t* stride, bool b_side) {
+        if (off < 0) return false;
+        for (int i = P.ndim - 1; i >= 0; --i) {
+            const int k = b_side ? P.perm[i] : i;
+            const int64_t c = off / stride[k];
+            if (c >= P.size[k]) return false;
+            off -= c * stride[k];
+        }
+        return off == 0;
+    };
+    std::vector<int64_t> lds((size_t)(m.rows * (int64_t)m.pitch));
+    std::vector<char> seen(p.blocks, 0);
+    int64_t written = 0;
+    for (int64_t wg = 0; wg < rows_grid(p); ++wg) {
+        const uint32_t block = rows_block(p, (uint32_t)wg);
+        if (block >= p.blocks) continue;
+        if (seen[block]) return TTC_ERR_INTERNAL;
+        seen[block] = 1;
+        const BlockTile t = block_tile(p, block);
+        if (t.run_a < 1 || t.run_b < 1 || t.run_a > m.run_a || t.run_b > m.run_b) return TTC_ERR_INTERNAL;
+        std::fill(lds.begin(), lds.end(), (int64_t)-1);
+        for (uint32_t g = 0; g < (uint32_t)(m.unroll * kBlockThreads); ++g) {
+            const BlockLoad x = block_load(m, t, g, va);
+            for (int j = 0; j < va; ++j) {                       // every lane loads, whether it keeps what it got or not
+                const int64_t src = t.a + x.a + j;
+                if (!inside(src, P.stride_a, false)) return TTC_ERR_INTERNAL;
+                if (!x.ok || x.start + j < 0) continue;
+                const int64_t slot = (int64_t)x.lds + j;
+                if (slot < 0 || slot >= (int64_t)lds.size() || (x.start == x.col && x.lds % va != 0)) return TTC_ERR_INTERNAL;
+                if (lds[(size_t)slot] != -1 && lds[(size_t)slot] != src) return TTC_ERR_INTERNAL;
+                lds[(size_t)slot] = src;
+            }
+        }
+        for (uint32_t h = 0; h < (uint32_t)(stores * kBlockThreads); ++h) {
+            const BlockStore x = block_store(m, t, h, vb);
+            if (P.epilogue == TTC_EPI_AXPBY)
+                for (int j = 0; j < vb; ++j) if (!inside(t.b + x.from + j, P.stride_b, true)) return TTC_ERR_INTERNAL;
+            int32_t at = x.lds, x0 = x.x0, x1 = x.x1;
+            for (int j = 0; j < x.count; ++j) {
+                if (m.even) at = x.lds + j * m.x_lds[0];
+                else if (j > 0) block_next(m, &at, &x0, &x1);
+                const int64_t dst = t.b + x.b + j;
+                if (at < 0 || at >= (int64_t)lds.size() || lds[(size_t)at] < 0 || !inside(dst, P.stride_b, true) || b_from_a[dst] != -1) return TTC_ERR_INTERNAL;
+                b_from_a[dst] = lds[(size_t)at];
+                ++written;
+            }
+        }
+    }
+    return written == P.elements ? TTC_OK : TTC_ERR_INTERNAL;
+}
+
 static int emulate_map(ttc_plan_t plan, int64_t* b_from_a)
 {
     using namespace ttc;
@@ -2368,6 +2680,7 @@ static int emulate_map(ttc_plan_t plan, int64_t* b_from_a)
     if (C.kernel_class == TTC_KERNEL_ROWS) return emulate_rows(P, C, b_from_a);
     if (C.kernel_class == kKernelGather) return emulate_gather(P, C, b_from_a);
     if (C.kernel_class == TTC_KERNEL_MICRO) return emulate_micro(P, C, b_from_a);
+    if (C.kernel_class == kKernelBlock) return emulate_block(P, C, b_from_a);
     if (C.kernel_class == kKernelLines) {
         // where a tile is cut depends on the address B will have: every place inside a line that matters (the first,
         // the last, one between), the aligned one last

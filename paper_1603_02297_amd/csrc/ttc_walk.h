@@ -138,8 +138,9 @@ TTC_HD GatherPlace gather_next(const RowsParams& p, const GatherPlace& g, uint32
 }
 
 // Which chunk workgroup `wg` of a row-kernel launch moves (p.blocks: none): consecutive chunks, which share a line of
-// B and lines of A, go to one XCD a few at a time, as with tiles.
-TTC_HD uint32_t rows_block(const RowsParams& p, uint32_t wg)
+// B and lines of A, go to one XCD a few at a time, as with tiles.  The block kernel's tiles likewise.
+template <typename Params>       // RowsParams or BlockArgs
+TTC_HD uint32_t rows_block(const Params& p, uint32_t wg)
 {
     if (p.xcd_remap == 0) return wg;
     const uint32_t x = wg & 7u, q = wg >> 3;
@@ -152,7 +153,8 @@ TTC_HD uint32_t rows_block(const RowsParams& p, uint32_t wg)
 }
 
 // Workgroups to launch so that every chunk has one: whole rounds of chunks over the XCDs.
-TTC_HD int64_t rows_grid(const RowsParams& p)
+template <typename Params>
+TTC_HD int64_t rows_grid(const Params& p)
 {
     if (p.xcd_remap == 0) return p.blocks;
     const int64_t round = p.xcd_remap == 1 ? 8 : int64_t(8) << p.xcd_remap;
@@ -428,6 +430,91 @@ TTC_HD int32_t line_row(const MicroParams& m, const LineShape& s, const LineTile
 TTC_HD bool line_last(const MicroParams& m, const LineShape& s, uint32_t tid, int i)
 {
     return m.skewed && line_group(s, tid) + i * s.groups == s.lines - 1;
+}
+
+// ---- block kernel ------------------------------------------------------------------------------
+// a, b: element offsets of the tile in A and in B; run_a, run_b: elements of its runs that exist; lim_row, lim_out: how far
+// the cut digit of a row's, of an out's place goes.
+struct BlockTile { int64_t a, b; int32_t run_a, run_b, lim_row, lim_out; };
+
+TTC_HD BlockTile block_tile(const BlockArgs& p, uint32_t tile)
+{
+    const BlockParams& m = p.block;
+    BlockTile t;
+    t.a = 0; t.b = 0;
+    uint32_t rest = tile, ca = 0, cb = 0;
+#pragma unroll
+    for (int i = 0; i < kMaxDim; ++i) {
+        const uint32_t next = fdiv(rest, p.cnt[i]);
+        const uint32_t d = rest - next * p.cnt[i].div;
+        rest = next;
+        t.a += (int64_t)d * p.step_a[i];
+        t.b += (int64_t)d * p.step_b[i];
+        if (i == m.pos_a) ca = d;
+        if (i == m.pos_b) cb = d;
+    }
+    const int64_t left_a = m.size_a - (int64_t)ca * m.tile_a, left_b = m.size_b - (int64_t)cb * m.tile_b;
+    const int32_t lim_a = left_a < m.tile_a ? (int32_t)left_a : m.tile_a, lim_b = left_b < m.tile_b ? (int32_t)left_b : m.tile_b;
+    t.run_a = m.inner_a * lim_a;
+    t.run_b = m.inner_b * lim_b;
+    t.lim_row = lim_b;
+    t.lim_out = lim_a;
+    return t;
+}
+
+// Vector `g` of the tile in A's order: where it starts in A (relative to the tile) and in LDS.  start: its place in the run,
+// moved back to end with the run (negative, that is inside the tile before, if the run holds less than a vector).
+// ok: it is one of the tile's; if not, the tile's first vector is loaded in its place.
+struct BlockLoad { int64_t a; int32_t lds, col, start; bool ok; };
+
+TTC_HD BlockLoad block_load(const BlockParams& m, const BlockTile& t, uint32_t g, int32_t vec)
+{
+    BlockLoad r;
+    const uint32_t row = fdiv(g, m.va_div);
+    const uint32_t r1 = fdiv(row, m.row_div), r0 = row - r1 * m.row_div.div;
+    r.col = (int32_t)(g - row * m.va_div.div) * vec;
+    r.ok = row < (uint32_t)m.rows && r.col < t.run_a && (int32_t)(m.cut_row == 0 ? r0 : m.cut_row == 1 ? r1 : 0u) < t.lim_row;
+    r.start = r.ok ? r.col : 0;
+    if (r.start + vec > t.run_a) r.start = t.run_a - vec;
+    r.a = (r.ok ? (int64_t)r0 * m.row_step[0] + (int64_t)r1 * m.row_step[1] : 0) + r.start;
+    r.lds = (int32_t)row * m.pitch + r.start;
+    return r;
+}
+
+// Vector `h` of the tile in B's order: where it starts in B (relative to the tile), its first element's place in LDS, that
+// element's places along the first two indices of B's run, and how many of its elements are the tile's (0: none; fewer than
+// a vector at the end of a run).  from: where the whole vector starts in B that B is read with before an update.
+struct BlockStore { int64_t b, from; int32_t lds, x0, x1, count; };
+
+TTC_HD BlockStore block_store(const BlockParams& m, const BlockTile& t, uint32_t h, int32_t vec)
+{
+    BlockStore r;
+    const uint32_t out = fdiv(h, m.vb_div);
+    const uint32_t o1 = fdiv(out, m.out_div), o0 = out - o1 * m.out_div.div;
+    const int32_t x = (int32_t)(h - out * m.vb_div.div) * vec;
+    const bool ok = out < (uint32_t)m.outs && x < t.run_b && (int32_t)(m.cut_out == 0 ? o0 : m.cut_out == 1 ? o1 : 0u) < t.lim_out;
+    r.count = !ok ? 0 : t.run_b - x < vec ? t.run_b - x : vec;
+    const uint32_t q0 = fdiv((uint32_t)x, m.x_div[0]), q1 = fdiv(q0, m.x_div[1]);
+    r.x0 = x - (int32_t)(q0 * m.x_div[0].div);
+    r.x1 = (int32_t)(q0 - q1 * m.x_div[1].div);
+    r.lds = r.x0 * m.x_lds[0] + r.x1 * m.x_lds[1] + (int32_t)q1 * m.x_lds[2] + (int32_t)o0 * m.out_lds[0] + (int32_t)o1 * m.out_lds[1];
+    const int64_t place = ok ? (int64_t)o0 * m.out_step[0] + (int64_t)o1 * m.out_step[1] : 0;
+    r.b = place + x;
+    r.from = place + (!ok || x + vec > t.run_b ? (ok ? t.run_b - vec : t.run_b < vec ? t.run_b - vec : 0) : x);
+    if (!ok) r.lds = 0;
+    return r;
+}
+
+// The next element of a vector that runs across B's indices: its place in LDS and along the first two.
+TTC_HD void block_next(const BlockParams& m, int32_t* lds, int32_t* x0, int32_t* x1)
+{
+    *lds += m.x_lds[0];
+    if (++*x0 < (int32_t)m.x_div[0].div) return;
+    *x0 = 0;
+    *lds += m.x_lds[1] - (int32_t)m.x_div[0].div * m.x_lds[0];
+    if (++*x1 < (int32_t)m.x_div[1].div) return;
+    *x1 = 0;
+    *lds += m.x_lds[2] - (int32_t)m.x_div[1].div * m.x_lds[1];
 }
 
 // ---- lane entry ------------------------------------------------------------------------------

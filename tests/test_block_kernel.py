@@ -1,0 +1,106 @@
+"""The block kernel (tiles over the leading indices of both tensors): every candidate against the oracle, replayed on the host
+and run on the GPU, at the sizes where its tiles can go wrong: runs that are no multiple of a vector, runs that the tensor's
+edge cuts (to less than a vector too), vectors of B across one and two of its indices, an index that both runs end with."""
+import numpy as np
+import pytest
+
+import oracle
+import paper_1603_02297_amd as ttc
+from paper_1603_02297_amd import workloads as wl
+
+# sizes, perm, lda, ldb
+SHAPES = [
+    ((8, 6, 12, 5, 7), (2, 0, 4, 3, 1), None, None),          # A's first index inside B's run
+    ((6, 5, 4, 3, 7), (1, 0, 2, 4, 3), None, None),           # both runs over the same indices, ending with the same one
+    ((3, 301, 4), (1, 0, 2), None, None),                     # records to planes, an odd number of them
+    ((5, 7, 9, 11), (3, 2, 1, 0), None, None),
+    ((9, 4, 3, 5, 8), (4, 1, 3, 0, 2), None, (9, 4, 5, 9, 3)),
+    ((7, 6, 5, 9), (1, 3, 0, 2), (7, 8, 5, 9), None),
+    ((33, 5, 9), (1, 0, 2), None, None),                      # B's first index shorter than a line
+    ((10, 3, 50), (1, 2, 0), None, None),
+]
+DTYPES = [wl.F32, wl.F64, wl.C64, wl.C128, wl.F32_F64, wl.F64_F32, wl.C64_C128, wl.C128_C64]
+
+
+def block_candidates(plan):
+    for k in range(ttc.ttc_plan_candidate_count(plan)):
+        ttc.ttc_plan_select_candidate(plan, k)
+        info = ttc.ttc_plan_get_info(plan)
+        if info["kernel_class"] == ttc.TTC_KERNEL_MICRO and info["merged"] == 4:
+            yield k, info
+
+
+def scalars(dtype):
+    cplx = wl.COMPONENTS[dtype] == 2
+    return [(1.0, 0.0), (0.5 + 0.5j if cplx else 1.5, 0.0), (0.5 - 0.25j if cplx else 0.75, 1.0 + 0.5j if cplx else -1.25)]
+
+
+@pytest.mark.parametrize("dtype", DTYPES, ids=[wl.DTYPE_NAME[d] for d in DTYPES])
+def test_walks_of_every_block_candidate(dtype):
+    seen = 0
+    for sizes, perm, lda, ldb in SHAPES:
+        for beta in (0.0, 1.0):
+            p = ttc.ttc_plan_create_ex(dtype, len(sizes), sizes, perm, lda, ldb, 1.0, beta)
+            want = [-1] * ttc.ttc_plan_get_info(p)["span_b"]
+            for off_a, off_b in oracle.element_pairs(sizes, perm, lda, ldb):
+                want[off_b] = off_a
+            for k, info in block_candidates(p):
+                for mode in (-1, 1 + seen % 4):                    # tiles dealt to the XCDs unevenly too
+                    ttc.ttc_plan_set_tile_mapping(p, mode)
+                    assert list(ttc.ttc_debug_emulate_map(p)) == want, (sizes, perm, k, mode, info)
+                seen += 1
+            ttc.ttc_plan_destroy(p)
+    assert seen >= 40
+
+
+def test_where_the_block_kernel_is_offered():
+    """Not for runs of one index each, which are the micro-tile kernel's, nor where an index of more than 1 KB begins the run of
+    several, nor where the stride-1 index keeps its place."""
+    for sizes, perm, offered in (((24, 20, 18), (1, 0, 2), True), ((300, 300), (1, 0), False),
+                                 ((300, 20, 300), (2, 1, 0), False), ((24, 20, 18), (0, 2, 1), False)):
+        p = ttc.ttc_plan_create(ttc.TTC_F32, len(sizes), sizes, perm)
+        assert any(True for _ in block_candidates(p)) == offered, (sizes, perm)
+        ttc.ttc_plan_destroy(p)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", DTYPES, ids=[wl.DTYPE_NAME[d] for d in DTYPES])
+def test_block_kernel_against_the_oracle(dtype):
+    """Every candidate, every epilogue, both streaming settings; B at two places inside a line; what lies around the sub-tensor
+    stays as it was.  Fixed evaluation order on both sides: bit-equal but for the ulp the library allows."""
+    import torch
+    dev = torch.device("cuda:0")
+    stream = torch.cuda.current_stream().cuda_stream
+    prod = lambda v: int(np.prod(v))  # noqa: E731
+    ran = 0
+    for shape, (sizes, perm, lda, ldb) in enumerate(SHAPES):
+        na, nb = prod(lda or sizes), prod(ldb or sizes)
+        A = wl.uniform_tensor(dtype, na, 8000 + shape, "a")
+        B0 = wl.uniform_tensor(dtype, nb, 8100 + shape, "b")
+        comp, room = wl.COMPONENTS[dtype], 128
+        dA = torch.from_numpy(A).to(dev)
+        for alpha, beta in scalars(dtype):
+            want = oracle.transpose(dtype, sizes, perm, alpha, beta, A, B0.copy(), 4, lda=lda, ldb=ldb)
+            plan = ttc.ttc_plan_create_ex(dtype, len(sizes), sizes, perm, lda, ldb, alpha, beta)
+            try:
+                for k, info in block_candidates(plan):
+                    for nt, phase in ((0, 0), (1, 7)):
+                        ttc.ttc_plan_set_streaming(plan, nt, nt)
+                        ttc.ttc_plan_set_tile_mapping(plan, 2 * nt - 1 + nt * (k % 3))
+                        buf = torch.full((nb * comp + 2 * room,), 77.0, dtype=torch.from_numpy(B0).dtype, device=dev)
+                        at = room + phase * comp
+                        buf[at:at + nb * comp] = torch.from_numpy(B0).to(dev)
+                        ttc.ttc_execute(plan, dA.data_ptr(), buf.data_ptr() + at * buf.element_size(), stream)
+                        torch.cuda.synchronize()
+                        got = buf.cpu().numpy()
+                        assert (got[:at] == 77).all() and (got[at + nb * comp:] == 77).all(), (sizes, perm, k, info)
+                        got = got[at:at + nb * comp]
+                        if complex(alpha) == 1 and complex(beta) == 0:
+                            assert np.array_equal(got, want), (sizes, perm, k, info)
+                        else:
+                            ulp = np.spacing(np.abs(want).max())
+                            assert np.abs(got - want).max() <= ulp, (sizes, perm, alpha, beta, k, info)
+                        ran += 1
+            finally:
+                ttc.ttc_plan_destroy(plan)
+    assert ran >= 100
