@@ -287,6 +287,16 @@ constexpr int kBlockMaxLds = 64 * 1024;
 // vectors a lane stores where it loads `unroll`
 constexpr int block_stores(int unroll, int eb_a, int eb_b) { return unroll * eb_b / eb_a < 1 ? 1 : unroll * eb_b / eb_a; }
 
+// RowsParams of a small problem, packed.  Launches with up to 96 bytes of arguments, the two pointers included, leave the host
+// at 2.6-2.8 us each, larger ones at 3.4-3.6 (112 to 456 bytes; empty kernels in a row), which is most of what a small problem
+// takes; and its workgroups begin sooner.  70 x 33 x 45 fp32 (2,0,1) 3.46 -> 2.78 us a launch, 600 x 600 fp32 4.05 -> 3.44,
+// 96 x 80 x 70 fp32 (0,2,1) 3.3 -> 2.87.  From 2048 chunks of 4 KB on a launch is dealt to the XCDs in another way and
+// bound by memory: parameters go whole there, and where they do not fit (six indices, strides beyond 32 bits).  Four words (elements, chunks, per_xcd, rows), then per division two (the multiplier; divisor and shift), the
+// strides in A, and at an 8-byte boundary the scalars that the epilogue reads.
+struct SmallArgs { uint32_t w[20]; };
+constexpr int kSmallMaxDim = 5;
+constexpr int64_t kSmallMaxElements = int64_t(1) << 26;       // divisors leave five bits of their word to the shift
+
 // The line kernel's internal class.  Plans report it as TTC_KERNEL_LDS (its tile is staged through LDS) with a
 // non-zero `unroll`.
 constexpr int kKernelLines = 4;

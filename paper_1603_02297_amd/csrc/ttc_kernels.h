@@ -91,6 +91,8 @@ template <typename Z, typename R, int MODE> struct ComplexCore {  // Z = cfloat 
 template <int MODE> struct Core<cfloat, MODE> : ComplexCore<cfloat, float, MODE> { using ComplexCore<cfloat, float, MODE>::ComplexCore; };
 template <int MODE> struct Core<cdouble, MODE> : ComplexCore<cdouble, double, MODE> { using ComplexCore<cdouble, double, MODE>::ComplexCore; };
 
+template <typename T> struct IsComplex { static constexpr bool value = std::is_same<T, cfloat>::value || std::is_same<T, cdouble>::value; };
+
 // type the arithmetic runs in: the common type, or the double-precision one when they differ
 template <typename TA, typename TB> struct Wider;
 template <typename T> struct Wider<T, T> { using type = T; };
@@ -356,16 +358,10 @@ __global__ __launch_bounds__(kMaxThreads) void box_kernel(const KernelParams par
 constexpr int kRowsThreads = 256;
 
 template <typename TA, typename TB, int MODE, int V, int U, bool FLAT>
-__global__ __launch_bounds__(kRowsThreads) void rows_kernel(const RowsParams p, const TA* __restrict__ A, TB* __restrict__ B)
+__device__ __forceinline__ void rows_chunk(const RowsParams& p, int64_t base, uint32_t row0, uint32_t slot0, const TA* __restrict__ A, TB* __restrict__ B)
 {
     constexpr int32_t kScaleA = (int32_t)sizeof(TA), kScaleB = (int32_t)sizeof(TB);
-    const uint32_t block = rows_block(p, blockIdx.x);
-    if (block >= p.blocks) return;
     const Epilogue<TA, TB, MODE> epi(p.alpha, p.beta);
-    const int64_t base = (int64_t)block * (int64_t)p.chunk * (FLAT ? V : 1);
-    const int64_t row0_wide = base / (int64_t)p.slots;                  // wave-uniform: once per workgroup
-    const uint32_t row0 = (uint32_t)row0_wide;
-    const uint32_t slot0 = (uint32_t)(base - row0_wide * (int64_t)p.slots);
     const unsigned char* Ab = reinterpret_cast<const unsigned char*>(A);
     unsigned char* Bb = reinterpret_cast<unsigned char*>(B);
     auto run = [&](auto stream_a, auto stream_b) {
@@ -440,6 +436,26 @@ __global__ __launch_bounds__(kRowsThreads) void rows_kernel(const RowsParams p, 
     };
     if (p.nt_a) { if (p.nt_b) run(std::true_type(), std::true_type()); else run(std::true_type(), std::false_type()); }
     else        { if (p.nt_b) run(std::false_type(), std::true_type()); else run(std::false_type(), std::false_type()); }
+}
+
+template <typename TA, typename TB, int MODE, int V, int U, bool FLAT>
+__global__ __launch_bounds__(kRowsThreads) void rows_kernel(const RowsParams p, const TA* __restrict__ A, TB* __restrict__ B)
+{
+    const uint32_t block = rows_block(p, blockIdx.x);
+    if (block >= p.blocks) return;
+    const int64_t base = (int64_t)block * (int64_t)p.chunk * (FLAT ? V : 1);
+    const int64_t row0_wide = base / (int64_t)p.slots;                  // wave-uniform: once per workgroup
+    rows_chunk<TA, TB, MODE, V, U, FLAT>(p, base, (uint32_t)row0_wide, (uint32_t)(base - row0_wide * (int64_t)p.slots), A, B);
+}
+
+// The same for small problems over a dense B, with its arguments packed (SmallArgs) and the usual hints (A kept, B streamed).
+template <typename TA, typename TB, int MODE, int V, int N>
+__global__ __launch_bounds__(kRowsThreads) void rows_small_kernel(const SmallArgs args_by_value, const TA* __restrict__ A, TB* __restrict__ B)
+{
+    const SmallArgs& s = *reinterpret_cast<const SmallArgs*>((const void*)__builtin_amdgcn_kernarg_segment_ptr());
+    const RowsParams p = small_unpack<false, N, MODE, IsComplex<TA>::value>(s, V, kRowsThreads);
+    const uint32_t first = blockIdx.x * (uint32_t)(kRowsThreads * V), row0 = fdiv(first, p.slot_div);
+    rows_chunk<TA, TB, MODE, V, 1, true>(p, (int64_t)first, row0, first - row0 * p.row, A, B);
 }
 
 // ---------------------------------------------------------------------------------
@@ -934,11 +950,9 @@ inline hipError_t launch_one(const KernelParams& kp, const void* A, void* B, uin
 // 70 x 33 x 45 fp32 (2,0,1): 3.4 us a launch (box kernel 4.2), 2.4 line requests per line of A, all but 0.4 of them from L2.
 // ---------------------------------------------------------------------------------
 template <typename TA, typename TB, int MODE, int V>
-__global__ __launch_bounds__(kRowsThreads) void gather_kernel(const RowsParams p, const TA* __restrict__ A, TB* __restrict__ B)
+__device__ __forceinline__ void gather_chunk(const RowsParams& p, uint32_t block, const TA* __restrict__ A, TB* __restrict__ B)
 {
     static_assert(V * sizeof(TB) == 16, "one 16-byte vector of B");
-    const uint32_t block = rows_block(p, blockIdx.x);
-    if (block >= p.blocks) return;
     const uint32_t e = gather_first(p, block, threadIdx.x);
     if ((int64_t)e >= p.elements) return;
     const Epilogue<TA, TB, MODE> epi(p.alpha, p.beta);
@@ -981,6 +995,42 @@ __global__ __launch_bounds__(kRowsThreads) void gather_kernel(const RowsParams p
     else        { if (p.nt_b) run(std::false_type(), std::true_type()); else run(std::false_type(), std::false_type()); }
 }
 
+template <typename TA, typename TB, int MODE, int V>
+__global__ __launch_bounds__(kRowsThreads) void gather_kernel(const RowsParams p, const TA* __restrict__ A, TB* __restrict__ B)
+{
+    const uint32_t block = rows_block(p, blockIdx.x);
+    if (block >= p.blocks) return;
+    gather_chunk<TA, TB, MODE, V>(p, block, A, B);
+}
+
+// The same over a dense B with its arguments packed (SmallArgs), nothing streamed.
+template <typename TA, typename TB, int MODE, int V, int N>
+__global__ __launch_bounds__(kRowsThreads) void gather_small_kernel(const SmallArgs args_by_value, const TA* __restrict__ A, TB* __restrict__ B)
+{
+    const SmallArgs& s = *reinterpret_cast<const SmallArgs*>((const void*)__builtin_amdgcn_kernarg_segment_ptr());
+    const RowsParams p = small_unpack<true, N, MODE, IsComplex<TA>::value>(s, V, kRowsThreads);
+    gather_chunk<TA, TB, MODE, V>(p, blockIdx.x, A, B);
+}
+
+// Launch of either small kernel: the one compiled for `dims` indices (small_dims()).
+template <typename TA, typename TB, int MODE, int V, bool GATHER, int N = 2>
+inline hipError_t launch_small(const RowsParams& rp, int dims, int64_t grid, const TA* a, TB* b, hipStream_t stream)
+{
+    if constexpr (N <= kSmallMaxDim) {
+        if constexpr (small_fits(GATHER, N, MODE, IsComplex<TA>::value)) {
+            if (dims == N) {
+                SmallArgs ready = small_pack(rp, GATHER, N, MODE, IsComplex<TA>::value);
+                void* args[] = {&ready, &a, &b};
+                const void* fn = GATHER ? reinterpret_cast<const void*>(&gather_small_kernel<TA, TB, MODE, 16 / (int)sizeof(TB), N>)
+                                        : reinterpret_cast<const void*>(&rows_small_kernel<TA, TB, MODE, V, N>);
+                return hipLaunchKernel(fn, dim3((uint32_t)grid), dim3(kRowsThreads), args, 0, stream);
+            }
+        }
+        return launch_small<TA, TB, MODE, V, GATHER, N + 1>(rp, dims, grid, a, b, stream);
+    }
+    return hipErrorInvalidValue;
+}
+
 template <typename TA, typename TB, int MODE>
 inline hipError_t launch_gather(const Candidate& c, const void* A, void* B, hipStream_t stream)
 {
@@ -997,6 +1047,8 @@ inline hipError_t launch_gather(const Candidate& c, const void* A, void* B, hipS
     if (!launchable(grid, kRowsThreads)) return hipErrorInvalidValue;
     const TA* a = static_cast<const TA*>(A);
     TB* b = static_cast<TB*>(B);
+    const int dims = small_dims(rp, true, MODE, IsComplex<TA>::value, 0, 0);
+    if (dims) return launch_small<TA, TB, MODE, V, true>(rp, dims, grid, a, b, stream);
     void* args[] = {&rp, &a, &b};
     return hipLaunchKernel(reinterpret_cast<const void*>(&gather_kernel<TA, TB, MODE, V>), dim3((uint32_t)grid), dim3(kRowsThreads), args, 0, stream);
 }
@@ -1016,6 +1068,10 @@ inline hipError_t launch_rows_unrolled(const Candidate& c, const void* A, void* 
     if (!launchable(grid, kRowsThreads)) return hipErrorInvalidValue;
     const TA* a = static_cast<const TA*>(A);
     TB* b = static_cast<TB*>(B);
+    if constexpr (FLAT && U == 1) {
+        const int dims = small_dims(rp, false, MODE, IsComplex<TA>::value, 0, 1);
+        if (dims) return launch_small<TA, TB, MODE, V, false>(rp, dims, grid, a, b, stream);
+    }
     void* args[] = {&rp, &a, &b};
     return hipLaunchKernel(reinterpret_cast<const void*>(&rows_kernel<TA, TB, MODE, V, U, FLAT>), dim3((uint32_t)grid), dim3(kRowsThreads), args, 0, stream);
 }

@@ -2303,12 +2303,40 @@ int ttc_debug_emulate_map(ttc_plan_t plan, int64_t* b_from_a)
 
 }  // extern "C"
 
+// What the kernels of small problems see of the parameters: packed and unpacked again, if such a kernel runs.
+template <bool GATHER, int MODE, bool COMPLEX, int N = 2>
+static void small_round_trip(ttc::RowsParams* p)
+{
+    using namespace ttc;
+    if constexpr (N <= kSmallMaxDim) {
+        if constexpr (small_fits(GATHER, N, MODE, COMPLEX))
+            if (small_dims(*p, GATHER, MODE, COMPLEX, 0, GATHER ? 0 : 1) == N) {
+                const RowsParams q = small_unpack<GATHER, N, MODE, COMPLEX>(small_pack(*p, GATHER, N, MODE, COMPLEX), p->vec, p->chunk);
+                *p = q;
+                return;
+            }
+        small_round_trip<GATHER, MODE, COMPLEX, N + 1>(p);
+    }
+}
+
+template <bool GATHER>
+static void small_round_trip(const ttc::Problem& P, ttc::RowsParams* p)
+{
+    const bool cplx = P.kind_a >= ttc::kKindC64;
+    switch (P.epilogue) {
+    case TTC_EPI_COPY:  cplx ? small_round_trip<GATHER, TTC_EPI_COPY, true>(p) : small_round_trip<GATHER, TTC_EPI_COPY, false>(p); break;
+    case TTC_EPI_SCALE: cplx ? small_round_trip<GATHER, TTC_EPI_SCALE, true>(p) : small_round_trip<GATHER, TTC_EPI_SCALE, false>(p); break;
+    default:            cplx ? small_round_trip<GATHER, TTC_EPI_AXPBY, true>(p) : small_round_trip<GATHER, TTC_EPI_AXPBY, false>(p); break;
+    }
+}
+
 // Replay of the row kernel: every workgroup, every lane, the index code the kernel runs.
 static int emulate_rows(const ttc::Problem& P, const ttc::Candidate& C, int64_t* b_from_a)
 {
     using namespace ttc;
     RowsParams p = C.rows;
     p.xcd_remap = C.kp.xcd_remap;               // as the launch does
+    p.nt_a = C.kp.nt_a; p.nt_b = C.kp.nt_b;
     for (int64_t i = 0; i < P.span_b; ++i) b_from_a[i] = -1;
     const int64_t rows = P.elements / P.size[0];
     if ((p.vec != 1 && p.vec != 2 && p.vec != 4) || (p.unroll != 1 && p.unroll != 2 && p.unroll != 4 && p.unroll != 8) || C.threads != 256 ||
@@ -2319,6 +2347,7 @@ static int emulate_rows(const ttc::Problem& P, const ttc::Candidate& C, int64_t*
         p.overlap != (!p.flat && P.size[0] % p.vec != 0 ? 1 : 0) || (p.overlap && P.epilogue == TTC_EPI_AXPBY) ||
         P.size[0] >= (int64_t(1) << 30) || rows >= (int64_t(1) << 31))
         return TTC_ERR_INTERNAL;
+    if (p.unroll == 1) small_round_trip<false>(P, &p);
     auto inside = [&](int64_t off, const int64_t* stride, bool b_side) {
         if (off < 0) return false;
         for (int i = P.ndim - 1; i >= 0; --i) {
@@ -2381,6 +2410,8 @@ static int emulate_gather(const ttc::Problem& P, const ttc::Candidate& C, int64_
         (int64_t)p.per_xcd != (p.per_xcd ? (((p.elements + p.vec - 1) / p.vec + p.chunk - 1) / p.chunk + 7) / 8 : 0) ||
         (int64_t)p.blocks != (p.per_xcd ? 8 * (int64_t)p.per_xcd : ((p.elements + p.vec - 1) / p.vec + p.chunk - 1) / p.chunk))
         return TTC_ERR_INTERNAL;
+    p.nt_a = C.kp.nt_a; p.nt_b = C.kp.nt_b;
+    small_round_trip<true>(P, &p);
     for (int64_t i = 0; i < P.span_b; ++i) b_from_a[i] = -1;
     auto inside = [&](int64_t off, const int64_t* stride, bool b_side) {
         if (off < 0) return false;

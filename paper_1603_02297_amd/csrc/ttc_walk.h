@@ -161,6 +161,87 @@ TTC_HD int64_t rows_grid(const Params& p)
     return (p.blocks + round - 1) / round * round;
 }
 
+// ---- the arguments of small problems ---------------------------------------------------------
+// Words before the scalars.  Gather kernel: divisions for B's indices 0 ... n-2, strides of all; row kernel (flat): divisions for
+// the row and B's indices 1 ... n-2, strides of indices 1 ... n-1.
+constexpr int small_words(bool gather, int n) { return (4 + 2 * (n - 1) + (gather ? n : n - 1) + 1) / 2 * 2; }
+constexpr int small_scalars(int epilogue, bool is_complex) { return (epilogue == TTC_EPI_COPY ? 0 : epilogue == TTC_EPI_SCALE ? 1 : 2) * (is_complex ? 2 : 1); }
+constexpr bool small_fits(bool gather, int n, int epilogue, bool is_complex) { return small_words(gather, n) + 2 * small_scalars(epilogue, is_complex) <= 20; }
+
+// Which number of indices the kernels are compiled for serves this launch; 0: none, its arguments go unpacked.  nt_a, nt_b: the
+// hints the packed kernels are compiled with.
+inline int small_dims(const RowsParams& p, bool gather, int epilogue, bool is_complex, int nt_a, int nt_b)
+{
+    const int n = p.n < 2 ? 2 : p.n;
+    if (!p.flat || p.xcd_remap != 0 || p.nt_a != nt_a || p.nt_b != nt_b || n > kSmallMaxDim || p.elements >= kSmallMaxElements ||
+        !small_fits(gather, n, epilogue, is_complex)) return 0;
+    for (int d = 0; d < n; ++d)
+        if (p.stride_a[d] > INT32_MAX || (p.size_div[d].div > 1 && (p.size_div[d].div - 1) * p.stride_a[d] > INT32_MAX)) return 0;
+    return n;
+}
+
+inline SmallArgs small_pack(const RowsParams& p, bool gather, int n, int epilogue, bool is_complex)
+{
+    SmallArgs s = {};
+    int at = 0;
+    s.w[at++] = (uint32_t)p.elements;
+    s.w[at++] = p.blocks;
+    s.w[at++] = p.per_xcd;
+    s.w[at++] = p.rows;
+    for (int d = 0; d < n - 1; ++d) {
+        const FastDiv& f = !gather && d == 0 ? p.slot_div : p.size_div[d];
+        s.w[at++] = f.mul;
+        s.w[at++] = f.div | f.shift << 27;
+    }
+    for (int d = gather ? 0 : 1; d < n; ++d) s.w[at++] = (uint32_t)p.stride_a[d];
+    at = small_words(gather, n);
+    const int count = small_scalars(epilogue, is_complex), each = is_complex ? 2 : 1;
+    for (int k = 0; k < count; ++k) {
+        const double v = k < each ? p.alpha[k] : p.beta[k - each];
+        uint64_t bits;
+        __builtin_memcpy(&bits, &v, 8);
+        s.w[at++] = (uint32_t)bits;
+        s.w[at++] = (uint32_t)(bits >> 32);
+    }
+    return s;
+}
+
+// The parameters as the index code reads them; what is not packed follows from the rest or is never read.  The last index's
+// division only has to give quotient 0.
+template <bool GATHER, int N, int MODE, bool COMPLEX>
+TTC_HD RowsParams small_unpack(const SmallArgs& s, int vec, uint32_t chunk)
+{
+    RowsParams p;
+    p.n = N; p.vec = vec; p.unroll = 1; p.overlap = 0; p.flat = 1; p.xcd_remap = 0; p.chunk = chunk;
+    p.elements = (int64_t)s.w[0];
+    p.blocks = s.w[1];
+    p.per_xcd = s.w[2];
+    p.rows = s.w[3];
+    p.nt_a = 0; p.nt_b = GATHER ? 0 : 1;
+    p.vectors = 0;
+    int64_t b = 1;
+#pragma unroll
+    for (int d = 0; d < kMaxDim; ++d) {
+        FastDiv f = {0u, d == N - 1 ? 31u : 0u, d == N - 1 ? 0u : 1u};
+        if (d < N - 1) { f.mul = s.w[4 + 2 * d]; f.div = s.w[5 + 2 * d] & 0x7ffffffu; f.shift = s.w[5 + 2 * d] >> 27; }
+        if (d == 0) { p.row = f.div; p.slots = f.div; p.slot_div = f; }
+        p.size_div[d] = f;
+        p.stride_a[d] = d < N && (GATHER || d > 0) ? (int64_t)(int32_t)s.w[4 + 2 * (N - 1) + (GATHER ? d : d - 1)] : 0;
+        p.stride_b[d] = GATHER && d < N ? b : 0;
+        b *= (int64_t)f.div;
+    }
+    p.alpha[0] = p.alpha[1] = p.beta[0] = p.beta[1] = 0.0;
+    constexpr int kCount = small_scalars(MODE, COMPLEX), kEach = COMPLEX ? 2 : 1, kAt = small_words(GATHER, N);
+#pragma unroll
+    for (int k = 0; k < kCount; ++k) {
+        const uint64_t bits = (uint64_t)s.w[kAt + 2 * k] | (uint64_t)s.w[kAt + 2 * k + 1] << 32;
+        double v;
+        __builtin_memcpy(&v, &bits, 8);
+        if (k < kEach) p.alpha[k] = v; else p.beta[k - kEach] = v;
+    }
+    return p;
+}
+
 // ---- which tiles a workgroup walks ---------------------------------------------------------
 // Consecutive workgroup ids land on consecutive XCDs (8 of them, each with its own L2).  Every
 // XCD owns one contiguous range of tile ids; its workgroups take the tiles of that range round

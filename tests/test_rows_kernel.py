@@ -254,3 +254,46 @@ def test_many_gather_chunks_against_the_oracle(sizes, perm, dtype, shared):
             for setup in ((0, 1), (1, 0)):
                 execute_and_compare(plan, dtype, dA, B0, want, beta == 0, setup, (sizes, perm, beta, mapping, setup))
         ttc.ttc_plan_destroy(plan)
+
+
+# sizes, perm: two to six indices (what is packed ends between four and six, by the scalars), rows of one vector, one row
+SMALL_SHAPES = [((40, 30), (1, 0)), ((9, 7, 5), (2, 0, 1)), ((5, 4, 3, 6), (3, 1, 0, 2)), ((3, 4, 2, 5, 6), (4, 2, 0, 3, 1)), ((2, 3, 2, 5, 4, 3), (5, 3, 1, 0, 4, 2)),
+                ((4, 5, 3), (0, 2, 1)), ((16, 4, 3, 5), (0, 3, 2, 1)), ((6, 3, 4, 2, 5), (0, 4, 2, 1, 3)), ((513,), (0,))]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", range(8), ids=[wl.DTYPE_NAME[d] for d in range(8)])
+def test_small_problems_with_packed_parameters(dtype):
+    """Every number of indices and every epilogue through the row and the gather kernel of small problems, next to those whose
+    parameters are not packed: as created, with the hints and the dealing of tiles that only the unpacked form has."""
+    import torch
+    dev = torch.device("cuda:0")
+    stream = torch.cuda.current_stream().cuda_stream
+    cplx = wl.COMPONENTS[dtype] == 2
+    ran = 0
+    for shape, (sizes, perm) in enumerate(SMALL_SHAPES):
+        n = int(np.prod(sizes))
+        A = wl.uniform_tensor(dtype, n, 9000 + shape, "a")
+        B0 = wl.uniform_tensor(dtype, n, 9100 + shape, "b")
+        dA = torch.from_numpy(A).to(dev)
+        for alpha, beta in ((1.0, 0.0), (0.5 + 0.25j if cplx else 1.5, 0.0), (0.5 - 0.25j if cplx else 0.75, 1.0 + 0.5j if cplx else -1.25)):
+            want = oracle.transpose(dtype, sizes, perm, alpha, beta, A, B0.copy(), 4)
+            plan = ttc.ttc_plan_create_ex(dtype, len(sizes), sizes, perm, None, None, alpha, beta)
+            try:
+                for k in range(ttc.ttc_plan_candidate_count(plan)):
+                    ttc.ttc_plan_select_candidate(plan, k)
+                    if ttc.kernel_family(ttc.ttc_plan_get_info(plan)) not in ("rows", "gather"):
+                        continue
+                    for packed in (True, False):
+                        if not packed:
+                            ttc.ttc_plan_set_streaming(plan, 1, 1)
+                            ttc.ttc_plan_set_tile_mapping(plan, 2)
+                        dB = torch.from_numpy(B0).to(dev)
+                        ttc.ttc_execute(plan, dA.data_ptr(), dB.data_ptr(), stream)
+                        got = dB.cpu().numpy()
+                        allowed = 0.0 if complex(alpha) == 1 and complex(beta) == 0 else np.spacing(np.abs(want).max())
+                        assert np.abs(got - want).max() <= allowed, (sizes, perm, alpha, beta, k, packed)
+                        ran += 1
+            finally:
+                ttc.ttc_plan_destroy(plan)
+    assert ran >= 50
