@@ -1501,6 +1501,10 @@ static double line_cost(const Problem& P, const Candidate& C)
     const double run_a = std::min<double>(m.ta, cols) * P.eb_a;
     const double split = split_a ? (double)kLineBytes / run_a : 0.0;
     const double pad_cols = std::log((double)ceil_div(m.size_a0, m.ta) * m.ta / cols);
+    // Columns of B start inside lines unless B's first two indices are taken as one: such a problem's other candidates split
+    // lines as those of a skewed one do, and the kernel gains as much on them, whichever way its own tiles are cut.
+    bool odd = m.skewed != 0;
+    for (int k = 0; k < P.ndim; ++k) if (k != P.perm[0] && P.stride_b[k] * P.eb_b % kLineBytes != 0) odd = true;
     const bool one_precision = P.eb_a == P.eb_b && P.eb_a < 16;           // the others' first is then a micro-tile candidate, ranked by its own model
     const double line_rows = rows / S.line;                               // lines per column
     const double traffic = traffic_bytes(P);
@@ -1510,8 +1514,8 @@ static double line_cost(const Problem& P, const Candidate& C)
         int64_t loaded = segs * (int64_t)S.rows;                          // rows loaded per column: whole passes
         loaded -= S.rows - std::min<int64_t>(S.rows, ceil_div(m.size_p0 - last_row0, S.pass) * S.pass);
         if (m.skewed) loaded -= S.line / S.pass * S.pass;                 // the first tile needs no rows before it
-        e = -0.245 - (m.skewed ? 0.082 : 0.0) - (update ? 0.083 : 0.0);
-        if (one_precision) e += m.skewed ? -0.073 : (split_a || update ? -0.010 : 0.075);     // whole lines on both sides: the micro-tile kernel is as good
+        e = -0.245 - (odd ? 0.082 : 0.0) - (update ? 0.083 : 0.0);
+        if (one_precision) e += odd ? -0.073 : (split_a || update ? -0.010 : 0.075);     // whole lines on both sides: the micro-tile kernel is as good
         // Updates with whole lines on both sides, where neither kernel splits one: line against micro-tile kernel on one pair
         // of tensors, on pairs in rotation and on new ones, geometric means.  Tensors beyond the 256 MB of the last-level
         // cache (14 problems): 1.15, 1.01 and 1.30 times the micro-tile kernel's time (288 x 608 x 221 complex64 (1,0,2):
@@ -1529,6 +1533,10 @@ static double line_cost(const Problem& P, const Candidate& C)
         if (update && m.merged_a && P.size[0] * P.eb_a >= 512) e += 0.08 + (P.perm[1] == 0 ? 0.12 : 0.0);    // a tile that crosses the end of a row
                                                                           // reads and writes B in two places, and leaves a contiguous block
         e += 0.343 * std::log((double)loaded / rows) + 0.340 * pad_cols + 0.293 * std::log((double)segs * m.tb / rows) + 0.087 * split;
+        // Columns of 256 bytes before 128 in 4-byte elements, four lines before eight.  With `odd` above, over 120 problems of 16 to
+        // 500 MB: 2.4 % off the geometric mean, 7 % where both ways of cutting exist, none slower by more than 2 % (408^3 fp32 reversed
+        // 149 -> 115 us, 300^3 fp64 102 -> 90, 408 x 200 x 408 fp32 with an update 91 -> 76, 360^3 fp64 -> fp32 138 -> 110).
+        if (m.skewed) e += (P.eb_a == 4 && m.ta == 64 ? -0.03 : 0.0) + (m.lines == 8 ? 0.02 : 0.0);
         if (m.skewed) e += 0.178 * 2.0 / (line_rows + 1.0);               // lines that no tile writes whole: a column's first and last
         if (m.size_p0 < S.line) e += 0.258;
         if (m.lines == 2) e += 0.10;
@@ -1583,6 +1591,9 @@ static double block_cost(const Problem& P, const Candidate& C)
     e += std::log(1.0 + std::pow(starts, 6.0)) / 6.0;
     const double tile_bytes = (double)m.rows * m.run_a * P.eb_a;
     if (tile_bytes > 8192.0) e += (large ? 0.044 : 0.085) * std::log2(tile_bytes / 8192.0);
+    // eight vectors of A and eight of B a lane: few wavefronts fit, which a short launch does not make up for (25 x 13 x 4 x 26 x 19 x 5
+    // fp32 reversed with an update 17.0 us, the line kernel 14.6)
+    if (!large && update && m.unroll == 8) e += 0.12;
     // lines that a run shares with another one, per line of the run
     e += (large ? 0.072 : 0.18) * (1.0 - sh.align[0] / 128.0) * 128.0 / sh.run[0];
     e += (large && update ? 0.106 : 0.34) * (1.0 - sh.align[1] / 128.0) * 128.0 / sh.run[1];
