@@ -293,6 +293,8 @@ constexpr int block_stores(int unroll, int eb_a, int eb_b) { return unroll * eb_
 // 96 x 80 x 70 fp32 (0,2,1) 3.3 -> 2.87.  From 2048 chunks of 4 KB on a launch is dealt to the XCDs in another way and
 // bound by memory: parameters go whole there, and where they do not fit (six indices, strides beyond 32 bits).  Four words (elements, chunks, per_xcd, rows), then per division two (the multiplier; divisor and shift), the
 // strides in A, and at an 8-byte boundary the scalars that the epilogue reads.
+// The line kernel's MicroArgs are packed the same way: a word of places and flags, the first two divisions of the tile id, the
+// third index's steps, the extents, where columns lie in B and rows in A, and (MERGED) how a merged index is taken apart.
 struct SmallArgs { uint32_t w[20]; };
 constexpr int kSmallMaxDim = 5;
 constexpr int64_t kSmallMaxElements = int64_t(1) << 26;       // divisors leave five bits of their word to the shift

@@ -612,9 +612,8 @@ inline hipError_t launch_micro(const Candidate& c, const void* A, void* B, hipSt
 // before the barrier, beside the loads of A.  One tile per workgroup.
 // ---------------------------------------------------------------------------------
 template <typename TA, typename TB, int MODE, int COLS, int LINES>
-__global__ __launch_bounds__(kLineThreads) void line_kernel(const MicroArgs args_by_value, const TA* __restrict__ A, TB* __restrict__ B)
+__device__ __forceinline__ void line_tile_move(const MicroArgs& p, uint32_t tile, const TA* __restrict__ A, TB* __restrict__ B)
 {
-    const MicroArgs& p = *reinterpret_cast<const MicroArgs*>((const void*)__builtin_amdgcn_kernarg_segment_ptr());
     constexpr LineShape S = line_shape(COLS, LINES, (int)sizeof(TA), (int)sizeof(TB));
     static_assert(line_shape_ok(COLS, LINES, (int)sizeof(TA), (int)sizeof(TB)), "no such tile");
     constexpr int VA = S.va, VB = S.vb, L = S.line, U = S.passes;
@@ -625,105 +624,122 @@ __global__ __launch_bounds__(kLineThreads) void line_kernel(const MicroArgs args
     const Epilogue<TA, TB, MODE> epi(p.alpha, p.beta);
     const uint32_t tid = threadIdx.x;
     const int32_t rows = (int32_t)m.size_p0;
+    const LineTile t = line_tile(p, S, tile);
+    auto run = [&](auto stream_a, auto stream_b) {
+        constexpr bool NTA = decltype(stream_a)::value, NTB = decltype(stream_b)::value;
+        union Vec { Pack<TA, VA> p; uint32_t w[4]; };
+        Vec in[U];
+        const unsigned char* At = reinterpret_cast<const unsigned char*>(A + t.a);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const LineLoad x = line_load(m, S, t, tid, u);
+            if (x.needed) in[u].p = load_pack<TA, VA, NTA>(At, (micro_row_a(m, x.row) + (int64_t)x.start) * (int64_t)sizeof(TA));
+        }
+        // the lane's columns: where row 0 of each lies in B, and at which place of a line
+        unsigned char* to[G];
+        int32_t y0[G];
+        bool mine[G];
+        Pack<TB, VB> old[G][N];
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            const int32_t c = line_column(S, tid, g);
+            mine[g] = c < t.cols;
+            TB* col = B + (t.b + micro_col_b(m, t.col0 + (uint32_t)(mine[g] ? c : 0)));
+            const int32_t phase = (int32_t)((reinterpret_cast<uintptr_t>(col) & (kLineBytes - 1)) / sizeof(TB));
+            y0[g] = line_row(m, S, t, phase, tid);
+            to[g] = reinterpret_cast<unsigned char*>(col);
+            if (MODE == TTC_EPI_AXPBY) {
+#pragma unroll
+                for (int i = 0; i < N; ++i) {               // a vector that is not whole is loaded from the column's edge
+                    const int32_t y = y0[g] + i * S.groups * L, top = rows - VB;
+                    old[g][i] = load_pack<TB, VB, NTB>(to[g], (int64_t)(y < 0 ? 0 : (y > top ? top : y)) * (int64_t)sizeof(TB));
+                }
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const LineLoad x = line_load(m, S, t, tid, u);
+            if (!x.needed || x.col >= t.cols) continue;
+            TA* dst = lds + x.lds_row * S.pitch + x.start;
+            if (x.start == x.col) {
+                typedef uint32_t Half __attribute__((ext_vector_type(2)));
+                typedef uint32_t Quad __attribute__((ext_vector_type(4)));
+                if (sizeof(TA) == 4) {                     // rows start on 8-byte boundaries
+                    Half* h = reinterpret_cast<Half*>(dst);
+                    h[0] = Half{in[u].w[0], in[u].w[1]};
+                    h[1] = Half{in[u].w[2], in[u].w[3]};
+                } else {
+                    *reinterpret_cast<Quad*>(dst) = Quad{in[u].w[0], in[u].w[1], in[u].w[2], in[u].w[3]};
+                }
+            } else {                                       // moved back: what lies before the tile belongs to another one
+#pragma unroll
+                for (int j = 0; j < VA; ++j)
+                    if (x.start + j >= 0) dst[j] = in[u].p.v[j];
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            if (!mine[g]) continue;
+            const TA* src = lds + (y0[g] - t.row0) * S.pitch + line_column(S, tid, g);
+#pragma unroll
+            for (int i = 0; i < N; ++i) {
+                if (line_last(m, S, tid, i)) continue;
+                const int32_t y = y0[g] + i * S.groups * L;
+                TA a[VB];
+#pragma unroll
+                for (int j = 0; j < VB; ++j) a[j] = src[(i * S.groups * L + j) * S.pitch];
+                const int64_t at = (int64_t)y * (int64_t)sizeof(TB);
+                if (y >= 0 && y + VB <= rows) {
+                    Pack<TB, VB> out;
+#pragma unroll
+                    for (int j = 0; j < VB; ++j) {
+                        TB b_old = TB();
+                        if (MODE == TTC_EPI_AXPBY) b_old = old[g][i].v[j];
+                        out.v[j] = epi(a[j], b_old);
+                    }
+                    store_pack<TB, VB, NTB>(to[g], at, out);
+                } else {
+                    // The first and the last vector of a column: element by element.  What B held was loaded from
+                    // the column's edge: row y + j is element j + (y - edge) of that vector.  (Loads here, one
+                    // waiting for the other, made 85^4 fp32 (3,0,2,1) with an update 40 % slower.)
+                    const int32_t shift = y < 0 ? y : y - (rows - VB);
+#pragma unroll
+                    for (int j = 0; j < VB; ++j) {
+                        TB b_old = TB();
+                        if (MODE == TTC_EPI_AXPBY) {
+#pragma unroll
+                            for (int e = 0; e < VB; ++e) if (e == j + shift) b_old = old[g][i].v[e];
+                        }
+                        if (y + j >= 0 && y + j < rows) reinterpret_cast<TB*>(to[g] + at)[j] = epi(a[j], b_old);
+                    }
+                }
+            }
+        }
+    };
+    if (p.nt_a) { if (p.nt_b) run(std::true_type(), std::true_type()); else run(std::true_type(), std::false_type()); }
+    else        { if (p.nt_b) run(std::false_type(), std::true_type()); else run(std::false_type(), std::false_type()); }
+}
+
+template <typename TA, typename TB, int MODE, int COLS, int LINES>
+__global__ __launch_bounds__(kLineThreads) void line_kernel(const MicroArgs args_by_value, const TA* __restrict__ A, TB* __restrict__ B)
+{
+    const MicroArgs& p = *reinterpret_cast<const MicroArgs*>((const void*)__builtin_amdgcn_kernarg_segment_ptr());
     const TileSeq seq = tile_sequence(p, blockIdx.x);
     for (uint32_t q = seq.first; q < seq.end; q += seq.step) {
-        const LineTile t = line_tile(p, S, tile_of(seq, q));
-        auto run = [&](auto stream_a, auto stream_b) {
-            constexpr bool NTA = decltype(stream_a)::value, NTB = decltype(stream_b)::value;
-            union Vec { Pack<TA, VA> p; uint32_t w[4]; };
-            Vec in[U];
-            const unsigned char* At = reinterpret_cast<const unsigned char*>(A + t.a);
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const LineLoad x = line_load(m, S, t, tid, u);
-                if (x.needed) in[u].p = load_pack<TA, VA, NTA>(At, (micro_row_a(m, x.row) + (int64_t)x.start) * (int64_t)sizeof(TA));
-            }
-            // the lane's columns: where row 0 of each lies in B, and at which place of a line
-            unsigned char* to[G];
-            int32_t y0[G];
-            bool mine[G];
-            Pack<TB, VB> old[G][N];
-#pragma unroll
-            for (int g = 0; g < G; ++g) {
-                const int32_t c = line_column(S, tid, g);
-                mine[g] = c < t.cols;
-                TB* col = B + (t.b + micro_col_b(m, t.col0 + (uint32_t)(mine[g] ? c : 0)));
-                const int32_t phase = (int32_t)((reinterpret_cast<uintptr_t>(col) & (kLineBytes - 1)) / sizeof(TB));
-                y0[g] = line_row(m, S, t, phase, tid);
-                to[g] = reinterpret_cast<unsigned char*>(col);
-                if (MODE == TTC_EPI_AXPBY) {
-#pragma unroll
-                    for (int i = 0; i < N; ++i) {               // a vector that is not whole is loaded from the column's edge
-                        const int32_t y = y0[g] + i * S.groups * L, top = rows - VB;
-                        old[g][i] = load_pack<TB, VB, NTB>(to[g], (int64_t)(y < 0 ? 0 : (y > top ? top : y)) * (int64_t)sizeof(TB));
-                    }
-                }
-            }
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const LineLoad x = line_load(m, S, t, tid, u);
-                if (!x.needed || x.col >= t.cols) continue;
-                TA* dst = lds + x.lds_row * S.pitch + x.start;
-                if (x.start == x.col) {
-                    typedef uint32_t Half __attribute__((ext_vector_type(2)));
-                    typedef uint32_t Quad __attribute__((ext_vector_type(4)));
-                    if (sizeof(TA) == 4) {                     // rows start on 8-byte boundaries
-                        Half* h = reinterpret_cast<Half*>(dst);
-                        h[0] = Half{in[u].w[0], in[u].w[1]};
-                        h[1] = Half{in[u].w[2], in[u].w[3]};
-                    } else {
-                        *reinterpret_cast<Quad*>(dst) = Quad{in[u].w[0], in[u].w[1], in[u].w[2], in[u].w[3]};
-                    }
-                } else {                                       // moved back: what lies before the tile belongs to another one
-#pragma unroll
-                    for (int j = 0; j < VA; ++j)
-                        if (x.start + j >= 0) dst[j] = in[u].p.v[j];
-                }
-            }
-            __syncthreads();
-#pragma unroll
-            for (int g = 0; g < G; ++g) {
-                if (!mine[g]) continue;
-                const TA* src = lds + (y0[g] - t.row0) * S.pitch + line_column(S, tid, g);
-#pragma unroll
-                for (int i = 0; i < N; ++i) {
-                    if (line_last(m, S, tid, i)) continue;
-                    const int32_t y = y0[g] + i * S.groups * L;
-                    TA a[VB];
-#pragma unroll
-                    for (int j = 0; j < VB; ++j) a[j] = src[(i * S.groups * L + j) * S.pitch];
-                    const int64_t at = (int64_t)y * (int64_t)sizeof(TB);
-                    if (y >= 0 && y + VB <= rows) {
-                        Pack<TB, VB> out;
-#pragma unroll
-                        for (int j = 0; j < VB; ++j) {
-                            TB b_old = TB();
-                            if (MODE == TTC_EPI_AXPBY) b_old = old[g][i].v[j];
-                            out.v[j] = epi(a[j], b_old);
-                        }
-                        store_pack<TB, VB, NTB>(to[g], at, out);
-                    } else {
-                        // The first and the last vector of a column: element by element.  What B held was loaded from
-                        // the column's edge: row y + j is element j + (y - edge) of that vector.  (Loads here, one
-                        // waiting for the other, made 85^4 fp32 (3,0,2,1) with an update 40 % slower.)
-                        const int32_t shift = y < 0 ? y : y - (rows - VB);
-#pragma unroll
-                        for (int j = 0; j < VB; ++j) {
-                            TB b_old = TB();
-                            if (MODE == TTC_EPI_AXPBY) {
-#pragma unroll
-                                for (int e = 0; e < VB; ++e) if (e == j + shift) b_old = old[g][i].v[e];
-                            }
-                            if (y + j >= 0 && y + j < rows) reinterpret_cast<TB*>(to[g] + at)[j] = epi(a[j], b_old);
-                        }
-                    }
-                }
-            }
-        };
-        if (p.nt_a) { if (p.nt_b) run(std::true_type(), std::true_type()); else run(std::true_type(), std::false_type()); }
-        else        { if (p.nt_b) run(std::false_type(), std::true_type()); else run(std::false_type(), std::false_type()); }
+        line_tile_move<TA, TB, MODE, COLS, LINES>(p, tile_of(seq, q), A, B);
         __syncthreads();                                       // the tile buffer is refilled by the next tile
     }
+}
+
+// The same for small problems with its arguments packed (SmallArgs); A is not streamed.
+template <typename TA, typename TB, int MODE, int COLS, int LINES, bool MERGED>
+__global__ __launch_bounds__(kLineThreads) void line_small_kernel(const SmallArgs args_by_value, const TA* __restrict__ A, TB* __restrict__ B)
+{
+    const SmallArgs& s = *reinterpret_cast<const SmallArgs*>((const void*)__builtin_amdgcn_kernarg_segment_ptr());
+    constexpr LineShape S = line_shape(COLS, LINES, (int)sizeof(TA), (int)sizeof(TB));
+    const MicroArgs p = small_line_unpack<MODE, IsComplex<TA>::value, MERGED>(s, COLS, S);
+    line_tile_move<TA, TB, MODE, COLS, LINES>(p, blockIdx.x, A, B);
 }
 
 template <typename TA, typename TB, int MODE, int COLS, int LINES>
@@ -741,6 +757,17 @@ inline hipError_t launch_line_shape(const Candidate& c, const void* A, void* B, 
         const TA* a = static_cast<const TA*>(A);
         TB* b = static_cast<TB*>(B);
         MicroArgs ready = micro_args(c);
+        const int packed = small_line(ready, MODE, IsComplex<TA>::value);
+        if (packed) {
+            SmallArgs small = small_line_pack(ready, MODE, IsComplex<TA>::value);
+            void* args[] = {&small, &a, &b};
+            const void* small_fn = nullptr;
+            if constexpr (small_line_fits(false, MODE, IsComplex<TA>::value))
+                if (packed == 1) small_fn = reinterpret_cast<const void*>(&line_small_kernel<TA, TB, MODE, COLS, LINES, false>);
+            if constexpr (small_line_fits(true, MODE, IsComplex<TA>::value))
+                if (packed == 2) small_fn = reinterpret_cast<const void*>(&line_small_kernel<TA, TB, MODE, COLS, LINES, true>);
+            if (small_fn) return hipLaunchKernel(small_fn, dim3(kp.num_tiles), dim3(kLineThreads), args, 0, stream);
+        }
         void* args[] = {&ready, &a, &b};
         return hipLaunchKernel(fn, dim3(kp.num_tiles), dim3(kLineThreads), args, 0, stream);
     }

@@ -2570,7 +2570,8 @@ static int emulate_micro(const ttc::Problem& P, const ttc::Candidate& C, int64_t
 static int emulate_lines(const ttc::Problem& P, const ttc::Candidate& C, int phase0, int64_t* b_from_a)
 {
     using namespace ttc;
-    const MicroArgs p = micro_args(C);
+    const MicroArgs whole = micro_args(C);
+    MicroArgs p = whole;
     const MicroParams& m = p.micro;
     const int p0 = P.perm[0], p1 = P.ndim >= 2 ? P.perm[1] : -1, a1 = 1;
     if (p0 == 0 || P.ndim < 2 || !line_shape_ok(m.ta, m.lines, P.eb_a, P.eb_b)) return TTC_ERR_INTERNAL;
@@ -2587,6 +2588,15 @@ static int emulate_lines(const ttc::Problem& P, const ttc::Candidate& C, int pha
         m.col_b_in != P.stride_b[0] || m.col_b_out != (m.merged_a ? P.stride_b[a1] : 0) ||
         m.row_a_in != P.stride_a[p0] || m.row_a_out != (m.merged_b ? P.stride_a[p1] : 0))
         return TTC_ERR_INTERNAL;
+    const bool cplx = P.kind_a >= kKindC64;
+    const int packed = small_line(whole, P.epilogue, cplx);
+    if (packed) {                                              // as the kernel of small problems sees them
+        const SmallArgs small = small_line_pack(whole, P.epilogue, cplx);
+        p = packed == 2 ? (cplx ? small_line_unpack<TTC_EPI_COPY, true, true>(small, m.ta, S) : small_line_unpack<TTC_EPI_COPY, false, true>(small, m.ta, S))
+                        : (cplx ? small_line_unpack<TTC_EPI_COPY, true, false>(small, m.ta, S) : small_line_unpack<TTC_EPI_COPY, false, false>(small, m.ta, S));
+        p.num_tiles = p.grid = whole.num_tiles;
+        if (p.nt_b != whole.nt_b || m.tb != whole.micro.tb || m.skewed != whole.micro.skewed) return TTC_ERR_INTERNAL;
+    }
     for (int64_t i = 0; i < P.span_b; ++i) b_from_a[i] = -1;
     auto inside = [&](int64_t off, const int64_t* stride, bool b_side) {
         if (off < 0) return false;

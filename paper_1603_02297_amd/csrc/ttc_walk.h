@@ -598,6 +598,114 @@ TTC_HD void block_next(const BlockParams& m, int32_t* lds, int32_t* x0, int32_t*
     *lds += m.x_lds[2] - (int32_t)m.x_div[1].div * m.x_lds[1];
 }
 
+// The line kernel's arguments for small problems.
+constexpr int small_line_words(bool merged) { return merged ? 18 : 12; }
+constexpr bool small_line_fits(bool merged, int epilogue, bool is_complex) { return small_line_words(merged) + 2 * small_scalars(epilogue, is_complex) <= 20; }
+
+// 0: the arguments go unpacked; 1: packed; 2: packed with merged indices.
+inline int small_line(const MicroArgs& a, int epilogue, bool is_complex)
+{
+    const bool merged = a.micro.merged_a || a.micro.merged_b;
+    if (!small_line_fits(merged, epilogue, is_complex) || a.xcd_remap != 0 || a.nt_a != 0 || a.micro.size_a0 > INT32_MAX || a.micro.size_p0 > INT32_MAX) return 0;
+    int used = 0;                                              // places in the tile order that hold more than one tile, or a column or row
+    for (int i = 0; i < kMaxDim; ++i) {
+        if (a.cnt[i].div >= (1u << 27)) return 0;
+        if (a.cnt[i].div > 1 || i == a.col_pos || i == a.row_pos) ++used;
+        if (i != a.col_pos && i != a.row_pos && (a.step_a[i] > INT32_MAX || a.step_b[i] > INT32_MAX)) return 0;
+    }
+    const MicroParams& m = a.micro;
+    if (used > 3 || m.col_in_div.div >= (1u << 27) || m.row_in_div.div >= (1u << 27) || m.col_b_in > INT32_MAX || m.col_b_out > INT32_MAX ||
+        m.row_a_in > INT32_MAX || m.row_a_out > INT32_MAX) return 0;
+    return merged ? 2 : 1;
+}
+
+inline SmallArgs small_line_pack(const MicroArgs& a, int epilogue, bool is_complex)
+{
+    SmallArgs s = {};
+    const MicroParams& m = a.micro;
+    const bool merged = m.merged_a || m.merged_b;
+    uint32_t col = 0, row = 0, other = 3;
+    int place[3] = {-1, -1, -1}, n = 0;
+    for (int i = 0; i < kMaxDim; ++i) {
+        if (!(a.cnt[i].div > 1 || i == a.col_pos || i == a.row_pos)) continue;
+        if (i == a.col_pos) col = (uint32_t)n; else if (i == a.row_pos) row = (uint32_t)n; else other = (uint32_t)n;
+        place[n++] = i;
+    }
+    s.w[0] = col | row << 2 | other << 4 | (uint32_t)m.skewed << 6 | (uint32_t)a.nt_b << 7;
+    for (int k = 0; k < 2; ++k) {
+        s.w[1 + 2 * k] = a.cnt[place[k]].mul;
+        s.w[2 + 2 * k] = a.cnt[place[k]].div | a.cnt[place[k]].shift << 27;
+    }
+    if (other < 3) { s.w[5] = (uint32_t)a.step_a[place[other]]; s.w[6] = (uint32_t)a.step_b[place[other]]; }
+    s.w[7] = (uint32_t)m.size_a0; s.w[8] = (uint32_t)m.size_p0;
+    s.w[9] = (uint32_t)m.col_b_in; s.w[10] = (uint32_t)m.row_a_in;
+    if (merged) {
+        s.w[11] = m.merged_a ? m.col_in_div.mul : 0u;          // not merged: quotient 0
+        s.w[12] = m.merged_a ? m.col_in_div.div | m.col_in_div.shift << 27 : 31u << 27;
+        s.w[13] = (uint32_t)m.col_b_out;
+        s.w[14] = m.merged_b ? m.row_in_div.mul : 0u;
+        s.w[15] = m.merged_b ? m.row_in_div.div | m.row_in_div.shift << 27 : 31u << 27;
+        s.w[16] = (uint32_t)m.row_a_out;
+    }
+    int at = small_line_words(merged);
+    const int count = small_scalars(epilogue, is_complex), each = is_complex ? 2 : 1;
+    for (int k = 0; k < count; ++k) {
+        const double v = k < each ? a.alpha[k] : a.beta[k - each];
+        uint64_t bits;
+        __builtin_memcpy(&bits, &v, 8);
+        s.w[at++] = (uint32_t)bits;
+        s.w[at++] = (uint32_t)(bits >> 32);
+    }
+    return s;
+}
+
+// The arguments as the line kernel's index code reads them (a tile's number is its workgroup's: the fields of the dealing are not
+// set).
+template <int MODE, bool COMPLEX, bool MERGED>
+TTC_HD MicroArgs small_line_unpack(const SmallArgs& s, int cols, const LineShape& shape)
+{
+    MicroArgs a;
+    a.xcd_remap = 0; a.debug_stop = 0; a.nt_a = 0;
+    a.nt_b = (int32_t)(s.w[0] >> 7 & 1u);
+    a.col_pos = (int32_t)(s.w[0] & 3u);
+    a.row_pos = (int32_t)(s.w[0] >> 2 & 3u);
+    const int32_t other = (int32_t)(s.w[0] >> 4 & 3u);
+    MicroParams& m = a.micro;
+    m.skewed = (int32_t)(s.w[0] >> 6 & 1u);
+    m.lines = shape.lines;
+    m.ta = cols;
+    m.tb = (shape.lines - m.skewed) * shape.line;
+    m.size_a0 = (int64_t)s.w[7]; m.size_p0 = (int64_t)s.w[8];
+#pragma unroll
+    for (int i = 0; i < kMaxDim; ++i) {
+        FastDiv f = {0u, i == 2 ? 31u : 0u, i == 2 ? 0u : 1u};
+        if (i < 2) { f.mul = s.w[1 + 2 * i]; f.div = s.w[2 + 2 * i] & 0x7ffffffu; f.shift = s.w[2 + 2 * i] >> 27; }
+        a.cnt[i] = f;
+        a.step_a[i] = i > 2 ? 0 : i == a.col_pos ? (int64_t)cols : i == other ? (int64_t)s.w[5] : 0;
+        a.step_b[i] = i > 2 ? 0 : i == a.row_pos ? (int64_t)m.tb : i == other ? (int64_t)s.w[6] : 0;
+    }
+    m.col_b_in = (int64_t)s.w[9]; m.row_a_in = (int64_t)s.w[10];
+    if (MERGED) {
+        m.col_in_div = FastDiv{s.w[11], s.w[12] >> 27, s.w[12] & 0x7ffffffu};
+        m.col_b_out = (int64_t)s.w[13];
+        m.row_in_div = FastDiv{s.w[14], s.w[15] >> 27, s.w[15] & 0x7ffffffu};
+        m.row_a_out = (int64_t)s.w[16];
+    } else {
+        m.col_in_div = m.row_in_div = FastDiv{0u, 31u, 0u};
+        m.col_b_out = m.row_a_out = 0;
+    }
+    a.alpha[0] = a.alpha[1] = a.beta[0] = a.beta[1] = 0.0;
+    constexpr int kCount = small_scalars(MODE, COMPLEX), kEach = COMPLEX ? 2 : 1, kAt = small_line_words(MERGED);
+#pragma unroll
+    for (int k = 0; k < kCount; ++k) {
+        const uint64_t bits = (uint64_t)s.w[kAt + 2 * k] | (uint64_t)s.w[kAt + 2 * k + 1] << 32;
+        double v;
+        __builtin_memcpy(&v, &bits, 8);
+        if (k < kEach) a.alpha[k] = v; else a.beta[k - kEach] = v;
+    }
+    return a;
+}
+
 // ---- lane entry ------------------------------------------------------------------------------
 // Offsets are in BYTES.  A walk has three element sizes: of the tensor it follows (g), of B in
 // the direct kernel (g2), and of the LDS tile, which holds elements of A (l).
