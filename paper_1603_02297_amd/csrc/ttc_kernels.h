@@ -732,14 +732,22 @@ __global__ __launch_bounds__(kLineThreads) void line_kernel(const MicroArgs args
     }
 }
 
-// The same for small problems with its arguments packed (SmallArgs); A is not streamed.
-template <typename TA, typename TB, int MODE, int COLS, int LINES, bool MERGED>
+// The same with its arguments packed (SmallArgs), one tile per workgroup: what nearly all launches take.  Not DEALT, for fewer than
+// 2048 tiles: a workgroup's number is its tile's (1024 x 1024 fp32 2.77 us, with the dealing 3.04; 1680 x 289 complex64 with an
+// update 4.26 and 5.18).
+template <typename TA, typename TB, int MODE, int COLS, int LINES, bool MERGED, bool DEALT>
 __global__ __launch_bounds__(kLineThreads) void line_small_kernel(const SmallArgs args_by_value, const TA* __restrict__ A, TB* __restrict__ B)
 {
     const SmallArgs& s = *reinterpret_cast<const SmallArgs*>((const void*)__builtin_amdgcn_kernarg_segment_ptr());
     constexpr LineShape S = line_shape(COLS, LINES, (int)sizeof(TA), (int)sizeof(TB));
-    const MicroArgs p = small_line_unpack<MODE, IsComplex<TA>::value, MERGED>(s, COLS, S);
-    line_tile_move<TA, TB, MODE, COLS, LINES>(p, blockIdx.x, A, B);
+    uint32_t tile = blockIdx.x;
+    if (DEALT) {
+        const SmallDeal deal = small_line_deal(s, MERGED);
+        tile = rows_block(deal, tile);
+        if (tile >= deal.blocks) return;
+    }
+    const MicroArgs p = small_line_unpack<MODE, IsComplex<TA>::value, MERGED, DEALT>(s, COLS, S);
+    line_tile_move<TA, TB, MODE, COLS, LINES>(p, tile, A, B);
 }
 
 template <typename TA, typename TB, int MODE, int COLS, int LINES>
@@ -762,11 +770,15 @@ inline hipError_t launch_line_shape(const Candidate& c, const void* A, void* B, 
             SmallArgs small = small_line_pack(ready, MODE, IsComplex<TA>::value);
             void* args[] = {&small, &a, &b};
             const void* small_fn = nullptr;
+            const bool dealt = small_line_dealt(ready);
             if constexpr (small_line_fits(false, MODE, IsComplex<TA>::value))
-                if (packed == 1) small_fn = reinterpret_cast<const void*>(&line_small_kernel<TA, TB, MODE, COLS, LINES, false>);
+                if (packed == 1) small_fn = dealt ? reinterpret_cast<const void*>(&line_small_kernel<TA, TB, MODE, COLS, LINES, false, true>)
+                                                  : reinterpret_cast<const void*>(&line_small_kernel<TA, TB, MODE, COLS, LINES, false, false>);
             if constexpr (small_line_fits(true, MODE, IsComplex<TA>::value))
-                if (packed == 2) small_fn = reinterpret_cast<const void*>(&line_small_kernel<TA, TB, MODE, COLS, LINES, true>);
-            if (small_fn) return hipLaunchKernel(small_fn, dim3(kp.num_tiles), dim3(kLineThreads), args, 0, stream);
+                if (packed == 2) small_fn = dealt ? reinterpret_cast<const void*>(&line_small_kernel<TA, TB, MODE, COLS, LINES, true, true>)
+                                                  : reinterpret_cast<const void*>(&line_small_kernel<TA, TB, MODE, COLS, LINES, true, false>);
+            const int64_t grid = rows_grid(small_line_deal(small, packed == 2));
+            if (small_fn && launchable(grid, kLineThreads)) return hipLaunchKernel(small_fn, dim3((uint32_t)grid), dim3(kLineThreads), args, 0, stream);
         }
         void* args[] = {&ready, &a, &b};
         return hipLaunchKernel(fn, dim3(kp.num_tiles), dim3(kLineThreads), args, 0, stream);

@@ -2590,12 +2590,14 @@ static int emulate_lines(const ttc::Problem& P, const ttc::Candidate& C, int pha
         return TTC_ERR_INTERNAL;
     const bool cplx = P.kind_a >= kKindC64;
     const int packed = small_line(whole, P.epilogue, cplx);
+    SmallDeal deal = {0, 0};
     if (packed) {                                              // as the kernel of small problems sees them
         const SmallArgs small = small_line_pack(whole, P.epilogue, cplx);
-        p = packed == 2 ? (cplx ? small_line_unpack<TTC_EPI_COPY, true, true>(small, m.ta, S) : small_line_unpack<TTC_EPI_COPY, false, true>(small, m.ta, S))
-                        : (cplx ? small_line_unpack<TTC_EPI_COPY, true, false>(small, m.ta, S) : small_line_unpack<TTC_EPI_COPY, false, false>(small, m.ta, S));
+        p = packed == 2 ? (cplx ? small_line_unpack<TTC_EPI_COPY, true, true, true>(small, m.ta, S) : small_line_unpack<TTC_EPI_COPY, false, true, true>(small, m.ta, S))
+                        : (cplx ? small_line_unpack<TTC_EPI_COPY, true, false, true>(small, m.ta, S) : small_line_unpack<TTC_EPI_COPY, false, false, true>(small, m.ta, S));
+        deal = small_line_deal(small, packed == 2);
         p.num_tiles = p.grid = whole.num_tiles;
-        if (p.nt_b != whole.nt_b || m.tb != whole.micro.tb || m.skewed != whole.micro.skewed) return TTC_ERR_INTERNAL;
+        if (p.nt_a != whole.nt_a || deal.blocks != whole.num_tiles || deal.xcd_remap != whole.xcd_remap || p.nt_b != whole.nt_b || m.tb != whole.micro.tb || m.skewed != whole.micro.skewed) return TTC_ERR_INTERNAL;
     }
     for (int64_t i = 0; i < P.span_b; ++i) b_from_a[i] = -1;
     auto inside = [&](int64_t off, const int64_t* stride, bool b_side) {
@@ -2611,10 +2613,16 @@ static int emulate_lines(const ttc::Problem& P, const ttc::Candidate& C, int pha
     std::vector<int64_t> lds((size_t)(S.rows * S.pitch));
     std::vector<char> seen(p.num_tiles, 0);
     int64_t written = 0;
-    for (uint32_t wg = 0; wg < p.grid; ++wg) {
-        const TileSeq seq = tile_sequence(p, wg);
+    const int64_t grid = packed ? rows_grid(deal) : (int64_t)p.grid;
+    for (int64_t wg = 0; wg < grid; ++wg) {
+        TileSeq seq = {(uint32_t)wg, (uint32_t)wg + 1u, 1u, 0u, 0u, 0u};
+        if (packed) {
+            if (rows_block(deal, (uint32_t)wg) >= deal.blocks) continue;
+        } else {
+            seq = tile_sequence(p, (uint32_t)wg);
+        }
         for (uint32_t q = seq.first; q < seq.end; q += seq.step) {
-            const uint32_t tile = tile_of(seq, q);
+            const uint32_t tile = packed ? rows_block(deal, (uint32_t)wg) : tile_of(seq, q);
             if (tile >= p.num_tiles || seen[tile]) return TTC_ERR_INTERNAL;
             seen[tile] = 1;
             const LineTile t = line_tile(p, S, tile);

@@ -139,7 +139,7 @@ TTC_HD GatherPlace gather_next(const RowsParams& p, const GatherPlace& g, uint32
 
 // Which chunk workgroup `wg` of a row-kernel launch moves (p.blocks: none): consecutive chunks, which share a line of
 // B and lines of A, go to one XCD a few at a time, as with tiles.  The block kernel's tiles likewise.
-template <typename Params>       // RowsParams or BlockArgs
+template <typename Params>       // RowsParams, BlockArgs or SmallDeal
 TTC_HD uint32_t rows_block(const Params& p, uint32_t wg)
 {
     if (p.xcd_remap == 0) return wg;
@@ -598,7 +598,7 @@ TTC_HD void block_next(const BlockParams& m, int32_t* lds, int32_t* x0, int32_t*
     *lds += m.x_lds[2] - (int32_t)m.x_div[1].div * m.x_lds[1];
 }
 
-// The line kernel's arguments for small problems.
+// The line kernel's arguments, packed.
 constexpr int small_line_words(bool merged) { return merged ? 18 : 12; }
 constexpr bool small_line_fits(bool merged, int epilogue, bool is_complex) { return small_line_words(merged) + 2 * small_scalars(epilogue, is_complex) <= 20; }
 
@@ -606,7 +606,7 @@ constexpr bool small_line_fits(bool merged, int epilogue, bool is_complex) { ret
 inline int small_line(const MicroArgs& a, int epilogue, bool is_complex)
 {
     const bool merged = a.micro.merged_a || a.micro.merged_b;
-    if (!small_line_fits(merged, epilogue, is_complex) || a.xcd_remap != 0 || a.nt_a != 0 || a.micro.size_a0 > INT32_MAX || a.micro.size_p0 > INT32_MAX) return 0;
+    if (!small_line_fits(merged, epilogue, is_complex) || a.micro.size_a0 > INT32_MAX || a.micro.size_p0 > INT32_MAX) return 0;
     int used = 0;                                              // places in the tile order that hold more than one tile, or a column or row
     for (int i = 0; i < kMaxDim; ++i) {
         if (a.cnt[i].div >= (1u << 27)) return 0;
@@ -631,7 +631,7 @@ inline SmallArgs small_line_pack(const MicroArgs& a, int epilogue, bool is_compl
         if (i == a.col_pos) col = (uint32_t)n; else if (i == a.row_pos) row = (uint32_t)n; else other = (uint32_t)n;
         place[n++] = i;
     }
-    s.w[0] = col | row << 2 | other << 4 | (uint32_t)m.skewed << 6 | (uint32_t)a.nt_b << 7;
+    s.w[0] = col | row << 2 | other << 4 | (uint32_t)m.skewed << 6 | (uint32_t)a.nt_b << 7 | (uint32_t)a.nt_a << 8 | (uint32_t)a.xcd_remap << 9;
     for (int k = 0; k < 2; ++k) {
         s.w[1 + 2 * k] = a.cnt[place[k]].mul;
         s.w[2 + 2 * k] = a.cnt[place[k]].div | a.cnt[place[k]].shift << 27;
@@ -647,6 +647,7 @@ inline SmallArgs small_line_pack(const MicroArgs& a, int epilogue, bool is_compl
         s.w[15] = m.merged_b ? m.row_in_div.div | m.row_in_div.shift << 27 : 31u << 27;
         s.w[16] = (uint32_t)m.row_a_out;
     }
+    s.w[merged ? 17 : 11] = a.num_tiles;
     int at = small_line_words(merged);
     const int count = small_scalars(epilogue, is_complex), each = is_complex ? 2 : 1;
     for (int k = 0; k < count; ++k) {
@@ -659,13 +660,20 @@ inline SmallArgs small_line_pack(const MicroArgs& a, int epilogue, bool is_compl
     return s;
 }
 
-// The arguments as the line kernel's index code reads them (a tile's number is its workgroup's: the fields of the dealing are not
-// set).
-template <int MODE, bool COMPLEX, bool MERGED>
+inline bool small_line_dealt(const MicroArgs& a) { return a.xcd_remap != 0 || a.nt_a != 0; }
+
+// How its tiles are dealt: one workgroup each, as the row kernel's chunks.
+struct SmallDeal { int32_t xcd_remap; uint32_t blocks; };
+TTC_HD SmallDeal small_line_deal(const SmallArgs& s, bool merged) { return SmallDeal{(int32_t)(s.w[0] >> 9 & 15u), s.w[merged ? 17 : 11]}; }
+
+// The arguments as the line kernel's index code reads them (the fields of the dealing are not set).
+// DEALT: what a small problem does without: tiles dealt to the XCDs in chunks, A streamed.
+template <int MODE, bool COMPLEX, bool MERGED, bool DEALT>
 TTC_HD MicroArgs small_line_unpack(const SmallArgs& s, int cols, const LineShape& shape)
 {
     MicroArgs a;
-    a.xcd_remap = 0; a.debug_stop = 0; a.nt_a = 0;
+    a.xcd_remap = 0; a.debug_stop = 0;
+    a.nt_a = DEALT ? (int32_t)(s.w[0] >> 8 & 1u) : 0;
     a.nt_b = (int32_t)(s.w[0] >> 7 & 1u);
     a.col_pos = (int32_t)(s.w[0] & 3u);
     a.row_pos = (int32_t)(s.w[0] >> 2 & 3u);
