@@ -62,7 +62,7 @@ def parse():
     ap.add_argument("--problem", type=str, default="",
                     help="time this problem instead of the suite: dtype:sizes:perm[:alpha:beta], e.g. f32:85x85x85x85:3210:1:0 "
                          "(what profiles/ uses for shapes outside the suite; not a bench line)")
-    ap.add_argument("--force-class", type=str, default="", choices=("", "direct", "lds", "line", "rows", "gather", "micro"),
+    ap.add_argument("--force-class", type=str, default="", choices=("", "direct", "lds", "line", "rows", "gather", "micro", "block"),
                     help="run the best-ranked candidate of this kernel family instead of the stored or searched plan")
     ap.add_argument("--store-plans", type=str, default="",
                     help="append what the run selected for every case to this file (the format of --plan-cache)")

@@ -53,10 +53,10 @@ enum { TTC_KERNEL_DIRECT = 0 /* tiles, no staging: stride-1 index fixed */, TTC_
                                indices, or (unroll != 0) the line kernel: columns of A's direction by whole 128-byte lines of B */,
        TTC_KERNEL_ROWS = 2 /* B walked front to back: rows gathered from A (stride-1 index fixed), or (unroll == 0) single elements
                                (the gather kernel: small problems, any permutation) */,
-       TTC_KERNEL_MICRO = 3 /* tile over the two stride-1 indices only (each possibly merged with the index next to it in
-                               its tensor): 128-bit LDS accesses, XOR-swizzled rows, register transposes of 4x4 (2x2)
-                               blocks; one precision of 4- or 8-byte elements.  Or (merged == 4) the block kernel: a tile over
-                               the leading indices of both tensors, which may overlap; every type pair */ };
+       TTC_KERNEL_MICRO = 3 /* the micro-tile kernel: a tile over the two stride-1 indices only (each possibly merged with the index
+                               next to it in its tensor), 128-bit LDS accesses, XOR-swizzled rows, register transposes of 4x4
+                               (2x2) blocks, one precision of 4- or 8-byte elements; or (merged == 4) the block kernel: a tile
+                               over the leading indices of both tensors, which may overlap, every type pair */ };
 /* Epilogues chosen from alpha, beta. */
 enum { TTC_EPI_COPY = 0 /* alpha=1, beta=0 */, TTC_EPI_SCALE = 1 /* beta=0: B never read */, TTC_EPI_AXPBY = 2 };
 

@@ -19,7 +19,7 @@ TTC_OK = 0
  TTC_ERR_NOT_FOUND, TTC_ERR_IO) = range(1, 13)
 TTC_KERNEL_DIRECT, TTC_KERNEL_LDS, TTC_KERNEL_ROWS, TTC_KERNEL_MICRO = 0, 1, 2, 3
 TTC_EPI_COPY, TTC_EPI_SCALE, TTC_EPI_AXPBY = 0, 1, 2
-KERNEL_FAMILIES = ("direct", "lds", "line", "rows", "gather", "micro")     # lds: the box kernel that stages its tile
+KERNEL_FAMILIES = ("direct", "lds", "line", "rows", "gather", "micro", "block")     # lds: the box kernel that stages its tile
 
 EXPORTS = (
     "ttc_plan_create", "ttc_plan_create_ex", "ttc_execute", "ttc_plan_destroy", "ttc_last_status", "ttc_status_string",
@@ -30,14 +30,16 @@ EXPORTS = (
 
 
 def kernel_family(info: dict) -> str:
-    """Which kernel a plan (ttc_plan_get_info) runs, one of KERNEL_FAMILIES.  Two classes hold two kernels each, told
-    apart by `unroll`: the line kernel reports the class of the staged box kernel, the gather kernel that of the row
-    kernel."""
+    """Which kernel a plan (ttc_plan_get_info) runs, one of KERNEL_FAMILIES.  Three classes hold two kernels each,
+    told apart by `unroll` and `merged`: the line kernel reports the class of the staged box kernel, the gather kernel that of
+    the row kernel, the block kernel that of the micro-tile kernel."""
     if info["kernel_class"] == TTC_KERNEL_LDS:
         return "line" if info["unroll"] > 0 else "lds"
     if info["kernel_class"] == TTC_KERNEL_ROWS:
         return "rows" if info["unroll"] > 0 else "gather"
-    return {TTC_KERNEL_DIRECT: "direct", TTC_KERNEL_MICRO: "micro"}[info["kernel_class"]]
+    if info["kernel_class"] == TTC_KERNEL_MICRO:
+        return "block" if info["merged"] == 4 else "micro"
+    return {TTC_KERNEL_DIRECT: "direct"}[info["kernel_class"]]
 
 
 class ttc_plan_info_t(ctypes.Structure):

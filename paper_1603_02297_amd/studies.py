@@ -189,7 +189,7 @@ def micro_family(info):
     """1: the micro-tile kernel over single indices; 2: over two indices taken as one on a side; 3: the line kernel; 0: others."""
     if ttc.kernel_family(info) == "line":
         return 3
-    if ttc.kernel_family(info) != "micro" or info["merged"] == 4:          # 4: the block kernel, ranked with the box kernels'
+    if ttc.kernel_family(info) != "micro":
         return 0
     return 2 if info["merged"] else 1
 
@@ -474,7 +474,7 @@ def study_fit(out, dumps, ridge=0.05, sharpness=3.0, folds=8, family="box"):
             for line in fh:
                 d = json.loads(line)
                 if family == "micro":
-                    d["rows"] = [r for r in d["rows"] if ttc.kernel_family(r) == "micro" and r["merged"] != 4]
+                    d["rows"] = [r for r in d["rows"] if ttc.kernel_family(r) == "micro"]
                 else:
                     d["rows"] = [r for r in d["rows"] if ttc.kernel_family(r) in BOX]
                 if len(d["rows"]) >= 4:

@@ -26,7 +26,7 @@ def block_candidates(plan):
     for k in range(ttc.ttc_plan_candidate_count(plan)):
         ttc.ttc_plan_select_candidate(plan, k)
         info = ttc.ttc_plan_get_info(plan)
-        if info["kernel_class"] == ttc.TTC_KERNEL_MICRO and info["merged"] == 4:
+        if ttc.kernel_family(info) == "block":
             yield k, info
 
 

@@ -301,7 +301,7 @@ def test_random_problems_through_the_micro_tile_families():
             for k in range(ttc.ttc_plan_candidate_count(plan)):
                 ttc.ttc_plan_select_candidate(plan, k)
                 info = ttc.ttc_plan_get_info(plan)
-                if info["kernel_class"] != ttc.TTC_KERNEL_MICRO:
+                if ttc.kernel_family(info) != "micro":
                     continue
                 fam = 2 if info["merged"] else 1
                 if taken[fam] >= 3:

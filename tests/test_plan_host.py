@@ -237,7 +237,7 @@ def test_walks_of_every_micro_tile_candidate(dtype, sizes, perm):
     seen = 0
     for k in range(ttc.ttc_plan_candidate_count(p)):
         ttc.ttc_plan_select_candidate(p, k)
-        if ttc.ttc_plan_get_info(p)["kernel_class"] != ttc.TTC_KERNEL_MICRO:
+        if ttc.kernel_family(ttc.ttc_plan_get_info(p)) != "micro":
             continue
         seen += 1
         assert list(ttc.ttc_debug_emulate_map(p, len(want))) == want, (sizes, perm, k, ttc.ttc_plan_get_info(p))
@@ -256,7 +256,7 @@ def test_micro_tile_kernel_updates_every_element_of_a_ragged_tensor_once():
         seen = 0
         for k in range(ttc.ttc_plan_candidate_count(p)):
             ttc.ttc_plan_select_candidate(p, k)
-            if ttc.ttc_plan_get_info(p)["kernel_class"] != ttc.TTC_KERNEL_MICRO:
+            if ttc.kernel_family(ttc.ttc_plan_get_info(p)) != "micro":
                 continue
             seen += 1
             assert list(ttc.ttc_debug_emulate_map(p, len(want))) == want, (sizes, perm, k, ttc.ttc_plan_get_info(p))

@@ -54,8 +54,8 @@ def test_search_set_keeps_places_for_both_micro_tile_families():
 
 
 def test_every_kernel_has_a_family_of_its_own():
-    """The line and the gather kernel report another kernel's class: the studies, the benchmark and the smoke run tell
-    them apart by it, and nothing but box kernels enters the box model's fit and its ablation."""
+    """The line, the gather and the block kernel report another kernel's class: the studies, the benchmark and the smoke run
+    tell them apart by it, and nothing but box kernels enters the box model's fit and its ablation."""
     def families(dtype, sizes, perm):
         p = ttc.ttc_plan_create(dtype, len(sizes), sizes, perm, 1.0, 0.0)
         seen = {}
@@ -67,10 +67,13 @@ def test_every_kernel_has_a_family_of_its_own():
         return seen
 
     moved, fixed = families(ttc.TTC_F32, (70, 33, 45), (2, 0, 1)), families(ttc.TTC_F32, (96, 20, 31), (0, 2, 1))
-    assert set(moved) == {"lds", "line", "gather", "micro"} and set(fixed) == {"direct", "lds", "rows", "gather"}
+    assert set(moved) == {"lds", "line", "gather", "micro", "block"} and set(fixed) == {"direct", "lds", "rows", "gather"}
     assert len(moved["gather"]) == len(fixed["gather"]) == 1             # one candidate, whatever the problem
+    assert set(moved) | set(fixed) == set(ttc.KERNEL_FAMILIES)
+    assert {i["unroll"] for i in moved["block"]} <= {2, 4, 8} and {i["merged"] for i in moved["micro"]} <= {0, 1, 2, 3}
+    assert {st.micro_family(i) for i in moved["block"]} == {0}           # no micro-tile candidate of either kind
     assert {i["unroll"] for i in moved["line"]} <= {2, 4, 8} and {i["unroll"] for i in fixed["rows"]} <= {1, 2, 4, 8}
-    assert all(i["wg_per_cu"] == 0 for f in ("line", "gather", "micro") for i in moved[f])
+    assert all(i["wg_per_cu"] == 0 for f in ("line", "gather", "micro", "block") for i in moved[f])
     assert all(i["wg_per_cu"] > 0 for f in st.BOX for i in moved.get(f, []) + fixed.get(f, []))
     rows = [(i, 1.0 if f in st.BOX else 0.5) for f in moved for i in moved[f]]
     rows.sort(key=lambda r: r[0]["candidate_index"])
@@ -89,7 +92,7 @@ def test_micro_tile_features_mirror_the_library_model():
     for k in range(ttc.ttc_plan_candidate_count(p)):
         ttc.ttc_plan_select_candidate(p, k)
         info = ttc.ttc_plan_get_info(p)
-        if info["kernel_class"] != ttc.TTC_KERNEL_MICRO:
+        if ttc.kernel_family(info) != "micro":
             continue
         seen += 1
         assert st.micro_family(info) == (2 if info["merged"] else 1)
