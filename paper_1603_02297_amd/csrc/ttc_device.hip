@@ -253,16 +253,17 @@ static int tune_pairs(ttc_plan_t plan, int npairs, const void* const* A_list, vo
     // What is timed: the `cap` best-ranked candidates; a fifth of the places goes to the best-ranked micro-tile
     // candidates over single indices, and another fifth to those over merged indices, where the ranking would have
     // left them out (the families are ranked by separate models, each good at ordering its own family and only
-    // roughly calibrated against the others).  They take the places of the lowest-ranked others, never of the line
-    // kernel: where the first hundred were mostly micro-tile candidates, the best line candidate went although it was
+    // roughly calibrated against the others).  They take the places of the lowest-ranked others, never of the line or the
+    // block kernel: where the first hundred were mostly micro-tile candidates, the best line candidate went although it was
     // among the first ten of the ranking (a 5-D reversal of the 57-case benchmark: 95.8 % of the best of all with 100
-    // candidates, 100 % with 10).
+    // candidates, 100 % with 10), and 18 of the 28 block candidates among the first hundred of 7 x 56 x 3 x 64 x 40 complex64
+    // (2,3,1,0,4), from the eleventh of the ranking on.
     std::vector<int> chosen;
     for (int i = 0; i < cap; ++i) chosen.push_back(i);
     if (cap >= 10 && cap < total) {
         auto family = [&](int i) {
             const ttc::Candidate& c = plan->cands[i];
-            if (c.kernel_class == ttc::kKernelLines) return 3;
+            if (c.kernel_class == ttc::kKernelLines || c.kernel_class == ttc::kKernelBlock) return 3;
             if (c.kernel_class != TTC_KERNEL_MICRO) return 0;
             return (c.kp.micro.merged_a || c.kp.micro.merged_b) ? 2 : 1;
         };

@@ -161,7 +161,7 @@ def search_set(families, cap):
     """Ranks the library's search times when capped at `cap` candidates (the rule of ttc_plan_tune_pairs): the
     first `cap` of the ranking, a fifth of the places going to the best-ranked micro-tile candidates over single
     indices and another fifth to those over merged indices where the ranking would have left them out, instead of the
-    lowest-ranked candidates of the box, row and gather kernels.
+    lowest-ranked candidates of the box, row and gather kernels (the line and the block kernel's keep theirs).
     families: per candidate in rank order, micro_family()."""
     total = len(families)
     cap = min(cap, total)
@@ -186,8 +186,9 @@ def search_set(families, cap):
 
 
 def micro_family(info):
-    """1: the micro-tile kernel over single indices; 2: over two indices taken as one on a side; 3: the line kernel; 0: others."""
-    if ttc.kernel_family(info) == "line":
+    """1: the micro-tile kernel over single indices; 2: over two indices taken as one on a side; 3: the line and the block kernel;
+    0: others."""
+    if ttc.kernel_family(info) in ("line", "block"):
         return 3
     if ttc.kernel_family(info) != "micro":
         return 0
