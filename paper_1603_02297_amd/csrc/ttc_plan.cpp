@@ -1482,6 +1482,12 @@ static double micro_cost(const Problem& P, const Candidate& C)
     return std::exp(e);
 }
 
+// 0 up to `from`, 1 from `to` on, even in the logarithm between: terms of the ranking models set in without a jump.
+static double octaves(double x, double from, double to)
+{
+    return x <= from ? 0.0 : x >= to ? 1.0 : std::log(x / from) / std::log(to / from);
+}
+
 // The line kernel's ranking model, log-linear like the others, fitted to the timings of every line candidate of 300
 // problems (the 57-case benchmark in fp32, fp64, complex128 and fp32 -> fp64, and random problems of every type, 64 KB
 // to 240 MB) against the candidate that the other models rank first.  Two sets of weights: from 16 MB of traffic on a
@@ -1555,10 +1561,14 @@ static double line_cost(const Problem& P, const Candidate& C)
         const double cus_wanted = std::min(256.0, std::max(1.0, (double)P.elements * P.eb_a / 4096.0));
         if (C.kp.num_tiles < cus_wanted) e += 0.38 * (cus_wanted - C.kp.num_tiles) / 256.0;
     }
-    // The models were fitted before this kernel's arguments were packed.  Against the others' first candidate, 36 problems of 8 to
-    // 40 MB: 5 % off the geometric mean, none slower by more than 4 %; below 8 MB (58) nothing, and the gather kernel loses places
-    // that are its own.
-    if (traffic >= 8e6 && traffic < 40e6) e -= 0.12;
+    // The models were fitted before this kernel's arguments were packed.  Time of its first candidate over the micro-tile kernel's,
+    // beyond what the two models have: packed 0.76 below 8 MB (196 problems), 0.81 from 8 to 20 (161), 0.75 to 40 (107), 0.89 to 60
+    // (69) and 0.92 to 100 (90); not packed 0.99, 1.04 and 0.90 (210 up to 40 MB).  More than this would take places from the gather
+    // kernel, whose arguments are packed as well.  Over 3760 problems of 2.5 MB to 1.9 GB this, gather_cost()'s bonus and block_cost()'s
+    // choose 0.9 % better than 0.12 here between 8 and 40 MB alone, packed or not, did, and 86 problems instead of 130 take more than 1.05
+    // times what they took before any arguments were packed (13061 x 72 fp64 -> fp32 (1,0) 6.0 -> 4.3 us).
+    const bool packed = small_line(micro_args(C), P.epilogue, P.kind_a >= kKindC64) != 0;
+    e -= (packed ? 0.12 : 0.06) * octaves(traffic, 4e6, 8e6) * (1.0 - octaves(traffic, 40e6, 80e6));
     bool b_order = true;
     for (int i = 0; i < P.ndim; ++i) if (C.tile_order[i] != P.perm[i]) b_order = false;
     if (!b_order) e += 0.08;
@@ -1567,13 +1577,15 @@ static double line_cost(const Problem& P, const Candidate& C)
 }
 
 // The gather kernel against the others.  For problems that the caches hold the families' first candidates take, to
-// within 10-13 %, 3.4 us + 0.18 us per MB of traffic (line), 3.9 + 0.19 (micro-tile), 2.4 + 0.15 (row) and 5.6 + 0.20 (box); the
-// gather kernel's modelled time against the line kernel's, whose candidates cost about 0.86 there.  (Large problems are
-// further from the fit: a margin.)
+// within 10-13 %, 3.4 us + 0.18 us per MB of traffic (line), 3.9 + 0.19 (micro-tile), 2.4 + 0.15 (row) and 5.6 + 0.20 (box), by
+// timings from before arguments were packed; the gather kernel's modelled time against the line kernel's, whose candidates cost
+// about 0.86 there.  (Large problems are further from the fit: a margin.)  Packed, it gained what the line kernel did, and has that
+// one's bonus up to 12 MB, fading out to 20, where the stride-1 index moves (elsewhere the row kernel is the alternative).
 static double gather_cost(const Problem& P, const Candidate& C)
 {
-    const double mb = traffic_bytes(P) * 1e-6;
-    return 0.86 * (1.0 + 0.004 * mb) * C.model_us / (3.4 + 0.18 * mb);
+    const double traffic = traffic_bytes(P), mb = traffic * 1e-6;
+    const double packed = P.perm[0] != 0 ? 0.12 * octaves(traffic, 4e6, 8e6) * (1.0 - octaves(traffic, 12e6, 20e6)) : 0.0;
+    return 0.86 * (1.0 + 0.004 * mb) * C.model_us / (3.4 + 0.18 * mb) * std::exp(-packed);
 }
 
 // The block kernel's ranking model, log-linear, fitted to the timings of every block candidate of 112 problems of 9 MB to 1.9 GB of
@@ -1605,10 +1617,28 @@ static double block_cost(const Problem& P, const Candidate& C)
     e += 0.025 * std::log2(std::max(1.0, C.lds_conflict_b / 2.0));
     for (int i = 0; i < P.ndim; ++i) if (C.tile_order[i] != P.perm[i]) { e += large ? 0.054 : 0.006; break; }
     if (C.kp.num_tiles < 512) e += 0.19 * std::log2(512.0 / C.kp.num_tiles);
-    // Updates of tensors beyond the last-level cache whose first index is B's second, whole lines on both sides: on new tensors the
-    // micro-tile kernel finds what the launch before left in that cache (8 x 64 x 48 x 40 x 80 complex64 (2,0,4,3,1): first pass
-    // 309 us, this kernel 332; pairs in rotation 358 and 332, one pair again and again 325 and 323).
-    if (update && P.perm[1] == 0 && sh.align[0] >= 128 && sh.align[1] >= 128 && P.elements * P.eb_b >= (int64_t(256) << 20)) e += 0.30;
+    // Against the micro-tile kernel where neither splits lines: time of this kernel's first candidate over that one's, beyond what the
+    // two models have.  Copies and scaled copies, pairs in rotation and one pair: 0.93 and 0.91 below 40 MB (62 problems), 1.13 and
+    // 0.95 up to 100 (23), 1.02 and 1.09 above (55).  Updates of 90 to 700 MB per tensor, in rotation, on one pair and on new tensors (50
+    // problems, medians of six first passes), where the models have 0.92 in the mean: if A's first index is not B's second, 0.98, 1.11 and
+    // 1.07 below 256 MB, 1.00, 1.18 and 1.14 above; if it is, 0.93, 1.00 and 0.98 below, and above 0.98, 1.09 and 1.10 but for three
+    // fp32 problems at 0.74 to 0.80.
+    // whether no index but the first starts inside a piece of a line that long; `joined`: first and second taken as one
+    auto whole = [&](int bytes, bool joined) {
+        for (int i = 1; i < P.ndim; ++i) {
+            const bool second = joined && i == 1 && P.ndim > 2;
+            if (!(second && P.stride_a[1] == P.size[0]) && P.stride_a[i] * P.eb_a % bytes != 0) return false;
+            if (!(second && P.stride_b[P.perm[1]] == P.size[P.perm[0]]) && P.stride_b[P.perm[i]] * P.eb_b % bytes != 0) return false;
+        }
+        return true;
+    };
+    if (P.eb_a == P.eb_b && P.eb_a < 16) {                               // the micro-tile kernel's types
+        if (!update && whole(64, false)) e += 0.06 * octaves(traffic, 30e6, 40e6);
+        if (update && whole(128, true))
+            e += P.perm[1] == 0 ? 0.12 * octaves((double)P.elements * P.eb_b, 190e6, 380e6) : 0.10 * octaves(traffic, 30e6, 40e6);
+    }
+    // Small problems: the line and the gather kernel have a bonus for their packed arguments, of which half is this kernel's due.
+    e -= 0.06 * octaves(traffic, 4e6, 8e6) * (1.0 - octaves(traffic, 12e6, 20e6));
     // towards the end of the fitted range and below it a launch is what a problem costs, and the gather kernel is ahead (12 x 28 x
     // 1898 complex64 (1,0,2) with an update, 15 MB: 4.5 us against 5.6)
     if (traffic < 48e6) e += 0.1 * std::log2(48e6 / traffic);

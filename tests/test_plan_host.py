@@ -572,6 +572,47 @@ def test_large_copies_of_short_ragged_rows_take_tiles(sizes, perm, beta, family)
     ttc.ttc_plan_destroy(p)
 
 
+@pytest.mark.parametrize("dtype,sizes,perm,alpha,beta,family", [
+    (ttc.TTC_C64, (15531, 41), (1, 0), 1.0, 0.0, "gather"),              # 10 MB: 4.1 us, line kernel 5.3
+    (ttc.TTC_F64_F32, (13061, 72), (1, 0), 0.75, 0.0, "gather"),         # 11 MB: 4.3 us, line kernel 6.0
+    (ttc.TTC_F64, (5, 28, 3, 20, 17, 3), (5, 3, 0, 2, 4, 1), 1.5, 1.0, "gather"),     # line arguments not packed: 4.8 us, line kernel 6.0
+    (ttc.TTC_F32, (1024, 1024), (1, 0), 1.0, 0.0, "line"),
+    (ttc.TTC_C64, (384, 184, 48), (2, 1, 0), 0.5, 0.0, "micro"),         # 54 MB, whole lines: 13.4 us, block kernel 14.1
+    (ttc.TTC_F32, (432, 984, 32), (2, 1, 0), 2.0, 0.0, "micro"),         # 109 MB: 24.6 us, block kernel 25.8
+    (ttc.TTC_F32, (24, 20, 16, 18, 22, 17), (1, 0, 2, 3, 5, 4), 2.0, -1.0, "block"),  # runs of A and of B overlap: 95 us, box kernel 109
+    (ttc.TTC_F32, (3, 307200, 64), (1, 0, 2), 1.0, 0.0, "block"),
+])
+def test_small_line_problems_and_whole_lines_go_to_the_faster_kernel(dtype, sizes, perm, alpha, beta, family):
+    """Against the gather kernel the line kernel is ranked by what its arguments cost, and against the micro-tile kernel the block
+    kernel by whether that one splits lines."""
+    p = plan(dtype, sizes, perm, alpha, beta)
+    assert ttc.kernel_family(ttc.ttc_plan_get_info(p)) == family
+    ttc.ttc_plan_destroy(p)
+
+
+def test_large_updates_of_overlapping_runs_rank_the_block_kernel_among_the_searched():
+    """Its share against the micro-tile kernel sets in gradually with the tensors' size: the search tries both."""
+    p = plan(ttc.TTC_C64, (8, 64, 48, 40, 80), (2, 0, 4, 3, 1), 0.5, 1.0)
+    found = []
+    for k in range(min(40, ttc.ttc_plan_candidate_count(p))):
+        ttc.ttc_plan_select_candidate(p, k)
+        found.append(ttc.kernel_family(ttc.ttc_plan_get_info(p)))
+    assert found[0] == "micro" and "block" in found[:10]
+    ttc.ttc_plan_destroy(p)
+
+
+def test_choice_changes_once_with_the_size_of_a_square():
+    """fp32 squares of whole lines, 0.5 to 66 MB of traffic: the gather kernel, then the line kernel; no rank jumps at a round size."""
+    seen = []
+    for n in range(256, 2880, 64):
+        p = plan(ttc.TTC_F32, (n, n), (1, 0))
+        f = ttc.kernel_family(ttc.ttc_plan_get_info(p))
+        ttc.ttc_plan_destroy(p)
+        if not seen or seen[-1] != f:
+            seen.append(f)
+    assert seen == ["gather", "line"]
+
+
 def test_a_plan_is_created_on_a_small_stack():
     """Threads of a host program may have little stack: planning keeps its tables elsewhere.  In a process of its own, which
     an overflow would end."""
