@@ -765,7 +765,7 @@ inline hipError_t launch_line_shape(const Candidate& c, const void* A, void* B, 
         const TA* a = static_cast<const TA*>(A);
         TB* b = static_cast<TB*>(B);
         MicroArgs ready = micro_args(c);
-        const int packed = small_line(ready, MODE, IsComplex<TA>::value);
+        const int packed = small_line(ready, MODE, IsComplex<TA>::value, S.passes);
         if (packed) {
             SmallArgs small = small_line_pack(ready, MODE, IsComplex<TA>::value);
             void* args[] = {&small, &a, &b};

@@ -1567,7 +1567,7 @@ static double line_cost(const Problem& P, const Candidate& C)
     // kernel, whose arguments are packed as well.  Over 3760 problems of 2.5 MB to 1.9 GB this, gather_cost()'s bonus and block_cost()'s
     // choose 0.9 % better than 0.12 here between 8 and 40 MB alone, packed or not, did, and 86 problems instead of 130 take more than 1.05
     // times what they took before any arguments were packed (13061 x 72 fp64 -> fp32 (1,0) 6.0 -> 4.3 us).
-    const bool packed = small_line(micro_args(C), P.epilogue, P.kind_a >= kKindC64) != 0;
+    const bool packed = small_line(micro_args(C), P.epilogue, P.kind_a >= kKindC64, S.passes) != 0;
     e -= (packed ? 0.12 : 0.06) * octaves(traffic, 4e6, 8e6) * (1.0 - octaves(traffic, 40e6, 80e6));
     bool b_order = true;
     for (int i = 0; i < P.ndim; ++i) if (C.tile_order[i] != P.perm[i]) b_order = false;
@@ -2625,7 +2625,7 @@ static int emulate_lines(const ttc::Problem& P, const ttc::Candidate& C, int pha
         m.row_a_in != P.stride_a[p0] || m.row_a_out != (m.merged_b ? P.stride_a[p1] : 0))
         return TTC_ERR_INTERNAL;
     const bool cplx = P.kind_a >= kKindC64;
-    const int packed = small_line(whole, P.epilogue, cplx);
+    const int packed = small_line(whole, P.epilogue, cplx, S.passes);
     SmallDeal deal = {0, 0};
     if (packed) {                                              // as the kernel of small problems sees them
         const SmallArgs small = small_line_pack(whole, P.epilogue, cplx);

@@ -602,10 +602,17 @@ TTC_HD void block_next(const BlockParams& m, int32_t* lds, int32_t* x0, int32_t*
 constexpr int small_line_words(bool merged) { return merged ? 18 : 12; }
 constexpr bool small_line_fits(bool merged, int epilogue, bool is_complex) { return small_line_words(merged) + 2 * small_scalars(epilogue, is_complex) <= 20; }
 
-// 0: the arguments go unpacked; 1: packed; 2: packed with merged indices.
-inline int small_line(const MicroArgs& a, int epilogue, bool is_complex)
+inline bool small_line_dealt(const MicroArgs& a) { return a.xcd_remap != 0 || a.nt_a != 0; }
+
+// 0: the arguments go unpacked; 1: packed; 2: packed with merged indices.  `passes`: vectors of A a lane loads.
+// Updates of many tiles (dealt) whose lanes load eight vectors of A keep the whole arguments: that kernel waits for arguments between
+// its loads, the packed one issues eight of A and up to eight of B in a row, and is slower by 3 % (fp32, 18 problems; 40 x 1064 x 344
+// (1,0,2) 36.8 -> 40.3 us), 2 % (fp64, 10), 1 % (complex64, 8; complex128, 6) and 10 and 7 % (complex128 -> complex64, fp64 -> fp32, 3 and
+// 2).  With four vectors it is 1-3 % faster, and 5 % and more where there are fewer tiles.
+inline int small_line(const MicroArgs& a, int epilogue, bool is_complex, int passes)
 {
     const bool merged = a.micro.merged_a || a.micro.merged_b;
+    if (epilogue == TTC_EPI_AXPBY && passes >= 8 && small_line_dealt(a)) return 0;
     if (!small_line_fits(merged, epilogue, is_complex) || a.micro.size_a0 > INT32_MAX || a.micro.size_p0 > INT32_MAX) return 0;
     int used = 0;                                              // places in the tile order that hold more than one tile, or a column or row
     for (int i = 0; i < kMaxDim; ++i) {
@@ -659,8 +666,6 @@ inline SmallArgs small_line_pack(const MicroArgs& a, int epilogue, bool is_compl
     }
     return s;
 }
-
-inline bool small_line_dealt(const MicroArgs& a) { return a.xcd_remap != 0 || a.nt_a != 0; }
 
 // How its tiles are dealt: one workgroup each, as the row kernel's chunks.
 struct SmallDeal { int32_t xcd_remap; uint32_t blocks; };
