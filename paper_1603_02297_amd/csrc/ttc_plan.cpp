@@ -7,6 +7,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <new>
+#include <type_traits>
 #include <unordered_map>
 
 #include "ttc_internal.h"
@@ -2629,8 +2630,13 @@ static int emulate_lines(const ttc::Problem& P, const ttc::Candidate& C, int pha
     SmallDeal deal = {0, 0};
     if (packed) {                                              // as the kernel of small problems sees them
         const SmallArgs small = small_line_pack(whole, P.epilogue, cplx);
-        p = packed == 2 ? (cplx ? small_line_unpack<TTC_EPI_COPY, true, true, true>(small, m.ta, S) : small_line_unpack<TTC_EPI_COPY, false, true, true>(small, m.ta, S))
-                        : (cplx ? small_line_unpack<TTC_EPI_COPY, true, false, true>(small, m.ta, S) : small_line_unpack<TTC_EPI_COPY, false, false, true>(small, m.ta, S));
+        const bool dealt = small_line_dealt(whole);
+        auto unpack = [&](auto cx, auto merged) {
+            constexpr bool kComplex = decltype(cx)::value, kMerged = decltype(merged)::value;
+            return dealt ? small_line_unpack<TTC_EPI_COPY, kComplex, kMerged, true>(small, m.ta, S) : small_line_unpack<TTC_EPI_COPY, kComplex, kMerged, false>(small, m.ta, S);
+        };
+        p = packed == 2 ? (cplx ? unpack(std::true_type(), std::true_type()) : unpack(std::false_type(), std::true_type()))
+                        : (cplx ? unpack(std::true_type(), std::false_type()) : unpack(std::false_type(), std::false_type()));
         deal = small_line_deal(small, packed == 2);
         p.num_tiles = p.grid = whole.num_tiles;
         if (p.nt_a != whole.nt_a || deal.blocks != whole.num_tiles || deal.xcd_remap != whole.xcd_remap || p.nt_b != whole.nt_b || m.tb != whole.micro.tb || m.skewed != whole.micro.skewed) return TTC_ERR_INTERNAL;

@@ -33,6 +33,22 @@ def line_candidates(plan):
             yield k, info
 
 
+def form(info, dtype):
+    """How a line candidate's arguments go to the kernel, mirrored from the library: "whole", or packed, "small" (a workgroup's number is
+    its tile's) or "dealt" (tiles dealt to the XCDs, or A streamed); and whether its indices are merged."""
+    cols, lines, ea, eb = info["digit_tile_a"][0], info["unroll"], wl.ELEM_BYTES[dtype], wl.ELEM_BYTES_B[dtype]
+    merged, update = bool(info["merged"]), info["epilogue"] == ttc.TTC_EPI_AXPBY
+    dealt = info["xcd_remap"] != 0 or info["nt_a"] != 0
+    passes = lines * (128 // eb) * (cols * ea // 16) // 256              # vectors of A a lane loads
+    words = (18 if merged else 12) + 2 * info["epilogue"] * wl.COMPONENTS[dtype]
+    used = {k for k in range(info["ndim"]) if info["tile"][k] < info["sizes"][k]} | {0, info["perm"][0]}
+    whole = words > 20 or len(used) > 3 or (update and passes >= 8 and dealt)
+    return ("whole" if whole else "dealt" if dealt else "small"), merged
+
+
+FORMS = {(f, m) for f in ("whole", "small", "dealt") for m in (False, True)}
+
+
 def scalars(dtype):
     cplx = wl.COMPONENTS[dtype] == 2
     return [(1.0, 0.0), (0.5 + 0.5j if cplx else 1.5, 0.0), (0.5 - 0.25j if cplx else 0.75, 1.0 + 0.5j if cplx else -1.25)]
@@ -40,7 +56,7 @@ def scalars(dtype):
 
 @pytest.mark.parametrize("dtype", DTYPES, ids=[wl.DTYPE_NAME[d] for d in DTYPES])
 def test_walks_of_every_line_candidate(dtype):
-    seen = 0
+    seen, forms = 0, set()
     for sizes, perm, lda, ldb in SHAPES:
         for beta in (0.0, 1.0):
             p = ttc.ttc_plan_create_ex(dtype, len(sizes), sizes, perm, lda, ldb, 1.0, beta)
@@ -48,10 +64,14 @@ def test_walks_of_every_line_candidate(dtype):
             for off_a, off_b in oracle.element_pairs(sizes, perm, lda, ldb):
                 want[off_b] = off_a
             for k, info in line_candidates(p):
-                assert list(ttc.ttc_debug_emulate_map(p)) == want, (sizes, perm, k, info)
+                for mode, nt in ((-1, 0), ((1, 2, 5)[seen % 3], seen // 3 % 2)):      # tiles dealt to the XCDs, surplus workgroups among them
+                    ttc.ttc_plan_set_tile_mapping(p, mode)
+                    ttc.ttc_plan_set_streaming(p, nt, nt)
+                    forms.add(form(ttc.ttc_plan_get_info(p), dtype))
+                    assert list(ttc.ttc_debug_emulate_map(p)) == want, (sizes, perm, k, mode, nt, info)
                 seen += 1
             ttc.ttc_plan_destroy(p)
-    assert seen >= 40
+    assert seen >= 40 and forms == FORMS
 
 
 def multiplicity(addresses, words):
@@ -84,13 +104,14 @@ def test_reported_bank_conflicts_are_those_of_the_tile(dtype):
 @pytest.mark.gpu
 @pytest.mark.parametrize("dtype", DTYPES, ids=[wl.DTYPE_NAME[d] for d in DTYPES])
 def test_line_kernel_against_the_oracle(dtype):
-    """Every candidate, every epilogue, both streaming settings; B at three places inside a line; what lies around the
-    sub-tensor stays as it was.  Fixed evaluation order on both sides: bit-equal but for the ulp the library allows."""
+    """Every candidate, every epilogue, both streaming settings, tiles dealt and not (packed and whole arguments of either kind); B at
+    three places inside a line; what lies around the sub-tensor stays as it was.  Fixed evaluation order on both sides: bit-equal
+    but for the ulp the library allows."""
     import torch
     dev = torch.device("cuda:0")
     stream = torch.cuda.current_stream().cuda_stream
     prod = lambda v: int(np.prod(v))  # noqa: E731
-    ran = 0
+    ran, forms = 0, set()
     for shape, (sizes, perm, lda, ldb) in enumerate(SHAPES):
         na, nb = prod(lda or sizes), prod(ldb or sizes)
         A = wl.uniform_tensor(dtype, na, 7000 + shape, "a")
@@ -102,8 +123,10 @@ def test_line_kernel_against_the_oracle(dtype):
             plan = ttc.ttc_plan_create_ex(dtype, len(sizes), sizes, perm, lda, ldb, alpha, beta)
             try:
                 for k, info in line_candidates(plan):
-                    for nt, phase in ((0, 0), (1, 1), (0, 7)):
+                    for nt, phase, mode in ((0, 0, -1), (1, 1, (-1, 1, 2, 5)[k % 4]), (0, 7, (1, 2, 5)[k % 3])):
                         ttc.ttc_plan_set_streaming(plan, nt, nt)
+                        ttc.ttc_plan_set_tile_mapping(plan, mode)
+                        forms.add(form(ttc.ttc_plan_get_info(plan), dtype))
                         buf = torch.full((nb * comp + 2 * room,), 77.0, dtype=torch.from_numpy(B0).dtype, device=dev)
                         at = room + phase * comp
                         buf[at:at + nb * comp] = torch.from_numpy(B0).to(dev)
@@ -120,7 +143,7 @@ def test_line_kernel_against_the_oracle(dtype):
                         ran += 1
             finally:
                 ttc.ttc_plan_destroy(plan)
-    assert ran >= 100
+    assert ran >= 100 and forms == FORMS
 
 
 @pytest.mark.gpu
