@@ -18,6 +18,9 @@ SHAPES = [
     ((7, 6, 5, 9), (1, 3, 0, 2), (7, 8, 5, 9), None),
     ((33, 5, 9), (1, 0, 2), None, None),                      # B's first index shorter than a line
     ((10, 3, 50), (1, 2, 0), None, None),
+    ((64, 24, 20, 5), (2, 0, 1, 3), None, None),              # tiles up to the largest: eight vectors a lane, every type
+    ((24, 20, 18, 7), (1, 0, 2, 3), None, None),
+    ((13, 41, 37, 3), (2, 0, 1, 3), None, None),              # ragged runs that the edge cuts in tiles of more than 16 KB
 ]
 DTYPES = [wl.F32, wl.F64, wl.C64, wl.C128, wl.F32_F64, wl.F64_F32, wl.C64_C128, wl.C128_C64]
 
@@ -28,6 +31,14 @@ def block_candidates(plan):
         info = ttc.ttc_plan_get_info(plan)
         if ttc.kernel_family(info) == "block":
             yield k, info
+
+
+def ulp_distance(x, y):
+    """Largest distance of two arrays in representable numbers between them, element by element; equal bits are 0."""
+    ints = np.int64 if x.dtype == np.float64 else np.int32
+    a, b = x.view(ints).astype(np.int64), y.view(ints).astype(np.int64)
+    a, b = np.where(a < 0, np.iinfo(ints).min - a, a), np.where(b < 0, np.iinfo(ints).min - b, b)
+    return int(np.abs(a - b).max())
 
 
 def scalars(dtype):
@@ -72,7 +83,7 @@ def test_block_kernel_against_the_oracle(dtype):
     dev = torch.device("cuda:0")
     stream = torch.cuda.current_stream().cuda_stream
     prod = lambda v: int(np.prod(v))  # noqa: E731
-    ran = 0
+    ran, unrolls = 0, set()
     for shape, (sizes, perm, lda, ldb) in enumerate(SHAPES):
         na, nb = prod(lda or sizes), prod(ldb or sizes)
         A = wl.uniform_tensor(dtype, na, 8000 + shape, "a")
@@ -95,15 +106,39 @@ def test_block_kernel_against_the_oracle(dtype):
                         got = buf.cpu().numpy()
                         assert (got[:at] == 77).all() and (got[at + nb * comp:] == 77).all(), (sizes, perm, k, info)
                         got = got[at:at + nb * comp]
-                        if complex(alpha) == 1 and complex(beta) == 0:
-                            assert np.array_equal(got, want), (sizes, perm, k, info)
-                        else:
-                            ulp = np.spacing(np.abs(want).max())
-                            assert np.abs(got - want).max() <= ulp, (sizes, perm, alpha, beta, k, info)
+                        d = ulp_distance(got, want)
+                        assert d <= (0 if complex(alpha) == 1 and complex(beta) == 0 else 1), (sizes, perm, alpha, beta, k, d, info)
                         ran += 1
+                        unrolls.add((info["unroll"], complex(beta) != 0))
             finally:
                 ttc.ttc_plan_destroy(plan)
-    assert ran >= 100
+    assert ran >= 100 and unrolls == {(u, update) for u in (2, 4, 8) for update in (False, True)}
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", [wl.F32, wl.C128, wl.F32_F64], ids=["f32", "c128", "f32f64"])
+def test_tiles_of_a_large_launch_are_dealt_to_the_xcds(dtype):
+    """From 2048 tiles on the default mapping deals them in chunks of 32; the grid holds workgroups that have none."""
+    import torch
+    sizes, perm = (24, 20, 18, 40, 7), (1, 0, 2, 4, 3)
+    n, stream = int(np.prod(sizes)), torch.cuda.current_stream().cuda_stream
+    A, B0 = wl.uniform_tensor(dtype, n, 8200, "a"), wl.uniform_tensor(dtype, n, 8300, "b")
+    dA, dB0 = torch.from_numpy(A).cuda(), torch.from_numpy(B0).cuda()
+    ran = 0
+    for alpha, beta in scalars(dtype)[::2]:
+        want = oracle.transpose(dtype, sizes, perm, alpha, beta, A, B0.copy(), 8)
+        plan = ttc.ttc_plan_create(dtype, len(sizes), sizes, perm, alpha, beta)
+        for k, info in block_candidates(plan):
+            if info["num_tiles"] < 2048:
+                continue
+            assert info["xcd_remap"] == 5
+            dB = dB0.clone()
+            ttc.ttc_execute(plan, dA.data_ptr(), dB.data_ptr(), stream)
+            d = ulp_distance(dB.cpu().numpy(), want)
+            assert d <= (0 if complex(alpha) == 1 and complex(beta) == 0 else 1), (alpha, beta, k, d, info)
+            ran += info["num_tiles"] % 256 != 0
+        ttc.ttc_plan_destroy(plan)
+    assert ran >= 4
 
 
 @pytest.mark.gpu
