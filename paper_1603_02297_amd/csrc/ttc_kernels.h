@@ -603,7 +603,8 @@ inline hipError_t launch_micro(const Candidate& c, const void* A, void* B, hipSt
 // leading dimension; 79 against 92-105 us with both at 7241.
 // How much of that comes from the caches depends on the order of the tiles.  The 6-D reversal 24 x 20 x 16 x 18 x 22 x 17
 // (merged on both sides, 24-element runs of A) asks for 1.32 lines per line of A and reads 1.03 times A from memory (81 us);
-// 85^4 reversed asks for 2.25 and reads A 2.03 times (97 us): the next tile along A comes 33 tiles later there, on another XCD.
+// 85^4 reversed asks for 1.98 and reads A 1.51 times (90 us; in tiles of 32 columns 2.25, 2.03 times and 97 us): the next tile along A
+// comes tens of tiles later there, on another XCD.
 // It also takes what the micro-tile kernel does not: 16-byte elements and two precisions (B's lines aligned or not).
 //
 // Loads: 16 bytes a lane along A, all of a tile's rows in flight at once, parked row by row in LDS.
@@ -732,8 +733,8 @@ __global__ __launch_bounds__(kLineThreads) void line_kernel(const MicroArgs args
     }
 }
 
-// The same with its arguments packed (SmallArgs), one tile per workgroup: what nearly all launches take.  Not DEALT, for fewer than
-// 2048 tiles: a workgroup's number is its tile's (1024 x 1024 fp32 2.77 us, with the dealing 3.04; 1680 x 289 complex64 with an
+// The same with its arguments packed (SmallArgs), one tile per workgroup, where small_line() finds room for them: 96 of 154 plans of
+// random problems of 64 KB to 1.9 GB (not four places in the tile order, not updates over merged indices).  Not DEALT, for fewer than 2048 tiles: a workgroup's number is its tile's (1024 x 1024 fp32 2.77 us, with the dealing 3.04; 1680 x 289 complex64 with an
 // update 4.26 and 5.18).
 template <typename TA, typename TB, int MODE, int COLS, int LINES, bool MERGED, bool DEALT>
 __global__ __launch_bounds__(kLineThreads) void line_small_kernel(const SmallArgs args_by_value, const TA* __restrict__ A, TB* __restrict__ B)
@@ -815,11 +816,13 @@ inline hipError_t launch_lines(const Candidate& c, const void* A, void* B, hipSt
 // a workgroup first builds position tables and then walks several tiles between barriers; here a lane finds its U vectors
 // by a few divisions, has all of them in flight at once (an update: B's as well), and one barrier separates loads from stores.
 // What bounds it is memory, then how fast the device starts workgroups: one of 256 threads every 1.7 ns, so a tile of 6-12 KB is
-// best (24 x 20 x 16 x 18 x 22 x 17 fp32 (1,0,2,3,5,4), tiles of 1.9, 3.8, 5.8, 11.5 and 31 KB: 181, 97, 75, 70 and 74 us).  Reads reach
-// 6.0-6.9 TB/s in any order of whole lines, writes 6.4 TB/s front to back but 4.7-5.8 where a launch writes 32 and more
+// best (24 x 20 x 16 x 18 x 22 x 17 fp32 (1,0,2,3,5,4), tiles of 1.9, 3.8, 5.8, 11.5 and 31 KB: 181, 97, 75, 70 and 74 us).  Kernels that
+// only read reach 6.0-6.9 TB/s in any order of whole lines, kernels that only write 6.4 TB/s front to back but 4.7-5.8 where a launch writes 32 and more
 // places at once: as much of B's run as the tile can hold is better than more of A's.
 // Box kernel -> here: the same problem as an update 109 -> 95 us (6.5 TB/s), 3 x 307200 x 64 fp32 (1,0,2) 82.4 -> 74.0
-// (6.4 TB/s), 12 x 1000 x 12 x 300 fp32 (2,1,0,3) 62 -> 56, 8 x 9 x 7 x 96 x 104 complex128 (1,2,3,4,0) 35.5 -> 28.6.
+// (6.4 TB/s), 12 x 1000 x 12 x 300 fp32 (2,1,0,3) 62 -> 56, 8 x 9 x 7 x 96 x 104 complex128 (1,2,3,4,0) 35.5 -> 28.6.  The first two
+// pass 1.0002 and 1.0006 times what they have to through memory; of 9.6 and 8.0 LDS cycles an instruction 6.4 and 4.8 are bank conflicts,
+// which the memory hides.
 // One tile per workgroup, and no loop over tiles around it: with one the same two problems took 111 and 89 us.
 // ---------------------------------------------------------------------------------
 template <typename TA, typename TB, int MODE, int U>
@@ -986,7 +989,8 @@ inline hipError_t launch_one(const KernelParams& kp, const void* A, void* B, uin
 // ---------------------------------------------------------------------------------
 // The gather kernel: B is walked front to back, a lane writes 16 bytes of it and fetches their elements from A one by one.
 // No tiles, no LDS, no barrier: one memory latency between launch and store, which is what a small problem costs.
-// 70 x 33 x 45 fp32 (2,0,1): 3.4 us a launch (box kernel 4.2), 2.4 line requests per line of A, all but 0.4 of them from L2.
+// 70 x 33 x 45 fp32 (2,0,1): 2.3-2.8 us a launch, from host to host (3.3-3.5 with its arguments whole, box kernel 4.2), 2.4 line requests
+// per line of A, all but 0.4 of them from L2.
 // ---------------------------------------------------------------------------------
 template <typename TA, typename TB, int MODE, int V>
 __device__ __forceinline__ void gather_chunk(const RowsParams& p, uint32_t block, const TA* __restrict__ A, TB* __restrict__ B)

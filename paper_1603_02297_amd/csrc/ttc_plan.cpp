@@ -1542,7 +1542,8 @@ static double line_cost(const Problem& P, const Candidate& C)
         e += 0.343 * std::log((double)loaded / rows) + 0.340 * pad_cols + 0.293 * std::log((double)segs * m.tb / rows) + 0.087 * split;
         // Columns of 256 bytes before 128 in 4-byte elements, four lines before eight.  With `odd` above, over 120 problems of 16 to
         // 500 MB: 2.4 % off the geometric mean, 7 % where both ways of cutting exist, none slower by more than 2 % (408^3 fp32 reversed
-        // 149 -> 115 us, 300^3 fp64 102 -> 90, 408 x 200 x 408 fp32 with an update 91 -> 76, 360^3 fp64 -> fp32 138 -> 110).
+        // 149 -> 115 us, 300^3 fp64 103 -> 95, 408 x 200 x 408 fp32 with an update 91 -> 76, 360^3 fp64 -> fp32 138 -> 125; with their
+        // arguments packed as well 113, 84, 75 and 108).
         if (m.skewed) e += (P.eb_a == 4 && m.ta == 64 ? -0.03 : 0.0) + (m.lines == 8 ? 0.02 : 0.0);
         if (m.skewed) e += 0.178 * 2.0 / (line_rows + 1.0);               // lines that no tile writes whole: a column's first and last
         if (m.size_p0 < S.line) e += 0.258;
