@@ -772,11 +772,12 @@ inline hipError_t launch_line_shape(const Candidate& c, const void* A, void* B, 
             void* args[] = {&small, &a, &b};
             const void* small_fn = nullptr;
             const bool dealt = small_line_dealt(ready);
+            constexpr bool kDeals = small_line_deals(MODE, S.passes);          // if not, `dealt` is false here and no such kernel is compiled
             if constexpr (small_line_fits(false, MODE, IsComplex<TA>::value))
-                if (packed == 1) small_fn = dealt ? reinterpret_cast<const void*>(&line_small_kernel<TA, TB, MODE, COLS, LINES, false, true>)
+                if (packed == 1) small_fn = dealt ? reinterpret_cast<const void*>(&line_small_kernel<TA, TB, MODE, COLS, LINES, false, kDeals>)
                                                   : reinterpret_cast<const void*>(&line_small_kernel<TA, TB, MODE, COLS, LINES, false, false>);
             if constexpr (small_line_fits(true, MODE, IsComplex<TA>::value))
-                if (packed == 2) small_fn = dealt ? reinterpret_cast<const void*>(&line_small_kernel<TA, TB, MODE, COLS, LINES, true, true>)
+                if (packed == 2) small_fn = dealt ? reinterpret_cast<const void*>(&line_small_kernel<TA, TB, MODE, COLS, LINES, true, kDeals>)
                                                   : reinterpret_cast<const void*>(&line_small_kernel<TA, TB, MODE, COLS, LINES, true, false>);
             const int64_t grid = rows_grid(small_line_deal(small, packed == 2));
             if (small_fn && launchable(grid, kLineThreads)) return hipLaunchKernel(small_fn, dim3((uint32_t)grid), dim3(kLineThreads), args, 0, stream);

@@ -604,15 +604,18 @@ constexpr bool small_line_fits(bool merged, int epilogue, bool is_complex) { ret
 
 inline bool small_line_dealt(const MicroArgs& a) { return a.xcd_remap != 0 || a.nt_a != 0; }
 
-// 0: the arguments go unpacked; 1: packed; 2: packed with merged indices.  `passes`: vectors of A a lane loads.
-// Updates of many tiles (dealt) whose lanes load eight vectors of A keep the whole arguments: that kernel waits for arguments between
+// Whether there is a packed kernel for dealt tiles; `passes`: vectors of A a lane loads.
+// Updates of many tiles whose lanes load eight vectors of A keep the whole arguments: that kernel waits for arguments between
 // its loads, the packed one issues eight of A and up to eight of B in a row, and is slower by 3 % (fp32, 18 problems; 40 x 1064 x 344
 // (1,0,2) 36.8 -> 40.3 us), 2 % (fp64, 10), 1 % (complex64, 8; complex128, 6) and 10 and 7 % (complex128 -> complex64, fp64 -> fp32, 3 and
 // 2).  With four vectors it is 1-3 % faster, and 5 % and more where there are fewer tiles.
+constexpr bool small_line_deals(int epilogue, int passes) { return epilogue != TTC_EPI_AXPBY || passes < 8; }
+
+// 0: the arguments go unpacked; 1: packed; 2: packed with merged indices.
 inline int small_line(const MicroArgs& a, int epilogue, bool is_complex, int passes)
 {
     const bool merged = a.micro.merged_a || a.micro.merged_b;
-    if (epilogue == TTC_EPI_AXPBY && passes >= 8 && small_line_dealt(a)) return 0;
+    if (small_line_dealt(a) && !small_line_deals(epilogue, passes)) return 0;
     if (!small_line_fits(merged, epilogue, is_complex) || a.micro.size_a0 > INT32_MAX || a.micro.size_p0 > INT32_MAX) return 0;
     int used = 0;                                              // places in the tile order that hold more than one tile, or a column or row
     for (int i = 0; i < kMaxDim; ++i) {
