@@ -1621,7 +1621,7 @@ static double block_cost(const Problem& P, const Candidate& C)
     if (C.kp.num_tiles < 512) e += 0.19 * std::log2(512.0 / C.kp.num_tiles);
     // Against the micro-tile kernel where neither splits lines: time of this kernel's first candidate over that one's, beyond what the
     // two models have.  Copies and scaled copies, pairs in rotation and one pair: 0.93 and 0.91 below 40 MB (62 problems), 1.13 and
-    // 0.95 up to 100 (23), 1.02 and 1.09 above (55).  Updates of 90 to 700 MB per tensor, in rotation, on one pair and on new tensors (50
+    // 0.95 up to 100 (23), 1.02 and 1.09 above (55).  Updates of 90 to 700 MB per tensor, in rotation, on one pair and on new tensors (60
     // problems, medians of six first passes), where the models have 0.92 in the mean: if A's first index is not B's second, 0.98, 1.11 and
     // 1.07 below 256 MB, 1.00, 1.18 and 1.14 above; if it is, 0.93, 1.00 and 0.98 below, and above 0.98, 1.09 and 1.10 but for three
     // fp32 problems at 0.74 to 0.80.
