@@ -349,7 +349,7 @@ def study_sweep(out, limit=None, dump=None):
             "tile order": "tiles numbered in B's index order", "LDS buffering": "two tile buffers",
             "launch shape": "256 threads, 16 workgroups per CU",
             "LDS pads": "the best configuration with an unpadded LDS tile",
-            "kernel family": "box kernels only (no micro-tile, line, row or gather kernel)"}
+            "kernel family": "box kernels only (no micro-tile, line, block, row or gather kernel)"}
     for name in held:
         g = [r["abl"][name] - 1.0 for r in results if r["abl"][name] == r["abl"][name]]
         if g:
