@@ -337,14 +337,15 @@ static int tune_pairs(ttc_plan_t plan, int npairs, const void* const* A_list, vo
         // Trying them made the search keep round robin on 384^3 (74.2 us, default 72.9).
         const int mapping0 = c.kp.xcd_remap;
         int keep_map = mapping0;
-        for (int mode : {1, 3}) {
+        for (int mode : {1, 3, ttc::kDefaultTileMapping}) {
             if (c.kernel_class == TTC_KERNEL_ROWS) break;
-            if (mode == mapping0 || !ttc::set_tile_mapping(&c.kp, mode)) continue;
+            if (mode == ttc::kDefaultTileMapping && c.kernel_class != ttc::kKernelLines) break;      // the line kernel has a rule of its own
+            if (!ttc::set_tile_mapping(&c.kp, mode) || c.kp.xcd_remap == mapping0) continue;
             float ms = 0.f;
             const int st3 = time_one(c, 2, reps2, &ms);
             if (st3 == kNotLaunched) continue;
             if (st3 != TTC_OK) { (void)ttc::set_tile_mapping(&c.kp, mapping0); return st3; }
-            if (ms < cand_ms) { cand_ms = ms; keep_map = mode; }
+            if (ms < cand_ms) { cand_ms = ms; keep_map = c.kp.xcd_remap; }
         }
         (void)ttc::set_tile_mapping(&c.kp, keep_map);
         c.tuned_ms = cand_ms;

@@ -734,21 +734,35 @@ __global__ __launch_bounds__(kLineThreads) void line_kernel(const MicroArgs args
 }
 
 // The same with its arguments packed (SmallArgs), one tile per workgroup, where small_line() finds room for them: 96 of 154 plans of
-// random problems of 64 KB to 1.9 GB (not four places in the tile order, not updates over merged indices).  Not DEALT, for fewer than 2048 tiles: a workgroup's number is its tile's (1024 x 1024 fp32 2.77 us, with the dealing 3.04; 1680 x 289 complex64 with an
-// update 4.26 and 5.18).
-template <typename TA, typename TB, int MODE, int COLS, int LINES, bool MERGED, bool DEALT>
+// random problems of 64 KB to 1.9 GB (not four places in the tile order, not updates over merged indices).  Three ways of dealing tiles.
+// kDealNone, for fewer than 2048 tiles that share nothing: a workgroup's number is its tile's (1024 x 1024 fp32 2.77 us, with kDealAll
+// 3.04; 1680 x 289 complex64 with an update 4.26 and 5.18; a kernel that serves kDealRanges too, and so has to look at its arguments
+// before it may go on, is 1-2 % slower in the mean over 5000 problems below 32 MB and 6-8 % on a tenth of them).  kDealRanges: one
+// range per XCD.  kDealAll: any mapping, and A may be streamed.
+template <typename TA, typename TB, int MODE, int COLS, int LINES, bool MERGED, int DEAL>
 __global__ __launch_bounds__(kLineThreads) void line_small_kernel(const SmallArgs args_by_value, const TA* __restrict__ A, TB* __restrict__ B)
 {
     const SmallArgs& s = *reinterpret_cast<const SmallArgs*>((const void*)__builtin_amdgcn_kernarg_segment_ptr());
     constexpr LineShape S = line_shape(COLS, LINES, (int)sizeof(TA), (int)sizeof(TB));
     uint32_t tile = blockIdx.x;
-    if (DEALT) {
+    if (DEAL != kDealNone) {
         const SmallDeal deal = small_line_deal(s, MERGED);
-        tile = rows_block(deal, tile);
+        tile = DEAL == kDealAll ? rows_block(deal, tile) : small_line_range(deal, tile);
         if (tile >= deal.blocks) return;
     }
-    const MicroArgs p = small_line_unpack<MODE, IsComplex<TA>::value, MERGED, DEALT>(s, COLS, S);
+    const MicroArgs p = small_line_unpack<MODE, IsComplex<TA>::value, MERGED, DEAL == kDealAll>(s, COLS, S);
     line_tile_move<TA, TB, MODE, COLS, LINES>(p, tile, A, B);
+}
+
+// The packed kernel for a way of dealing.  Where there is none for kDealAll (small_line_deals()), such a launch is not packed.
+template <typename TA, typename TB, int MODE, int COLS, int LINES, bool MERGED>
+inline const void* small_line_function(int deal)
+{
+    constexpr LineShape S = line_shape(COLS, LINES, (int)sizeof(TA), (int)sizeof(TB));
+    if (deal == kDealNone) return reinterpret_cast<const void*>(&line_small_kernel<TA, TB, MODE, COLS, LINES, MERGED, kDealNone>);
+    if (deal == kDealRanges) return reinterpret_cast<const void*>(&line_small_kernel<TA, TB, MODE, COLS, LINES, MERGED, kDealRanges>);
+    if constexpr (small_line_deals(MODE, S.passes)) return reinterpret_cast<const void*>(&line_small_kernel<TA, TB, MODE, COLS, LINES, MERGED, kDealAll>);
+    return nullptr;
 }
 
 template <typename TA, typename TB, int MODE, int COLS, int LINES>
@@ -771,14 +785,11 @@ inline hipError_t launch_line_shape(const Candidate& c, const void* A, void* B, 
             SmallArgs small = small_line_pack(ready, MODE, IsComplex<TA>::value);
             void* args[] = {&small, &a, &b};
             const void* small_fn = nullptr;
-            const bool dealt = small_line_dealt(ready);
-            constexpr bool kDeals = small_line_deals(MODE, S.passes);          // if not, `dealt` is false here and no such kernel is compiled
+            const int deal = small_line_dealing(ready);
             if constexpr (small_line_fits(false, MODE, IsComplex<TA>::value))
-                if (packed == 1) small_fn = dealt ? reinterpret_cast<const void*>(&line_small_kernel<TA, TB, MODE, COLS, LINES, false, kDeals>)
-                                                  : reinterpret_cast<const void*>(&line_small_kernel<TA, TB, MODE, COLS, LINES, false, false>);
+                if (packed == 1) small_fn = small_line_function<TA, TB, MODE, COLS, LINES, false>(deal);
             if constexpr (small_line_fits(true, MODE, IsComplex<TA>::value))
-                if (packed == 2) small_fn = dealt ? reinterpret_cast<const void*>(&line_small_kernel<TA, TB, MODE, COLS, LINES, true, kDeals>)
-                                                  : reinterpret_cast<const void*>(&line_small_kernel<TA, TB, MODE, COLS, LINES, true, false>);
+                if (packed == 2) small_fn = small_line_function<TA, TB, MODE, COLS, LINES, true>(deal);
             const int64_t grid = rows_grid(small_line_deal(small, packed == 2));
             if (small_fn && launchable(grid, kLineThreads)) return hipLaunchKernel(small_fn, dim3((uint32_t)grid), dim3(kLineThreads), args, 0, stream);
         }

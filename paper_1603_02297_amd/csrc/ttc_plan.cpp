@@ -828,6 +828,8 @@ static bool make_micro_candidate(const Problem& P, int ta, int tb, int threads, 
     return true;
 }
 
+static int default_tile_mapping(const Problem& P, const Candidate& C);
+
 // The line kernel's candidate: `cols` columns by `lines` lines of B per column.  Columns and rows are what the
 // micro-tile kernel takes (A's index 0 and B's first index, each possibly merged with the next), for every type pair.
 static bool make_line_candidate(const Problem& P, int cols_tile, int lines, const int* tile_order, bool merge_a, bool merge_b, Candidate* out)
@@ -885,7 +887,6 @@ static bool make_line_candidate(const Problem& P, int cols_tile, int lines, cons
     kp.num_tiles = (uint32_t)ntiles;
     kp.tiles_per_xcd = kp.num_tiles / 8;
     kp.tiles_rem_xcd = kp.num_tiles % 8;
-    if (!set_tile_mapping(&kp, kDefaultTileMapping)) return false;
     set_grid(&kp, kp.num_tiles);
     kp.alpha[0] = P.alpha[0]; kp.alpha[1] = P.alpha[1];
     kp.beta[0] = P.beta[0];   kp.beta[1] = P.beta[1];
@@ -906,6 +907,7 @@ static bool make_line_candidate(const Problem& P, int cols_tile, int lines, cons
     m.row_in_div = make_fastdiv((uint32_t)P.size[p0]);
     m.col_b_in = P.stride_b[0];  m.col_b_out = merge_a ? P.stride_b[a1] : 0;
     m.row_a_in = P.stride_a[p0]; m.row_a_out = merge_b ? P.stride_a[p1] : 0;
+    if (!set_tile_mapping(&kp, default_tile_mapping(P, C))) return false;
     // the tile per index of A, as the plan reports it
     C.tile[0] = (int)std::min<int64_t>(cols_tile, P.size[0]);
     if (merge_a) C.tile[a1] = (int)std::min<int64_t>(ceil_div(cols_tile, P.size[0]), P.size[a1]);
@@ -1309,6 +1311,30 @@ static bool make_gather_candidate(const Problem& P, Candidate* out)
     C.dtile_b[0] = C.dlane_b[0] = kWave * r.vec;
     *out = C;
     return true;
+}
+
+// The line kernel's tiles read lines that their neighbours read as well: rows of A at the edge along B's runs where columns are cut at
+// their own lines (skewed), lines of A at the edge along A's runs where those split lines.  One contiguous range of tiles per XCD lets
+// neighbours meet in one L2; from 200 MB on the eight distant windows cost more than that gives.  Time of one range over the rule of
+// set_tile_mapping(), pairs in rotation, 21 000 random problems: skewed, copies of 8-16, 16-32, 32-64, 64-128 and 128-200 MB of
+// traffic 0.89, 0.83, 0.87, 0.90, 0.95 (4-8 MB 0.98-1.03), updates from 2 MB on 0.94, 0.93, 0.92, 0.86, 0.88, 0.92, 0.93; 200-300 MB 1.01, beyond
+// 1.03.  (7145 x 536 fp32 9.7 -> 6.7 us, 2001^2 10.2 -> 7.0, 2334 x 4390 18.9 -> 14.3.)  Where A's lines are split the next tile along A's
+// run has to be under way at the same time, `between` tiles later: up to 160 of them 0.90, 192-256 0.93-0.99, beyond 0.95-1.01 and
+// up to 1.5 (25 x 143639 complex64); where a range is shorter than that 0.93, with a twentieth of them above 1.1.  Not skewed, lines split at multiples of 32 bytes or less, 8 to 200 MB and up to 64 tiles
+// between 0.91; at 64 bytes or with more between 0.98-1.06; whole lines on both sides share nothing (0.99-1.02).
+static int default_tile_mapping(const Problem& P, const Candidate& C)
+{
+    if (C.kernel_class != kKernelLines) return C.rows.per_xcd ? 0 : kDefaultTileMapping;
+    const MicroParams& m = C.kp.micro;
+    int64_t align = kLineBytes, between = 1;
+    for (int k = 1; k < P.ndim; ++k)
+        while (!(m.merged_a && k == 1) && P.stride_a[k] * P.eb_a % align != 0) align /= 2;
+    for (int i = 0; i < P.ndim && C.tile_order[i] != 0; ++i) between *= (int64_t)C.kp.tile_cnt[C.tile_order[i]].div;
+    const double traffic = traffic_bytes(P);
+    const bool near = between <= 160 && between * 8 <= (int64_t)C.kp.num_tiles;
+    const bool ranges = m.skewed ? traffic >= (P.epilogue == TTC_EPI_AXPBY ? 2e6 : 8e6) && (align == kLineBytes || near)
+                                 : traffic >= 8e6 && align <= 32 && between <= 64;
+    return ranges && traffic <= 200e6 ? 1 : kDefaultTileMapping;
 }
 
 bool set_tile_mapping(KernelParams* kp, int mode)
@@ -2315,7 +2341,7 @@ int ttc_plan_set_tile_mapping(ttc_plan_t plan, int mode)
     if (!plan) return TTC_ERR_NULL_POINTER;
     if (mode < -1 || mode > ttc::kMaxTileMapping) return TTC_ERR_INVALID_VALUE;
     ttc::Candidate& C = plan->cands[plan->selected];
-    return ttc::set_tile_mapping(&C.kp, mode < 0 && C.rows.per_xcd ? 0 : mode) ? TTC_OK : TTC_ERR_INVALID_VALUE;
+    return ttc::set_tile_mapping(&C.kp, mode < 0 ? ttc::default_tile_mapping(plan->prob, C) : mode) ? TTC_OK : TTC_ERR_INVALID_VALUE;
 }
 
 int ttc_plan_candidate_count(ttc_plan_t plan)
@@ -2629,12 +2655,12 @@ static int emulate_lines(const ttc::Problem& P, const ttc::Candidate& C, int pha
     const bool cplx = P.kind_a >= kKindC64;
     const int packed = small_line(whole, P.epilogue, cplx, S.passes);
     SmallDeal deal = {0, 0};
+    const int dealing = small_line_dealing(whole);
     if (packed) {                                              // as the kernel of small problems sees them
         const SmallArgs small = small_line_pack(whole, P.epilogue, cplx);
-        const bool dealt = small_line_dealt(whole);
         auto unpack = [&](auto cx, auto merged) {
             constexpr bool kComplex = decltype(cx)::value, kMerged = decltype(merged)::value;
-            return dealt ? small_line_unpack<TTC_EPI_COPY, kComplex, kMerged, true>(small, m.ta, S) : small_line_unpack<TTC_EPI_COPY, kComplex, kMerged, false>(small, m.ta, S);
+            return dealing == kDealAll ? small_line_unpack<TTC_EPI_COPY, kComplex, kMerged, true>(small, m.ta, S) : small_line_unpack<TTC_EPI_COPY, kComplex, kMerged, false>(small, m.ta, S);
         };
         p = packed == 2 ? (cplx ? unpack(std::true_type(), std::true_type()) : unpack(std::false_type(), std::true_type()))
                         : (cplx ? unpack(std::true_type(), std::false_type()) : unpack(std::false_type(), std::false_type()));
@@ -2659,13 +2685,14 @@ static int emulate_lines(const ttc::Problem& P, const ttc::Candidate& C, int pha
     const int64_t grid = packed ? rows_grid(deal) : (int64_t)p.grid;
     for (int64_t wg = 0; wg < grid; ++wg) {
         TileSeq seq = {(uint32_t)wg, (uint32_t)wg + 1u, 1u, 0u, 0u, 0u};
+        const uint32_t mine = dealing == kDealAll ? rows_block(deal, (uint32_t)wg) : dealing == kDealRanges ? small_line_range(deal, (uint32_t)wg) : (uint32_t)wg;
         if (packed) {
-            if (rows_block(deal, (uint32_t)wg) >= deal.blocks) continue;
+            if (mine >= deal.blocks) continue;
         } else {
             seq = tile_sequence(p, (uint32_t)wg);
         }
         for (uint32_t q = seq.first; q < seq.end; q += seq.step) {
-            const uint32_t tile = packed ? rows_block(deal, (uint32_t)wg) : tile_of(seq, q);
+            const uint32_t tile = packed ? mine : tile_of(seq, q);
             if (tile >= p.num_tiles || seen[tile]) return TTC_ERR_INTERNAL;
             seen[tile] = 1;
             const LineTile t = line_tile(p, S, tile);

@@ -112,10 +112,13 @@ TTC_HD GatherPlace gather_place(const RowsParams& p, uint32_t e)
     return r;
 }
 
+// Workgroup `wg`'s place where each XCD has one range of `per_xcd` places.
+TTC_HD uint32_t range_place(uint32_t per_xcd, uint32_t wg) { return (wg & 7u) * per_xcd + (wg >> 3); }
+
 // First element of lane `tid` of chunk `block` (past the end of B: nothing to do).
 TTC_HD uint32_t gather_first(const RowsParams& p, uint32_t block, uint32_t tid)
 {
-    if (p.per_xcd && p.xcd_remap == 0) block = (block & 7u) * p.per_xcd + (block >> 3);
+    if (p.per_xcd && p.xcd_remap == 0) block = range_place(p.per_xcd, block);
     return (block * p.chunk + tid) * (uint32_t)p.vec;
 }
 
@@ -602,7 +605,9 @@ TTC_HD void block_next(const BlockParams& m, int32_t* lds, int32_t* x0, int32_t*
 constexpr int small_line_words(bool merged) { return merged ? 18 : 12; }
 constexpr bool small_line_fits(bool merged, int epilogue, bool is_complex) { return small_line_words(merged) + 2 * small_scalars(epilogue, is_complex) <= 20; }
 
-inline bool small_line_dealt(const MicroArgs& a) { return a.xcd_remap != 0 || a.nt_a != 0; }
+// Which packed kernel a launch needs: tiles as they come, one range per XCD, or any dealing and A streamed.
+constexpr int kDealNone = 0, kDealRanges = 1, kDealAll = 2;
+inline int small_line_dealing(const MicroArgs& a) { return a.nt_a != 0 || a.xcd_remap > 1 ? kDealAll : a.xcd_remap == 1 ? kDealRanges : kDealNone; }
 
 // Whether there is a packed kernel for dealt tiles; `passes`: vectors of A a lane loads.
 // Updates of many tiles whose lanes load eight vectors of A keep the whole arguments: that kernel waits for arguments between
@@ -615,7 +620,7 @@ constexpr bool small_line_deals(int epilogue, int passes) { return epilogue != T
 inline int small_line(const MicroArgs& a, int epilogue, bool is_complex, int passes)
 {
     const bool merged = a.micro.merged_a || a.micro.merged_b;
-    if (small_line_dealt(a) && !small_line_deals(epilogue, passes)) return 0;
+    if (small_line_dealing(a) == kDealAll && !small_line_deals(epilogue, passes)) return 0;
     if (!small_line_fits(merged, epilogue, is_complex) || a.micro.size_a0 > INT32_MAX || a.micro.size_p0 > INT32_MAX) return 0;
     int used = 0;                                              // places in the tile order that hold more than one tile, or a column or row
     for (int i = 0; i < kMaxDim; ++i) {
@@ -673,6 +678,9 @@ inline SmallArgs small_line_pack(const MicroArgs& a, int epilogue, bool is_compl
 // How its tiles are dealt: one workgroup each, as the row kernel's chunks.
 struct SmallDeal { int32_t xcd_remap; uint32_t blocks; };
 TTC_HD SmallDeal small_line_deal(const SmallArgs& s, bool merged) { return SmallDeal{(int32_t)(s.w[0] >> 9 & 15u), s.w[merged ? 17 : 11]}; }
+
+// The tile of workgroup `wg` with one range per XCD (num_tiles or more: none).
+TTC_HD uint32_t small_line_range(const SmallDeal& d, uint32_t wg) { return range_place((d.blocks + 7u) / 8u, wg); }
 
 // The arguments as the line kernel's index code reads them (the fields of the dealing are not set).
 // DEALT: what a small problem does without: tiles dealt to the XCDs in chunks, A streamed.

@@ -177,3 +177,57 @@ def test_elements_that_start_halfway(dtype):
             finally:
                 ttc.ttc_plan_destroy(plan)
     assert ran >= 40
+
+
+# (type, extents, permutation, beta, whether each XCD gets one range of tiles): either side of every line of the rule
+DEALT_BY_DEFAULT = [
+    (wl.F32, (1301, 1303), (1, 0), 0.0, True), (wl.F32, (901, 903), (1, 0), 0.0, False),           # 13.6 MB, 6.5 MB of traffic
+    (wl.F32, (521, 503), (1, 0), 1.0, True), (wl.F32, (301, 303), (1, 0), 1.0, False),             # updates of 3.1 and 1.1 MB
+    (wl.F64, (17, 40009), (1, 0), 0.0, False), (wl.F64, (16, 40009), (1, 0), 0.0, True),           # hundreds of tiles before the next one along A: lines split, or none
+    (wl.F32, (1031, 1024), (1, 0), 0.0, True), (wl.F32, (1032, 1024), (1, 0), 0.0, True),          # whole lines of B, A's split at 4 and 32 bytes
+    (wl.F32, (1040, 1024), (1, 0), 0.0, False), (wl.F32, (1024, 1024), (1, 0), 0.0, False),        # at 64 bytes, and none
+]
+
+
+def default_of(plan):
+    """The mapping that the first line candidate in B's order has."""
+    perm = ttc.ttc_plan_get_info(plan)["perm"]
+    for k, info in line_candidates(plan):
+        if info["tile_order"] == perm:
+            return info
+    raise AssertionError("no line candidate")
+
+
+@pytest.mark.parametrize("dtype,sizes,perm,beta,ranges", DEALT_BY_DEFAULT)
+def test_tiles_that_share_lines_are_dealt_in_ranges(dtype, sizes, perm, beta, ranges):
+    p = ttc.ttc_plan_create(dtype, len(sizes), sizes, perm, 1.0, beta)
+    info = default_of(p)
+    plain = 5 if info["num_tiles"] >= 2048 else 0
+    assert info["xcd_remap"] == (1 if ranges else plain)
+    ttc.ttc_plan_set_tile_mapping(p, 3)
+    ttc.ttc_plan_set_tile_mapping(p, -1)
+    assert ttc.ttc_plan_get_info(p)["xcd_remap"] == (1 if ranges else plain)
+    ttc.ttc_plan_destroy(p)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype,sizes,perm,beta,ranges", [c for c in DEALT_BY_DEFAULT if c[-1]])
+def test_ranges_against_the_oracle(dtype, sizes, perm, beta, ranges):
+    """The plan as created and its line candidates over ranges: tile counts that do not divide by eight, packed arguments and whole ones."""
+    import torch
+    n, stream = int(np.prod(sizes)), torch.cuda.current_stream().cuda_stream
+    A, B0 = wl.uniform_tensor(dtype, n, 7300, "a"), wl.uniform_tensor(dtype, n, 7301, "b")
+    want = oracle.transpose(dtype, sizes, perm, 1.0, beta, A, B0.copy(), 8)
+    dA, dB0 = torch.from_numpy(A).cuda(), torch.from_numpy(B0).cuda()
+    plan = ttc.ttc_plan_create(dtype, len(sizes), sizes, perm, 1.0, beta)
+    seen = 0
+    for k, info in [(0, None)] + list(line_candidates(plan)):
+        ttc.ttc_plan_select_candidate(plan, k)
+        ttc.ttc_plan_set_tile_mapping(plan, -1 if info is None else 1)
+        seen += ttc.ttc_plan_get_info(plan)["num_tiles"] % 8 != 0
+        dB = dB0.clone()
+        ttc.ttc_execute(plan, dA.data_ptr(), dB.data_ptr(), stream)
+        allowed = 0.0 if beta == 0 else np.spacing(np.abs(want).max())          # bits are copied; one ulp with an update
+        assert np.abs(dB.cpu().numpy() - want).max() <= allowed, (k, ttc.ttc_plan_get_info(plan))
+    assert seen
+    ttc.ttc_plan_destroy(plan)
