@@ -448,13 +448,15 @@ __global__ __launch_bounds__(kRowsThreads) void rows_kernel(const RowsParams p, 
     rows_chunk<TA, TB, MODE, V, U, FLAT>(p, base, (uint32_t)row0_wide, (uint32_t)(base - row0_wide * (int64_t)p.slots), A, B);
 }
 
-// The same for small problems over a dense B, with its arguments packed (SmallArgs) and the usual hints (A kept, B streamed).
-template <typename TA, typename TB, int MODE, int V, int N>
+// The same for small problems over a dense B, with its arguments packed (SmallArgs) and the usual hints (A kept, B streamed).  RANGES: each
+// XCD has one range of chunks (those behind the last one find nothing valid).
+template <typename TA, typename TB, int MODE, int V, int N, bool RANGES>
 __global__ __launch_bounds__(kRowsThreads) void rows_small_kernel(const SmallArgs args_by_value, const TA* __restrict__ A, TB* __restrict__ B)
 {
     const SmallArgs& s = *reinterpret_cast<const SmallArgs*>((const void*)__builtin_amdgcn_kernarg_segment_ptr());
     const RowsParams p = small_unpack<false, N, MODE, IsComplex<TA>::value>(s, V, kRowsThreads);
-    const uint32_t first = blockIdx.x * (uint32_t)(kRowsThreads * V), row0 = fdiv(first, p.slot_div);
+    const uint32_t block = RANGES ? range_place(p.per_xcd, blockIdx.x) : blockIdx.x;
+    const uint32_t first = block * (uint32_t)(kRowsThreads * V), row0 = fdiv(first, p.slot_div);
     rows_chunk<TA, TB, MODE, V, 1, true>(p, (int64_t)first, row0, first - row0 * p.row, A, B);
 }
 
@@ -1077,7 +1079,8 @@ inline hipError_t launch_small(const RowsParams& rp, int dims, int64_t grid, con
                 SmallArgs ready = small_pack(rp, GATHER, N, MODE, IsComplex<TA>::value);
                 void* args[] = {&ready, &a, &b};
                 const void* fn = GATHER ? reinterpret_cast<const void*>(&gather_small_kernel<TA, TB, MODE, 16 / (int)sizeof(TB), N>)
-                                        : reinterpret_cast<const void*>(&rows_small_kernel<TA, TB, MODE, V, N>);
+                               : rp.xcd_remap == 1 ? reinterpret_cast<const void*>(&rows_small_kernel<TA, TB, MODE, V, N, true>)
+                                                   : reinterpret_cast<const void*>(&rows_small_kernel<TA, TB, MODE, V, N, false>);
                 return hipLaunchKernel(fn, dim3((uint32_t)grid), dim3(kRowsThreads), args, 0, stream);
             }
         }
@@ -1124,6 +1127,7 @@ inline hipError_t launch_rows_unrolled(const Candidate& c, const void* A, void* 
     const TA* a = static_cast<const TA*>(A);
     TB* b = static_cast<TB*>(B);
     if constexpr (FLAT && U == 1) {
+        rp.per_xcd = rp.xcd_remap == 1 ? (rp.blocks + 7u) / 8u : 0u;
         const int dims = small_dims(rp, false, MODE, IsComplex<TA>::value, 0, 1);
         if (dims) return launch_small<TA, TB, MODE, V, false>(rp, dims, grid, a, b, stream);
     }

@@ -1186,7 +1186,7 @@ static bool make_rows_candidate(const Problem& P, int vec, int unroll, bool flat
     kp.num_tiles = (uint32_t)grid;
     kp.grid = (uint32_t)grid;
     r.blocks = (uint32_t)grid;
-    if (!set_tile_mapping(&kp, kDefaultTileMapping)) return false;
+    if (!set_tile_mapping(&kp, default_tile_mapping(P, C))) return false;
     for (int k = 0; k < kMaxDim; ++k) {
         C.tile[k] = (k == 0) ? (int)row : 1;
         C.tile_order[k] = (k < P.ndim) ? P.perm[k] : k;
@@ -1313,6 +1313,37 @@ static bool make_gather_candidate(const Problem& P, Candidate* out)
     return true;
 }
 
+// The row kernel's chunks: rows that split lines of A share them with chunks that lie far apart in B, which meet in one L2 where each XCD
+// has one range of chunks; and a launch without groups of chunks (none or ranges) packs its arguments.  Time of ranges over the rule of
+// set_tile_mapping(), pairs in rotation, 19 000 random problems.  Packed copies: 8-16, 16-32, 32-64, 64-128 MB of traffic, rows
+// below 64 bytes 0.72, 0.80, 0.82, 0.86, to 128 0.80, 0.83, 0.85, 0.84, to 512 0.92, 0.85, 0.89, 0.88, longer 0.95, 0.86, 0.91, 0.91,
+// whole lines 0.96, 0.91, 0.93, 0.93; 128-200 MB below 512 bytes 0.90-0.92, longer and whole lines 0.96-1.05, beyond 200 MB 0.94-1.06.  (6 x 258 x 2475 fp32
+// (0,2,1) 12.0 -> 8.2 us.)  Packed updates of rows that split lines: below 128 bytes 0.80-0.94 from 8 MB on, to
+// 512 0.92-0.97 from 16 MB on, longer 0.94-0.99; others from 16 MB on as they come: 0.95-0.99 (ranges 0.97-1.02).  Not packed: split rows below
+// 256 bytes 0.76-0.99 (copies to 512 0.92-0.98) from 8 to 200 MB; the others 0.99-1.06.
+// An XCD has about 1 MB of B under way (32 compute units, eight chunks of 4 KB each): rows below 128 bytes whose neighbours in A lie `apart`
+// further than that do not meet (1.00-1.10, as they come 0.92-0.99); up to 512 KB 0.63-0.93, up to 1 MB 0.79-0.99.
+static int rows_tile_mapping(const Problem& P, const Candidate& C)
+{
+    const double traffic = traffic_bytes(P);
+    const int64_t row = P.size[0] * P.eb_a;
+    const int64_t apart = P.ndim > 1 ? P.stride_b[1] * P.eb_b : 0;
+    const bool split = row % kLineBytes != 0, update = P.epilogue == TTC_EPI_AXPBY;
+    if (traffic < 8e6 || traffic > 200e6) return kDefaultTileMapping;
+    Candidate rule = C;
+    default_streaming(P, &rule);
+    RowsParams r = C.rows;
+    r.nt_a = rule.kp.nt_a;
+    r.nt_b = rule.kp.nt_b;
+    r.xcd_remap = 1;
+    const bool packed = r.unroll == 1 && small_dims(r, false, P.epilogue, P.kind_a >= kKindC64, 0, 1) != 0;
+    if (row < 128 && apart > (row < 64 && traffic < 32e6 ? int64_t(1) << 19 : int64_t(1) << 20)) return packed ? 0 : kDefaultTileMapping;
+    if (!packed) return split && row < (update ? 256 : 512) ? 1 : kDefaultTileMapping;
+    if (!update) return traffic <= 128e6 || (split && row < 512) ? 1 : kDefaultTileMapping;
+    if (traffic < 16e6) return split && row < 128 ? 1 : kDefaultTileMapping;
+    return split && row < 2048 ? 1 : 0;
+}
+
 // The line kernel's tiles read lines that their neighbours read as well: rows of A at the edge along B's runs where columns are cut at
 // their own lines (skewed), lines of A at the edge along A's runs where those split lines.  One contiguous range of tiles per XCD lets
 // neighbours meet in one L2; from 200 MB on the eight distant windows cost more than that gives.  Time of one range over the rule of
@@ -1324,6 +1355,7 @@ static bool make_gather_candidate(const Problem& P, Candidate* out)
 // between 0.91; at 64 bytes or with more between 0.98-1.06; whole lines on both sides share nothing (0.99-1.02).
 static int default_tile_mapping(const Problem& P, const Candidate& C)
 {
+    if (C.kernel_class == TTC_KERNEL_ROWS) return rows_tile_mapping(P, C);
     if (C.kernel_class != kKernelLines) return C.rows.per_xcd ? 0 : kDefaultTileMapping;
     const MicroParams& m = C.kp.micro;
     int64_t align = kLineBytes, between = 1;
@@ -2422,7 +2454,9 @@ static int emulate_rows(const ttc::Problem& P, const ttc::Candidate& C, int64_t*
         p.overlap != (!p.flat && P.size[0] % p.vec != 0 ? 1 : 0) || (p.overlap && P.epilogue == TTC_EPI_AXPBY) ||
         P.size[0] >= (int64_t(1) << 30) || rows >= (int64_t(1) << 31))
         return TTC_ERR_INTERNAL;
+    p.per_xcd = p.xcd_remap == 1 ? (p.blocks + 7u) / 8u : 0u;
     if (p.unroll == 1) small_round_trip<false>(P, &p);
+    p.xcd_remap = C.kp.xcd_remap;               // packed: none, or ranges by per_xcd
     auto inside = [&](int64_t off, const int64_t* stride, bool b_side) {
         if (off < 0) return false;
         for (int i = P.ndim - 1; i >= 0; --i) {
@@ -2439,6 +2473,7 @@ static int emulate_rows(const ttc::Problem& P, const ttc::Candidate& C, int64_t*
     std::vector<char> seen((size_t)p.blocks, 0);
     for (int64_t wg = 0; wg < grid && !bad; ++wg) {
         const uint32_t block = rows_block(p, (uint32_t)wg);
+        if (p.xcd_remap == 1 && range_place(p.per_xcd, (uint32_t)wg) != block && block < p.blocks) return TTC_ERR_INTERNAL;
         if (block >= p.blocks) continue;
         if (seen[block]) return TTC_ERR_INTERNAL;
         seen[block] = 1;

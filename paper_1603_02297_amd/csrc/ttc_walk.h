@@ -176,7 +176,7 @@ constexpr bool small_fits(bool gather, int n, int epilogue, bool is_complex) { r
 inline int small_dims(const RowsParams& p, bool gather, int epilogue, bool is_complex, int nt_a, int nt_b)
 {
     const int n = p.n < 2 ? 2 : p.n;
-    if (!p.flat || p.xcd_remap != 0 || p.nt_a != nt_a || p.nt_b != nt_b || n > kSmallMaxDim || p.elements >= kSmallMaxElements ||
+    if (!p.flat || p.xcd_remap > (gather ? 0 : 1) || p.nt_a != nt_a || p.nt_b != nt_b || n > kSmallMaxDim || p.elements >= kSmallMaxElements ||
         !small_fits(gather, n, epilogue, is_complex)) return 0;
     for (int d = 0; d < n; ++d)
         if (p.stride_a[d] > INT32_MAX || (p.size_div[d].div > 1 && (p.size_div[d].div - 1) * p.stride_a[d] > INT32_MAX)) return 0;
