@@ -133,6 +133,8 @@ def lib() -> ctypes.CDLL:
         L.ttc_debug_emulate_map.restype = i
         L.ttc_debug_emulate_map.argtypes = [vp, i64p]
         _lib = L
+        if _call is not None:
+            _call.bind(ctypes.cast(L.ttc_execute, vp).value)
     return _lib
 
 
@@ -194,6 +196,20 @@ def ttc_execute(plan: int, A: int, B: int, stream: Optional[int] = None) -> None
     st = lib().ttc_execute(plan, A, B, stream or None)
     if st != TTC_OK:
         raise TtcError(st, "ttc_execute")
+
+
+def _execute_failed(status: int) -> None:
+    raise TtcError(status, "ttc_execute")
+
+
+_execute_ctypes = ttc_execute
+try:                                        # the same without ctypes' conversions: plain ints go straight to the library, the rest as above
+    from . import _call
+except ImportError:                         # not built (no Python headers)
+    _call = None
+else:
+    _call.bind(_execute_ctypes, _execute_failed)
+    ttc_execute = _call.ttc_execute
 
 
 def ttc_plan_destroy(plan: Optional[int]) -> None:

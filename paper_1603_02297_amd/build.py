@@ -9,12 +9,14 @@ import glob
 import os
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libttc.so")
+CALL = os.path.join(HERE, "_call" + (sysconfig.get_config_var("EXT_SUFFIX") or ".so"))      # the binding's ttc_execute
 SOURCES = ["ttc_launch_f32.hip", "ttc_launch_mixed_real.hip", "ttc_launch_f64.hip", "ttc_launch_c64.hip",
            "ttc_launch_mixed_complex.hip", "ttc_launch_c128.hip", "ttc_plan.cpp", "ttc_cache.cpp", "ttc_device.hip"]
 
@@ -61,7 +63,22 @@ def build(verbose: bool = False, incremental: bool = False) -> str:
     if res.returncode != 0:
         sys.stderr.write(res.stdout + res.stderr)
         raise RuntimeError("hipcc failed linking libttc.so")
+    build_call()
     return LIB
+
+
+def build_call() -> None:
+    """Compile the CPython form of ttc_execute (host code only).  Without Python's headers there is none and the binding calls
+    through ctypes."""
+    include = sysconfig.get_paths()["include"]
+    if not os.path.exists(os.path.join(include, "Python.h")):
+        sys.stderr.write(f"no Python.h in {include}: ttc_execute goes through ctypes\n")
+        return
+    res = subprocess.run(["gcc", "-O2", "-Wall", "-shared", "-fPIC", "-I", include, os.path.join(CSRC, "ttc_call.c"), "-o", CALL],
+                         capture_output=True, text=True)
+    if res.returncode != 0:
+        sys.stderr.write(res.stdout + res.stderr)
+        raise RuntimeError("gcc failed compiling ttc_call.c")
 
 
 if __name__ == "__main__":

@@ -2,6 +2,9 @@
 import ctypes
 import os
 import re
+import sysconfig
+
+import pytest
 
 import paper_1603_02297_amd as ttc
 from paper_1603_02297_amd import binding
@@ -49,3 +52,29 @@ def test_info_struct_layout_matches_header():
     assert n > 1 and again["candidate_count"] == n and again["candidate_index"] == 0
     assert {k: v for k, v in again.items() if k != "candidate_count"} == {k: v for k, v in info.items() if k != "candidate_count"}
     ttc.ttc_plan_destroy(p)
+
+
+@pytest.mark.parametrize("args,kwargs", [
+    ((None, 64, 4096, 0), {}), ((0, 64, 4096), {}), (("plan", 0, 64), {}), (("plan", 64, 0, None), {}), (("plan", 64, 68), {}), (("plan", 65, 4096, 7), {}),
+    (("plan", 64, None), {}), (("plan", 1 << 70, 64), {}), (("plan", -(1 << 64), 64), {}), ((), {"plan": 0, "A": 64, "B": 4096}),
+    (("plan", 64, 4096, 0, 1), {}), (("plan", 64), {}), (("plan", 1.5, 64), {}), (("plan", "64", 64), {}), (("plan", 64, 4096), {"streams": 1})])
+def test_execute_and_its_ctypes_form_refuse_alike(args, kwargs):
+    """The CPython form of ttc_execute takes plain ints itself and leaves the rest to the ctypes form: same errors from both, whichever
+    of them sees the arguments (none of these reaches a device)."""
+    p = ttc.ttc_plan_create(ttc.TTC_F32, 2, (8, 8), (1, 0))
+    seen = []
+    for f in (ttc.ttc_execute, binding._execute_ctypes):
+        try:
+            f(*[p if a == "plan" else a for a in args], **kwargs)
+            seen.append(None)
+        except Exception as e:                      # noqa: BLE001: the type is what is compared
+            seen.append((type(e), str(e)))
+    assert seen[0] is not None and seen[0] == seen[1]
+    ttc.ttc_plan_destroy(p)
+
+
+def test_the_cpython_form_is_the_one_in_use():
+    include = sysconfig.get_paths()["include"]
+    if not os.path.exists(os.path.join(include, "Python.h")):
+        pytest.skip("no Python headers")
+    assert binding._call is not None and ttc.ttc_execute is binding._call.ttc_execute
