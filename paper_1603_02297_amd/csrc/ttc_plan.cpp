@@ -1353,15 +1353,22 @@ static int rows_tile_mapping(const Problem& P, const Candidate& C)
 // run has to be under way at the same time, `between` tiles later: up to 160 of them 0.90, 192-256 0.93-0.99, beyond 0.95-1.01 and
 // up to 1.5 (25 x 143639 complex64); where a range is shorter than that 0.93, with a twentieth of them above 1.1.  Not skewed, lines split at multiples of 32 bytes or less, 8 to 200 MB and up to 64 tiles
 // between 0.91; at 64 bytes or with more between 0.98-1.06; whole lines on both sides share nothing (0.99-1.02).
+static int64_t tiles_between(const Problem& P, const Candidate& C)
+{
+    int64_t between = 1;
+    for (int i = 0; i < P.ndim && C.tile_order[i] != 0; ++i) between *= (int64_t)C.kp.tile_cnt[C.tile_order[i]].div;
+    return between;
+}
+
 static int default_tile_mapping(const Problem& P, const Candidate& C)
 {
     if (C.kernel_class == TTC_KERNEL_ROWS) return rows_tile_mapping(P, C);
     if (C.kernel_class != kKernelLines) return C.rows.per_xcd ? 0 : kDefaultTileMapping;
     const MicroParams& m = C.kp.micro;
-    int64_t align = kLineBytes, between = 1;
+    int64_t align = kLineBytes;
     for (int k = 1; k < P.ndim; ++k)
         while (!(m.merged_a && k == 1) && P.stride_a[k] * P.eb_a % align != 0) align /= 2;
-    for (int i = 0; i < P.ndim && C.tile_order[i] != 0; ++i) between *= (int64_t)C.kp.tile_cnt[C.tile_order[i]].div;
+    const int64_t between = tiles_between(P, C);
     const double traffic = traffic_bytes(P);
     const bool near = between <= 160 && between * 8 <= (int64_t)C.kp.num_tiles;
     const bool ranges = m.skewed ? traffic >= (P.epilogue == TTC_EPI_AXPBY ? 2e6 : 8e6) && (align == kLineBytes || near)
@@ -1594,7 +1601,22 @@ static double line_cost(const Problem& P, const Candidate& C)
         // last-level cache: the line kernel takes 1.09, 1.02 and 1.09 times the micro-tile kernel's time (one pair, pairs in
         // rotation, new ones; 28 problems of 32 to 64 MB per tensor: 795 x 6248 fp64 19.7 us against 17.2, 22.7 against 21.3
         // and 22.2 against 20.3).  Below, 0.93, 0.94 and 0.95 (15 problems from 9 MB on); above, 1.01, 0.97 and 1.04 (17 up to 127 MB).
-        if (one_precision && !update && m.skewed && P.eb_a == 8 && traffic >= 64e6 && traffic < 128e6) e += 0.16;
+        // Not where its tiles have one range per XCD: there it takes 0.77 times the micro-tile kernel's (350 problems).  That holds for two
+        // indices as well, but the choice that was made for them before ranges is one that tests state, and stays.
+        const bool ranges = C.kp.xcd_remap == 1, short_runs = P.span_b != P.elements && rows * P.eb_b < 512.0;
+        if (one_precision && !update && m.skewed && P.eb_a == 8 && traffic >= 64e6 && traffic < 128e6 && !(ranges && P.ndim > 2)) {
+            e += 0.16;
+        } else if (ranges && !short_runs) {
+            // With ranges, what the fit (tiles dealt by number) does not know.  How much they are worth depends on how far away the next tile along
+            // A's run is; without skewed columns they are worth half.  In copies columns of 256 bytes before 128 in 4-byte elements take 1.08
+            // times as long, and the narrowest tiles of the wider ones are better with eight lines than with four (0.97).  Runs of B below
+            // 512 bytes between leading dimensions gain less (choosing this kernel for them: gather 0.82, block 0.94).  Time of the first candidate
+            // before over this one's, random problems of 12 to 240 MB in which it changed: another tile of this kernel 1.04 (950), instead of the
+            // block kernel 1.10 (235), of the micro-tile kernel 1.26 (113).
+            const double between = (double)tiles_between(P, C);
+            e -= m.skewed ? 0.12 * (1.0 - octaves(between, 64.0, 160.0)) : 0.06 * (1.0 - octaves(between, 16.0, 64.0));
+            if (!update) e += P.eb_a == 4 ? (m.ta == 64 ? 0.04 : 0.0) : m.lines == 4 && m.ta == 16 ? 0.03 : 0.0;
+        }
         if (update && m.merged_a && P.size[0] * P.eb_a >= 512) e += 0.08 + (P.perm[1] == 0 ? 0.12 : 0.0);    // a tile that crosses the end of a row
                                                                           // reads and writes B in two places, and leaves a contiguous block
         e += 0.343 * std::log((double)loaded / rows) + 0.340 * pad_cols + 0.293 * std::log((double)segs * m.tb / rows) + 0.087 * split;
@@ -1640,11 +1662,12 @@ static double line_cost(const Problem& P, const Candidate& C)
 // within 10-13 %, 3.4 us + 0.18 us per MB of traffic (line), 3.9 + 0.19 (micro-tile), 2.4 + 0.15 (row) and 5.6 + 0.20 (box), by
 // timings from before arguments were packed; the gather kernel's modelled time against the line kernel's, whose candidates cost
 // about 0.86 there.  (Large problems are further from the fit: a margin.)  Packed, it gained what the line kernel did, and has that
-// one's bonus up to 12 MB, fading out to 20, where the stride-1 index moves (elsewhere the row kernel is the alternative).
+// one's bonus up to 12 MB, fading out to 20, where the stride-1 index moves (elsewhere the row kernel is the alternative).  From 16 MB on it
+// keeps its distance to the line kernel's candidates with one range per XCD (without: 0.91 of its time where they took its place, 35 problems).
 static double gather_cost(const Problem& P, const Candidate& C)
 {
     const double traffic = traffic_bytes(P), mb = traffic * 1e-6;
-    const double packed = P.perm[0] != 0 ? 0.12 * octaves(traffic, 4e6, 8e6) * (1.0 - octaves(traffic, 12e6, 20e6)) : 0.0;
+    const double packed = P.perm[0] != 0 ? 0.12 * octaves(traffic, 4e6, 8e6) * (1.0 - octaves(traffic, 12e6, 20e6)) + (traffic >= 16e6 ? 0.05 : 0.0) : 0.0;
     return 0.86 * (1.0 + 0.004 * mb) * C.model_us / (3.4 + 0.18 * mb) * std::exp(-packed);
 }
 
