@@ -188,9 +188,10 @@ int ttc_plan_set_streaming(ttc_plan_t plan, int stream_a, int stream_b);
  * paper's loop-order question (Section 3.3) one level up.  mode 0: tile ids round robin over all workgroups;
  * 1: one contiguous range of tile ids per XCD; 2..10: chunks of 2^mode consecutive tile ids dealt to the
  * XCDs in turn; -1: the default (chunks of 32; round robin below 2048 tiles, and for the gather kernel where neighbouring
- * workgroups share lines of A: its tile ids are then numbered so that mode 0 gives every XCD one range of B).  Reported as
- * xcd_remap by ttc_plan_get_info.  The search times its finalists with modes 1 and 3 as well (not those of the row
- * kernel).  Host only.
+ * workgroups share lines of A: its tile ids are then numbered so that mode 0 gives every XCD one range of B; mode 1 for line and row
+ * kernel plans of 2 to 200 MB of traffic whose tiles share lines, mode 0 for some updates of long rows).  Reported as
+ * xcd_remap by ttc_plan_get_info.  The search times its finalists with modes 1 and 3 as well, those of the line kernel also without a rule of
+ * their own (not those of the row kernel).  Host only.
  */
 int ttc_plan_set_tile_mapping(ttc_plan_t plan, int mode);
 

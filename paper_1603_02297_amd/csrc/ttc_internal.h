@@ -290,8 +290,8 @@ constexpr int block_stores(int unroll, int eb_a, int eb_b) { return unroll * eb_
 // RowsParams of a small problem, packed.  Launches with up to 96 bytes of arguments, the two pointers included, leave the host
 // at 2.6-2.8 us each, larger ones at 3.4-3.6 (112 to 456 bytes; empty kernels in a row), which is most of what a small problem
 // takes; and its workgroups begin sooner.  70 x 33 x 45 fp32 (2,0,1) 3.46 -> 2.78 us a launch, 600 x 600 fp32 4.05 -> 3.44,
-// 96 x 80 x 70 fp32 (0,2,1) 3.3 -> 2.87.  From 2048 chunks of 4 KB on a launch is dealt to the XCDs in another way and
-// bound by memory: parameters go whole there, and where they do not fit (six indices, strides beyond 32 bits).  Four words (elements, chunks, per_xcd, rows), then per division two (the multiplier; divisor and shift), the
+// 96 x 80 x 70 fp32 (0,2,1) 3.3 -> 2.87.  Where chunks are dealt to the XCDs in groups parameters go whole, and where they
+// do not fit (six indices, strides beyond 32 bits).  Four words (elements, chunks, per_xcd, rows), then per division two (the multiplier; divisor and shift), the
 // strides in A, and at an 8-byte boundary the scalars that the epilogue reads.
 // The line kernel's MicroArgs are packed the same way: a word of places and flags, the first two divisions of the tile id, the
 // third index's steps, the extents, where columns lie in B and rows in A, and (MERGED) how a merged index is taken apart.
@@ -370,7 +370,7 @@ int cache_lookup(ttc_plan_s* plan, const char* path);
 uint32_t launch_grid(const Candidate& c, int cus);
 void set_grid(KernelParams* kp, uint32_t grid);
 // tile ids -> XCDs: 0 round robin, 1 one contiguous range per XCD, 2..10: chunks of 2^mode tiles dealt in turn
-// mode -1: the default, chunks of 32 tiles; round robin below 2048 tiles
+// mode -1: the default, chunks of 32 tiles; round robin below 2048 tiles (line and row kernel: default_tile_mapping() has the say)
 constexpr int kDefaultTileMapping = -1;
 constexpr int kMaxTileMapping = 10;                  // chunks of 2^10
 bool set_tile_mapping(KernelParams* kp, int mode);

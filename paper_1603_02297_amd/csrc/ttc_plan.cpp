@@ -1318,7 +1318,7 @@ static bool make_gather_candidate(const Problem& P, Candidate* out)
 // set_tile_mapping(), pairs in rotation, 19 000 random problems.  Packed copies: 8-16, 16-32, 32-64, 64-128 MB of traffic, rows
 // below 64 bytes 0.72, 0.80, 0.82, 0.86, to 128 0.80, 0.83, 0.85, 0.84, to 512 0.92, 0.85, 0.89, 0.88, longer 0.95, 0.86, 0.91, 0.91,
 // whole lines 0.96, 0.91, 0.93, 0.93; 128-200 MB below 512 bytes 0.90-0.92, longer and whole lines 0.96-1.05, beyond 200 MB 0.94-1.06.  (6 x 258 x 2475 fp32
-// (0,2,1) 12.0 -> 8.2 us.)  Packed updates of rows that split lines: below 128 bytes 0.80-0.94 from 8 MB on, to
+// (0,2,1) reads 18 MB instead of 50, of 15: 11.9 -> 7.6 us.)  Packed updates of rows that split lines: below 128 bytes 0.80-0.94 from 8 MB on, to
 // 512 0.92-0.97 from 16 MB on, longer 0.94-0.99; others from 16 MB on as they come: 0.95-0.99 (ranges 0.97-1.02).  Not packed: split rows below
 // 256 bytes 0.76-0.99 (copies to 512 0.92-0.98) from 8 to 200 MB; the others 0.99-1.06.
 // An XCD has about 1 MB of B under way (32 compute units, eight chunks of 4 KB each): rows below 128 bytes whose neighbours in A lie `apart`
@@ -1349,7 +1349,8 @@ static int rows_tile_mapping(const Problem& P, const Candidate& C)
 // neighbours meet in one L2; from 200 MB on the eight distant windows cost more than that gives.  Time of one range over the rule of
 // set_tile_mapping(), pairs in rotation, 21 000 random problems: skewed, copies of 8-16, 16-32, 32-64, 64-128 and 128-200 MB of
 // traffic 0.89, 0.83, 0.87, 0.90, 0.95 (4-8 MB 0.98-1.03), updates from 2 MB on 0.94, 0.93, 0.92, 0.86, 0.88, 0.92, 0.93; 200-300 MB 1.01, beyond
-// 1.03.  (7145 x 536 fp32 9.7 -> 6.7 us, 2001^2 10.2 -> 7.0, 2334 x 4390 18.9 -> 14.3.)  Where A's lines are split the next tile along A's
+// 1.03.  (2334 x 4390 fp32 reads 93 MB from beyond the L2s instead of 45, of 41 that it has to, and a request takes 1073 cycles instead of
+// 688: 20.0 -> 13.8 us; 7145 x 536 9.7 -> 6.9, 2001^2 10.9 -> 7.0.)  Where A's lines are split the next tile along A's
 // run has to be under way at the same time, `between` tiles later: up to 160 of them 0.90, 192-256 0.93-0.99, beyond 0.95-1.01 and
 // up to 1.5 (25 x 143639 complex64); where a range is shorter than that 0.93, with a twentieth of them above 1.1.  Not skewed, lines split at multiples of 32 bytes or less, 8 to 200 MB and up to 64 tiles
 // between 0.91; at 64 bytes or with more between 0.98-1.06; whole lines on both sides share nothing (0.99-1.02).
