@@ -1344,6 +1344,14 @@ static int rows_tile_mapping(const Problem& P, const Candidate& C)
     return split && row < 2048 ? 1 : 0;
 }
 
+// Tiles from one to the next along A's run, in the candidate's order.
+static int64_t tiles_between(const Problem& P, const Candidate& C)
+{
+    int64_t between = 1;
+    for (int i = 0; i < P.ndim && C.tile_order[i] != 0; ++i) between *= (int64_t)C.kp.tile_cnt[C.tile_order[i]].div;
+    return between;
+}
+
 // The line kernel's tiles read lines that their neighbours read as well: rows of A at the edge along B's runs where columns are cut at
 // their own lines (skewed), lines of A at the edge along A's runs where those split lines.  One contiguous range of tiles per XCD lets
 // neighbours meet in one L2; from 200 MB on the eight distant windows cost more than that gives.  Time of one range over the rule of
@@ -1354,13 +1362,6 @@ static int rows_tile_mapping(const Problem& P, const Candidate& C)
 // run has to be under way at the same time, `between` tiles later: up to 160 of them 0.90, 192-256 0.93-0.99, beyond 0.95-1.01 and
 // up to 1.5 (25 x 143639 complex64); where a range is shorter than that 0.93, with a twentieth of them above 1.1.  Not skewed, lines split at multiples of 32 bytes or less, 8 to 200 MB and up to 64 tiles
 // between 0.91; at 64 bytes or with more between 0.98-1.06; whole lines on both sides share nothing (0.99-1.02).
-static int64_t tiles_between(const Problem& P, const Candidate& C)
-{
-    int64_t between = 1;
-    for (int i = 0; i < P.ndim && C.tile_order[i] != 0; ++i) between *= (int64_t)C.kp.tile_cnt[C.tile_order[i]].div;
-    return between;
-}
-
 static int default_tile_mapping(const Problem& P, const Candidate& C)
 {
     if (C.kernel_class == TTC_KERNEL_ROWS) return rows_tile_mapping(P, C);
