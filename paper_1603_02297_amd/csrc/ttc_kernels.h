@@ -449,15 +449,14 @@ __global__ __launch_bounds__(kRowsThreads) void rows_kernel(const RowsParams p, 
 }
 
 // The same for small problems over a dense B, with its arguments packed (SmallArgs) and the usual hints (A kept, B streamed).  RANGES: each
-// XCD has one range of chunks (those behind the last one find nothing valid).
+// XCD has one range of chunks.
 template <typename TA, typename TB, int MODE, int V, int N, bool RANGES>
 __global__ __launch_bounds__(kRowsThreads) void rows_small_kernel(const SmallArgs args_by_value, const TA* __restrict__ A, TB* __restrict__ B)
 {
     const SmallArgs& s = *reinterpret_cast<const SmallArgs*>((const void*)__builtin_amdgcn_kernarg_segment_ptr());
     const RowsParams p = small_unpack<false, N, MODE, IsComplex<TA>::value>(s, V, kRowsThreads);
-    const uint32_t block = RANGES ? range_place(p.per_xcd, blockIdx.x) : blockIdx.x;
-    const uint32_t first = block * (uint32_t)(kRowsThreads * V), row0 = fdiv(first, p.slot_div);
-    rows_chunk<TA, TB, MODE, V, 1, true>(p, (int64_t)first, row0, first - row0 * p.row, A, B);
+    const SmallRowsStart at = small_rows_start<RANGES>(p, blockIdx.x);
+    rows_chunk<TA, TB, MODE, V, 1, true>(p, (int64_t)at.first, at.row0, at.col0, A, B);
 }
 
 // ---------------------------------------------------------------------------------

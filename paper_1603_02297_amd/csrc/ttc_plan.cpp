@@ -2480,7 +2480,8 @@ static int emulate_rows(const ttc::Problem& P, const ttc::Candidate& C, int64_t*
         P.size[0] >= (int64_t(1) << 30) || rows >= (int64_t(1) << 31))
         return TTC_ERR_INTERNAL;
     p.per_xcd = p.xcd_remap == 1 ? (p.blocks + 7u) / 8u : 0u;
-    if (p.unroll == 1) small_round_trip<false>(P, &p);
+    const bool packed = p.unroll == 1 && small_dims(p, false, P.epilogue, P.kind_a >= kKindC64, 0, 1) != 0;
+    if (packed) small_round_trip<false>(P, &p);
     p.xcd_remap = C.kp.xcd_remap;               // packed: none, or ranges by per_xcd
     auto inside = [&](int64_t off, const int64_t* stride, bool b_side) {
         if (off < 0) return false;
@@ -2497,14 +2498,20 @@ static int emulate_rows(const ttc::Problem& P, const ttc::Candidate& C, int64_t*
     const int64_t grid = rows_grid(p);
     std::vector<char> seen((size_t)p.blocks, 0);
     for (int64_t wg = 0; wg < grid && !bad; ++wg) {
-        const uint32_t block = rows_block(p, (uint32_t)wg);
-        if (p.xcd_remap == 1 && range_place(p.per_xcd, (uint32_t)wg) != block && block < p.blocks) return TTC_ERR_INTERNAL;
-        if (block >= p.blocks) continue;
-        if (seen[block]) return TTC_ERR_INTERNAL;
-        seen[block] = 1;
+        // the packed kernel runs every workgroup of the grid, those behind the last chunk too; the other one returns there
+        const uint32_t block = !packed ? rows_block(p, (uint32_t)wg) : p.xcd_remap == 1 ? range_place(p.per_xcd, (uint32_t)wg) : (uint32_t)wg;
+        if (block >= p.blocks && !packed) continue;
+        if (block < p.blocks) {
+            if (seen[block]) return TTC_ERR_INTERNAL;
+            seen[block] = 1;
+        }
         const int64_t base = block * (int64_t)p.chunk * (p.flat ? p.vec : 1);
         const int64_t row0_wide = base / (int64_t)p.slots;
         const uint32_t row0 = (uint32_t)row0_wide, slot0 = (uint32_t)(base - row0_wide * (int64_t)p.slots);
+        if (packed) {
+            const SmallRowsStart at = p.xcd_remap == 1 ? small_rows_start<true>(p, (uint32_t)wg) : small_rows_start<false>(p, (uint32_t)wg);
+            if ((int64_t)at.first != base || at.row0 != row0 || at.col0 != slot0) return TTC_ERR_INTERNAL;
+        }
         for (uint32_t i = 0; p.flat && i < p.chunk && !bad; ++i) {
             const FlatAccess x = flat_access(p, base, row0, slot0, i);
             for (int j = 0; j < p.vec; ++j) {                // what is loaded: whole vectors inside the tensors

@@ -245,6 +245,20 @@ TTC_HD RowsParams small_unpack(const SmallArgs& s, int vec, uint32_t chunk)
     return p;
 }
 
+// Where workgroup `wg` of the row kernel with packed arguments starts: its first element of B, the row that one lies in and its place
+// there.  RANGES: each XCD has one range of chunks; the workgroups behind the last chunk start past the end of B and find nothing valid.
+struct SmallRowsStart { uint32_t first, row0, col0; };
+
+template <bool RANGES>
+TTC_HD SmallRowsStart small_rows_start(const RowsParams& p, uint32_t wg)
+{
+    SmallRowsStart s;
+    s.first = (RANGES ? range_place(p.per_xcd, wg) : wg) * (p.chunk * (uint32_t)p.vec);
+    s.row0 = fdiv(s.first, p.slot_div);
+    s.col0 = s.first - s.row0 * p.row;
+    return s;
+}
+
 // ---- which tiles a workgroup walks ---------------------------------------------------------
 // Consecutive workgroup ids land on consecutive XCDs (8 of them, each with its own L2).  Every
 // XCD owns one contiguous range of tile ids; its workgroups take the tiles of that range round

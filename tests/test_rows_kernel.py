@@ -2,6 +2,9 @@
 (reported as the same class), which takes any permutation: every candidate and
 every way of dealing its chunks to the XCDs against the oracle, replayed on the host and run on the GPU.  Sizes: rows
 of one vector, one element more, odd ones; a tensor that is no multiple of the vector; chunks that do not fill a round."""
+import os
+import subprocess
+
 import numpy as np
 import pytest
 
@@ -350,3 +353,14 @@ def test_row_ranges_against_the_oracle(dtype, sizes, perm, beta, mapping):
         ran += 1
     assert ran >= 2
     ttc.ttc_plan_destroy(plan)
+
+
+def test_the_replay_runs_every_workgroup_of_a_packed_launch(tmp_path):
+    """Over ranges a launch has up to seven workgroups behind the last chunk; the packed kernel loads there as everywhere, so the host replay
+    has to follow them (replay_driver.cpp records where each replayed workgroup starts)."""
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    csrc, exe = os.path.join(root, "paper_1603_02297_amd", "csrc"), str(tmp_path / "replay_driver")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Wno-unused-function", "-Wno-unknown-pragmas", "-I", os.path.join(root, "include"), "-I", csrc,
+                    os.path.join(root, "tests", "replay_driver.cpp"), os.path.join(csrc, "ttc_cache.cpp"), "-o", exe], check=True)
+    res = subprocess.run([exe], capture_output=True, text=True, timeout=300)
+    assert res.returncode == 0 and "replay driver ok" in res.stdout, res.stdout + res.stderr
