@@ -1313,22 +1313,29 @@ static bool make_gather_candidate(const Problem& P, Candidate* out)
     return true;
 }
 
-// The row kernel's chunks: rows that split lines of A share them with chunks that lie far apart in B, which meet in one L2 where each XCD
-// has one range of chunks; and a launch without groups of chunks (none or ranges) packs its arguments.  Time of ranges over the rule of
-// set_tile_mapping(), pairs in rotation, 19 000 random problems.  Packed copies: 8-16, 16-32, 32-64, 64-128 MB of traffic, rows
+// The row kernel's chunks: rows that share lines of A (they start inside lines, and the next one begins in the line where this one ends)
+// lie in chunks that are far apart in B and meet in one L2 where each XCD has one range of chunks; and a launch without groups of
+// chunks (none or ranges) packs its arguments.  Time of ranges over the rule of set_tile_mapping(), pairs in rotation, 19 000 random
+// problems with a dense A.  Packed copies: 8-16, 16-32, 32-64, 64-128 MB of traffic, rows
 // below 64 bytes 0.72, 0.80, 0.82, 0.86, to 128 0.80, 0.83, 0.85, 0.84, to 512 0.92, 0.85, 0.89, 0.88, longer 0.95, 0.86, 0.91, 0.91,
 // whole lines 0.96, 0.91, 0.93, 0.93; 128-200 MB below 512 bytes 0.90-0.92, longer and whole lines 0.96-1.05, beyond 200 MB 0.94-1.06.  (6 x 258 x 2475 fp32
 // (0,2,1) reads 18 MB instead of 50, of 15: 11.9 -> 7.6 us.)  Packed updates of rows that split lines: below 128 bytes 0.80-0.94 from 8 MB on, to
 // 512 0.92-0.97 from 16 MB on, longer 0.94-0.99; others from 16 MB on as they come: 0.95-0.99 (ranges 0.97-1.02).  Not packed: split rows below
 // 256 bytes 0.76-0.99 (copies to 512 0.92-0.98) from 8 to 200 MB; the others 0.99-1.06.
+// With a padded A it is the distance of the rows that counts, not their length.  Ranges over chunks as they come, 400 problems: shared
+// lines 0.79 (copies) and 0.84 (updates) in rows below 128 bytes, 0.95 and 0.98 in longer ones; rows on lines of their own, or a line
+// and more apart, 0.99-1.02.  400 problems where that is another mapping than the rows' length gives: 0.990 of the time in rotation, 0.992
+// on one pair, 0.985 on new tensors (32 x 800 x 331 fp32 (0,2,1) at a distance of 33 with an update 20.0 -> 16.8 us, a copy of 64 x 560 x 558
+// at 65 32.0 -> 25.0).
 // An XCD has about 1 MB of B under way (32 compute units, eight chunks of 4 KB each): rows below 128 bytes whose neighbours in A lie `apart`
 // further than that do not meet (1.00-1.10, as they come 0.92-0.99); up to 512 KB 0.63-0.93, up to 1 MB 0.79-0.99.
 static int rows_tile_mapping(const Problem& P, const Candidate& C)
 {
     const double traffic = traffic_bytes(P);
     const int64_t row = P.size[0] * P.eb_a;
-    const int64_t apart = P.ndim > 1 ? P.stride_b[1] * P.eb_b : 0;
-    const bool split = row % kLineBytes != 0, update = P.epilogue == TTC_EPI_AXPBY;
+    const int64_t apart = P.ndim > 1 ? P.stride_b[1] * P.eb_b : 0, step = P.ndim > 1 ? P.stride_a[1] * P.eb_a : 0;
+    const bool update = P.epilogue == TTC_EPI_AXPBY;
+    const bool shared = step % kLineBytes != 0 && step - row < kLineBytes;       // (strides of later indices are multiples of index 1's)
     if (traffic < 8e6 || traffic > 200e6) return kDefaultTileMapping;
     Candidate rule = C;
     default_streaming(P, &rule);
@@ -1338,10 +1345,10 @@ static int rows_tile_mapping(const Problem& P, const Candidate& C)
     r.xcd_remap = 1;
     const bool packed = r.unroll == 1 && small_dims(r, false, P.epilogue, P.kind_a >= kKindC64, 0, 1) != 0;
     if (row < 128 && apart > (row < 64 && traffic < 32e6 ? int64_t(1) << 19 : int64_t(1) << 20)) return packed ? 0 : kDefaultTileMapping;
-    if (!packed) return split && row < (update ? 256 : 512) ? 1 : kDefaultTileMapping;
-    if (!update) return traffic <= 128e6 || (split && row < 512) ? 1 : kDefaultTileMapping;
-    if (traffic < 16e6) return split && row < 128 ? 1 : kDefaultTileMapping;
-    return split && row < 2048 ? 1 : 0;
+    if (!packed) return shared && row < (update ? 256 : 512) ? 1 : kDefaultTileMapping;
+    if (!update) return traffic <= 128e6 || (shared && row < 512) ? 1 : kDefaultTileMapping;
+    if (traffic < 16e6) return shared && row < 128 ? 1 : kDefaultTileMapping;
+    return shared && row < 2048 ? 1 : 0;
 }
 
 // Tiles from one to the next along A's run, in the candidate's order.

@@ -302,25 +302,32 @@ def test_small_problems_with_packed_parameters(dtype):
     assert ran >= 50
 
 
-# (type, extents, permutation, beta, mapping that the rule gives a row plan): either side of the lines of the rule
+# (type, extents, permutation, beta, mapping that the rule gives a row plan, leading dimensions of A): either side of the lines of the rule
 ROWS_DEALT_BY_DEFAULT = [
-    (wl.F32, (27, 211, 199), (0, 2, 1), 0.0, 1), (wl.F32, (27, 199, 173), (0, 2, 1), 0.0, 0),          # 9.1 and 7.4 MB of traffic
-    (wl.F32, (13, 91, 3001), (0, 2, 1), 0.0, 1), (wl.F32, (13, 21, 12001), (0, 2, 1), 0.0, 0),         # neighbours 156 and 624 KB apart, 28 and 26 MB
-    (wl.F32, (64, 300, 299), (0, 2, 1), 0.0, 1),                                                       # whole lines: ranges, packed
-    (wl.F32, (13, 331, 307), (0, 2, 1), 1.0, 1), (wl.F32, (31, 331, 307), (0, 2, 1), 1.0, 1),          # updates, 15.9 and 37.8 MB
-    (wl.F32, (37, 231, 107), (0, 2, 1), 1.0, 0), (wl.F32, (64, 300, 299), (0, 2, 1), 1.0, 0),          # rows beyond 128 bytes below 16 MB; whole lines
-    (wl.C128, (5, 7, 5, 9, 11, 61), (0, 2, 1, 5, 4, 3), 1.0, 1), (wl.C128, (35, 5, 9, 11, 7, 13), (0, 5, 2, 4, 3, 1), 0.0, 5),     # six indices: not packed
+    (wl.F32, (27, 211, 199), (0, 2, 1), 0.0, 1, None), (wl.F32, (27, 199, 173), (0, 2, 1), 0.0, 0, None),          # 9.1 and 7.4 MB of traffic
+    (wl.F32, (13, 91, 3001), (0, 2, 1), 0.0, 1, None), (wl.F32, (13, 21, 12001), (0, 2, 1), 0.0, 0, None),         # neighbours 156 and 624 KB apart, 28 and 26 MB
+    (wl.F32, (64, 300, 299), (0, 2, 1), 0.0, 1, None),                                                       # whole lines: ranges, packed
+    (wl.F32, (13, 331, 307), (0, 2, 1), 1.0, 1, None), (wl.F32, (31, 331, 307), (0, 2, 1), 1.0, 1, None),          # updates, 15.9 and 37.8 MB
+    (wl.F32, (37, 231, 107), (0, 2, 1), 1.0, 0, None), (wl.F32, (64, 300, 299), (0, 2, 1), 1.0, 0, None),          # rows beyond 128 bytes below 16 MB; whole lines
+    (wl.C128, (5, 7, 5, 9, 11, 61), (0, 2, 1, 5, 4, 3), 1.0, 1, None), (wl.C128, (35, 5, 9, 11, 7, 13), (0, 5, 2, 4, 3, 1), 0.0, 5, None),     # six indices: not packed
+    # rows of a larger A: each on lines of its own, or starting inside lines that they share, whatever their own length is; the third and the sixth lie
+    # more than a line apart
+    (wl.F32, (27, 800, 331), (0, 2, 1), 1.0, 0, (32, 800, 331)), (wl.F32, (32, 800, 331), (0, 2, 1), 1.0, 1, (33, 800, 331)), (wl.F32, (27, 800, 331), (0, 2, 1), 1.0, 0, (60, 800, 331)),
+    (wl.F32, (64, 560, 558), (0, 2, 1), 0.0, 1, (65, 560, 558)), (wl.F32, (63, 560, 558), (0, 2, 1), 0.0, 5, (64, 560, 558)), (wl.F32, (63, 560, 558), (0, 2, 1), 0.0, 5, (97, 560, 558)),
+    (wl.F32, (33, 800, 331), (0, 2, 1), 1.0, 1, (33, 801, 331)),                                       # dense rows, padded behind the second index
 ]
 
 
-@pytest.mark.parametrize("dtype,sizes,perm,beta,mapping", ROWS_DEALT_BY_DEFAULT)
-def test_rows_that_share_lines_are_dealt_in_ranges(dtype, sizes, perm, beta, mapping):
-    p = ttc.ttc_plan_create(dtype, len(sizes), sizes, perm, 1.5, beta)
+@pytest.mark.parametrize("dtype,sizes,perm,beta,mapping,lda", ROWS_DEALT_BY_DEFAULT)
+def test_rows_that_share_lines_are_dealt_in_ranges(dtype, sizes, perm, beta, mapping, lda):
+    p = ttc.ttc_plan_create_ex(dtype, len(sizes), sizes, perm, lda, None, 1.5, beta)
     for k in range(ttc.ttc_plan_candidate_count(p)):
         ttc.ttc_plan_select_candidate(p, k)
         info = ttc.ttc_plan_get_info(p)
         if ttc.kernel_family(info) == "rows" and info["unroll"] == 1 and info["partial_a"] == 0 and info["vec_a"] == 16 // max(wl.ELEM_BYTES[dtype], wl.ELEM_BYTES_B[dtype]):
             break
+    else:
+        raise AssertionError("no row candidate of whole vectors")
     assert info["xcd_remap"] == mapping
     ttc.ttc_plan_set_tile_mapping(p, 2)
     ttc.ttc_plan_set_tile_mapping(p, -1)
@@ -329,17 +336,17 @@ def test_rows_that_share_lines_are_dealt_in_ranges(dtype, sizes, perm, beta, map
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("dtype,sizes,perm,beta,mapping", [c for c in ROWS_DEALT_BY_DEFAULT if c[-1] == 1])
-def test_row_ranges_against_the_oracle(dtype, sizes, perm, beta, mapping):
+@pytest.mark.parametrize("dtype,sizes,perm,beta,mapping,lda", [c for c in ROWS_DEALT_BY_DEFAULT if c[4] == 1])
+def test_row_ranges_against_the_oracle(dtype, sizes, perm, beta, mapping, lda):
     """Every row candidate with one range of chunks per XCD, the plan as created first; chunk counts that do not divide by eight, B with a last vector
     that is not whole."""
     import torch
     n, stream, cplx = int(np.prod(sizes)), torch.cuda.current_stream().cuda_stream, wl.COMPONENTS[dtype] == 2
-    A, B0 = wl.uniform_tensor(dtype, n, 7400, "a"), wl.uniform_tensor(dtype, n, 7401, "b")
+    A, B0 = wl.uniform_tensor(dtype, int(np.prod(lda or sizes)), 7400, "a"), wl.uniform_tensor(dtype, n, 7401, "b")
     alpha = 0.5 + 0.5j if cplx else 1.5
-    want = oracle.transpose(dtype, sizes, perm, alpha, beta, A, B0.copy(), 8)
+    want = oracle.transpose(dtype, sizes, perm, alpha, beta, A, B0.copy(), 8, lda=lda)
     dA, dB0 = torch.from_numpy(A).cuda(), torch.from_numpy(B0).cuda()
-    plan = ttc.ttc_plan_create(dtype, len(sizes), sizes, perm, alpha, beta)
+    plan = ttc.ttc_plan_create_ex(dtype, len(sizes), sizes, perm, lda, None, alpha, beta)
     ran = 0
     for k in range(ttc.ttc_plan_candidate_count(plan)):
         ttc.ttc_plan_select_candidate(plan, k)
