@@ -1608,12 +1608,12 @@ static double line_cost(const Problem& P, const Candidate& C)
         }
         // Copies of 8-byte elements whose columns of B start inside lines, both tensors together a quarter to a half of the
         // last-level cache: the line kernel takes 1.09, 1.02 and 1.09 times the micro-tile kernel's time (one pair, pairs in
-        // rotation, new ones; 28 problems of 32 to 64 MB per tensor: 795 x 6248 fp64 19.7 us against 17.2, 22.7 against 21.3
+        // rotation, new ones; 28 problems of 32 to 64 MB per tensor, tiles dealt by number: 795 x 6248 fp64 19.7 us against 17.2, 22.7 against 21.3
         // and 22.2 against 20.3).  Below, 0.93, 0.94 and 0.95 (15 problems from 9 MB on); above, 1.01, 0.97 and 1.04 (17 up to 127 MB).
-        // Not where its tiles have one range per XCD: there it takes 0.77 times the micro-tile kernel's (350 problems).  That holds for two
-        // indices as well, but the choice that was made for them before ranges is one that tests state, and stays.
+        // Not where its tiles have one range per XCD: there it takes 0.84, 0.80 and 0.94 times what the first candidate with this term does (60
+        // problems of three to six indices), 0.84, 0.77 and 0.92 with two (80; 1379 x 5230 fp64 23.3 -> 19.2, 27.4 -> 19.2 and 29.2 -> 25.5 us).
         const bool ranges = C.kp.xcd_remap == 1, short_runs = P.span_b != P.elements && rows * P.eb_b < 512.0;
-        if (one_precision && !update && m.skewed && P.eb_a == 8 && traffic >= 64e6 && traffic < 128e6 && !(ranges && P.ndim > 2)) {
+        if (one_precision && !update && m.skewed && P.eb_a == 8 && traffic >= 64e6 && traffic < 128e6 && !ranges) {
             e += 0.16;
         } else if (ranges && !short_runs) {
             // With ranges, what the fit (tiles dealt by number) does not know.  How much they are worth depends on how far away the next tile along

@@ -549,13 +549,16 @@ def test_large_updates_with_whole_lines_take_the_micro_tile_kernel(dtype, sizes,
 
 @pytest.mark.parametrize("dtype,sizes,family", [
     (ttc.TTC_F64, (816, 1341), "line"),          # 9 MB per tensor
-    (ttc.TTC_F64, (795, 6248), "micro"),         # 40 MB
-    (ttc.TTC_C64, (5007, 1102), "micro"),        # 44 MB
+    (ttc.TTC_F64, (795, 6248), "line"),          # 40 MB, tiles in ranges: 13.8 us, micro-tile kernel 17.2
+    (ttc.TTC_C64, (5007, 1102), "line"),         # 44 MB: 14.3 us, micro-tile kernel 17.7
+    (ttc.TTC_F64, (1379, 5230), "line"),         # 58 MB: 19.2 us, micro-tile kernel 27.4
+    (ttc.TTC_F64, (291, 22693), "micro"),        # 53 MB, too many tiles between those that share lines of A: dealt by number
     (ttc.TTC_F64, (16509, 535), "line"),         # 71 MB
     (ttc.TTC_F32, (3163, 3577), "line"),         # 45 MB of 4-byte elements
 ])
 def test_copies_of_8_byte_elements_whose_columns_start_inside_lines(dtype, sizes, family):
-    """A quarter to a half of the last-level cache in both tensors together: the micro-tile kernel is ahead."""
+    """A quarter to a half of the last-level cache in both tensors together: the micro-tile kernel is ahead where the line kernel's tiles
+    are dealt by number, the line kernel where each XCD has one range of them."""
     p = plan(dtype, sizes, (1, 0))
     assert ttc.kernel_family(ttc.ttc_plan_get_info(p)) == family
     ttc.ttc_plan_destroy(p)
