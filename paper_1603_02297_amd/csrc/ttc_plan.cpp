@@ -1667,17 +1667,34 @@ static double line_cost(const Problem& P, const Candidate& C)
     return std::exp(e);
 }
 
+// Whether the line kernel has candidates, tiles in B's order, that run in one range per XCD.
+static bool lines_in_ranges(const Problem& P)
+{
+    for (int merged = 0; merged < 4; ++merged)
+        for (int cols : {16, 32, 64})
+            for (int lines : {4, 8, 2}) {
+                Candidate c;
+                if (make_line_candidate(P, cols, lines, P.perm, (merged & 1) != 0, (merged & 2) != 0, &c) && c.kp.xcd_remap == 1) return true;
+            }
+    return false;
+}
+
 // The gather kernel against the others.  For problems that the caches hold the families' first candidates take, to
 // within 10-13 %, 3.4 us + 0.18 us per MB of traffic (line), 3.9 + 0.19 (micro-tile), 2.4 + 0.15 (row) and 5.6 + 0.20 (box), by
 // timings from before arguments were packed; the gather kernel's modelled time against the line kernel's, whose candidates cost
 // about 0.86 there.  (Large problems are further from the fit: a margin.)  Packed, it gained what the line kernel did, and has that
 // one's bonus up to 12 MB, fading out to 20, where the stride-1 index moves (elsewhere the row kernel is the alternative).  From 16 MB on it
-// keeps its distance to the line kernel's candidates with one range per XCD (without: 0.91 of its time where they took its place, 35 problems).
+// keeps its distance to the line kernel's candidates with one range per XCD, which rank up to 12 % better there, if the problem has such
+// candidates and B is dense (a lane then writes whole vectors).  Time of the gather kernel over that of the first candidate without this
+// term, in rotation, on one pair and on new tensors, problems of 15 to 65 MB in which it decides: 0.89, 0.84 and 1.00 (141); where
+// there are none, or between leading dimensions, it would be 1.11, 1.11 and 1.16 (105; 5 x 14 x 20 x 102 x 12 complex64 reversed 34 us, box
+// kernel 11.7).
 static double gather_cost(const Problem& P, const Candidate& C)
 {
     const double traffic = traffic_bytes(P), mb = traffic * 1e-6;
-    const double packed = P.perm[0] != 0 ? 0.12 * octaves(traffic, 4e6, 8e6) * (1.0 - octaves(traffic, 12e6, 20e6)) + (traffic >= 16e6 ? 0.05 : 0.0) : 0.0;
-    return 0.86 * (1.0 + 0.004 * mb) * C.model_us / (3.4 + 0.18 * mb) * std::exp(-packed);
+    const double packed = P.perm[0] != 0 ? 0.12 * octaves(traffic, 4e6, 8e6) * (1.0 - octaves(traffic, 12e6, 20e6)) : 0.0;
+    const double distance = traffic >= 16e6 && C.rows.flat && lines_in_ranges(P) ? 0.05 : 0.0;       // (P.perm[0] == 0: there are none)
+    return 0.86 * (1.0 + 0.004 * mb) * C.model_us / (3.4 + 0.18 * mb) * std::exp(-packed - distance);
 }
 
 // The block kernel's ranking model, log-linear, fitted to the timings of every block candidate of 112 problems of 9 MB to 1.9 GB of
