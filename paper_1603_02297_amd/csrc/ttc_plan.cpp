@@ -1658,6 +1658,8 @@ static double line_cost(const Problem& P, const Candidate& C)
     // kernel, whose arguments are packed as well.  Over 3760 problems of 2.5 MB to 1.9 GB this, gather_cost()'s bonus and block_cost()'s
     // choose 0.9 % better than 0.12 here between 8 and 40 MB alone, packed or not, did, and 86 problems instead of 130 take more than 1.05
     // times what they took before any arguments were packed (13061 x 72 fp64 -> fp32 (1,0) 6.0 -> 4.3 us).
+    // Updates whose lanes load eight vectors of A are packed in ranges only: with half for these, 1.01, 0.99 and 1.01 (rotation, one pair, new
+    // tensors; 170 problems whose first candidate that changes).
     const bool packed = small_line(micro_args(C), P.epilogue, P.kind_a >= kKindC64, S.passes) != 0;
     e -= (packed ? 0.12 : 0.06) * octaves(traffic, 4e6, 8e6) * (1.0 - octaves(traffic, 40e6, 80e6));
     bool b_order = true;

@@ -623,11 +623,14 @@ constexpr bool small_line_fits(bool merged, int epilogue, bool is_complex) { ret
 constexpr int kDealNone = 0, kDealRanges = 1, kDealAll = 2;
 inline int small_line_dealing(const MicroArgs& a) { return a.nt_a != 0 || a.xcd_remap > 1 ? kDealAll : a.xcd_remap == 1 ? kDealRanges : kDealNone; }
 
-// Whether there is a packed kernel for dealt tiles; `passes`: vectors of A a lane loads.
-// Updates of many tiles whose lanes load eight vectors of A keep the whole arguments: that kernel waits for arguments between
+// Whether there is a packed kernel for tiles dealt in any way (kDealAll); `passes`: vectors of A a lane loads.
+// Updates of many tiles whose lanes load eight vectors of A keep the whole arguments there: that kernel waits for arguments between
 // its loads, the packed one issues eight of A and up to eight of B in a row, and is slower by 3 % (fp32, 18 problems; 40 x 1064 x 344
-// (1,0,2) 36.8 -> 40.3 us), 2 % (fp64, 10), 1 % (complex64, 8; complex128, 6) and 10 and 7 % (complex128 -> complex64, fp64 -> fp32, 3 and
+// (1,0,2) in chunks of 32 36.8 -> 40.3 us), 2 % (fp64, 10), 1 % (complex64, 8; complex128, 6) and 10 and 7 % (complex128 -> complex64, fp64 -> fp32, 3 and
 // 2).  With four vectors it is 1-3 % faster, and 5 % and more where there are fewer tiles.
+// With one range per XCD (kDealRanges) it is the packed kernel that is faster with eight vectors as well: 0.94-0.96 of the time from 700 tiles
+// on (130 problems of every type, in rotation; one pair 0.95, new tensors 0.96), 0.99 below (23, from 0.77 to 1.18); 40 x 1064 x 344 29.8 us,
+// whole arguments 30.7 (and 31.0 in chunks of 32).
 constexpr bool small_line_deals(int epilogue, int passes) { return epilogue != TTC_EPI_AXPBY || passes < 8; }
 
 // 0: the arguments go unpacked; 1: packed; 2: packed with merged indices.
