@@ -205,7 +205,7 @@ def _execute_failed(status: int) -> None:
 _execute_ctypes = ttc_execute
 try:                                        # the same without ctypes' conversions: plain ints go straight to the library, the rest as above
     from . import _call
-except ImportError:                         # not built (no Python headers)
+except ImportError:                         # not built (no Python headers or no C compiler)
     _call = None
 else:
     _call.bind(_execute_ctypes, _execute_failed)

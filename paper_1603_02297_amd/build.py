@@ -7,6 +7,7 @@ from __future__ import annotations
 
 import glob
 import os
+import shutil
 import subprocess
 import sys
 import sysconfig
@@ -68,13 +69,16 @@ def build(verbose: bool = False, incremental: bool = False) -> str:
 
 
 def build_call() -> None:
-    """Compile the CPython form of ttc_execute (host code only).  Without Python's headers there is none and the binding calls
-    through ctypes."""
-    include = sysconfig.get_paths()["include"]
-    if not os.path.exists(os.path.join(include, "Python.h")):
-        sys.stderr.write(f"no Python.h in {include}: ttc_execute goes through ctypes\n")
+    """Compile the CPython form of ttc_execute (host code only).  Without Python's headers or a C compiler there is none and the
+    binding calls through ctypes."""
+    include, gcc = sysconfig.get_paths()["include"], shutil.which("gcc")
+    missing = f"no Python.h in {include}" if not os.path.exists(os.path.join(include, "Python.h")) else "no gcc" if gcc is None else None
+    if missing:
+        sys.stderr.write(f"{missing}: ttc_execute goes through ctypes\n")
+        if os.path.exists(CALL):            # of an older source
+            os.remove(CALL)
         return
-    res = subprocess.run(["gcc", "-O2", "-Wall", "-shared", "-fPIC", "-I", include, os.path.join(CSRC, "ttc_call.c"), "-o", CALL],
+    res = subprocess.run([gcc, "-O2", "-Wall", "-shared", "-fPIC", "-I", include, os.path.join(CSRC, "ttc_call.c"), "-o", CALL],
                          capture_output=True, text=True)
     if res.returncode != 0:
         sys.stderr.write(res.stdout + res.stderr)

@@ -2,12 +2,13 @@
 import ctypes
 import os
 import re
+import shutil
 import sysconfig
 
 import pytest
 
 import paper_1603_02297_amd as ttc
-from paper_1603_02297_amd import binding
+from paper_1603_02297_amd import binding, build
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
@@ -75,6 +76,16 @@ def test_execute_and_its_ctypes_form_refuse_alike(args, kwargs):
 
 def test_the_cpython_form_is_the_one_in_use():
     include = sysconfig.get_paths()["include"]
-    if not os.path.exists(os.path.join(include, "Python.h")):
-        pytest.skip("no Python headers")
+    if not os.path.exists(os.path.join(include, "Python.h")) or shutil.which("gcc") is None:
+        pytest.skip("no Python headers or no C compiler")
     assert binding._call is not None and ttc.ttc_execute is binding._call.ttc_execute
+
+
+def test_building_the_package_needs_no_c_compiler(tmp_path, monkeypatch):
+    """hipcc alone builds the library: without gcc the binding calls through ctypes, and no older CPython form is left to be loaded."""
+    call = tmp_path / "_call.so"
+    call.write_bytes(b"")
+    monkeypatch.setattr(build, "CALL", str(call))
+    monkeypatch.setenv("PATH", str(tmp_path))
+    build.build_call()
+    assert not call.exists()
