@@ -34,19 +34,20 @@ def line_candidates(plan):
 
 
 def form(info, dtype):
-    """How a line candidate's arguments go to the kernel, mirrored from the library: "whole", or packed, "small" (a workgroup's number is
-    its tile's) or "dealt" (tiles dealt to the XCDs, or A streamed); and whether its indices are merged."""
+    """How a line candidate's arguments go to the kernel, mirrored from the library: "whole", or packed, for tiles as they come ("small": a
+    workgroup's number is its tile's), for one range of tiles per XCD ("ranges") or for any other dealing, or A streamed ("dealt"); and whether
+    its indices are merged."""
     cols, lines, ea, eb = info["digit_tile_a"][0], info["unroll"], wl.ELEM_BYTES[dtype], wl.ELEM_BYTES_B[dtype]
     merged, update = bool(info["merged"]), info["epilogue"] == ttc.TTC_EPI_AXPBY
-    dealt = info["xcd_remap"] != 0 or info["nt_a"] != 0
+    dealing = "dealt" if info["xcd_remap"] > 1 or info["nt_a"] != 0 else "ranges" if info["xcd_remap"] == 1 else "small"
     passes = lines * (128 // eb) * (cols * ea // 16) // 256              # vectors of A a lane loads
     words = (18 if merged else 12) + 2 * info["epilogue"] * wl.COMPONENTS[dtype]
     used = {k for k in range(info["ndim"]) if info["tile"][k] < info["sizes"][k]} | {0, info["perm"][0]}
-    whole = words > 20 or len(used) > 3 or (update and passes >= 8 and dealt)
-    return ("whole" if whole else "dealt" if dealt else "small"), merged
+    whole = words > 20 or len(used) > 3 or (update and passes >= 8 and dealing == "dealt")
+    return ("whole" if whole else dealing), merged
 
 
-FORMS = {(f, m) for f in ("whole", "small", "dealt") for m in (False, True)}
+FORMS = {(f, m) for f in ("whole", "small", "ranges", "dealt") for m in (False, True)}
 
 
 def scalars(dtype):
@@ -64,7 +65,7 @@ def test_walks_of_every_line_candidate(dtype):
             for off_a, off_b in oracle.element_pairs(sizes, perm, lda, ldb):
                 want[off_b] = off_a
             for k, info in line_candidates(p):
-                for mode, nt in ((-1, 0), ((1, 2, 5)[seen % 3], seen // 3 % 2)):      # tiles dealt to the XCDs, surplus workgroups among them
+                for mode, nt in ((-1, 0), (1, 0), ((1, 2, 5)[seen % 3], seen // 3 % 2)):      # tiles dealt to the XCDs, surplus workgroups among them
                     ttc.ttc_plan_set_tile_mapping(p, mode)
                     ttc.ttc_plan_set_streaming(p, nt, nt)
                     forms.add(form(ttc.ttc_plan_get_info(p), dtype))
@@ -104,8 +105,8 @@ def test_reported_bank_conflicts_are_those_of_the_tile(dtype):
 @pytest.mark.gpu
 @pytest.mark.parametrize("dtype", DTYPES, ids=[wl.DTYPE_NAME[d] for d in DTYPES])
 def test_line_kernel_against_the_oracle(dtype):
-    """Every candidate, every epilogue, both streaming settings, tiles dealt and not (packed and whole arguments of either kind); B at
-    three places inside a line; what lies around the sub-tensor stays as it was.  Fixed evaluation order on both sides: bit-equal
+    """Every candidate, every epilogue, both streaming settings, tiles as they come, in ranges and dealt otherwise (packed and whole arguments of each); B at
+    four places inside a line; what lies around the sub-tensor stays as it was.  Fixed evaluation order on both sides: bit-equal
     but for the ulp the library allows."""
     import torch
     dev = torch.device("cuda:0")
@@ -123,7 +124,7 @@ def test_line_kernel_against_the_oracle(dtype):
             plan = ttc.ttc_plan_create_ex(dtype, len(sizes), sizes, perm, lda, ldb, alpha, beta)
             try:
                 for k, info in line_candidates(plan):
-                    for nt, phase, mode in ((0, 0, -1), (1, 1, (-1, 1, 2, 5)[k % 4]), (0, 7, (1, 2, 5)[k % 3])):
+                    for nt, phase, mode in ((0, 0, -1), (1, 1, (-1, 1, 2, 5)[k % 4]), (0, 3, 1), (0, 7, (2, 5)[k % 2])):
                         ttc.ttc_plan_set_streaming(plan, nt, nt)
                         ttc.ttc_plan_set_tile_mapping(plan, mode)
                         forms.add(form(ttc.ttc_plan_get_info(plan), dtype))
@@ -186,6 +187,9 @@ DEALT_BY_DEFAULT = [
     (wl.F64, (17, 40009), (1, 0), 0.0, False), (wl.F64, (16, 40009), (1, 0), 0.0, True),           # hundreds of tiles before the next one along A: lines split, or none
     (wl.F32, (1031, 1024), (1, 0), 0.0, True), (wl.F32, (1032, 1024), (1, 0), 0.0, True),          # whole lines of B, A's split at 4 and 32 bytes
     (wl.F32, (1040, 1024), (1, 0), 0.0, False), (wl.F32, (1024, 1024), (1, 0), 0.0, False),        # at 64 bytes, and none
+    (wl.C64, (37, 41, 701), (2, 1, 0), 0.0, True), (wl.C64, (37, 41, 701), (2, 1, 0), 1.0, True),  # merged indices: packed, and whole arguments with an update
+    (wl.C128_C64, (13, 47, 611), (2, 1, 0), 0.0, True), (wl.F32_F64, (299, 19, 203), (2, 0, 1), 0.0, True),        # two types
+    (wl.F32, (23, 31, 41, 101), (3, 2, 1, 0), 0.0, True),                                          # more places in the tile order than are packed
 ]
 
 
@@ -213,21 +217,25 @@ def test_tiles_that_share_lines_are_dealt_in_ranges(dtype, sizes, perm, beta, ra
 @pytest.mark.gpu
 @pytest.mark.parametrize("dtype,sizes,perm,beta,ranges", [c for c in DEALT_BY_DEFAULT if c[-1]])
 def test_ranges_against_the_oracle(dtype, sizes, perm, beta, ranges):
-    """The plan as created and its line candidates over ranges: tile counts that do not divide by eight, packed arguments and whole ones."""
+    """The plan as created and its line candidates over ranges: tile counts that do not divide by eight, packed arguments, with merged indices too,
+    and whole ones."""
     import torch
     n, stream = int(np.prod(sizes)), torch.cuda.current_stream().cuda_stream
     A, B0 = wl.uniform_tensor(dtype, n, 7300, "a"), wl.uniform_tensor(dtype, n, 7301, "b")
     want = oracle.transpose(dtype, sizes, perm, 1.0, beta, A, B0.copy(), 8)
     dA, dB0 = torch.from_numpy(A).cuda(), torch.from_numpy(B0).cuda()
     plan = ttc.ttc_plan_create(dtype, len(sizes), sizes, perm, 1.0, beta)
-    seen = 0
+    seen, forms = 0, set()
     for k, info in [(0, None)] + list(line_candidates(plan)):
         ttc.ttc_plan_select_candidate(plan, k)
         ttc.ttc_plan_set_tile_mapping(plan, -1 if info is None else 1)
         seen += ttc.ttc_plan_get_info(plan)["num_tiles"] % 8 != 0
+        if info is not None:
+            forms.add(form(ttc.ttc_plan_get_info(plan), dtype))
         dB = dB0.clone()
         ttc.ttc_execute(plan, dA.data_ptr(), dB.data_ptr(), stream)
         allowed = 0.0 if beta == 0 else np.spacing(np.abs(want).max())          # bits are copied; one ulp with an update
         assert np.abs(dB.cpu().numpy() - want).max() <= allowed, (k, ttc.ttc_plan_get_info(plan))
-    assert seen
+    few, merged = len(sizes) < 4, sizes == (37, 41, 701) or sizes == (13, 47, 611)
+    assert seen and (("ranges", False) in forms) == few and (("ranges", True) in forms) == (merged and beta == 0)
     ttc.ttc_plan_destroy(plan)
