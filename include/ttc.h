@@ -187,11 +187,13 @@ int ttc_plan_set_streaming(ttc_plan_t plan, int stream_a, int stream_b);
  * How the selected candidate deals its tiles to the 8 XCDs (each has its own L2): the MI355X form of the
  * paper's loop-order question (Section 3.3) one level up.  mode 0: tile ids round robin over all workgroups;
  * 1: one contiguous range of tile ids per XCD; 2..10: chunks of 2^mode consecutive tile ids dealt to the
- * XCDs in turn; -1: the default (chunks of 32; round robin below 2048 tiles, and for the gather kernel where neighbouring
- * workgroups share lines of A: its tile ids are then numbered so that mode 0 gives every XCD one range of B; mode 1 for line and row
- * kernel plans of 2 to 200 MB of traffic whose tiles share lines, mode 0 for some updates of long rows).  Reported as
- * xcd_remap by ttc_plan_get_info.  The search times its finalists with modes 1 and 3 as well, those of the line kernel also without a rule of
- * their own (not those of the row kernel).  Host only.
+ * XCDs in turn; -1: the default: chunks of 32, or round robin below 2048 tiles, but
+ *   gather kernel, where neighbouring workgroups share lines of A: mode 0, its tile ids being numbered so that this gives every XCD one range of B;
+ *   line kernel, up to 200 MB of traffic, from 8 on (2 with an update), where neighbouring tiles share lines of a tensor and run close enough together: mode 1;
+ *   row kernel, 8 to 200 MB: mode 1 for rows that share lines of A and are short enough to gain by it, and for copies up to 128 MB that fit the small argument
+ *   block; mode 0 for what else fits that block where rows below 128 bytes that are neighbours in A lie too far apart in B, or with an update from 16 MB on.
+ * Reported as xcd_remap by ttc_plan_get_info.  The search times its finalists with modes 1 and 3 as well, those of the line kernel also with
+ * the default that the other kernels have (not those of the row kernel).  Host only.
  */
 int ttc_plan_set_tile_mapping(ttc_plan_t plan, int mode);
 

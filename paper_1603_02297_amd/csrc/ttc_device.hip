@@ -330,10 +330,13 @@ static int tune_pairs(ttc_plan_t plan, int npairs, const void* const* A_list, vo
         }
         c.kp.nt_a = keep_a;
         c.kp.nt_b = keep_b;
-        // the same for the mapping of tiles to XCDs: the default (chunks of 32 if there are enough tiles), one
-        // range per XCD, chunks of 8.  Not for the row kernel, whose default is ahead: over eleven problems of 200 to 630 MB
-        // of traffic round robin took 0.2 % less at best (85^4 fp32 (0,3,2,1) with an update) and 4 % more at worst (208 x
-        // 115 x 63 x 35), chunks of 8 1-8 % more, one range 1-11 % more; at 16 MB (384 x 72 x 72) one range took 2 % less.
+        // the same for the mapping of tiles to XCDs: the family's default, one range per XCD, chunks of 8, and for the line kernel, whose
+        // default may be ranges by a rule of its own, what the others have (chunks of 32 if there are enough tiles).  Not for the row kernel,
+        // whose rule is ahead: 250 problems of 8 to 200 MB, in rotation, on one pair, on new tensors: round robin takes 1.10, 1.10 and 1.04 times
+        // as long as the rule, ranges 1.00, 1.01 and 1.01, chunks of 8 1.15, 1.19 and 1.09, of 32 1.12, 1.18 and 1.08, the best of the four
+        // 0.99, 0.98 and 0.99, and the one that a single pair picks 0.998 in rotation and on new tensors.  From 200 to 630 MB (eleven problems,
+        // the rule is chunks of 32) round robin took 0.2 % less at best (85^4 fp32 (0,3,2,1) with an update) and 4 % more at worst (208 x
+        // 115 x 63 x 35), chunks of 8 1-8 % more, one range 1-11 % more.
         // Trying them made the search keep round robin on 384^3 (74.2 us, default 72.9).
         const int mapping0 = c.kp.xcd_remap;
         int keep_map = mapping0;
