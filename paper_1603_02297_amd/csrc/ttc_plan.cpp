@@ -1616,12 +1616,14 @@ static double line_cost(const Problem& P, const Candidate& C)
         if (one_precision && !update && m.skewed && P.eb_a == 8 && traffic >= 64e6 && traffic < 128e6 && !ranges) {
             e += 0.16;
         } else if (ranges && !short_runs) {
-            // With ranges, what the fit (tiles dealt by number) does not know.  How much they are worth depends on how far away the next tile along
-            // A's run is; without skewed columns they are worth half.  In copies columns of 256 bytes before 128 in 4-byte elements take 1.08
-            // times as long, and the narrowest tiles of the wider ones are better with eight lines than with four (0.97).  Runs of B below
-            // 512 bytes between leading dimensions gain less (choosing this kernel for them: gather 0.82, block 0.94).  Time of the first candidate
-            // before over this one's, random problems of 12 to 240 MB in which it changed: another tile of this kernel 1.04 (950), instead of the
-            // block kernel 1.10 (235), of the micro-tile kernel 1.26 (113).
+            // With ranges, what the fit (tiles dealt by number) does not know: how much they are worth depends on how far away the next tile along
+            // A's run is, and without skewed columns they are worth half; it sets in and ends where ranges do, or with this branch.  In copies columns of
+            // 128 bytes go before 256 in 4-byte elements, and in the wider ones eight lines before four in the narrowest tiles.  Runs of B below 512
+            // bytes between leading dimensions gain less.  Each by itself: time of the first candidate with it over that without, in rotation, on one
+            // pair and on new tensors, drawn problems of 8 to 200 MB that it decides.  The share of ranges 0.94, 0.93 and 0.99 (150; at 16-32, 32-64,
+            // 64-128, 128-200 MB 0.96, 0.92, 0.93 and 0.93 in rotation; instead of the block kernel 0.91, 0.92 and 0.98, of another tile of this kernel 0.95, 0.94
+            // and 0.99, of the micro-tile kernel 0.86, 0.91 and 0.99); 128 bytes before 256 0.93, 0.93 and 0.99 (90); eight lines 0.99, 0.92 and 0.99 (75);
+            // short runs left out 0.90, 0.89 and 0.97 (27).
             const double between = (double)tiles_between(P, C);
             e -= m.skewed ? 0.12 * (1.0 - octaves(between, 64.0, 160.0)) : 0.06 * (1.0 - octaves(between, 16.0, 64.0));
             if (!update) e += P.eb_a == 4 ? (m.ta == 64 ? 0.04 : 0.0) : m.lines == 4 && m.ta == 16 ? 0.03 : 0.0;
