@@ -1324,7 +1324,8 @@ static bool make_gather_candidate(const Problem& P, Candidate* out)
 // 256 bytes 0.76-0.99 (copies to 512 0.92-0.98) from 8 to 200 MB; the others 0.99-1.06.
 // With a padded A it is the distance of the rows that counts, not their length.  Ranges over chunks as they come, 400 problems: shared
 // lines 0.79 (copies) and 0.84 (updates) in rows below 128 bytes, 0.95 and 0.98 in longer ones; rows on lines of their own, or a line
-// and more apart, 0.99-1.02.  400 problems where that is another mapping than the rows' length gives: 0.990 of the time in rotation, 0.992
+// and more apart, 0.99-1.02; not packed, rows of whole lines that share others gain nothing (123 below 512 bytes: 0.99 over chunks of 32, 1.04 on
+// new tensors).  400 problems where that is another mapping than the rows' length gives: 0.990 of the time in rotation, 0.992
 // on one pair, 0.985 on new tensors (32 x 800 x 331 fp32 (0,2,1) at a distance of 33 with an update 20.0 -> 16.8 us, a copy of 64 x 560 x 558
 // at 65 32.0 -> 25.0).
 // An XCD has about 1 MB of B under way (32 compute units, eight chunks of 4 KB each): rows below 128 bytes whose neighbours in A lie `apart`
@@ -1345,7 +1346,7 @@ static int rows_tile_mapping(const Problem& P, const Candidate& C)
     r.xcd_remap = 1;
     const bool packed = r.unroll == 1 && small_dims(r, false, P.epilogue, P.kind_a >= kKindC64, 0, 1) != 0;
     if (row < 128 && apart > (row < 64 && traffic < 32e6 ? int64_t(1) << 19 : int64_t(1) << 20)) return packed ? 0 : kDefaultTileMapping;
-    if (!packed) return shared && row < (update ? 256 : 512) ? 1 : kDefaultTileMapping;
+    if (!packed) return shared && row % kLineBytes != 0 && row < (update ? 256 : 512) ? 1 : kDefaultTileMapping;
     if (!update) return traffic <= 128e6 || (shared && row < 512) ? 1 : kDefaultTileMapping;
     if (traffic < 16e6) return shared && row < 128 ? 1 : kDefaultTileMapping;
     return shared && row < 2048 ? 1 : 0;

@@ -314,6 +314,9 @@ ROWS_DEALT_BY_DEFAULT = [
     # more than a line apart
     (wl.F32, (27, 800, 331), (0, 2, 1), 1.0, 0, (32, 800, 331)), (wl.F32, (32, 800, 331), (0, 2, 1), 1.0, 1, (33, 800, 331)), (wl.F32, (27, 800, 331), (0, 2, 1), 1.0, 0, (60, 800, 331)),
     (wl.F32, (64, 560, 558), (0, 2, 1), 0.0, 1, (65, 560, 558)), (wl.F32, (63, 560, 558), (0, 2, 1), 0.0, 5, (64, 560, 558)), (wl.F32, (63, 560, 558), (0, 2, 1), 0.0, 5, (97, 560, 558)),
+    # not packed: rows that share lines and are not whole lines themselves, rows of whole lines, rows on lines of their own
+    (wl.C128, (7, 7, 9, 11, 13, 15), (0, 2, 1, 5, 4, 3), 1.0, 1, (9, 7, 9, 11, 13, 15)), (wl.C128, (8, 7, 9, 11, 13, 15), (0, 2, 1, 5, 4, 3), 1.0, 5, (9, 7, 9, 11, 13, 15)),
+    (wl.C128, (7, 7, 9, 11, 13, 15), (0, 2, 1, 5, 4, 3), 1.0, 5, (8, 7, 9, 11, 13, 15)),
     (wl.F32, (33, 800, 331), (0, 2, 1), 1.0, 1, (33, 801, 331)),                                       # dense rows, padded behind the second index
 ]
 
