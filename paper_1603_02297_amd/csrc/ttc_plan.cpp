@@ -1690,15 +1690,15 @@ static bool lines_in_ranges(const Problem& P)
 // about 0.86 there.  (Large problems are further from the fit: a margin.)  Packed, it gained what the line kernel did, and has that
 // one's bonus up to 12 MB, fading out to 20, where the stride-1 index moves (elsewhere the row kernel is the alternative).  From 16 MB on it
 // keeps its distance to the line kernel's candidates with one range per XCD, which rank up to 12 % better there, if the problem has such
-// candidates and B is dense (a lane then writes whole vectors).  Time of the gather kernel over that of the first candidate without this
-// term, in rotation, on one pair and on new tensors, problems of 15 to 65 MB in which it decides: 0.89, 0.84 and 1.00 (141); where
-// there are none, or between leading dimensions, it would be 1.11, 1.11 and 1.16 (105; 5 x 14 x 20 x 102 x 12 complex64 reversed 34 us, box
-// kernel 11.7).
+// candidates and B is dense, or A's first index is B's second (neighbouring columns of B then read the same lines of A).  Time of the gather kernel over that of the first candidate without this
+// term, in rotation, on one pair and on new tensors, problems of 15 to 65 MB in which it decides: 0.88, 0.84 and 1.00 (169); in the others,
+// without line tiles in ranges or between leading dimensions, it would be 1.23, 1.23 and 1.22 (77; 5 x 14 x 20 x 102 x 12 complex64 reversed
+// 34 us, box kernel 11.7).
 static double gather_cost(const Problem& P, const Candidate& C)
 {
     const double traffic = traffic_bytes(P), mb = traffic * 1e-6;
     const double packed = P.perm[0] != 0 ? 0.12 * octaves(traffic, 4e6, 8e6) * (1.0 - octaves(traffic, 12e6, 20e6)) : 0.0;
-    const double distance = traffic >= 16e6 && C.rows.flat && lines_in_ranges(P) ? 0.05 : 0.0;       // (P.perm[0] == 0: there are none)
+    const double distance = traffic >= 16e6 && (C.rows.flat || P.perm[1] == 0) && lines_in_ranges(P) ? 0.05 : 0.0;       // (P.perm[0] == 0: there are none)
     return 0.86 * (1.0 + 0.004 * mb) * C.model_us / (3.4 + 0.18 * mb) * std::exp(-packed - distance);
 }
 

@@ -596,14 +596,15 @@ def test_small_line_problems_and_whole_lines_go_to_the_faster_kernel(dtype, size
 @pytest.mark.parametrize("dtype,sizes,perm,lda,ldb,alpha,beta,gather", [
     (ttc.TTC_C64, (132, 38, 325), (1, 0, 2), None, None, 1.0, 0.0, True),                 # line tiles in ranges: 5.6 us, block kernel 8.0
     (ttc.TTC_F64, (40, 12, 5, 64, 9), (2, 1, 0, 4, 3), None, None, 1.5, 0.0, True),       # 5.8 us, micro-tile kernel 8.0
+    (ttc.TTC_C64, (592, 53, 44), (2, 0, 1), (622, 55, 44), (49, 657, 53), 1.0, 0.0, True),                                  # A's first index is B's second: 5.8 us, micro-tile kernel 8.6
     (ttc.TTC_F32, (34144, 64), (1, 0), None, None, 1.5, 0.0, False),                      # line tiles dealt by number: 7.2 us, line kernel 3.7
     (ttc.TTC_C64, (5, 14, 20, 102, 12), (4, 3, 2, 1, 0), (6, 14, 20, 109, 12), (13, 113, 23, 15, 5), 0.5, 0.0, False),      # leading dimensions: 34 us, box kernel 11.7
     (ttc.TTC_F32, (9, 7, 13, 10, 34, 10), (5, 4, 2, 1, 0, 3), (11, 7, 14, 10, 35, 10), (12, 37, 15, 7, 11, 10), 1.0, 0.0, False),   # 24.9 us, box kernel 12.3
     (ttc.TTC_F64, (4, 64, 6, 62, 21), (4, 3, 2, 1, 0), (5, 72, 6, 64, 21), (22, 69, 6, 71, 4), 0.75, 1.0, False),           # 30.4 us, box kernel 14.5
 ])
 def test_gather_kernel_keeps_its_distance_only_to_line_tiles_in_ranges(dtype, sizes, perm, lda, ldb, alpha, beta, gather):
-    """16 to 64 MB: what the ranking gives the gather kernel so that line tiles in ranges do not take its places is for dense problems that have
-    such tiles."""
+    """16 to 64 MB: what the ranking gives the gather kernel so that line tiles in ranges do not take its places is for problems that have such
+    tiles and are dense, or whose neighbouring columns of B read the same lines of A."""
     p = ttc.ttc_plan_create_ex(dtype, len(sizes), sizes, perm, lda, ldb, alpha, beta)
     assert (ttc.kernel_family(ttc.ttc_plan_get_info(p)) == "gather") == gather
     ttc.ttc_plan_destroy(p)
